@@ -18,6 +18,14 @@
  * and a positively-constrained projected conjugate-gradient step minimising
  * Phi over I >= M (Eq. minproblem; M plays the role of the paper's G).
  *
+ * How the sums are evaluated: small problems by the separable direct
+ * contraction on matrix cores in the chosen precision; larger ones (where it
+ * is faster) through an oversampled grid with FP64 windows and sums, an
+ * evaluation of the same sums to working precision: FP64 contexts to FP64
+ * rounding (as the direct sum, ~1e-14), the other precisions to ~2e-8, below
+ * the rounding of their own contraction.  The choice depends on the sizes
+ * and the precision only.
+ *
  * Geometry: image side N (even), pixel (i, j) at x_j = (j - N/2) cell,
  * y_i = (i - N/2) cell (Alg. 3 with the phase centre at pixel (N/2, N/2));
  * linear pixel index N*i + j (row i <-> y).  u, v in wavelengths, cell in
@@ -67,7 +75,7 @@ typedef enum uvmem_status {
                             point's fixed scratch (UVMEM_NOALLOC_SCRATCH_BYTES) */
 } uvmem_status;
 
-/* Precision of the DFT contractions (the chi^2, entropy and line-search sums
+/* Precision of the direct DFT contractions (the chi^2, entropy and line-search sums
  * are FP64 in every mode, and so are the model visibilities and residuals). */
 typedef enum uvmem_precision {
     UVMEM_FP64 = 0,      /* FP64 operands, FP64 matrix cores                  */
@@ -279,7 +287,9 @@ int uvmem_timing_read(uvmem_ctx *ctx, int which, double *total_ms, int64_t *coun
  * pixel block, visibilities per visibility item, image planes n_img, forward
  * model, gridded-model grid side L (0 for the DFT), gradient model,
  * forward and adjoint workgroups of the focus-of-attention region's work
- * lists (0 without a region).  uvmem_chan_range gives a channel's offset into the concatenated
+ * lists (0 without a region), side of the oversampled grid in use (0: direct
+ * contraction; the work-list entries then describe the lists that the direct
+ * contraction would use).  uvmem_chan_range gives a channel's offset into the concatenated
  * visibility arrays and its count. */
 int uvmem_info(const uvmem_ctx *ctx, int64_t *out, int nout);
 int uvmem_chan_range(const uvmem_ctx *ctx, int chan, int64_t *offset, int64_t *nvis);

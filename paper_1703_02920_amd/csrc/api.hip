@@ -93,6 +93,8 @@ void free_all(uvmem_ctx *c) {
     dfree(c->d_gtw); dfree(c->d_gx1); dfree(c->d_ggrid); dfree(c->d_gcell); dfree(c->d_gperm);
     dfree(c->d_gfxy); dfree(c->d_gsc); dfree(c->d_gdidx); dfree(c->d_gdlist); dfree(c->d_gdsum);
     dfree(c->d_wscale); dfree(c->d_mask);
+    dfree(c->d_tritem); dfree(c->d_trbin); dfree(c->d_trperm); dfree(c->d_trdec); dfree(c->d_trpoly);
+    dfree(c->d_trtw); dfree(c->d_trx); dfree(c->d_trg); dfree(c->d_trtile);
     dfree(c->d_fwdp_m); dfree(c->d_adj_m); dfree(c->d_slot_base_m);
     if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
     if (c->graph) (void)hipGraphDestroy(c->graph);
@@ -128,6 +130,7 @@ void harvest(uvmem_ctx *c) {
 
 // Launch the forward (which = 0) or adjoint (which = 1) DFT, bracketed by
 // events when timing is on.
+// Coefficients without weights are a caller's vector, in the caller's order.
 // flag: the forward operand is a CG direction / the adjoint is a gradient
 // (region-restricted work lists under a focus-of-attention mask).
 hipError_t timed_dft(uvmem_ctx *c, int which, const void *bop, const double2 *coef, const float *w, int flag) {
@@ -143,7 +146,7 @@ hipError_t timed_dft(uvmem_ctx *c, int which, const void *bop, const double2 *co
             (void)hipEventRecord(e0, c->stream);
         }
     }
-    hipError_t e = which == 0 ? launch_forward(c, bop, c->stream, flag) : launch_adjoint(c, coef, w, c->stream, flag);
+    hipError_t e = which == 0 ? launch_forward(c, bop, c->stream, flag) : launch_adjoint(c, coef, w, c->stream, flag, w == nullptr);
     if (e0) {
         (void)hipEventRecord(e1, c->stream);
         c->pend[which].push_back({e0, e1});
@@ -195,6 +198,87 @@ int pick_schedule(int slots, const std::function<std::vector<double>(int)> &cost
     return best;
 }
 
+// Direct contraction or the fast evaluation of k_trans.hip (same sums to
+// rounding, O(L^2 log L + W^2 Z) instead of Z N^2)?  Estimated times of one
+// direction in microseconds, per channel on average so that the choice does
+// not depend on how channels are grouped in contexts.  Measured, both
+// directions and everything else of an evaluation: 256^2 x 99,840 FP64 918 us
+// direct, 179 us fast; 1024^2 x 5,000,250 bf16x3 91.6 ms and 0.63 ms; 64^2 x
+// 5,130 FP64 42 us direct (two launches against six, so small problems stay).
+void choose_transform(uvmem_ctx *c) {
+    c->tr_lg = 0;
+    if (c->fwd_model != UVMEM_FWD_DFT || c->ztot == 0 || c->ztot >= (int64_t)1 << 30) return;
+    int lg = 6;
+    while ((1 << lg) < 2 * c->n) ++lg;
+    if (lg > 12) return;
+    // grids and bin tables within 32 GiB and 2^28 entries
+    if ((double)c->nchan * std::ldexp(1.0, 2 * lg) > (double)(1 << 30) * 2) return;
+    const double L = (double)(1 << lg), z = (double)c->ztot / c->nchan;
+    const double rate = c->prec == UVMEM_FP64 ? 55.0 : c->prec == UVMEM_FP32 ? 115.0 : 330.0;   // TFLOP/s
+    const double direct = 4.0 * z * c->np * c->np / rate * 1e-6;
+    const double transform = 8.0 + 5e-6 * L * L + 1e-4 * z;
+    bool use = transform < direct;
+    if (const char *env = std::getenv("UVMEM_DFT"))
+        use = std::strcmp(env, "transform") == 0 ? true : std::strcmp(env, "direct") == 0 ? false : use;
+    if (!use) return;
+    c->tr_lg = lg;
+    c->tr_w = c->prec == UVMEM_FP64 ? 17 : 9;
+    c->tr_h = (c->tr_w - 1) / 2;
+    const int tb = c->tr_w - 1;   // nodes per bin side: 8 or 16
+    c->tr_nbx = (1 << lg) / 2 / tb + 1;
+    c->tr_nby = (1 << lg) / tb;
+    c->tr_lgc = (c->tr_nbx - 1) * tb + 2 * tb;
+}
+
+// Window of the fast evaluation: phi(x) = I0(beta sqrt(1 - (2 x / W)^2)) /
+// I0(beta) on |x| <= W / 2 (Kaiser-Bessel), whose transform is
+// W sinh(s) / s / I0(beta), s = sqrt(beta^2 - (pi W xi)^2).  beta / W = 2.3
+// is within a factor two of the best at every tried side (grid side >= 2 N).
+// poly: for tap u = 0 .. H the polynomial of phi(u - H - z / 2), z in [-1, 1]
+// (Chebyshev interpolation), even coefficients first, then the odd ones.
+void transform_window(int W, int ne, int n, int L, std::vector<double> &poly, std::vector<double> &dec) {
+    typedef long double ld;
+    const ld pi = 3.141592653589793238462643383279502884L;
+    const ld beta = 2.3L * W;
+    const int H = (W - 1) / 2, D = 2 * ne;
+    auto i0 = [](ld x) {
+        ld term = 1.0L, sum = 1.0L;
+        for (int k = 1; k < 400 && term > 1e-25L * sum; ++k) {
+            term *= (x / 2) * (x / 2) / ((ld)k * k);
+            sum += term;
+        }
+        return sum;
+    };
+    const ld i0b = i0(beta);
+    auto phi = [&](ld x) {
+        const ld y = 1.0L - (2 * x / W) * (2 * x / W);
+        return y <= 0 ? 1.0L / i0b : i0(beta * std::sqrt(y)) / i0b;
+    };
+    poly.assign((size_t)(H + 1) * D, 0.0);
+    for (int u = 0; u <= H; ++u) {
+        std::vector<ld> f(D), mono(D, 0.0L), t0(D, 0.0L), t1(D, 0.0L), t2(D, 0.0L);
+        for (int i = 0; i < D; ++i) f[i] = phi((ld)(u - H) - std::cos(pi * (i + 0.5L) / D) / 2);
+        t0[0] = 1.0L;
+        t1[1] = 1.0L;
+        for (int k = 0; k < D; ++k) {
+            ld ck = 0.0L;
+            for (int i = 0; i < D; ++i) ck += f[i] * std::cos(pi * k * (i + 0.5L) / D);
+            ck *= (k == 0 ? 1.0L : 2.0L) / D;
+            for (int m = 0; m < D; ++m) mono[m] += ck * t0[m];
+            for (int m = 0; m < D; ++m) t2[m] = (m ? 2 * t1[m - 1] : 0.0L) - t0[m];   // T_{k+2} = 2 z T_{k+1} - T_k
+            t0 = t1;
+            t1 = t2;
+        }
+        for (int m = 0; m < D; ++m) poly[(size_t)u * D + (m & 1) * ne + m / 2] = (double)mono[m];
+    }
+    dec.resize(n);
+    for (int j = 0; j < n; ++j) {
+        const ld x = pi * W * (ld)(j - n / 2) / L;
+        const ld s = std::sqrt(beta * beta - x * x);
+        dec[j] = (double)(i0b * s / (W * std::sinh(s)));
+    }
+}
+
 int build_layout(uvmem_ctx *c) {
     const int C = c->nchan;
     c->np = ((c->n + 63) / 64) * 64;
@@ -214,6 +298,7 @@ int build_layout(uvmem_ctx *c) {
     c->n_ib = c->np / c->ib_rows;
     c->n_jb = c->np / c->jb_cols;
     c->n_fparts = c->fwd_model == UVMEM_FWD_GRIDDED ? 1 : c->n_ib * c->n_jb;
+    c->n_vparts = c->n_fparts;
     // adjoint pixel tile: 256 x 256 for the FP32 and split kernels where the
     // padded side allows (halves their table work per product), else 128 x 128
     // (FP64 too: its twiddle tables then feed four times the products of a
@@ -242,6 +327,7 @@ int build_layout(uvmem_ctx *c) {
     c->pix_blk = (int)std::max<int64_t>(NTHR, roundup((npix * c->nimg + pix_wgs - 1) / pix_wgs, NTHR));
     c->n_pb = (int)((npix + c->pix_blk - 1) / c->pix_blk);
     c->vis_blk = (int)std::max<int64_t>(2 * NTHR, roundup((c->ztot + vis_wgs - 1) / vis_wgs, 2 * NTHR));
+    choose_transform(c);
     return UVMEM_OK;
 }
 
@@ -512,49 +598,79 @@ int uvmem_finalize(uvmem_ctx *c) {
 
 extern "C++" {
 namespace {
-int finalize_impl(uvmem_ctx *c) {
-    const int C = c->nchan;
-    for (int ch = 0; ch < C; ++ch) {
-        if (!c->has_uv[ch]) return fail(c, UVMEM_ESTATE, "channel %d has no uv", ch);
-        if (!c->has_vis[ch]) return fail(c, UVMEM_ESTATE, "channel %d has no visibilities", ch);
-        if (!c->has_w[ch]) return fail(c, UVMEM_ESTATE, "channel %d has no weights", ch);
-        if (!c->has_beam[ch]) return fail(c, UVMEM_ESTATE, "channel %d has no beam", ch);
-    }
-    if (!c->prior_set) return fail(c, UVMEM_ESTATE, "prior not set");
-    if (c->fwd_model == UVMEM_FWD_GRIDDED) {
-        int64_t z = 0;
-        for (int ch = 0; ch < C; ++ch) z += c->nvis[ch];
-        const int64_t L = (int64_t)1 << c->grid_lg;
-        if (z > (int64_t)INT32_MAX - 1) return fail(c, UVMEM_EINVAL, "gridded model: more than 2^31 visibilities");
-        if ((int64_t)C * (L * L + 1) > ((int64_t)1 << 30))
-            return fail(c, UVMEM_ENOMEM, "gridded model: cell tables of %d channels x %lld^2 cells too large", C,
-                        (long long)L);
-    }
-    HIPCHK(c, hipSetDevice(c->device));
-    c->fail_alloc_at = -1;
-    c->n_alloc = 0;
-    if (const char *env = std::getenv("UVMEM_TEST_FAIL_ALLOC")) c->fail_alloc_at = std::atoi(env);
-    build_layout(c);
-    const int n = c->n, np = c->np;
-    const size_t npix = (size_t)n * n;
-    const size_t rs = real_size(c);
+// A channel's beam image in the image's own type.
+hipError_t upload_beam(uvmem_ctx *c, int ch) {
+    const size_t npix = (size_t)c->n * c->n, at = ch * npix;
+    if (c->prec != UVMEM_FP64)
+        return hipMemcpy((float *)c->d_beam + at, c->hbeam[ch].data(), npix * sizeof(float), hipMemcpyHostToDevice);
+    const std::vector<double> b(c->hbeam[ch].begin(), c->hbeam[ch].end());
+    return hipMemcpy((double *)c->d_beam + at, b.data(), npix * sizeof(double), hipMemcpyHostToDevice);
+}
 
-    // ---- work tables
-    std::vector<VisItem> vis;
-    c->h_vis_base.assign(C + 1, 0);
+// Fast evaluation: the visibilities in bin order (a, b, V^o and w of every
+// channel, and the permutation) and the items of the tile kernels.  The raw
+// arrays are staged in buffers that the hot path will use later, sorted by
+// bin on the device (stable, so the order depends on the inputs alone), and
+// only the bin boundaries come back.
+hipError_t sort_bins(uvmem_ctx *c) {
+    const int C = c->nchan;
+    const size_t nbin = (size_t)c->tr_nbx * c->tr_nby;
+    double *u = (double *)c->d_R, *v = u + c->ztot;
+    float *vis = (float *)c->d_vpart, *w = vis + 2 * c->ztot;
+    hipError_t e = hipSuccess;
+    auto ok = [&](hipError_t x) { if (e == hipSuccess) e = x; };
     for (int ch = 0; ch < C; ++ch) {
-        const int64_t b = c->off[ch], e = c->off[ch + 1];
-        c->h_vis_base[ch] = (int)vis.size();
-        for (int64_t k = b; k < e; k += c->vis_blk)
-            vis.push_back(VisItem{ch, 0, (long long)k, (long long)std::min<int64_t>(k + c->vis_blk, e)});
+        const size_t nv = (size_t)c->nvis[ch], o = (size_t)c->off[ch];
+        if (nv == 0) continue;
+        ok(hipMemcpy(u + o, c->hu[ch].data(), nv * 8, hipMemcpyHostToDevice));
+        ok(hipMemcpy(v + o, c->hv[ch].data(), nv * 8, hipMemcpyHostToDevice));
+        ok(hipMemcpy(vis + 2 * o, c->hvis[ch].data(), nv * 8, hipMemcpyHostToDevice));
+        ok(hipMemcpy(w + o, c->hw[ch].data(), nv * 4, hipMemcpyHostToDevice));
     }
-    c->h_vis_base[C] = (int)vis.size();
+    if (e == hipSuccess) e = launch_tr_sort(c, u, v, vis, w);
+    std::vector<int> start(C * nbin + 1), first(C * nbin + 1);
+    ok(hipMemcpy(start.data(), c->d_trbin, start.size() * sizeof(int), hipMemcpyDeviceToHost));
+    if (e != hipSuccess) return e;
+    // an item's visibilities: enough items to fill the chip, few tiles
+    const int64_t chunk = std::max<int64_t>(64, std::min<int64_t>(1024, (c->ztot / 8192 + 31) / 32 * 32));
+    std::vector<TrItem> items;
+    for (size_t t = 0; t < C * nbin; ++t) {
+        first[t] = (int)items.size();
+        const int bin = (int)(t % nbin);
+        for (int64_t k = start[t]; k < start[t + 1]; k += chunk)
+            items.push_back(TrItem{(int)(t / nbin), bin / c->tr_nby, bin % c->tr_nby, 0, (long long)k,
+                                   (long long)std::min<int64_t>(k + chunk, start[t + 1])});
+    }
+    first[C * nbin] = c->n_tritem = (int)items.size();
+    const size_t ts = 2 * (size_t)(c->tr_w - 1);
+    ok(dalloc(c, &c->d_tritem, items.size()));
+    ok(dalloc(c, &c->d_trtile, items.size() * ts * ts));
+    if (e == hipSuccess)
+        ok(hipMemcpy(c->d_tritem, items.data(), items.size() * sizeof(TrItem), hipMemcpyHostToDevice));
+    if (e == hipSuccess) ok(hipMemcpy(c->d_trbin, first.data(), first.size() * sizeof(int), hipMemcpyHostToDevice));
+    // the staging buffers start out as zeros again
+    if (e == hipSuccess) ok(hipMemset(c->d_R, 0, c->ztot * sizeof(double2)));
+    if (e == hipSuccess) ok(hipMemset(c->d_Vd, 0, c->ztot * sizeof(double2)));
+    return e;
+}
+
+// Work lists of the direct contraction (adjoint items and slots, forward
+// items; the restricted pair under a focus-of-attention mask).
+struct DirectLists {
+    std::vector<AdjItem> adj, adj_m;
+    std::vector<FwdPItem> fwdp, fwdp_m;
+    std::vector<int> slot_base, slot_base_m;
+    int slots = 0, slots_m = 0, fparts_m = 0;
+    bool region = false;
+};
+void direct_lists(const uvmem_ctx *c, DirectLists &d) {
+    const int C = c->nchan, n = c->n;
     // focus of attention: the union of the image planes' masks decides which
     // forward image blocks and adjoint pixel tiles the CG's direction
     // forward model and gradient adjoint visit (outside it the direction is
     // zero and the gradient is not needed)
     std::vector<unsigned char> umask;
-    bool region = false;
+    bool &region = d.region;
     if (c->fwd_model == UVMEM_FWD_DFT) {
         umask.assign((size_t)n * n, 0);
         for (int m = 0; m < c->nimg; ++m) {
@@ -637,18 +753,15 @@ int finalize_impl(uvmem_ctx *c) {
         });
         return slot;
     };
-    std::vector<AdjItem> adj, adj_m;
-    std::vector<int> slot_base_m;
     const int ntile = c->adj_nt * c->adj_nt;
-    int slot = build_adj(std::vector<char>(ntile, 1), adj, c->h_slot_base);
-    int slots_m = 0;
+    d.slots = build_adj(std::vector<char>(ntile, 1), d.adj, d.slot_base);
     if (region) {
         std::vector<char> used(ntile, 0);
         for (int ti = 0; ti < c->adj_nt; ++ti)
             for (int tj = 0; tj < c->adj_nt; ++tj)
                 used[(size_t)ti * c->adj_nt + tj] =
                     rect_used(ti * c->adj_tt, (ti + 1) * c->adj_tt, tj * c->adj_tt, (tj + 1) * c->adj_tt);
-        slots_m = build_adj(used, adj_m, slot_base_m);
+        d.slots_m = build_adj(used, d.adj_m, d.slot_base_m);
     }
     // ---- persistent forward: one resident workgroup per CU; the
     // (channel, image block) pairs are shared by g_c workgroups each, with
@@ -698,23 +811,68 @@ int finalize_impl(uvmem_ctx *c) {
             return (double)c->nvis[x.chan] / x.nwg > (double)c->nvis[y.chan] / y.nwg;
         });
     };
-    std::vector<FwdPItem> fwdp, fwdp_m;
-    c->n_fparts_m = 0;
     if (c->fwd_model == UVMEM_FWD_DFT) {
         const int nblk = c->n_ib * c->n_jb;
         std::vector<int> part_of(nblk);
         for (int b = 0; b < nblk; ++b) part_of[b] = b;
-        build_fwd(part_of, fwdp);
+        build_fwd(part_of, d.fwdp);
         if (region) {
             for (int ib = 0; ib < c->n_ib; ++ib)
                 for (int jb = 0; jb < c->n_jb; ++jb)
                     part_of[(size_t)ib * c->n_jb + jb] =
                         rect_used(ib * c->ib_rows, (ib + 1) * c->ib_rows, jb * c->jb_cols, (jb + 1) * c->jb_cols)
-                            ? c->n_fparts_m++
+                            ? d.fparts_m++
                             : -1;
-            build_fwd(part_of, fwdp_m);
+            build_fwd(part_of, d.fwdp_m);
         }
     }
+}
+
+int finalize_impl(uvmem_ctx *c) {
+    const int C = c->nchan;
+    for (int ch = 0; ch < C; ++ch) {
+        if (!c->has_uv[ch]) return fail(c, UVMEM_ESTATE, "channel %d has no uv", ch);
+        if (!c->has_vis[ch]) return fail(c, UVMEM_ESTATE, "channel %d has no visibilities", ch);
+        if (!c->has_w[ch]) return fail(c, UVMEM_ESTATE, "channel %d has no weights", ch);
+        if (!c->has_beam[ch]) return fail(c, UVMEM_ESTATE, "channel %d has no beam", ch);
+    }
+    if (!c->prior_set) return fail(c, UVMEM_ESTATE, "prior not set");
+    if (c->fwd_model == UVMEM_FWD_GRIDDED) {
+        int64_t z = 0;
+        for (int ch = 0; ch < C; ++ch) z += c->nvis[ch];
+        const int64_t L = (int64_t)1 << c->grid_lg;
+        if (z > (int64_t)INT32_MAX - 1) return fail(c, UVMEM_EINVAL, "gridded model: more than 2^31 visibilities");
+        if ((int64_t)C * (L * L + 1) > ((int64_t)1 << 30))
+            return fail(c, UVMEM_ENOMEM, "gridded model: cell tables of %d channels x %lld^2 cells too large", C,
+                        (long long)L);
+    }
+    HIPCHK(c, hipSetDevice(c->device));
+    c->fail_alloc_at = -1;
+    c->n_alloc = 0;
+    if (const char *env = std::getenv("UVMEM_TEST_FAIL_ALLOC")) c->fail_alloc_at = std::atoi(env);
+    build_layout(c);
+    const int n = c->n, np = c->np;
+    const size_t npix = (size_t)n * n;
+    const size_t rs = real_size(c);
+
+    // ---- work tables
+    std::vector<VisItem> vis;
+    c->h_vis_base.assign(C + 1, 0);
+    for (int ch = 0; ch < C; ++ch) {
+        const int64_t b = c->off[ch], e = c->off[ch + 1];
+        c->h_vis_base[ch] = (int)vis.size();
+        for (int64_t k = b; k < e; k += c->vis_blk)
+            vis.push_back(VisItem{ch, 0, (long long)k, (long long)std::min<int64_t>(k + c->vis_blk, e)});
+    }
+    c->h_vis_base[C] = (int)vis.size();
+    DirectLists d;
+    const bool tr = c->tr_lg > 0;
+    if (!tr) direct_lists(c, d);
+    const std::vector<AdjItem> &adj = d.adj, &adj_m = d.adj_m;
+    const std::vector<FwdPItem> &fwdp = d.fwdp, &fwdp_m = d.fwdp_m;
+    const std::vector<int> &slot_base_m = d.slot_base_m;
+    const bool region = d.region, split = c->prec == UVMEM_BF16X3 || c->prec == UVMEM_FP16X3;
+    const bool grid_adj = c->fwd_model == UVMEM_FWD_GRIDDED && c->grad_model == UVMEM_GRAD_ADJOINT;
     // the 256-tile FP32 adjoint folds at most ADJ_F32_SUM visibilities per
     // FP32 sum; when no chunk is longer, its partials are single FP32 sums and are
     // stored as such (half the traffic of the split-K planes)
@@ -723,10 +881,22 @@ int finalize_impl(uvmem_ctx *c) {
     for (auto &x : adj_m) maxchunk = std::max<int64_t>(maxchunk, x.kend - x.kbeg);
     c->gpart_f32 = split || (c->prec == UVMEM_FP32 && c->adj_tt == 256 && !grid_adj && maxchunk <= ADJ_F32_SUM);
     c->n_fwdp = (int)fwdp.size();
+    c->n_adj = (int)adj.size();
     c->n_fwdp_m = (int)fwdp_m.size();
     c->n_adj_m = (int)adj_m.size();
-    c->n_slots_m = slots_m;
+    c->n_slots = d.slots;
+    c->n_slots_m = d.slots_m;
+    c->n_fparts_m = c->n_vparts_m = d.fparts_m;
     c->has_region = region;
+    c->h_slot_base = d.slot_base;
+    if (tr) {
+        // one forward partial and one FP64 adjoint plane per channel; a
+        // region saves nothing there, so every pass covers the whole image
+        c->h_slot_base.resize(C + 1);
+        for (int ch = 0; ch <= C; ++ch) c->h_slot_base[ch] = ch;
+        c->n_vparts = c->n_vparts_m = 1;
+        c->gpart_f32 = false;
+    }
     // image planes: channel ranges, visibility-item ranges, channel -> image
     const int IMG = c->nimg;
     c->h_ichan_base.assign(IMG + 1, 0);
@@ -735,15 +905,15 @@ int finalize_impl(uvmem_ctx *c) {
     for (int m = 0; m <= IMG; ++m) c->h_ichan_base[m] = IMG == C ? m : (m == 0 ? 0 : C);
     for (int m = 0; m <= IMG; ++m) c->h_ivis_base[m] = c->h_vis_base[c->h_ichan_base[m]];
     for (int ch = 0; ch < C; ++ch) c->h_chan_img[ch] = IMG == C ? ch : 0;
-    c->n_slots = slot;
-    c->n_adj = (int)adj.size();
     c->n_visit = (int)vis.size();
 
     // ---- host-side conversions
-    std::vector<double> a(c->ztot), bb(c->ztot);
-    std::vector<double> vo(2 * c->ztot);
-    std::vector<float> w(c->ztot);
-    for (int ch = 0; ch < C; ++ch) {
+    // (the fast evaluation's are made on the device, below)
+    const int64_t zh = tr ? 0 : c->ztot;
+    std::vector<double> a(zh), bb(zh);
+    std::vector<double> vo(2 * zh);
+    std::vector<float> w(zh);
+    for (int ch = 0; ch < C && !tr; ++ch) {
         const int64_t o = c->off[ch];
         for (int64_t k = 0; k < c->nvis[ch]; ++k) {
             a[o + k] = c->hu[ch][k] * c->cell;
@@ -762,6 +932,18 @@ int finalize_impl(uvmem_ctx *c) {
                 vo[2 * (o + k) + 1] = c->hvis[ch][2 * k + 1];
             }
             w[o + k] = c->hw[ch][k];
+        }
+    }
+    // ---- fast evaluation: window and twiddles
+    std::vector<double> trpoly, trdec, trtw;
+    if (tr) {
+        const int L = 1 << c->tr_lg;
+        transform_window(c->tr_w, c->tr_w == 17 ? TR_NE17 : TR_NE9, n, L, trpoly, trdec);
+        trtw.resize(2 * (size_t)L);
+        for (int k = 0; k < L; ++k) {
+            const long double ang = -2.0L * 3.141592653589793238462643383279502884L * k / L;
+            trtw[2 * k] = (double)std::cos(ang);
+            trtw[2 * k + 1] = (double)std::sin(ang);
         }
     }
     // ---- gridded model: twiddles (FP64, rounded to the transform type) and
@@ -845,22 +1027,6 @@ int finalize_impl(uvmem_ctx *c) {
             if (!c->hmask[m].empty()) std::memcpy(mask.data() + (size_t)m * npix, c->hmask[m].data(), npix);
     }
 
-    std::vector<char> beam(C * npix * rs);
-    for (int ch = 0; ch < C; ++ch) {
-        for (size_t p = 0; p < npix; ++p) {
-            double A;
-            if (!c->hbeam[ch].empty()) {
-                A = c->hbeam[ch][p];
-            } else {
-                const double x = (double)((int)(p % n) - n / 2) * c->cell - c->cx[ch];
-                const double y = (double)((int)(p / n) - n / 2) * c->cell - c->cy[ch];
-                A = std::exp(-4.0 * std::log(2.0) * (x * x + y * y) / (c->fwhm[ch] * c->fwhm[ch]));
-            }
-            if (rs == 8) reinterpret_cast<double *>(beam.data())[ch * npix + p] = A;
-            else reinterpret_cast<float *>(beam.data())[ch * npix + p] = (float)A;
-        }
-    }
-
     // ---- device allocation
     hipError_t e = hipSuccess;
     auto ok = [&](hipError_t x) { if (e == hipSuccess) e = x; };
@@ -879,9 +1045,20 @@ int finalize_impl(uvmem_ctx *c) {
     ok(dalloc(c, &c->d_chan_img, C));
     ok(dalloc(c, &c->d_R, c->ztot));
     ok(dalloc(c, &c->d_Vd, c->ztot));
-    ok(dalloc(c, &c->d_vpart, (size_t)c->n_fparts * c->ztot));
-    ok(dalloc(c, (char **)&c->d_gpart,
-              (size_t)std::max(c->n_slots, c->n_slots_m) * np * np * (c->gpart_f32 ? sizeof(float) : sizeof(double))));
+    ok(dalloc(c, &c->d_vpart, (size_t)c->n_vparts * c->ztot));
+    const size_t planes = tr ? (size_t)C : (size_t)std::max(c->n_slots, c->n_slots_m);
+    ok(dalloc(c, (char **)&c->d_gpart, planes * np * np * (c->gpart_f32 ? sizeof(float) : sizeof(double))));
+    if (tr) {
+        const size_t L = (size_t)1 << c->tr_lg;
+        const size_t lx = L / 2 + 2 * c->tr_h + 1;
+        ok(dalloc(c, &c->d_trbin, (size_t)C * c->tr_nbx * c->tr_nby + 1));
+        ok(dalloc(c, &c->d_trperm, c->ztot));
+        ok(dalloc(c, &c->d_trdec, trdec.size()));
+        ok(dalloc(c, &c->d_trpoly, trpoly.size()));
+        ok(dalloc(c, &c->d_trtw, L));
+        ok(dalloc(c, &c->d_trx, C * lx * n));
+        ok(dalloc(c, &c->d_trg, C * c->tr_lgc * L));
+    }
     if (region) {
         ok(dalloc(c, &c->d_fwdp_m, fwdp_m.size()));
         ok(dalloc(c, &c->d_adj_m, adj_m.size()));
@@ -927,7 +1104,10 @@ int finalize_impl(uvmem_ctx *c) {
     up(c->d_b, bb.data(), bb.size() * 8);
     up(c->d_vo, vo.data(), vo.size() * 8);
     up(c->d_w, w.data(), w.size() * 4);
-    up(c->d_beam, beam.data(), beam.size());
+    // Gaussian beams are computed on the device; given beam images go through
+    // a staging copy there
+    for (int ch = 0; ch < C && e == hipSuccess; ++ch)
+        e = c->hbeam[ch].empty() ? launch_beam(c, ch) : upload_beam(c, ch);
     up(c->d_fwdp, fwdp.data(), fwdp.size() * sizeof(FwdPItem));
     up(c->d_adj, adj.data(), adj.size() * sizeof(AdjItem));
     up(c->d_vis, vis.data(), vis.size() * sizeof(VisItem));
@@ -943,6 +1123,12 @@ int finalize_impl(uvmem_ctx *c) {
         up(c->d_slot_base_m, slot_base_m.data(), (C + 1) * sizeof(int));
     }
     if (any_mask) up(c->d_mask, mask.data(), mask.size());
+    if (tr) {
+        up(c->d_trdec, trdec.data(), trdec.size() * 8);
+        up(c->d_trpoly, trpoly.data(), trpoly.size() * 8);
+        up(c->d_trtw, trtw.data(), trtw.size() * 8);
+        if (e == hipSuccess) e = sort_bins(c);
+    }
     if (gridded) {
         up(c->d_gtw, gtw.data(), gtw.size());
         up(c->d_gcell, gcell.data(), gcell.size() * sizeof(int));
@@ -955,7 +1141,7 @@ int finalize_impl(uvmem_ctx *c) {
     if (e != hipSuccess) {
         free_all(c);
         (void)hipGetLastError();
-        return fail(c, UVMEM_EDEVICE, "upload: %s", hipGetErrorString(e));
+        return fail(c, e == hipErrorOutOfMemory ? UVMEM_ENOMEM : UVMEM_EDEVICE, "upload: %s", hipGetErrorString(e));
     }
     e = hipDeviceSynchronize();
     if (e != hipSuccess) {
@@ -1013,7 +1199,9 @@ int uvmem_get_residual(uvmem_ctx *c, void *res) {
     int s = check_ready(c);
     if (s) return s;
     if (!res && c->ztot) return fail(c, UVMEM_EINVAL, "null output");
-    if (c->ztot)
+    if (c->tr_lg)
+        HIPCHK(c, launch_tr_permute(c, c->d_R, (double2 *)res, 0, c->stream));
+    else if (c->ztot)
         HIPCHK(c, hipMemcpyAsync(res, c->d_R, c->ztot * sizeof(double2), hipMemcpyDeviceToDevice, c->stream));
     return UVMEM_OK;
 }
@@ -1228,6 +1416,9 @@ int uvmem_cg_get_state(uvmem_ctx *c, void *blob, size_t *bytes) {
     if (!blob) { *bytes = need; return UVMEM_OK; }
     if (*bytes < need) return fail(c, UVMEM_EINVAL, "state buffer too small (%zu < %zu)", *bytes, need);
     if (!c->cg_ready) return fail(c, UVMEM_ESTATE, "no CG state");
+    // the blob holds R in the caller's order (Vd is scratch between steps)
+    const double2 *R = c->tr_lg ? c->d_Vd : c->d_R;
+    if (c->tr_lg) HIPCHK(c, launch_tr_permute(c, c->d_R, c->d_Vd, 0, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     char *p = (char *)blob;
     StateHeader h{STATE_MAGIC, c->n, c->nchan, c->prec, c->mode, c->fwd_model, c->grid_lg, c->grad_model, 0, c->ztot};
@@ -1236,7 +1427,7 @@ int uvmem_cg_get_state(uvmem_ctx *c, void *blob, size_t *bytes) {
     HIPCHK(c, hipMemcpy(p, c->d_dir, img, hipMemcpyDeviceToHost)); p += img;
     HIPCHK(c, hipMemcpy(p, c->d_gt, img, hipMemcpyDeviceToHost)); p += img;
     HIPCHK(c, hipMemcpy(p, c->d_g, img, hipMemcpyDeviceToHost)); p += img;
-    if (c->ztot) HIPCHK(c, hipMemcpy(p, c->d_R, c->ztot * sizeof(double2), hipMemcpyDeviceToHost));
+    if (c->ztot) HIPCHK(c, hipMemcpy(p, R, c->ztot * sizeof(double2), hipMemcpyDeviceToHost));
     p += c->ztot * sizeof(double2);
     HIPCHK(c, hipMemcpy(p, c->d_scal, c->nimg * UVMEM_NSCAL * sizeof(double), hipMemcpyDeviceToHost));
     p += c->nimg * UVMEM_NSCAL * sizeof(double);
@@ -1265,7 +1456,12 @@ int uvmem_cg_set_state(uvmem_ctx *c, const void *blob, size_t bytes) {
     HIPCHK(c, hipMemcpy(c->d_dir, p, img, hipMemcpyHostToDevice)); p += img;
     HIPCHK(c, hipMemcpy(c->d_gt, p, img, hipMemcpyHostToDevice)); p += img;
     HIPCHK(c, hipMemcpy(c->d_g, p, img, hipMemcpyHostToDevice)); p += img;
-    if (c->ztot) HIPCHK(c, hipMemcpy(c->d_R, p, c->ztot * sizeof(double2), hipMemcpyHostToDevice));
+    if (c->ztot)
+        HIPCHK(c, hipMemcpy(c->tr_lg ? c->d_Vd : c->d_R, p, c->ztot * sizeof(double2), hipMemcpyHostToDevice));
+    if (c->tr_lg) {
+        HIPCHK(c, launch_tr_permute(c, c->d_Vd, c->d_R, 1, c->stream));
+        HIPCHK(c, hipStreamSynchronize(c->stream));
+    }
     p += c->ztot * sizeof(double2);
     HIPCHK(c, hipMemcpy(c->d_scal, p, c->nimg * UVMEM_NSCAL * sizeof(double), hipMemcpyHostToDevice));
     p += c->nimg * UVMEM_NSCAL * sizeof(double);
@@ -1316,11 +1512,24 @@ int uvmem_timing_read(uvmem_ctx *c, int which, double *total_ms, int64_t *count,
 
 int uvmem_info(const uvmem_ctx *c, int64_t *out, int nout) {
     if (!c || !out) return UVMEM_EINVAL;
-    const int64_t vals[] = {c->n, c->np, c->nchan, c->prec, c->ztot, c->n_fparts, c->adj_tt, c->n_slots,
-                            c->n_fwdp, c->n_adj, c->n_visit, (int64_t)c->bytes_device, c->n_pb, c->pix_blk,
+    // with the fast evaluation the direct contraction's lists exist for this
+    // call only (and only if asked for: entry 7 is the first of them)
+    DirectLists d;
+    const bool tr = c->tr_lg > 0;
+    if (tr && nout > 7) {
+        try {
+            direct_lists(c, d);
+        } catch (...) {
+            return UVMEM_ENOMEM;
+        }
+    }
+    const int64_t vals[] = {c->n, c->np, c->nchan, c->prec, c->ztot, c->n_fparts, c->adj_tt,
+                            tr ? d.slots : c->n_slots, tr ? (int64_t)d.fwdp.size() : c->n_fwdp,
+                            tr ? (int64_t)d.adj.size() : c->n_adj, c->n_visit, (int64_t)c->bytes_device, c->n_pb, c->pix_blk,
                             c->vis_blk, c->nimg, c->fwd_model,
                             c->fwd_model == UVMEM_FWD_GRIDDED ? (int64_t)1 << c->grid_lg : 0, c->grad_model,
-                            c->n_fwdp_m, c->n_adj_m};
+                            tr ? (int64_t)d.fwdp_m.size() : c->n_fwdp_m, tr ? (int64_t)d.adj_m.size() : c->n_adj_m,
+                            c->tr_lg ? (int64_t)1 << c->tr_lg : 0};
     const int nv = (int)(sizeof vals / sizeof vals[0]);
     for (int i = 0; i < nout && i < nv; ++i) out[i] = vals[i];
     return UVMEM_OK;

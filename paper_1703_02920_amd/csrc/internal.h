@@ -36,6 +36,10 @@ constexpr double BOUND_TOL = 1e-12;
 // Gridded model: cells holding more visibilities than this are reduced by a
 // wave each before the node gather (bounds the gather's serial loops).
 constexpr int GRID_DENSE = 16;
+// Fast evaluation of the DFT (k_trans.hip): coefficients per parity and tap
+// pair of the window polynomials of width 9 and 17 (FP64 accuracy), and the
+// largest half width.
+constexpr int TR_NE9 = 7, TR_NE17 = 11, TR_HMAX = 8;
 // Default number of line-search passes per CG step after the start in the
 // direction's visibility pass (which already settles a step that reaches
 // alpha_max); a channel whose search has converged skips the remaining passes.
@@ -62,6 +66,17 @@ struct AdjItem {
     int ti;
     int tj;
     int slot;
+    long long kbeg;
+    long long kend;
+};
+
+// One wave of the fast evaluation's tile kernels: visibilities [kbeg, kend)
+// of one bin (bx, by) of a channel.
+struct TrItem {
+    int chan;
+    int bx;
+    int by;
+    int pad;
     long long kbeg;
     long long kend;
 };
@@ -150,7 +165,8 @@ struct uvmem_ctx {
     int64_t ztot = 0;
     int ib_rows = 0, n_ib = 0;         // forward i-blocks (image rows per block)
     int jb_cols = 0, n_jb = 1;         // forward j-blocks (image columns per block)
-    int n_fparts = 0;                  // forward partials per visibility: n_ib * n_jb
+    int n_fparts = 0;                  // image blocks of the direct forward: n_ib * n_jb
+    int n_vparts = 0, n_vparts_m = 0;  // forward partials per visibility in use (whole image / region)
     int adj_tt = 0, adj_nt = 0;        // adjoint tile side, tiles per side
     int n_slots = 0;
     int n_pb = 0;                      // pixel blocks per image plane
@@ -216,6 +232,17 @@ struct uvmem_ctx {
     int2 *d_gdlist = nullptr;
     double2 *d_gdsum = nullptr;
     int n_gdense = 0;
+    // fast evaluation of the DFT (k_trans.hip), used when tr_lg > 0: grid
+    // side 2^tr_lg, window width tr_w = 2 tr_h + 1, grid columns allocated
+    // tr_lgc, bins of a channel tr_nbx x tr_nby.  Visibilities are then kept
+    // in bin order: d_trperm[k] = caller's index << 1 | negated.
+    int tr_lg = 0, tr_w = 0, tr_h = 0, tr_lgc = 0, tr_nbx = 0, tr_nby = 0;
+    int n_tritem = 0;
+    uvm::TrItem *d_tritem = nullptr;
+    int *d_trbin = nullptr;                     // first item of each bin, [C][nbx][nby] + 1
+    unsigned *d_trperm = nullptr;
+    double *d_trdec = nullptr, *d_trpoly = nullptr;
+    double2 *d_trtw = nullptr, *d_trx = nullptr, *d_trg = nullptr, *d_trtile = nullptr;
     size_t bytes_device = 0;
 
     // CG
@@ -253,7 +280,9 @@ hipError_t launch_forward(const uvmem_ctx *c, const void *bop, hipStream_t st, i
 // Adjoint: gpart[slot] tiles of Re F^H (w coef) without the beam factor.
 // grad != 0: a gradient, needed inside a focus region only (its own tiles
 // and split-K slot table).
-hipError_t launch_adjoint(const uvmem_ctx *c, const double2 *coef, const float *w, hipStream_t st, int grad = 0);
+// caller != 0: coef is in the caller's visibility order.
+hipError_t launch_adjoint(const uvmem_ctx *c, const double2 *coef, const float *w, hipStream_t st, int grad = 0,
+                          int caller = 0);
 // Workgroups of that adjoint kernel resident on one CU at once (occupancy of
 // the compiled kernel; at least 1).
 int adjoint_wgs_per_cu(const uvmem_ctx *c);
@@ -262,6 +291,21 @@ int adjoint_wgs_per_cu(const uvmem_ctx *c);
 // channel's plane gpart[slot_base[c]] (one slot per channel).
 hipError_t launch_grid_forward(const uvmem_ctx *c, const void *bop, hipStream_t st);
 hipError_t launch_grid_adjoint(const uvmem_ctx *c, const double2 *coef, const float *w, hipStream_t st);
+
+// Fast evaluation of the DFT and its adjoint (k_trans.hip): as
+// launch_grid_forward / launch_grid_adjoint; perm (may be null) marks
+// coefficients in the caller's order.  launch_tr_permute copies a visibility
+// vector from bin order to the caller's (to_bins = 0) or back (1).
+hipError_t launch_tr_forward(const uvmem_ctx *c, const void *bop, hipStream_t st);
+hipError_t launch_tr_adjoint(const uvmem_ctx *c, const double2 *coef, const float *w, const unsigned *perm,
+                             hipStream_t st);
+// Finalize: sort the visibilities of raw arrays (device, caller's order) by
+// bin into the context's a, b, V^o, w and permutation; d_trbin gets the first
+// visibility of each bin.  Uses d_Vd as scratch.
+hipError_t launch_tr_sort(const uvmem_ctx *c, const double *u, const double *v, const float *vis, const float *w);
+// Gaussian primary beam of a channel.
+hipError_t launch_beam(const uvmem_ctx *c, int chan);
+hipError_t launch_tr_permute(const uvmem_ctx *c, const double2 *src, double2 *dst, int to_bins, hipStream_t st);
 
 // The FP32 forward on explicit buffers (the allocation-free entry point):
 // image blocks ib_rows x jb_cols (128 x 256, 128 x 128 or 64 x 64), work

@@ -201,7 +201,8 @@ __global__ __launch_bounds__(NTHR) void k_prologue(const R *__restrict__ I, cons
 }
 
 // ---------------------------------------------------------------- visibilities
-// mode 0: out[k] = V_k (model visibilities)
+// mode 0: out[k] = V_k (model visibilities); with perm, into the caller's
+//         order (out[perm[k] >> 1], conjugated where perm[k] is odd)
 // mode 1: R_k = V_k - Vo_k -> R; partial[0] = sum w |R|^2
 // mode 2: Vd_k = V_k -> Vd; partial[0] = sum w |Vd|^2, partial[1] = sum w Re(conj(R) Vd)
 // mode 3: R_k += alpha_c Vd_k; partial[0] = sum w |R|^2
@@ -212,7 +213,8 @@ __device__ __forceinline__ void vis_item(const VisItem it, int item, const doubl
                                          int n_parts, long long ztot, const double2 *__restrict__ vo,
                                          const float *__restrict__ w, double2 *__restrict__ R,
                                          double2 *__restrict__ Vd, double2 *__restrict__ out,
-                                         double *__restrict__ vispart, int mode, int with_max, double alpha) {
+                                         double *__restrict__ vispart, int mode, int with_max, double alpha,
+                                         const unsigned *__restrict__ perm = nullptr) {
     double acc[2] = {0.0, 0.0};
     double cmax = 0.0;   // max |Re|, |Im| of the adjoint's coefficients w R (mode 4: R alone)
     constexpr int U = 2;   // visibilities per thread and round, loads issued together
@@ -272,7 +274,8 @@ __device__ __forceinline__ void vis_item(const VisItem it, int item, const doubl
             if (k >= it.kend) continue;
             const double wv = ww[u];
             if (mode == 0) {
-                out[k] = v[u];
+                const unsigned pk = perm ? perm[k] : 0u;
+                out[perm ? (long long)(pk >> 1) : k] = make_double2(v[u].x, pk & 1u ? -v[u].y : v[u].y);
             } else if (mode == 1) {
                 const double2 o = ld[u];
                 const double2 r = make_double2(v[u].x - (double)o.x, v[u].y - (double)o.y);
@@ -321,11 +324,11 @@ __global__ __launch_bounds__(NTHR) void k_vis(const VisItem *__restrict__ items,
                                               double2 *__restrict__ R, double2 *__restrict__ Vd,
                                               double2 *__restrict__ out, const double *__restrict__ scal,
                                               double *__restrict__ vispart, const int *__restrict__ chan_img,
-                                              int mode, int with_max) {
+                                              int mode, int with_max, const unsigned *__restrict__ perm) {
     const VisItem it = items[blockIdx.x];
     const int img = chan_img ? chan_img[it.chan] : 0;
     const double alpha = mode == 3 ? scal[(size_t)img * UVMEM_NSCAL + UVMEM_S_ALPHA] : 0.0;
-    vis_item(it, blockIdx.x, vpart, n_parts, ztot, vo, w, R, Vd, out, vispart, mode, with_max, alpha);
+    vis_item(it, blockIdx.x, vpart, n_parts, ztot, vo, w, R, Vd, out, vispart, mode, with_max, alpha, perm);
 }
 
 // ---------------------------------------------------------------- gradient
@@ -1057,7 +1060,7 @@ inline double *pp(const uvmem_ctx *c, int buf) {
 inline unsigned *ctr(const uvmem_ctx *c, int site) { return c->d_ctr + (size_t)site * c->nimg; }
 // The fp16 split adjoint scales its coefficients by the channel's max |w R|,
 // which the visibility pass leaves in slot 2 of its partial records.
-inline int adj_scaled(const uvmem_ctx *c) { return c->prec == UVMEM_FP16X3 ? 1 : 0; }
+inline int adj_scaled(const uvmem_ctx *c) { return c->prec == UVMEM_FP16X3 && !c->tr_lg ? 1 : 0; }
 
 template <typename R>
 hipError_t t_prologue(const uvmem_ctx *c, const void *I, int with_entropy, hipStream_t st) {
@@ -1125,7 +1128,7 @@ hipError_t t_cg_phase(const uvmem_ctx *c, void *I, double *user, int phase, hipS
         // at alpha_max; the line search starts from them
         if (c->n_visit)
             hipLaunchKernelGGL(k_cg_vis<R>, dim3(c->n_visit + pix_grid(c)), blk, 0, st, c->d_vis, c->n_visit,
-                               c->d_vpart, c->has_region ? c->n_fparts_m : c->n_fparts, (long long)c->ztot,
+                               c->d_vpart, c->has_region ? c->n_vparts_m : c->n_vparts, (long long)c->ztot,
                                c->d_w, c->d_R, c->d_Vd, c->d_vispart, c->d_chan_img, c->d_ivis_base, CP<R>(I),
                                CP<R>(c->d_dir), pp(c, 1), c->n, c->n_pb, c->pix_blk, c->M, c->lam, c->d_chan,
                                c->d_ls, ctr(c, CTR_VIS));
@@ -1181,9 +1184,9 @@ hipError_t launch_prologue(const uvmem_ctx *c, const void *I, int with_entropy, 
 
 hipError_t launch_vis_sum(const uvmem_ctx *c, int mode, double2 *out, hipStream_t st) {
     if (c->n_visit == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_vis, dim3(c->n_visit), dim3(NTHR), 0, st, c->d_vis, c->d_vpart, c->n_fparts,
+    hipLaunchKernelGGL(k_vis, dim3(c->n_visit), dim3(NTHR), 0, st, c->d_vis, c->d_vpart, c->n_vparts,
                        (long long)c->ztot, c->d_vo, c->d_w, c->d_R, c->d_Vd, out, c->d_scal, c->d_vispart,
-                       c->d_chan_img, mode, adj_scaled(c));
+                       c->d_chan_img, mode, adj_scaled(c), c->d_trperm);
     return hipGetLastError();
 }
 
@@ -1192,15 +1195,16 @@ hipError_t launch_vis_sum_raw(const VisItem *items, int n_items, const double2 *
     if (n_items == 0) return hipSuccess;
     hipLaunchKernelGGL(k_vis, dim3(n_items), dim3(NTHR), 0, st, items, vpart, n_parts, ztot,
                        (const double2 *)nullptr, (const float *)nullptr, (double2 *)nullptr, (double2 *)nullptr,
-                       out, (const double *)nullptr, (double *)nullptr, (const int *)nullptr, 0, 0);
+                       out, (const double *)nullptr, (double *)nullptr, (const int *)nullptr, 0, 0,
+                       (const unsigned *)nullptr);
     return hipGetLastError();
 }
 
 hipError_t launch_coef_max(const uvmem_ctx *c, const double2 *coef, hipStream_t st) {
     if (c->n_visit == 0 || !adj_scaled(c)) return hipSuccess;
-    hipLaunchKernelGGL(k_vis, dim3(c->n_visit), dim3(NTHR), 0, st, c->d_vis, c->d_vpart, c->n_fparts,
+    hipLaunchKernelGGL(k_vis, dim3(c->n_visit), dim3(NTHR), 0, st, c->d_vis, c->d_vpart, c->n_vparts,
                        (long long)c->ztot, c->d_vo, (const float *)nullptr, const_cast<double2 *>(coef), c->d_Vd,
-                       (double2 *)nullptr, c->d_scal, c->d_vispart, c->d_chan_img, 4, 1);
+                       (double2 *)nullptr, c->d_scal, c->d_vispart, c->d_chan_img, 4, 1, (const unsigned *)nullptr);
     return hipGetLastError();
 }
 

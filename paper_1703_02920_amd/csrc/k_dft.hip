@@ -1628,6 +1628,7 @@ hipError_t launch_forward_f32_raw(int ib_rows, int jb_cols, const FwdPItem *item
 
 hipError_t launch_forward(const uvmem_ctx *c, const void *bop, hipStream_t st, int dir) {
     if (c->fwd_model == UVMEM_FWD_GRIDDED) return launch_grid_forward(c, bop, st);
+    if (c->tr_lg) return launch_tr_forward(c, bop, st);
     // the direction of a region-restricted CG is zero outside the region
     const bool rg = dir && c->has_region;
     const FwdPItem *it = rg ? c->d_fwdp_m : c->d_fwdp;
@@ -1667,7 +1668,9 @@ int adjoint_wgs_per_cu(const uvmem_ctx *c) {
     return (e == hipSuccess && nb > 0) ? nb : 1;
 }
 
-hipError_t launch_adjoint(const uvmem_ctx *c, const double2 *coef, const float *w, hipStream_t st, int grad) {
+hipError_t launch_adjoint(const uvmem_ctx *c, const double2 *coef, const float *w, hipStream_t st, int grad,
+                          int caller) {
+    if (c->tr_lg) return launch_tr_adjoint(c, coef, w, caller ? c->d_trperm : nullptr, st);
     if (c->fwd_model == UVMEM_FWD_GRIDDED && c->grad_model == UVMEM_GRAD_ADJOINT)
         return launch_grid_adjoint(c, coef, w, st);
     // a gradient of a region-restricted problem is needed inside the region only

@@ -1,0 +1,915 @@
+// Fast exact evaluation of the direct DFT and its adjoint on gfx950.
+//
+// Both contractions of k_dft.hip cost Z N^2.  Here the same sums are
+// evaluated to working precision through an oversampled grid (a non-uniform
+// FFT; the window is the Kaiser-Bessel function, whose transform is closed
+// form): with x_m = m, m = j - N/2, L = 2^lg >= 2 N and a window phi of W
+// grid nodes,
+//   e^{-2 pi i a m} = (1 / phi^(m / L)) sum_q phi(q - a L) e^{-2 pi i q m / L}  (1 + eps),
+// so that
+//   V_k = sum_{p,q near (b_k L, a_k L)} phi phi G[q][p],
+//   G = DFT_L of B[i][j] / (phi^(m_i / L) phi^(m_j / L)) zero-padded to L x L,
+// and the adjoint is the transpose of that map.  eps is set by W alone:
+// W = 17 reaches FP64 rounding (measured against extended precision: 4e-15 of
+// |V| on 64^2 to 300^2 images, where the direct FP64 sum is at 4e-15 to
+// 1.1e-14), W = 9 stays near 1e-8 (the FP32 contraction is at 1e-7, the
+// split ones above).  Everything is computed in FP64 whatever the context's
+// precision, so only W changes with it.
+//
+// The image is real, hence V(-u, -v) = conj V(u, v): visibilities are kept
+// with a_k in [0, 1/2] (the others negated and conjugated once at finalize)
+// and the grid holds only the columns q = -H .. L/2 + H, H = (W - 1) / 2.
+// Visibilities are sorted by bin of TB x TB nearest nodes; a bin's windows
+// fit one TS x TS node tile (TS = TB + W - 1 = 16 or 32), and both directions
+// work on such tiles with FP64 matrix instructions: gathering is
+// T = (tile) (column windows) followed by a short dot with the row windows,
+// spreading is (column windows x coefficient)^T (row windows) with the
+// visibilities as the contraction dimension.  Overlapping tiles are summed
+// in a fixed order when the inverse transform reads them, so results are
+// bitwise reproducible.
+#include <algorithm>
+#include <cmath>
+#include <cstdlib>
+
+#include "internal.h"
+
+namespace uvm {
+namespace {
+
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ doublex4 mma(double a, double b, doublex4 c) {
+    // lane l: A[l%16][l/16], B[l/16][l%16]; D[4 r + l/16][l%16] in register r
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ double2 cmul(double2 a, double2 b) {
+    return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+}
+__device__ __forceinline__ double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
+__device__ __forceinline__ double2 csub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
+// multiplication by -i (forward) or +i (inverse)
+template <bool INV>
+__device__ __forceinline__ double2 crot(double2 a) {
+    return INV ? make_double2(-a.y, a.x) : make_double2(a.y, -a.x);
+}
+
+// ---------------------------------------------------------------- FFT
+// In-place radix-R butterflies, outputs in natural order.
+template <bool INV>
+__device__ __forceinline__ void dft2(double2 &a, double2 &b) {
+    const double2 t = csub(a, b);
+    a = cadd(a, b);
+    b = t;
+}
+template <bool INV>
+__device__ __forceinline__ void dft4(double2 &a0, double2 &a1, double2 &a2, double2 &a3) {
+    const double2 s0 = cadd(a0, a2), d0 = csub(a0, a2), s1 = cadd(a1, a3), d1 = crot<INV>(csub(a1, a3));
+    a0 = cadd(s0, s1);
+    a1 = cadd(d0, d1);
+    a2 = csub(s0, s1);
+    a3 = csub(d0, d1);
+}
+template <bool INV>
+__device__ __forceinline__ void dft8(double2 (&v)[8]) {
+    constexpr double C = 0.70710678118654752440;
+    double2 e0 = v[0], e1 = v[2], e2 = v[4], e3 = v[6];
+    double2 o0 = v[1], o1 = v[3], o2 = v[5], o3 = v[7];
+    dft4<INV>(e0, e1, e2, e3);
+    dft4<INV>(o0, o1, o2, o3);
+    // o_k *= e^{-+ 2 pi i k / 8}
+    const double2 r1 = crot<INV>(o1), r3 = crot<INV>(o3);
+    o1 = make_double2(C * (o1.x + r1.x), C * (o1.y + r1.y));
+    o2 = crot<INV>(o2);
+    o3 = make_double2(C * (r3.x - o3.x), C * (r3.y - o3.y));
+    v[0] = cadd(e0, o0);
+    v[1] = cadd(e1, o1);
+    v[2] = cadd(e2, o2);
+    v[3] = cadd(e3, o3);
+    v[4] = csub(e0, o0);
+    v[5] = csub(e1, o1);
+    v[6] = csub(e2, o2);
+    v[7] = csub(e3, o3);
+}
+
+// LDS element of sequence position o: one pad element per eight keeps the
+// stride-8 stores of the first pass on distinct banks.
+__device__ __forceinline__ constexpr int fpad(int o) { return o + (o >> 3); }
+
+// Radix of pass p for L = 2^LG (0 past the last): eights first, then fours.
+__host__ __device__ constexpr int fft_radix(int lg, int p) {
+    // lg = 3 e + 2 f with f in {0, 1, 2}
+    const int f = lg % 3 == 0 ? 0 : lg % 3 == 2 ? 1 : 2;
+    const int e = (lg - 2 * f) / 3;
+    return p < e ? 8 : p < e + f ? 4 : 0;
+}
+constexpr int fft_threads(int lg) { return (1 << lg) / 8; }
+
+// One Stockham pass: thread t of L/8 holds, for butterfly b < 8/R and leg r,
+// sequence position (t + b L/8) + r L/R; Ns is the product of the earlier
+// radices.  Multiplies by the pass's twiddles and transforms in registers.
+template <int LG, int R, int NS, bool INV>
+__device__ __forceinline__ void fft_butterflies(double2 (&v)[8], int t, const double2 *__restrict__ tw) {
+    constexpr int L = 1 << LG, T = L / 8, NB = 8 / R;
+    if constexpr (NS > 1) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int k = ((t + b * T) & (NS - 1)) * (L / (NS * R));
+            auto w = [&](int m) {
+                double2 x = tw[k * m];
+                if (INV) x.y = -x.y;
+                return x;
+            };
+            const double2 w1 = w(1), w2 = w(2);
+            v[b * R + 1] = cmul(v[b * R + 1], w1);
+            v[b * R + 2] = cmul(v[b * R + 2], w2);
+            const double2 w3 = cmul(w1, w2);
+            v[b * R + 3] = cmul(v[b * R + 3], w3);
+            if constexpr (R == 8) {
+                const double2 w4 = w(4);
+                v[4] = cmul(v[4], w4);
+                v[5] = cmul(v[5], cmul(w1, w4));
+                v[6] = cmul(v[6], cmul(w2, w4));
+                v[7] = cmul(v[7], cmul(w3, w4));
+            }
+        }
+    }
+    if constexpr (R == 8) {
+        dft8<INV>(v);
+    } else {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) dft4<INV>(v[b * 4], v[b * 4 + 1], v[b * 4 + 2], v[b * 4 + 3]);
+    }
+}
+
+// Passes P.. of the transform of L = 2^LG points held 8 per thread by the
+// L/8 threads of a sequence, exchanged through s (fpad'ed); every sequence of
+// the workgroup runs in step (__syncthreads).  On return leg r of butterfly b
+// holds output position (t + b L/8) + r L/R of the last pass's radix R.
+template <int LG, int P, int NS, bool INV>
+__device__ __forceinline__ void fft_passes(double2 (&v)[8], int t, double2 *s, const double2 *__restrict__ tw) {
+    constexpr int L = 1 << LG, T = L / 8;
+    constexpr int R = fft_radix(LG, P), RN = fft_radix(LG, P + 1);
+    fft_butterflies<LG, R, NS, INV>(v, t, tw);
+    if constexpr (RN != 0) {
+        __syncthreads();   // the buffer's earlier readers are done
+#pragma unroll
+        for (int b = 0; b < 8 / R; ++b) {
+            const int jj = t + b * T;
+            const int base = (jj / NS) * (NS * R) + (jj & (NS - 1));
+#pragma unroll
+            for (int r = 0; r < R; ++r) s[fpad(base + r * NS)] = v[b * R + r];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int b = 0; b < 8 / RN; ++b)
+#pragma unroll
+            for (int r = 0; r < RN; ++r) v[b * RN + r] = s[fpad(t + b * T + r * (L / RN))];
+        fft_passes<LG, P + 1, NS * R, INV>(v, t, s, tw);
+    }
+}
+// Radix of the last pass.
+constexpr int fft_last(int lg) {
+    int p = 0;
+    while (fft_radix(lg, p + 1)) ++p;
+    return fft_radix(lg, p);
+}
+// Output position of register x (leg x % R of butterfly x / R).
+template <int LG>
+__device__ __forceinline__ int fft_out(int t, int x) {
+    constexpr int R = fft_last(LG);
+    return t + (x / R) * ((1 << LG) / 8) + (x % R) * ((1 << LG) / R);
+}
+
+// Image index of transform position p (pixel offset p or p - L), -1 in the
+// zero padding.
+__device__ __forceinline__ int pix_of(int p, int L, int n) {
+    const int half = n / 2;
+    return p < half ? p + half : p >= L - half ? p - (L - half) : -1;
+}
+
+// Sequences per workgroup: at least a wave of threads, at most 512 threads
+// and 74 KiB of LDS.
+constexpr int row_seqs(int lg) { return lg <= 8 ? 4 : lg <= 11 ? 2 : 1; }
+constexpr int col_seqs(int lg) { return lg <= 7 ? 4 : lg <= 8 ? 2 : 1; }
+
+// Rows: two image rows (i, i + 1) form one complex sequence; their spectra
+// are separated by symmetry and stored as X[q + H][i], i contiguous, for the
+// columns q = -H .. L/2 + H.
+template <int LG, typename R>
+__global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_fwd(
+    const R *__restrict__ bop, double2 *__restrict__ X, const double2 *__restrict__ tw,
+    const double *__restrict__ dec, int n, int np, int H) {
+    constexpr int L = 1 << LG, T = fft_threads(LG), NF = row_seqs(LG);
+    __shared__ double2 s[NF][fpad(L)];
+    const int f = threadIdx.x / T, t = threadIdx.x % T;
+    const int c = blockIdx.y, i0 = (blockIdx.x * NF + f) * 2;
+    const int Lx = L / 2 + 2 * H + 1;
+    double2 v[8];
+    const bool live = i0 < n;   // n is even
+    const R *r0 = bop + ((size_t)c * np + (live ? i0 : 0)) * np;
+    const double d0 = live ? dec[i0] : 0.0, d1 = live ? dec[i0 + 1] : 0.0;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+        const int j = pix_of(t + r * T, L, n);
+        const int jc = j < 0 ? 0 : j;
+        const double x = (double)r0[jc], y = (double)r0[np + jc], dj = dec[jc];
+        v[r] = j < 0 ? make_double2(0.0, 0.0) : make_double2(x * (d0 * dj), y * (d1 * dj));
+    }
+    fft_passes<LG, 0, 1, false>(v, t, s[f], tw);
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < 8; ++x) s[f][fpad(fft_out<LG>(t, x))] = v[x];
+    __syncthreads();
+    const int rows0 = blockIdx.x * NF * 2;
+    for (int e = threadIdx.x; e < Lx * NF; e += NF * T) {
+        const int qc = e / NF, g = e % NF;
+        const int i = rows0 + 2 * g;
+        if (i >= n) continue;
+        const int q = (qc - H) & (L - 1), qm = (H - qc) & (L - 1);
+        const double2 z = s[g][fpad(q)], zm = s[g][fpad(qm)];
+        double2 *o = X + ((size_t)c * Lx + qc) * n + i;
+        o[0] = make_double2(0.5 * (z.x + zm.x), 0.5 * (z.y - zm.y));
+        o[1] = make_double2(0.5 * (z.y + zm.y), 0.5 * (zm.x - z.x));
+    }
+}
+
+// Columns: X[q][i] -> G[q][p], p = 0 .. L - 1 contiguous.
+template <int LG>
+__global__ __launch_bounds__(col_seqs(LG) * fft_threads(LG)) void k_tr_cols_fwd(
+    const double2 *__restrict__ X, double2 *__restrict__ G, const double2 *__restrict__ tw, int n, int Lx, int Lg) {
+    constexpr int L = 1 << LG, T = fft_threads(LG), NF = col_seqs(LG);
+    __shared__ double2 s[NF][fpad(L)];
+    const int f = threadIdx.x / T, t = threadIdx.x % T;
+    const int c = blockIdx.y, qc = blockIdx.x * NF + f;
+    const bool live = qc < Lx;
+    const double2 *x = X + ((size_t)c * Lx + (live ? qc : 0)) * n;
+    double2 v[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+        const int i = pix_of(t + r * T, L, n);
+        const double2 y = x[i < 0 ? 0 : i];
+        v[r] = i < 0 ? make_double2(0.0, 0.0) : y;
+    }
+    fft_passes<LG, 0, 1, false>(v, t, s[f], tw);
+    if (!live) return;
+    double2 *o = G + ((size_t)c * Lg + qc) * L;
+#pragma unroll
+    for (int y = 0; y < 8; ++y) o[fft_out<LG>(t, y)] = v[y];
+}
+
+// ---------------------------------------------------------------- windows
+// W nodes, TB nodes per bin side, TS = TB + W - 1 nodes per tile side.
+template <int W> struct Win;
+template <> struct Win<9> {
+    static constexpr int TB = 8, TS = 16, NE = TR_NE9;
+};
+template <> struct Win<17> {
+    static constexpr int TB = 16, TS = 32, NE = TR_NE17;
+};
+
+// Window values of 32 visibilities into s[axis][visibility][TS + 1] (zero off
+// the window): lane l takes visibility l % 32, axis l / 32 (0: columns from
+// a, 1: rows from b).  Tap u of a visibility whose nearest node is at tile
+// offset `off` sits at off + u; taps u and W - 1 - u are E +- z O, E and O the
+// even and odd parts in z = 2 (a L - nearest node) of the tap's polynomial
+// (coefficients in poly: NE even and NE odd ones per tap pair, uniform over
+// the wave).  Visibilities past the item's end get zero windows.
+template <int W>
+__device__ __forceinline__ void windows32(double (*s)[32][Win<W>::TS + 1], const double *__restrict__ ab,
+                                          long long k0, long long kend, int L, int n0,
+                                          const double *__restrict__ poly) {
+    constexpr int H = (W - 1) / 2, TS = Win<W>::TS, NE = Win<W>::NE;
+    const int lane = threadIdx.x & 63, vv = lane & 31, axis = lane >> 5;
+    const long long k = k0 + vv;
+    const bool ok = k < kend;
+    const double X = ab[ok ? k : kend - 1] * (double)L;
+    const double nd = rint(X);
+    const double z = 2.0 * (X - nd), z2 = z * z;
+    const int off = ok ? (((int)nd & (L - 1)) - n0) : 0;
+    double *row = &s[axis][vv][0];
+#pragma unroll
+    for (int u = W; u < TS; ++u) row[(off + u) & (TS - 1)] = 0.0;
+#pragma unroll
+    for (int u = 0; u <= H; ++u) {
+        const double *pe = poly + u * 2 * NE, *po = pe + NE;
+        double e = pe[NE - 1], o = po[NE - 1];
+#pragma unroll
+        for (int m = NE - 2; m >= 0; --m) {
+            e = fma(e, z2, pe[m]);
+            if (u < H) o = fma(o, z2, po[m]);
+        }
+        if (u < H) {
+            row[off + u] = ok ? fma(z, o, e) : 0.0;
+            row[off + W - 1 - u] = ok ? fma(-z, o, e) : 0.0;
+        } else {
+            row[off + u] = ok ? e : 0.0;
+        }
+    }
+}
+
+// The per-wave LDS exchange: other lanes' stores are visible after it.
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+constexpr int TR_WAVES = 4;   // items per workgroup of the tile kernels
+
+// Gather: one wave per item; the item's grid tile is held in registers.
+template <int W>
+__global__ __launch_bounds__(64 * TR_WAVES) void k_tr_interp(const TrItem *__restrict__ items, int n_items,
+                                                            const double *__restrict__ a,
+                                                            const double *__restrict__ b,
+                                                            const double2 *__restrict__ G,
+                                                            double2 *__restrict__ V,
+                                                            const double *__restrict__ poly, int L, int Lg) {
+    constexpr int H = (W - 1) / 2, TB = Win<W>::TB, TS = Win<W>::TS, NT = TS / 16, NS = TS / 4;
+    __shared__ double s[TR_WAVES][2][32][TS + 1];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int q = lane & 15, g = lane >> 4;
+    const int item = blockIdx.x * TR_WAVES + wave;
+    if (item >= n_items) return;
+    const TrItem it = items[item];
+    double gr[NT][NS], gi[NT][NS];
+#pragma unroll
+    for (int x = 0; x < NS; ++x) {
+        const double2 *col = G + ((size_t)it.chan * Lg + it.bx * TB + 4 * x + g) * L;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            const double2 v = col[(it.by * TB - H + 16 * t + q) & (L - 1)];
+            gr[t][x] = v.x;
+            gi[t][x] = v.y;
+        }
+    }
+    const double *ab = lane < 32 ? a : b;
+    const int n0 = TB * (lane < 32 ? it.bx : it.by);
+    for (long long k0 = it.kbeg; k0 < it.kend; k0 += 32) {
+        windows32<W>(s[wave], ab, k0, it.kend, L, n0, poly);
+        wave_sync();
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            if (k0 + 16 * h >= it.kend) break;
+            const double *kx = &s[wave][0][16 * h + q][0], *ky = &s[wave][1][16 * h + q][0];
+            doublex4 ar[NT], ai[NT];
+#pragma unroll
+            for (int t = 0; t < NT; ++t) ar[t] = ai[t] = doublex4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int x = 0; x < NS; ++x) {
+                const double w = kx[4 * x + g];
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {
+                    ar[t] = mma(gr[t][x], w, ar[t]);
+                    ai[t] = mma(gi[t][x], w, ai[t]);
+                }
+            }
+            double vr = 0.0, vi = 0.0;
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const double w = ky[16 * t + 4 * r + g];
+                    vr = fma(w, ar[t][r], vr);
+                    vi = fma(w, ai[t][r], vi);
+                }
+            vr += __shfl_xor(vr, 16, 64);
+            vi += __shfl_xor(vi, 16, 64);
+            vr += __shfl_xor(vr, 32, 64);
+            vi += __shfl_xor(vi, 32, 64);
+            const long long k = k0 + 16 * h + q;
+            if (g == 0 && k < it.kend) V[k] = make_double2(vr, vi);
+        }
+        wave_sync();
+    }
+}
+
+// Spread: one wave per item, the visibilities as the contraction dimension;
+// the item's tile goes to its own slot tiles[item][column][row].  perm (may
+// be null): coef is in the caller's order (index << 1 | negated).
+template <int W>
+__global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const TrItem *__restrict__ items, int n_items,
+                                                            const double *__restrict__ a,
+                                                            const double *__restrict__ b,
+                                                            const double2 *__restrict__ coef,
+                                                            const float *__restrict__ w,
+                                                            const unsigned *__restrict__ perm,
+                                                            double2 *__restrict__ tiles,
+                                                            const double *__restrict__ poly, int L) {
+    constexpr int TB = Win<W>::TB, TS = Win<W>::TS, NT = TS / 16;
+    __shared__ double s[TR_WAVES][2][32][TS + 1];
+    __shared__ double2 sc[TR_WAVES][32];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int q = lane & 15, g = lane >> 4;
+    const int item = blockIdx.x * TR_WAVES + wave;
+    if (item >= n_items) return;
+    const TrItem it = items[item];
+    const double *ab = lane < 32 ? a : b;
+    const int n0 = TB * (lane < 32 ? it.bx : it.by);
+    doublex4 ar[NT][NT], ai[NT][NT];
+#pragma unroll
+    for (int x = 0; x < NT; ++x)
+#pragma unroll
+        for (int y = 0; y < NT; ++y) ar[x][y] = ai[x][y] = doublex4{0.0, 0.0, 0.0, 0.0};
+    for (long long k0 = it.kbeg; k0 < it.kend; k0 += 32) {
+        if (lane < 32) {
+            const long long k = k0 + lane;
+            double2 cv = make_double2(0.0, 0.0);
+            if (k < it.kend) {
+                const double wv = w ? (double)w[k] : 1.0;
+                if (perm) {
+                    const unsigned pk = perm[k];
+                    cv = coef[pk >> 1];
+                    if (pk & 1u) cv.y = -cv.y;
+                } else {
+                    cv = coef[k];
+                }
+                cv.x *= wv;
+                cv.y *= wv;
+            }
+            sc[wave][lane] = cv;
+        }
+        windows32<W>(s[wave], ab, k0, it.kend, L, n0, poly);
+        wave_sync();
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+            if (k0 + 4 * m >= it.kend) break;
+            const int v = 4 * m + g;
+            const double2 cv = sc[wave][v];
+            double ky[NT];
+#pragma unroll
+            for (int y = 0; y < NT; ++y) ky[y] = s[wave][1][v][16 * y + q];
+#pragma unroll
+            for (int x = 0; x < NT; ++x) {
+                const double kx = s[wave][0][v][16 * x + q];
+                const double cr = kx * cv.x, ci = kx * cv.y;
+#pragma unroll
+                for (int y = 0; y < NT; ++y) {
+                    ar[x][y] = mma(cr, ky[y], ar[x][y]);
+                    ai[x][y] = mma(ci, ky[y], ai[x][y]);
+                }
+            }
+        }
+        wave_sync();
+    }
+    double2 *o = tiles + (size_t)item * (TS * TS);
+#pragma unroll
+    for (int x = 0; x < NT; ++x)
+#pragma unroll
+        for (int y = 0; y < NT; ++y)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                o[(16 * x + 4 * r + g) * TS + 16 * y + q] = make_double2(ar[x][y][r], ai[x][y][r]);
+}
+
+// Inverse columns: node (q, p) sums the tiles that cover it (at most two bin
+// columns by two bin rows, each bin's items in order), then the transform
+// over p; the image rows are kept: Y[q][i].
+template <int LG, int W>
+__global__ __launch_bounds__(col_seqs(LG) * fft_threads(LG)) void k_tr_cols_inv(
+    const double2 *__restrict__ tiles, const int *__restrict__ bin_item, double2 *__restrict__ Y,
+    const double2 *__restrict__ tw, int n, int Lx, int nbx) {
+    constexpr int L = 1 << LG, T = fft_threads(LG), NF = col_seqs(LG);
+    constexpr int H = (W - 1) / 2, TB = Win<W>::TB, TS = Win<W>::TS, NBY = L / TB;
+    __shared__ double2 s[NF][fpad(L)];
+    const int f = threadIdx.x / T, t = threadIdx.x % T;
+    const int c = blockIdx.y, qc = blockIdx.x * NF + f;
+    const bool live = qc < Lx;
+    const int *bins = bin_item + (size_t)c * nbx * NBY;
+    double2 v[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) v[r] = make_double2(0.0, 0.0);
+    if (live) {
+        const int bxh = qc / TB;
+#pragma unroll
+        for (int dx = 1; dx >= 0; --dx) {
+            const int bx = bxh - dx;
+            if (bx < 0 || bx >= nbx) continue;
+            const int co = (qc - bx * TB) * TS;
+            int s0[8][2], s1[8][2];
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                const int pr = (t + r * T + H) & (L - 1);
+                const int bh = pr / TB, bl = (bh - 1) & (NBY - 1);
+                s0[r][0] = bins[bx * NBY + bl];
+                s1[r][0] = bins[bx * NBY + bl + 1];
+                s0[r][1] = bins[bx * NBY + bh];
+                s1[r][1] = bins[bx * NBY + bh + 1];
+            }
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                const int pr = (t + r * T + H) & (TB - 1);
+#pragma unroll
+                for (int d = 0; d < 2; ++d) {
+                    const double2 *p = tiles + co + pr + (d == 0 ? TB : 0);
+                    for (int x = s0[r][d]; x < s1[r][d]; ++x) v[r] = cadd(v[r], p[(size_t)x * (TS * TS)]);
+                }
+            }
+        }
+    }
+    fft_passes<LG, 0, 1, true>(v, t, s[f], tw);
+    if (!live) return;
+    double2 *o = Y + ((size_t)c * Lx + qc) * n;
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+        const int i = pix_of(fft_out<LG>(t, x), L, n);
+        if (i >= 0) o[i] = v[x];
+    }
+}
+
+// Inverse rows: the real part over the half grid of two image rows at once
+// (their Hermitian halves packed as one complex sequence), times the window's
+// inverse transform, into the channel's plane.
+template <int LG>
+__global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_inv(
+    const double2 *__restrict__ Y, double *__restrict__ plane, const double2 *__restrict__ tw,
+    const double *__restrict__ dec, const int *__restrict__ slot_base, int n, int np, int H) {
+    constexpr int L = 1 << LG, T = fft_threads(LG), NF = row_seqs(LG);
+    constexpr int LXM = L / 2 + 2 * TR_HMAX + 1;
+    // [NF] half spectra of two rows, then (reused) the transform's exchange
+    constexpr int NSH = 2 * LXM > fpad(L) ? 2 * LXM : fpad(L);
+    __shared__ double2 s[NF][NSH];
+    const int f = threadIdx.x / T, t = threadIdx.x % T;
+    const int c = blockIdx.y, rows0 = blockIdx.x * NF * 2;
+    const int Lx = L / 2 + 2 * H + 1;
+    for (int e = threadIdx.x; e < Lx * NF; e += NF * T) {
+        const int qc = e / NF, g = e % NF;
+        const int i = rows0 + 2 * g;
+        const double2 *y = Y + ((size_t)c * Lx + qc) * n + (i < n ? i : 0);
+        s[g][2 * qc] = y[0];
+        s[g][2 * qc + 1] = y[1];
+    }
+    __syncthreads();
+    double2 v[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+        const int q = t + r * T, qm = (L - q) & (L - 1);
+        auto col = [&](int x) { return x <= L / 2 + H ? x + H : x >= L - H ? x - (L - H) : -1; };
+        const int cp = col(q), cm = col(qm);
+        double2 z = make_double2(0.0, 0.0);
+        if (cp >= 0) {
+            const double2 a = s[f][2 * cp], b = s[f][2 * cp + 1];
+            z.x += a.x - b.y;
+            z.y += a.y + b.x;
+        }
+        if (cm >= 0) {
+            const double2 a = s[f][2 * cm], b = s[f][2 * cm + 1];
+            z.x += a.x + b.y;
+            z.y += b.x - a.y;
+        }
+        v[r] = make_double2(0.5 * z.x, 0.5 * z.y);
+    }
+    fft_passes<LG, 0, 1, true>(v, t, s[f], tw);
+    const int i = rows0 + 2 * f;
+    if (i >= n) return;
+    double *o = plane + ((size_t)slot_base[c] * np + i) * np;
+    const double d0 = dec[i], d1 = dec[i + 1];
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+        const int j = pix_of(fft_out<LG>(t, x), L, n);
+        if (j < 0) continue;
+        const double dj = dec[j];
+        o[j] = v[x].x * (d0 * dj);
+        o[np + j] = v[x].y * (d1 * dj);
+    }
+}
+
+// dst[caller's order] = src[bin order], conjugated where negated (dir = 0);
+// the reverse for dir = 1.
+__global__ void k_tr_permute(const double2 *__restrict__ src, double2 *__restrict__ dst,
+                             const unsigned *__restrict__ perm, long long count, int dir) {
+    long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long long stride = (long long)gridDim.x * blockDim.x;
+    for (; k < count; k += stride) {
+        const unsigned pk = perm[k];
+        double2 v = dir ? src[pk >> 1] : src[k];
+        if (pk & 1u) v.y = -v.y;
+        dst[dir ? k : (long long)(pk >> 1)] = v;
+    }
+}
+
+// ---------------------------------------------------------------- set-up
+// Coordinates of raw visibility k: a in [0, 1/2], b in [-1/2, 1/2] (the sums
+// have period one in both; the reduction is exact), and whether the pair was
+// negated.
+__device__ __forceinline__ bool reduce_ab(double u, double v, double cell, double &a, double &b) {
+    a = u * cell;
+    b = v * cell;
+    a -= rint(a);
+    b -= rint(b);
+    const bool neg = a < 0.0;
+    if (neg) {
+        a = -a;
+        b = -b;
+    }
+    return neg;
+}
+
+// Sort keys: the bin of every visibility, channel by channel.
+__global__ __launch_bounds__(NTHR) void k_tr_keys(const VisItem *__restrict__ items, const double *__restrict__ u,
+                                                  const double *__restrict__ v, double cell,
+                                                  unsigned *__restrict__ key, unsigned *__restrict__ val, int L,
+                                                  int tb, int nbx, int nby) {
+    const VisItem it = items[blockIdx.x];
+    for (long long k = it.kbeg + threadIdx.x; k < it.kend; k += NTHR) {
+        double a, b;
+        const bool neg = reduce_ab(u[k], v[k], cell, a, b);
+        const int nx = (int)rint(a * (double)L), ny = (int)rint(b * (double)L) & (L - 1);
+        key[k] = ((unsigned)it.chan * nbx + nx / tb) * nby + ny / tb;
+        val[k] = (unsigned)k << 1 | (neg ? 1u : 0u);
+    }
+}
+
+// Stable least-significant-digit radix sort, 8 bits a pass: digit counts of
+// SORT_BLK consecutive elements per block, their prefix sums (digit major),
+// then every block places its elements in order (ranks within a wave by
+// matching digits, waves and rounds in element order).
+constexpr int SORT_BLK = 4096;
+
+__global__ __launch_bounds__(NTHR) void k_sort_count(const unsigned *__restrict__ key, long long count, int shift,
+                                                     unsigned *__restrict__ hist, int nblk) {
+    __shared__ unsigned h[256];
+    h[threadIdx.x] = 0;
+    __syncthreads();
+    const long long k0 = (long long)blockIdx.x * SORT_BLK;
+    for (int r = 0; r < SORT_BLK / NTHR; ++r) {
+        const long long k = k0 + r * NTHR + threadIdx.x;
+        if (k < count) atomicAdd(&h[(key[k] >> shift) & 255u], 1u);
+    }
+    __syncthreads();
+    hist[(size_t)threadIdx.x * nblk + blockIdx.x] = h[threadIdx.x];
+}
+
+// Exclusive prefix sums of one digit's block counts (a workgroup per digit),
+// its total into tot[digit].
+__global__ __launch_bounds__(NTHR) void k_sort_scan(unsigned *__restrict__ hist, unsigned *__restrict__ tot,
+                                                    int nblk) {
+    __shared__ unsigned s[NTHR];
+    unsigned *h = hist + (size_t)blockIdx.x * nblk;
+    unsigned run = 0;
+    for (int b0 = 0; b0 < nblk; b0 += NTHR) {
+        const int b = b0 + threadIdx.x;
+        const unsigned x = b < nblk ? h[b] : 0u;
+        s[threadIdx.x] = x;
+        __syncthreads();
+        for (int o = 1; o < NTHR; o <<= 1) {
+            const unsigned y = threadIdx.x >= (unsigned)o ? s[threadIdx.x - o] : 0u;
+            __syncthreads();
+            s[threadIdx.x] += y;
+            __syncthreads();
+        }
+        if (b < nblk) h[b] = run + s[threadIdx.x] - x;
+        run += s[NTHR - 1];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) tot[blockIdx.x] = run;
+}
+
+__global__ __launch_bounds__(NTHR) void k_sort_place(const unsigned *__restrict__ key,
+                                                     const unsigned *__restrict__ val, long long count, int shift,
+                                                     const unsigned *__restrict__ hist,
+                                                     const unsigned *__restrict__ tot, int nblk,
+                                                     unsigned *__restrict__ key2, unsigned *__restrict__ val2) {
+    constexpr int NW = NTHR / 64, PER = SORT_BLK / NW;
+    __shared__ unsigned cnt[NW][256];   // next position of each digit, per wave
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const long long k0 = (long long)blockIdx.x * SORT_BLK + (long long)wave * PER;
+    for (int x = lane; x < 256; x += 64) cnt[wave][x] = 0;
+    __syncthreads();
+    for (int r = 0; r < PER / 64; ++r) {
+        const long long k = k0 + r * 64 + lane;
+        if (k < count) atomicAdd(&cnt[wave][(key[k] >> shift) & 255u], 1u);
+    }
+    __syncthreads();
+    {
+        const int d = threadIdx.x;   // digit
+        unsigned base = hist[(size_t)d * nblk + blockIdx.x];
+        for (int x = 0; x < d; ++x) base += tot[x];
+        for (int x = 0; x < NW; ++x) {
+            const unsigned y = cnt[x][d];
+            cnt[x][d] = base;
+            base += y;
+        }
+    }
+    __syncthreads();
+    for (int r = 0; r < PER / 64; ++r) {
+        const long long k = k0 + r * 64 + lane;
+        const bool ok = k < count;
+        const unsigned kk = ok ? key[k] : 0u;
+        const unsigned d = (kk >> shift) & 255u;
+        unsigned long long same = __ballot(ok);
+#pragma unroll
+        for (int m = 0; m < 8; ++m) {
+            const unsigned long long bm = __ballot((d >> m) & 1u);
+            same &= (d >> m) & 1u ? bm : ~bm;
+        }
+        const unsigned rank = __popcll(same & ((1ull << lane) - 1ull));
+        unsigned at = 0;
+        if (ok) at = cnt[wave][d] + rank;
+        wave_sync();
+        if (ok && rank == 0) cnt[wave][d] = at + (unsigned)__popcll(same);
+        wave_sync();
+        if (ok) {
+            key2[at] = kk;
+            val2[at] = val[k];
+        }
+    }
+}
+
+// start[t] = first position whose key is >= t, for t = 0 .. nkeys (nkeys: the
+// number of bins of all channels).
+__global__ __launch_bounds__(NTHR) void k_tr_bounds(const unsigned *__restrict__ key, long long count,
+                                                    int *__restrict__ start, unsigned nkeys) {
+    const long long k = (long long)blockIdx.x * NTHR + threadIdx.x;
+    if (k > count) return;
+    const unsigned lo = k == 0 ? 0u : key[k - 1] + 1u;
+    const unsigned hi = k == count ? nkeys : key[k];
+    for (unsigned t = lo; t <= hi; ++t) start[t] = (int)k;
+}
+
+// The sorted arrays.  A pointing's visibilities are rotated to the image
+// centre: V^o e^{-2 pi i (u x0 + v y0)}, phase reduced mod 1.
+__global__ __launch_bounds__(NTHR) void k_tr_gather(const VisItem *__restrict__ items, const double *__restrict__ u,
+                                                    const double *__restrict__ v, const float2 *__restrict__ vis,
+                                                    const float *__restrict__ w, const unsigned *__restrict__ val,
+                                                    double cell, const double2 *__restrict__ centre,
+                                                    double *__restrict__ a, double *__restrict__ b,
+                                                    double2 *__restrict__ vo, float *__restrict__ ws,
+                                                    unsigned *__restrict__ perm) {
+    const VisItem it = items[blockIdx.x];
+    const double2 x0 = centre[it.chan];
+    for (long long d = it.kbeg + threadIdx.x; d < it.kend; d += NTHR) {
+        const unsigned p = val[d];
+        const long long k = p >> 1;
+        double av, bv;
+        reduce_ab(u[k], v[k], cell, av, bv);
+        a[d] = av;
+        b[d] = bv;
+        ws[d] = w[k];
+        perm[d] = p;
+        const float2 o = vis[k];
+        double re = o.x, im = o.y;
+        if (x0.x != 0.0 || x0.y != 0.0) {
+            const double ph = u[k] * x0.x + v[k] * x0.y;
+            double sn, cs;
+            sincospi(2.0 * (ph - rint(ph)), &sn, &cs);
+            const double t = re * cs + im * sn;
+            im = im * cs - re * sn;
+            re = t;
+        }
+        vo[d] = make_double2(re, p & 1u ? -im : im);
+    }
+}
+
+// A = exp(-4 ln2 |x - x0|^2 / fwhm^2) of one channel.
+template <typename R>
+__global__ void k_beam(R *__restrict__ beam, int n, double cell, double cx, double cy, double fwhm) {
+    const long long npix = (long long)n * n;
+    long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long long stride = (long long)gridDim.x * blockDim.x;
+    for (; p < npix; p += stride) {
+        const double x = (double)((int)(p % n) - n / 2) * cell - cx;
+        const double y = (double)((int)(p / n) - n / 2) * cell - cy;
+        beam[p] = (R)exp(-4.0 * 0.69314718055994530942 * (x * x + y * y) / (fwhm * fwhm));
+    }
+}
+
+template <int LG>
+hipError_t fwd_lg(const uvmem_ctx *c, const void *bop, hipStream_t st) {
+    const int H = c->tr_h, L = 1 << LG, Lx = L / 2 + 2 * H + 1;
+    constexpr int T = fft_threads(LG), RS = row_seqs(LG), CS = col_seqs(LG);
+    const dim3 gr((c->n / 2 + RS - 1) / RS, c->nchan), gc((Lx + CS - 1) / CS, c->nchan);
+    if (c->prec == UVMEM_FP64)
+        hipLaunchKernelGGL((k_tr_rows_fwd<LG, double>), gr, dim3(RS * T), 0, st, (const double *)bop, c->d_trx,
+                           c->d_trtw, c->d_trdec, c->n, c->np, H);
+    else
+        hipLaunchKernelGGL((k_tr_rows_fwd<LG, float>), gr, dim3(RS * T), 0, st, (const float *)bop, c->d_trx,
+                           c->d_trtw, c->d_trdec, c->n, c->np, H);
+    hipLaunchKernelGGL((k_tr_cols_fwd<LG>), gc, dim3(CS * T), 0, st, c->d_trx, c->d_trg, c->d_trtw, c->n, Lx,
+                       c->tr_lgc);
+    return hipGetLastError();
+}
+
+template <int LG>
+hipError_t inv_lg(const uvmem_ctx *c, hipStream_t st) {
+    const int H = c->tr_h, L = 1 << LG, Lx = L / 2 + 2 * H + 1;
+    constexpr int T = fft_threads(LG), RS = row_seqs(LG), CS = col_seqs(LG);
+    const dim3 gr((c->n / 2 + RS - 1) / RS, c->nchan), gc((Lx + CS - 1) / CS, c->nchan);
+    if (c->tr_w == 17)
+        hipLaunchKernelGGL((k_tr_cols_inv<LG, 17>), gc, dim3(CS * T), 0, st, c->d_trtile, c->d_trbin, c->d_trx,
+                           c->d_trtw, c->n, Lx, c->tr_nbx);
+    else
+        hipLaunchKernelGGL((k_tr_cols_inv<LG, 9>), gc, dim3(CS * T), 0, st, c->d_trtile, c->d_trbin, c->d_trx,
+                           c->d_trtw, c->n, Lx, c->tr_nbx);
+    hipLaunchKernelGGL((k_tr_rows_inv<LG>), gr, dim3(RS * T), 0, st, c->d_trx, (double *)c->d_gpart, c->d_trtw,
+                       c->d_trdec, c->d_slot_base, c->n, c->np, H);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_tr_forward(const uvmem_ctx *c, const void *bop, hipStream_t st) {
+    if (c->n_tritem == 0) return hipSuccess;
+    hipError_t e = hipErrorInvalidValue;
+    switch (c->tr_lg) {
+    case 6: e = fwd_lg<6>(c, bop, st); break;
+    case 7: e = fwd_lg<7>(c, bop, st); break;
+    case 8: e = fwd_lg<8>(c, bop, st); break;
+    case 9: e = fwd_lg<9>(c, bop, st); break;
+    case 10: e = fwd_lg<10>(c, bop, st); break;
+    case 11: e = fwd_lg<11>(c, bop, st); break;
+    case 12: e = fwd_lg<12>(c, bop, st); break;
+    }
+    if (e != hipSuccess) return e;
+    const dim3 grid((c->n_tritem + TR_WAVES - 1) / TR_WAVES), blk(64 * TR_WAVES);
+    if (c->tr_w == 17)
+        hipLaunchKernelGGL(k_tr_interp<17>, grid, blk, 0, st, c->d_tritem, c->n_tritem, c->d_a, c->d_b, c->d_trg,
+                           c->d_vpart, c->d_trpoly, 1 << c->tr_lg, c->tr_lgc);
+    else
+        hipLaunchKernelGGL(k_tr_interp<9>, grid, blk, 0, st, c->d_tritem, c->n_tritem, c->d_a, c->d_b, c->d_trg,
+                           c->d_vpart, c->d_trpoly, 1 << c->tr_lg, c->tr_lgc);
+    return hipGetLastError();
+}
+
+hipError_t launch_tr_adjoint(const uvmem_ctx *c, const double2 *coef, const float *w, const unsigned *perm,
+                             hipStream_t st) {
+    if (c->n_tritem) {
+        const dim3 grid((c->n_tritem + TR_WAVES - 1) / TR_WAVES), blk(64 * TR_WAVES);
+        if (c->tr_w == 17)
+            hipLaunchKernelGGL(k_tr_spread<17>, grid, blk, 0, st, c->d_tritem, c->n_tritem, c->d_a, c->d_b, coef, w,
+                               perm, c->d_trtile, c->d_trpoly, 1 << c->tr_lg);
+        else
+            hipLaunchKernelGGL(k_tr_spread<9>, grid, blk, 0, st, c->d_tritem, c->n_tritem, c->d_a, c->d_b, coef, w,
+                               perm, c->d_trtile, c->d_trpoly, 1 << c->tr_lg);
+    }
+    switch (c->tr_lg) {
+    case 6: return inv_lg<6>(c, st);
+    case 7: return inv_lg<7>(c, st);
+    case 8: return inv_lg<8>(c, st);
+    case 9: return inv_lg<9>(c, st);
+    case 10: return inv_lg<10>(c, st);
+    case 11: return inv_lg<11>(c, st);
+    case 12: return inv_lg<12>(c, st);
+    }
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_beam(const uvmem_ctx *c, int chan) {
+    const size_t npix = (size_t)c->n * c->n;
+    const dim3 grid((unsigned)std::min<size_t>((npix + NTHR - 1) / NTHR, 4096)), blk(NTHR);
+    if (c->prec == UVMEM_FP64)
+        hipLaunchKernelGGL(k_beam<double>, grid, blk, 0, nullptr, (double *)c->d_beam + chan * npix, c->n, c->cell,
+                           c->cx[chan], c->cy[chan], c->fwhm[chan]);
+    else
+        hipLaunchKernelGGL(k_beam<float>, grid, blk, 0, nullptr, (float *)c->d_beam + chan * npix, c->n, c->cell,
+                           c->cx[chan], c->cy[chan], c->fwhm[chan]);
+    return hipGetLastError();
+}
+
+hipError_t launch_tr_sort(const uvmem_ctx *c, const double *u, const double *v, const float *vis, const float *w) {
+    const long long count = c->ztot;
+    const int L = 1 << c->tr_lg, nblk = (int)((count + SORT_BLK - 1) / SORT_BLK);
+    const unsigned nkeys = (unsigned)c->nchan * c->tr_nbx * c->tr_nby;
+    unsigned *key = (unsigned *)c->d_Vd, *val = key + count, *key2 = val + count, *val2 = key2 + count;
+    unsigned *hist = nullptr;
+    double2 *centre = nullptr;
+    std::vector<double2> hc(c->nchan);
+    for (int ch = 0; ch < c->nchan; ++ch) hc[ch] = make_double2(c->cx[ch], c->cy[ch]);
+    hipError_t e = hipMalloc((void **)&hist, ((size_t)nblk + 1) * 256 * sizeof(unsigned));
+    if (e == hipSuccess) e = hipMalloc((void **)&centre, hc.size() * sizeof(double2));
+    if (e == hipSuccess) e = hipMemcpy(centre, hc.data(), hc.size() * sizeof(double2), hipMemcpyHostToDevice);
+    if (e == hipSuccess) {
+        unsigned *tot = hist + (size_t)nblk * 256;
+        hipLaunchKernelGGL(k_tr_keys, dim3(c->n_visit), dim3(NTHR), 0, nullptr, c->d_vis, u, v, c->cell, key, val, L,
+                           c->tr_w - 1, c->tr_nbx, c->tr_nby);
+        for (int shift = 0; shift < 32 && (nkeys - 1) >> shift; shift += 8) {
+            hipLaunchKernelGGL(k_sort_count, dim3(nblk), dim3(NTHR), 0, nullptr, key, count, shift, hist, nblk);
+            hipLaunchKernelGGL(k_sort_scan, dim3(256), dim3(NTHR), 0, nullptr, hist, tot, nblk);
+            hipLaunchKernelGGL(k_sort_place, dim3(nblk), dim3(NTHR), 0, nullptr, key, val, count, shift, hist, tot,
+                               nblk, key2, val2);
+            std::swap(key, key2);
+            std::swap(val, val2);
+        }
+        hipLaunchKernelGGL(k_tr_bounds, dim3((unsigned)(count / NTHR + 1)), dim3(NTHR), 0, nullptr, key, count,
+                           c->d_trbin, nkeys);
+        hipLaunchKernelGGL(k_tr_gather, dim3(c->n_visit), dim3(NTHR), 0, nullptr, c->d_vis, u, v,
+                           (const float2 *)vis, w, val, c->cell, centre, c->d_a, c->d_b, c->d_vo, c->d_w,
+                           c->d_trperm);
+        e = hipGetLastError();
+        const hipError_t e2 = hipDeviceSynchronize();
+        if (e == hipSuccess) e = e2;
+    }
+    if (hist) (void)hipFree(hist);
+    if (centre) (void)hipFree(centre);
+    return e;
+}
+
+hipError_t launch_tr_permute(const uvmem_ctx *c, const double2 *src, double2 *dst, int to_bins, hipStream_t st) {
+    if (c->ztot == 0) return hipSuccess;
+    const int blocks = (int)std::min<long long>((c->ztot + NTHR - 1) / NTHR, 4096);
+    hipLaunchKernelGGL(k_tr_permute, dim3(blocks), dim3(NTHR), 0, st, src, dst, c->d_trperm, (long long)c->ztot,
+                       to_bins);
+    return hipGetLastError();
+}
+
+}  // namespace uvm

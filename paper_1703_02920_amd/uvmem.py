@@ -237,8 +237,9 @@ class Context:
 
     def finalize(self):
         self._call("uvmem_finalize")
-        info = self.info()
-        self.np, self.ztot = info["np"], info["ztot"]
+        head = (ctypes.c_int64 * 5)()   # the first entries of info()
+        self._call("uvmem_info", head, len(head))
+        self.np, self.ztot = int(head[1]), int(head[4])
         return self
 
     @classmethod
@@ -267,7 +268,8 @@ class Context:
     def info(self) -> dict:
         keys = ["n", "np", "n_chan", "prec", "ztot", "n_fwd_parts", "adj_tile", "n_slots", "n_fwd_wgs",
                 "n_adj_items", "n_vis_items", "device_bytes", "n_pix_blocks", "pix_block", "vis_block",
-                "n_img", "fwd_model", "grid_side", "grad_model", "n_fwd_wgs_region", "n_adj_wgs_region"]
+                "n_img", "fwd_model", "grid_side", "grad_model", "n_fwd_wgs_region", "n_adj_wgs_region",
+                "transform_side"]
         out = (ctypes.c_int64 * len(keys))()
         self._call("uvmem_info", out, len(keys))
         return dict(zip(keys, [int(x) for x in out]))
