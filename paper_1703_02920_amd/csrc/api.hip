@@ -94,6 +94,7 @@ void free_all(uvmem_ctx *c) {
     dfree(c->d_gfxy); dfree(c->d_gsc); dfree(c->d_gdidx); dfree(c->d_gdlist); dfree(c->d_gdsum);
     dfree(c->d_wscale); dfree(c->d_mask);
     dfree(c->d_tritem); dfree(c->d_trbin); dfree(c->d_trperm); dfree(c->d_trdec); dfree(c->d_trpoly);
+    dfree(c->d_trspan); dfree(c->d_trspread); dfree(c->d_trgbase); dfree(c->d_trpart);
     dfree(c->d_trtw); dfree(c->d_trx); dfree(c->d_trg); dfree(c->d_trtile);
     dfree(c->d_fwdp_m); dfree(c->d_adj_m); dfree(c->d_slot_base_m);
     if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
@@ -131,9 +132,12 @@ void harvest(uvmem_ctx *c) {
 // Launch the forward (which = 0) or adjoint (which = 1) DFT, bracketed by
 // events when timing is on.
 // Coefficients without weights are a caller's vector, in the caller's order.
+// mode, out: the visibility pass that the fast evaluation's forward includes
+// (launch_forward).
 // flag: the forward operand is a CG direction / the adjoint is a gradient
 // (region-restricted work lists under a focus-of-attention mask).
-hipError_t timed_dft(uvmem_ctx *c, int which, const void *bop, const double2 *coef, const float *w, int flag) {
+hipError_t timed_dft(uvmem_ctx *c, int which, const void *bop, const double2 *coef, const float *w, int flag,
+                     int mode = 0, double2 *out = nullptr) {
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (c->timing) {
         if (c->ev_pool.size() < 2) {
@@ -146,7 +150,8 @@ hipError_t timed_dft(uvmem_ctx *c, int which, const void *bop, const double2 *co
             (void)hipEventRecord(e0, c->stream);
         }
     }
-    hipError_t e = which == 0 ? launch_forward(c, bop, c->stream, flag) : launch_adjoint(c, coef, w, c->stream, flag, w == nullptr);
+    hipError_t e = which == 0 ? launch_forward(c, bop, c->stream, flag, mode, out)
+                              : launch_adjoint(c, coef, w, c->stream, flag, w == nullptr);
     if (e0) {
         (void)hipEventRecord(e1, c->stream);
         c->pend[which].push_back({e0, e1});
@@ -631,23 +636,84 @@ hipError_t sort_bins(uvmem_ctx *c) {
     std::vector<int> start(C * nbin + 1), first(C * nbin + 1);
     ok(hipMemcpy(start.data(), c->d_trbin, start.size() * sizeof(int), hipMemcpyDeviceToHost));
     if (e != hipSuccess) return e;
-    // an item's visibilities: enough items to fill the chip, few tiles
+    // an item's visibilities: about eight waves' shares per SIMD, and at least
+    // two batches
     const int64_t chunk = std::max<int64_t>(64, std::min<int64_t>(1024, (c->ztot / 8192 + 31) / 32 * 32));
     std::vector<TrItem> items;
+    std::vector<int4> spread;
+    std::vector<std::pair<int, int>> single;   // runs of consecutive one-item bins
+    int slot = 0;
     for (size_t t = 0; t < C * nbin; ++t) {
-        first[t] = (int)items.size();
-        const int bin = (int)(t % nbin);
+        first[t] = slot;
+        const int bin = (int)(t % nbin), i0 = (int)items.size();
         for (int64_t k = start[t]; k < start[t + 1]; k += chunk)
-            items.push_back(TrItem{(int)(t / nbin), bin / c->tr_nby, bin % c->tr_nby, 0, (long long)k,
+            items.push_back(TrItem{(int)(t / nbin), bin / c->tr_nby, bin % c->tr_nby,
+                                   slot + ((int)items.size() - i0) / TR_WAVES, (long long)k,
                                    (long long)std::min<int64_t>(k + chunk, start[t + 1])});
+        const int ni = (int)items.size() - i0;
+        if (ni == 1) {
+            ++slot;
+            if (!single.empty() && single.back().second == i0) ++single.back().second;
+            else single.push_back({i0, i0 + 1});
+        } else {
+            for (int x = 0; x < ni; x += TR_WAVES, ++slot)
+                for (int v = 0; v < TR_WAVES; ++v) {
+                    const int i = std::min(i0 + x + v, i0 + ni);
+                    spread.push_back(make_int4(i, std::min(i + 1, i0 + ni), std::min(TR_WAVES, ni - x), 0));
+                }
+        }
     }
-    first[C * nbin] = c->n_tritem = (int)items.size();
+    first[C * nbin] = slot;
+    c->n_tritem = (int)items.size();
+    // spans of consecutive items of equal cost: whole batches of 32
+    // visibilities plus one for the tile, two spans per wave slot of the chip
+    auto cost = [](const TrItem &x) { return (x.kend - x.kbeg + 31) / 32 + 1; };
+    int64_t total = 0;
+    for (const TrItem &x : items) total += cost(x);
+    const int64_t per = std::max<int64_t>(2, (total + 8191) / 8192);
+    auto span_end = [&](int i, int end) {
+        int64_t got = cost(items[i]);
+        int j = i + 1;
+        while (j < end && items[j].chan == items[i].chan && got + cost(items[j]) / 2 < per) got += cost(items[j++]);
+        return j;
+    };
+    for (auto &run : single)
+        for (int i = run.first; i < run.second;) {
+            const int j = span_end(i, run.second);
+            spread.push_back(make_int4(i, j, 0, 0));
+            i = j;
+        }
+    while (spread.size() % TR_WAVES) spread.push_back(make_int4(0, 0, 0, 0));
+    c->n_trspread = (int)(spread.size() / TR_WAVES);
+    // gather: the same over all items, workgroups within one channel
+    std::vector<int2> spans;
+    std::vector<int> gbase(c->nimg + 1, 0);
+    for (int i = 0; i < c->n_tritem;) {
+        const int j = span_end(i, c->n_tritem);
+        spans.push_back(make_int2(i, j));
+        if (j == c->n_tritem || items[j].chan != items[i].chan) {
+            while (spans.size() % TR_WAVES) spans.push_back(make_int2(0, 0));
+            for (int m = c->nimg == C ? items[i].chan + 1 : 1; m <= c->nimg; ++m)
+                gbase[m] = (int)(spans.size() / TR_WAVES);
+        }
+        i = j;
+    }
+    c->n_trgroup = (int)(spans.size() / TR_WAVES);
     const size_t ts = 2 * (size_t)(c->tr_w - 1);
     ok(dalloc(c, &c->d_tritem, items.size()));
-    ok(dalloc(c, &c->d_trtile, items.size() * ts * ts));
-    if (e == hipSuccess)
-        ok(hipMemcpy(c->d_tritem, items.data(), items.size() * sizeof(TrItem), hipMemcpyHostToDevice));
-    if (e == hipSuccess) ok(hipMemcpy(c->d_trbin, first.data(), first.size() * sizeof(int), hipMemcpyHostToDevice));
+    ok(dalloc(c, &c->d_trspan, spans.size()));
+    ok(dalloc(c, &c->d_trspread, spread.size()));
+    ok(dalloc(c, &c->d_trgbase, gbase.size()));
+    ok(dalloc(c, &c->d_trpart, (size_t)c->n_trgroup * NPART));
+    ok(dalloc(c, &c->d_trtile, slot * ts * ts));
+    auto up = [&](void *dst, const void *src, size_t bytes) {
+        if (e == hipSuccess) e = hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice);
+    };
+    up(c->d_tritem, items.data(), items.size() * sizeof(TrItem));
+    up(c->d_trspan, spans.data(), spans.size() * sizeof(int2));
+    up(c->d_trspread, spread.data(), spread.size() * sizeof(int4));
+    up(c->d_trgbase, gbase.data(), gbase.size() * sizeof(int));
+    up(c->d_trbin, first.data(), first.size() * sizeof(int));
     // the staging buffers start out as zeros again
     if (e == hipSuccess) ok(hipMemset(c->d_R, 0, c->ztot * sizeof(double2)));
     if (e == hipSuccess) ok(hipMemset(c->d_Vd, 0, c->ztot * sizeof(double2)));
@@ -1168,7 +1234,7 @@ int uvmem_phi_and_grad(uvmem_ctx *c, const void *I, void *grad, double *scal) {
     if (s) return s;
     if (!I || !grad) return fail(c, UVMEM_EINVAL, "null image or gradient");
     HIPCHK(c, launch_prologue(c, I, 1, c->stream));
-    HIPCHK(c, timed_dft(c, 0, c->d_bop, nullptr, nullptr, 0));
+    HIPCHK(c, timed_dft(c, 0, c->d_bop, nullptr, nullptr, 0, 1));
     HIPCHK(c, launch_vis_sum(c, 1, nullptr, c->stream));
     HIPCHK(c, timed_dft(c, 1, nullptr, c->d_R, c->d_w, 1));
     HIPCHK(c, launch_grad(c, I, grad, 1, scal, c->stream));
@@ -1180,7 +1246,7 @@ int uvmem_forward(uvmem_ctx *c, const void *I, void *vis) {
     if (s) return s;
     if (!I || (!vis && c->ztot)) return fail(c, UVMEM_EINVAL, "null image or output");
     HIPCHK(c, launch_prologue(c, I, 0, c->stream));
-    HIPCHK(c, timed_dft(c, 0, c->d_bop, nullptr, nullptr, 0));
+    HIPCHK(c, timed_dft(c, 0, c->d_bop, nullptr, nullptr, 0, 0, (double2 *)vis));
     HIPCHK(c, launch_vis_sum(c, 0, (double2 *)vis, c->stream));
     return UVMEM_OK;
 }
@@ -1340,7 +1406,7 @@ int uvmem_cg_step(uvmem_ctx *c, void *I, double *scal) {
     if (!c->cg_ready) return fail(c, UVMEM_ESTATE, "cg_step before cg_init");
     if (I != c->cg_I) return fail(c, UVMEM_EINVAL, "cg_step image differs from cg_init's");
     HIPCHK(c, launch_cg_phase(c, I, scal, 0, c->stream));
-    HIPCHK(c, timed_dft(c, 0, c->d_bop, nullptr, nullptr, 1));
+    HIPCHK(c, timed_dft(c, 0, c->d_bop, nullptr, nullptr, 1, 2));
     HIPCHK(c, launch_cg_phase(c, I, scal, 1, c->stream));
     HIPCHK(c, timed_dft(c, 1, nullptr, c->d_R, c->d_w, 1));
     HIPCHK(c, launch_cg_phase(c, I, scal, 2, c->stream));

@@ -37,9 +37,11 @@ constexpr double BOUND_TOL = 1e-12;
 // wave each before the node gather (bounds the gather's serial loops).
 constexpr int GRID_DENSE = 16;
 // Fast evaluation of the DFT (k_trans.hip): coefficients per parity and tap
-// pair of the window polynomials of width 9 and 17 (FP64 accuracy), and the
-// largest half width.
-constexpr int TR_NE9 = 7, TR_NE17 = 11, TR_HMAX = 8;
+// pair of the window polynomials of width 9 (3e-10 of the peak) and 17 (6e-15,
+// FP64 rounding), and the largest half width.
+constexpr int TR_NE9 = 5, TR_NE17 = 8, TR_HMAX = 8;
+// Waves per workgroup of its gather and spread kernels.
+constexpr int TR_WAVES = 4;
 // Default number of line-search passes per CG step after the start in the
 // direction's visibility pass (which already settles a step that reaches
 // alpha_max); a channel whose search has converged skips the remaining passes.
@@ -76,7 +78,7 @@ struct TrItem {
     int chan;
     int bx;
     int by;
-    int pad;
+    int slot;                           // its tile (shared within a bin's workgroup)
     long long kbeg;
     long long kend;
 };
@@ -239,7 +241,17 @@ struct uvmem_ctx {
     int tr_lg = 0, tr_w = 0, tr_h = 0, tr_lgc = 0, tr_nbx = 0, tr_nby = 0;
     int n_tritem = 0;
     uvm::TrItem *d_tritem = nullptr;
-    int *d_trbin = nullptr;                     // first item of each bin, [C][nbx][nby] + 1
+    int *d_trbin = nullptr;                     // first tile slot of each bin, [C][nbx][nby] + 1
+    // gather: spans of items, TR_WAVES per workgroup, each workgroup within
+    // one channel; its partial records d_trpart [n_trgroup][NPART], those of
+    // an image in [d_trgbase[img], d_trgbase[img + 1]).  Spread:
+    // TR_WAVES per workgroup (first item, end, live waves of a workgroup
+    // whose items share a bin or 0)
+    int n_trgroup = 0, n_trspread = 0;
+    int2 *d_trspan = nullptr;
+    int4 *d_trspread = nullptr;
+    int *d_trgbase = nullptr;
+    double *d_trpart = nullptr;
     unsigned *d_trperm = nullptr;
     double *d_trdec = nullptr, *d_trpoly = nullptr;
     double2 *d_trtw = nullptr, *d_trx = nullptr, *d_trg = nullptr, *d_trtile = nullptr;
@@ -275,8 +287,10 @@ namespace uvm {
 
 // Forward DFT: vpart[part][k] = the image block's share of V_k (see
 // k_dft.hip).  dir != 0: the operand is a CG direction, zero outside a focus
-// region, and only the region's blocks are visited (compact partials).
-hipError_t launch_forward(const uvmem_ctx *c, const void *bop, hipStream_t st, int dir = 0);
+// region, and only the region's blocks are visited (compact partials).  The
+// fast evaluation includes the visibility pass: mode as in launch_vis_sum (2
+// for a direction), out its output for mode 0.
+hipError_t launch_forward(const uvmem_ctx *c, const void *bop, hipStream_t st, int dir, int mode, double2 *out);
 // Adjoint: gpart[slot] tiles of Re F^H (w coef) without the beam factor.
 // grad != 0: a gradient, needed inside a focus region only (its own tiles
 // and split-K slot table).
@@ -292,11 +306,13 @@ int adjoint_wgs_per_cu(const uvmem_ctx *c);
 hipError_t launch_grid_forward(const uvmem_ctx *c, const void *bop, hipStream_t st);
 hipError_t launch_grid_adjoint(const uvmem_ctx *c, const double2 *coef, const float *w, hipStream_t st);
 
-// Fast evaluation of the DFT and its adjoint (k_trans.hip): as
-// launch_grid_forward / launch_grid_adjoint; perm (may be null) marks
-// coefficients in the caller's order.  launch_tr_permute copies a visibility
+// Fast evaluation of the DFT and its adjoint (k_trans.hip).  The forward's
+// visibility pass is part of it: what = 0 writes V to out in the caller's
+// order, 1 the residuals and their chi^2 partials, 2 the direction
+// visibilities and the partials of a and b.  The adjoint writes the channels'
+// planes; perm (may be null) marks coefficients in the caller's order.  launch_tr_permute copies a visibility
 // vector from bin order to the caller's (to_bins = 0) or back (1).
-hipError_t launch_tr_forward(const uvmem_ctx *c, const void *bop, hipStream_t st);
+hipError_t launch_tr_forward(const uvmem_ctx *c, const void *bop, int what, double2 *out, hipStream_t st);
 hipError_t launch_tr_adjoint(const uvmem_ctx *c, const double2 *coef, const float *w, const unsigned *perm,
                              hipStream_t st);
 // Finalize: sort the visibilities of raw arrays (device, caller's order) by

@@ -201,8 +201,7 @@ __global__ __launch_bounds__(NTHR) void k_prologue(const R *__restrict__ I, cons
 }
 
 // ---------------------------------------------------------------- visibilities
-// mode 0: out[k] = V_k (model visibilities); with perm, into the caller's
-//         order (out[perm[k] >> 1], conjugated where perm[k] is odd)
+// mode 0: out[k] = V_k (model visibilities)
 // mode 1: R_k = V_k - Vo_k -> R; partial[0] = sum w |R|^2
 // mode 2: Vd_k = V_k -> Vd; partial[0] = sum w |Vd|^2, partial[1] = sum w Re(conj(R) Vd)
 // mode 3: R_k += alpha_c Vd_k; partial[0] = sum w |R|^2
@@ -213,8 +212,7 @@ __device__ __forceinline__ void vis_item(const VisItem it, int item, const doubl
                                          int n_parts, long long ztot, const double2 *__restrict__ vo,
                                          const float *__restrict__ w, double2 *__restrict__ R,
                                          double2 *__restrict__ Vd, double2 *__restrict__ out,
-                                         double *__restrict__ vispart, int mode, int with_max, double alpha,
-                                         const unsigned *__restrict__ perm = nullptr) {
+                                         double *__restrict__ vispart, int mode, int with_max, double alpha) {
     double acc[2] = {0.0, 0.0};
     double cmax = 0.0;   // max |Re|, |Im| of the adjoint's coefficients w R (mode 4: R alone)
     constexpr int U = 2;   // visibilities per thread and round, loads issued together
@@ -274,8 +272,7 @@ __device__ __forceinline__ void vis_item(const VisItem it, int item, const doubl
             if (k >= it.kend) continue;
             const double wv = ww[u];
             if (mode == 0) {
-                const unsigned pk = perm ? perm[k] : 0u;
-                out[perm ? (long long)(pk >> 1) : k] = make_double2(v[u].x, pk & 1u ? -v[u].y : v[u].y);
+                out[k] = v[u];
             } else if (mode == 1) {
                 const double2 o = ld[u];
                 const double2 r = make_double2(v[u].x - (double)o.x, v[u].y - (double)o.y);
@@ -324,11 +321,11 @@ __global__ __launch_bounds__(NTHR) void k_vis(const VisItem *__restrict__ items,
                                               double2 *__restrict__ R, double2 *__restrict__ Vd,
                                               double2 *__restrict__ out, const double *__restrict__ scal,
                                               double *__restrict__ vispart, const int *__restrict__ chan_img,
-                                              int mode, int with_max, const unsigned *__restrict__ perm) {
+                                              int mode, int with_max) {
     const VisItem it = items[blockIdx.x];
     const int img = chan_img ? chan_img[it.chan] : 0;
     const double alpha = mode == 3 ? scal[(size_t)img * UVMEM_NSCAL + UVMEM_S_ALPHA] : 0.0;
-    vis_item(it, blockIdx.x, vpart, n_parts, ztot, vo, w, R, Vd, out, vispart, mode, with_max, alpha, perm);
+    vis_item(it, blockIdx.x, vpart, n_parts, ztot, vo, w, R, Vd, out, vispart, mode, with_max, alpha);
 }
 
 // ---------------------------------------------------------------- gradient
@@ -849,12 +846,15 @@ __device__ __forceinline__ void ls_eval(const double *st, const double *pp, int 
 // parts of phi', phi'' at alpha_max (pixel workgroups of the images that have
 // visibilities; zero without a finite alpha_max).  The last workgroup of an
 // image starts its line search from these totals and the direction pass's.
+// n_visit = 0: the forward model has left Vd and the partials already
+// (vispart records rec_base[img] .. of the image).
 template <typename R>
 __global__ __launch_bounds__(NTHR) void k_cg_vis(const VisItem *__restrict__ items, int n_visit,
                                                  const double2 *__restrict__ vpart, int n_parts, long long ztot,
                                                  const float *__restrict__ w, double2 *__restrict__ Rv,
                                                  double2 *__restrict__ Vd, double *__restrict__ vispart,
                                                  const int *__restrict__ chan_img, const int *__restrict__ ivis_base,
+                                                 const int *__restrict__ rec_base,
                                                  const R *__restrict__ I, const R *__restrict__ dir,
                                                  double *__restrict__ ppart, int n, int n_pb, int pb_len, double M,
                                                  double lam, const double *__restrict__ chan,
@@ -896,8 +896,8 @@ __global__ __launch_bounds__(NTHR) void k_cg_vis(const VisItem *__restrict__ ite
             coh_store(ppart + ((size_t)img * n_pb + pb) * NPART + 1, acc[1]);
         }
     }
-    const int v0 = ivis_base[img], v1 = ivis_base[img + 1];
-    if (!arrive_last(ctr + img, (unsigned)(v1 - v0 + n_pb))) return;
+    const int v0 = rec_base[img], v1 = rec_base[img + 1];
+    if (!arrive_last(ctr + img, (unsigned)((n_visit ? v1 - v0 : 0) + n_pb))) return;
     double ab[2], fh[2];
     sum_partials2<2, 2>(vispart + (size_t)v0 * NPART, v1 - v0, 0, ab, ppart + (size_t)img * n_pb * NPART, n_pb, 0,
                         fh);
@@ -1080,7 +1080,9 @@ void grad_launch_t(const uvmem_ctx *c, const void *I, void *out, double *ppart, 
     // gradients (modes 1, 2) follow the region-restricted adjoint and its slots
     const int *slots = (mode == 1 || mode == 2) && c->has_region ? c->d_slot_base_m : c->d_slot_base;
     const bool hist = mode == 2 && c->hist_in_grad;
-    const GradTail tail{ctr(c, CTR_GRAD), c->d_vispart, c->d_ivis_base, pp(c, 0), c->d_scal, c->d_chan, user,
+    // an evaluation's chi^2 partials come from the forward's visibility pass
+    const bool tr1 = c->tr_lg && mode == 1;
+    const GradTail tail{ctr(c, CTR_GRAD), tr1 ? c->d_trpart : c->d_vispart, tr1 ? c->d_trgbase : c->d_ivis_base, pp(c, 0), c->d_scal, c->d_chan, user,
                         hist ? c->d_hist_ptr : nullptr, hist ? c->d_iter_ctr : nullptr};
     if (c->pix_blk >= 4 * NTHR)
         hipLaunchKernelGGL((k_grad<R, 4, PT>), dim3(pix_grid(c)), dim3(NTHR), 0, st, gp, slots,
@@ -1126,10 +1128,13 @@ hipError_t t_cg_phase(const uvmem_ctx *c, void *I, double *user, int phase, hipS
     if (phase == 1) {
         // 5. Vd, the quadratic coefficients a, b of chi^2 along d and phi'
         // at alpha_max; the line search starts from them
+        const bool tr = c->tr_lg > 0;
+        const int nv = tr ? 0 : c->n_visit;
         if (c->n_visit)
-            hipLaunchKernelGGL(k_cg_vis<R>, dim3(c->n_visit + pix_grid(c)), blk, 0, st, c->d_vis, c->n_visit,
+            hipLaunchKernelGGL(k_cg_vis<R>, dim3(nv + pix_grid(c)), blk, 0, st, c->d_vis, nv,
                                c->d_vpart, c->has_region ? c->n_vparts_m : c->n_vparts, (long long)c->ztot,
-                               c->d_w, c->d_R, c->d_Vd, c->d_vispart, c->d_chan_img, c->d_ivis_base, CP<R>(I),
+                               c->d_w, c->d_R, c->d_Vd, tr ? c->d_trpart : c->d_vispart, c->d_chan_img, c->d_ivis_base,
+                               tr ? c->d_trgbase : c->d_ivis_base, CP<R>(I),
                                CP<R>(c->d_dir), pp(c, 1), c->n, c->n_pb, c->pix_blk, c->M, c->lam, c->d_chan,
                                c->d_ls, ctr(c, CTR_VIS));
         // 6-7. line-search passes (the last one accepts a step)
@@ -1183,10 +1188,10 @@ hipError_t launch_prologue(const uvmem_ctx *c, const void *I, int with_entropy, 
 }
 
 hipError_t launch_vis_sum(const uvmem_ctx *c, int mode, double2 *out, hipStream_t st) {
-    if (c->n_visit == 0) return hipSuccess;
+    if (c->n_visit == 0 || c->tr_lg) return hipSuccess;   // part of the fast evaluation's forward
     hipLaunchKernelGGL(k_vis, dim3(c->n_visit), dim3(NTHR), 0, st, c->d_vis, c->d_vpart, c->n_vparts,
                        (long long)c->ztot, c->d_vo, c->d_w, c->d_R, c->d_Vd, out, c->d_scal, c->d_vispart,
-                       c->d_chan_img, mode, adj_scaled(c), c->d_trperm);
+                       c->d_chan_img, mode, adj_scaled(c));
     return hipGetLastError();
 }
 
@@ -1195,8 +1200,7 @@ hipError_t launch_vis_sum_raw(const VisItem *items, int n_items, const double2 *
     if (n_items == 0) return hipSuccess;
     hipLaunchKernelGGL(k_vis, dim3(n_items), dim3(NTHR), 0, st, items, vpart, n_parts, ztot,
                        (const double2 *)nullptr, (const float *)nullptr, (double2 *)nullptr, (double2 *)nullptr,
-                       out, (const double *)nullptr, (double *)nullptr, (const int *)nullptr, 0, 0,
-                       (const unsigned *)nullptr);
+                       out, (const double *)nullptr, (double *)nullptr, (const int *)nullptr, 0, 0);
     return hipGetLastError();
 }
 
@@ -1204,7 +1208,7 @@ hipError_t launch_coef_max(const uvmem_ctx *c, const double2 *coef, hipStream_t 
     if (c->n_visit == 0 || !adj_scaled(c)) return hipSuccess;
     hipLaunchKernelGGL(k_vis, dim3(c->n_visit), dim3(NTHR), 0, st, c->d_vis, c->d_vpart, c->n_vparts,
                        (long long)c->ztot, c->d_vo, (const float *)nullptr, const_cast<double2 *>(coef), c->d_Vd,
-                       (double2 *)nullptr, c->d_scal, c->d_vispart, c->d_chan_img, 4, 1, (const unsigned *)nullptr);
+                       (double2 *)nullptr, c->d_scal, c->d_vispart, c->d_chan_img, 4, 1);
     return hipGetLastError();
 }
 
@@ -1238,7 +1242,7 @@ hipError_t launch_cg_phase(const uvmem_ctx *c, void *I, double *user, int phase,
 hipError_t launch_cg_step(const uvmem_ctx *c, void *I, double *user, hipStream_t st) {
     hipError_t e;
     if ((e = launch_cg_phase(c, I, user, 0, st)) != hipSuccess) return e;
-    if ((e = launch_forward(c, c->d_bop, st, 1)) != hipSuccess) return e;
+    if ((e = launch_forward(c, c->d_bop, st, 1, 2, nullptr)) != hipSuccess) return e;
     if ((e = launch_cg_phase(c, I, user, 1, st)) != hipSuccess) return e;
     if ((e = launch_adjoint(c, c->d_R, c->d_w, st, 1)) != hipSuccess) return e;
     return launch_cg_phase(c, I, user, 2, st);

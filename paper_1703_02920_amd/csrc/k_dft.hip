@@ -1626,9 +1626,9 @@ hipError_t launch_forward_f32_raw(int ib_rows, int jb_cols, const FwdPItem *item
     return hipGetLastError();
 }
 
-hipError_t launch_forward(const uvmem_ctx *c, const void *bop, hipStream_t st, int dir) {
+hipError_t launch_forward(const uvmem_ctx *c, const void *bop, hipStream_t st, int dir, int mode, double2 *out) {
     if (c->fwd_model == UVMEM_FWD_GRIDDED) return launch_grid_forward(c, bop, st);
-    if (c->tr_lg) return launch_tr_forward(c, bop, st);
+    if (c->tr_lg) return launch_tr_forward(c, bop, mode, out, st);
     // the direction of a region-restricted CG is zero outside the region
     const bool rg = dir && c->has_region;
     const FwdPItem *it = rg ? c->d_fwdp_m : c->d_fwdp;

@@ -268,28 +268,28 @@ template <> struct Win<17> {
     static constexpr int TB = 16, TS = 32, NE = TR_NE17;
 };
 
-// Window values of 32 visibilities into s[axis][visibility][TS + 1] (zero off
-// the window): lane l takes visibility l % 32, axis l / 32 (0: columns from
-// a, 1: rows from b).  Tap u of a visibility whose nearest node is at tile
-// offset `off` sits at off + u; taps u and W - 1 - u are E +- z O, E and O the
-// even and odd parts in z = 2 (a L - nearest node) of the tap's polynomial
-// (coefficients in poly: NE even and NE odd ones per tap pair, uniform over
-// the wave).  Visibilities past the item's end get zero windows.
+// Window values of 32 visibilities into s[axis][visibility][TS + 2] (zero off
+// the window): lane l takes visibility l % 32 of the batch, axis l / 32 (0:
+// columns, 1: rows), whose grid coordinate is X = a L or b L.  Tap u of a
+// visibility whose nearest node is at tile offset `off` sits at off + u; taps
+// u and W - 1 - u are E +- z O, E and O the even and odd parts in z = 2 (X -
+// nearest node) of the tap's polynomial (coefficients in poly: NE even and NE
+// odd ones per tap pair, uniform over the wave).  A lane past the item's end
+// (ok false) writes some finite window at offset 0; whoever uses it drops the
+// result or multiplies by a zero coefficient.
 template <int W>
-__device__ __forceinline__ void windows32(double (*s)[32][Win<W>::TS + 1], const double *__restrict__ ab,
-                                          long long k0, long long kend, int L, int n0,
+__device__ __forceinline__ void windows32(double (*s)[32][Win<W>::TS + 2], double X, bool ok, int L, int n0,
                                           const double *__restrict__ poly) {
     constexpr int H = (W - 1) / 2, TS = Win<W>::TS, NE = Win<W>::NE;
     const int lane = threadIdx.x & 63, vv = lane & 31, axis = lane >> 5;
-    const long long k = k0 + vv;
-    const bool ok = k < kend;
-    const double X = ab[ok ? k : kend - 1] * (double)L;
     const double nd = rint(X);
     const double z = 2.0 * (X - nd), z2 = z * z;
     const int off = ok ? (((int)nd & (L - 1)) - n0) : 0;
     double *row = &s[axis][vv][0];
+    double2 *r2 = reinterpret_cast<double2 *>(row);
 #pragma unroll
-    for (int u = W; u < TS; ++u) row[(off + u) & (TS - 1)] = 0.0;
+    for (int u = 0; u < TS / 2; ++u) r2[u] = make_double2(0.0, 0.0);
+    row += off;
 #pragma unroll
     for (int u = 0; u <= H; ++u) {
         const double *pe = poly + u * 2 * NE, *po = pe + NE;
@@ -300,10 +300,10 @@ __device__ __forceinline__ void windows32(double (*s)[32][Win<W>::TS + 1], const
             if (u < H) o = fma(o, z2, po[m]);
         }
         if (u < H) {
-            row[off + u] = ok ? fma(z, o, e) : 0.0;
-            row[off + W - 1 - u] = ok ? fma(-z, o, e) : 0.0;
+            row[u] = fma(z, o, e);
+            row[W - 1 - u] = fma(-z, o, e);
         } else {
-            row[off + u] = ok ? e : 0.0;
+            row[u] = e;
         }
     }
 }
@@ -315,159 +315,282 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-constexpr int TR_WAVES = 4;   // items per workgroup of the tile kernels
+// x + y after exchanging 16-lane rows (SW16: odd rows of x with even rows of
+// y) or half waves (upper half of x with lower half of y): row or half r of
+// the result holds the sum over a pair of rows (halves) of x (r even / lower)
+// or of y.
+template <bool SW16>
+__device__ __forceinline__ double swap_add(double x, double y) {
+    const long long bx = __double_as_longlong(x), by = __double_as_longlong(y);
+    typedef unsigned u2 __attribute__((ext_vector_type(2)));
+    u2 lo, hi;
+    if constexpr (SW16) {
+        lo = __builtin_amdgcn_permlane16_swap((unsigned)bx, (unsigned)by, false, false);
+        hi = __builtin_amdgcn_permlane16_swap((unsigned)(bx >> 32), (unsigned)(by >> 32), false, false);
+    } else {
+        lo = __builtin_amdgcn_permlane32_swap((unsigned)bx, (unsigned)by, false, false);
+        hi = __builtin_amdgcn_permlane32_swap((unsigned)(bx >> 32), (unsigned)(by >> 32), false, false);
+    }
+    return __longlong_as_double(((long long)hi.x << 32) | lo.x) + __longlong_as_double(((long long)hi.y << 32) | lo.y);
+}
 
-// Gather: one wave per item; the item's grid tile is held in registers.
-template <int W>
-__global__ __launch_bounds__(64 * TR_WAVES) void k_tr_interp(const TrItem *__restrict__ items, int n_items,
-                                                            const double *__restrict__ a,
-                                                            const double *__restrict__ b,
-                                                            const double2 *__restrict__ G,
-                                                            double2 *__restrict__ V,
-                                                            const double *__restrict__ poly, int L, int Lg) {
+// What the gather does with V_k (component by component):
+//   TV_OUT: out[caller's index] = V_k
+//   TV_RES: R_k = V_k - Vo_k; partial [0] = sum w |R|^2
+//   TV_DIR: Vd_k = V_k; partials [0] = sum w |Vd|^2, [1] = sum w Re(conj(R) Vd)
+// (each workgroup's partials in record blockIdx.x of `part`).
+enum { TV_OUT, TV_RES, TV_DIR };
+
+// Gather: a workgroup's four waves take one span of consecutive items each
+// (spans are cut to equal cost at finalize); an item's grid tile is held in
+// registers.  The visibilities of a span are consecutive, so the next batch's
+// coordinates are loaded while the current one computes.
+template <int W, int MODE>
+__global__ __launch_bounds__(64 * TR_WAVES) void k_tr_interp(
+    const int2 *__restrict__ spans, const TrItem *__restrict__ items, const double *__restrict__ a,
+    const double *__restrict__ b, const double2 *__restrict__ G, const double *__restrict__ poly, int L, int Lg,
+    long long ztot, double *__restrict__ out, const double *__restrict__ ref, const float *__restrict__ w,
+    const unsigned *__restrict__ perm, double *__restrict__ part) {
     constexpr int H = (W - 1) / 2, TB = Win<W>::TB, TS = Win<W>::TS, NT = TS / 16, NS = TS / 4;
-    __shared__ double s[TR_WAVES][2][32][TS + 1];
+    __shared__ __attribute__((aligned(16))) double s[TR_WAVES][2][32][TS + 2];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int q = lane & 15, g = lane >> 4;
-    const int item = blockIdx.x * TR_WAVES + wave;
-    if (item >= n_items) return;
-    const TrItem it = items[item];
-    double gr[NT][NS], gi[NT][NS];
-#pragma unroll
-    for (int x = 0; x < NS; ++x) {
-        const double2 *col = G + ((size_t)it.chan * Lg + it.bx * TB + 4 * x + g) * L;
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            const double2 v = col[(it.by * TB - H + 16 * t + q) & (L - 1)];
-            gr[t][x] = v.x;
-            gi[t][x] = v.y;
-        }
-    }
+    const int2 span = spans[blockIdx.x * TR_WAVES + wave];
     const double *ab = lane < 32 ? a : b;
-    const int n0 = TB * (lane < 32 ? it.bx : it.by);
-    for (long long k0 = it.kbeg; k0 < it.kend; k0 += 32) {
-        windows32<W>(s[wave], ab, k0, it.kend, L, n0, poly);
-        wave_sync();
+    double acc0 = 0.0, acc1 = 0.0;
+    double xn = 0.0;
+    if (span.x < span.y) {
+        const long long k = items[span.x].kbeg + (lane & 31);
+        xn = ab[k < ztot ? k : ztot - 1];
+    }
+    for (int item = span.x; item < span.y; ++item) {
+        const TrItem it = items[item];
+        double gr[NT][NS], gi[NT][NS];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            if (k0 + 16 * h >= it.kend) break;
-            const double *kx = &s[wave][0][16 * h + q][0], *ky = &s[wave][1][16 * h + q][0];
-            doublex4 ar[NT], ai[NT];
+        for (int x = 0; x < NS; ++x) {
+            const double2 *col = G + ((size_t)it.chan * Lg + it.bx * TB + 4 * x + g) * L;
 #pragma unroll
-            for (int t = 0; t < NT; ++t) ar[t] = ai[t] = doublex4{0.0, 0.0, 0.0, 0.0};
+            for (int t = 0; t < NT; ++t) {
+                const double2 v = col[(it.by * TB - H + 16 * t + q) & (L - 1)];
+                gr[t][x] = v.x;
+                gi[t][x] = v.y;
+            }
+        }
+        const int n0 = TB * (lane < 32 ? it.bx : it.by);
+        for (long long k0 = it.kbeg; k0 < it.kend; k0 += 32) {
+            const double X = xn * (double)L;
+            {
+                const long long k = (k0 + 32 < it.kend ? k0 + 32 : it.kend) + (lane & 31);
+                xn = ab[k < ztot ? k : ztot - 1];
+            }
+            // this lane's visibility and component of the result
+            const long long kv = k0 + 16 * (g >> 1) + q;
+            const bool ok = kv < it.kend;
+            const long long kc = ok ? kv : it.kend - 1;
+            const int comp = g & 1;
+            double rv = 0.0;
+            float wv = 0.f;
+            unsigned pk = 0;
+            if constexpr (MODE == TV_OUT) {
+                pk = perm[kc];
+            } else {
+                rv = ref[2 * kc + comp];
+                wv = w[kc];
+            }
+            windows32<W>(s[wave], X, k0 + (lane & 31) < it.kend, L, n0, poly);
+            wave_sync();
+            double half[2] = {0.0, 0.0};
 #pragma unroll
-            for (int x = 0; x < NS; ++x) {
-                const double w = kx[4 * x + g];
+            for (int h = 0; h < 2; ++h) {
+                if (k0 + 16 * h >= it.kend) break;
+                const double *kx = &s[wave][0][16 * h + q][0], *ky = &s[wave][1][16 * h + q][0];
+                doublex4 ar[NT], ai[NT];
 #pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    ar[t] = mma(gr[t][x], w, ar[t]);
-                    ai[t] = mma(gi[t][x], w, ai[t]);
+                for (int t = 0; t < NT; ++t) ar[t] = ai[t] = doublex4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int x = 0; x < NS; ++x) {
+                    const double wx = kx[4 * x + g];
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        ar[t] = mma(gr[t][x], wx, ar[t]);
+                        ai[t] = mma(gi[t][x], wx, ai[t]);
+                    }
+                }
+                double vr = 0.0, vi = 0.0;
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const double wy = ky[16 * t + 4 * r + g];
+                        vr = fma(wy, ar[t][r], vr);
+                        vi = fma(wy, ai[t][r], vi);
+                    }
+                half[h] = swap_add<true>(vr, vi);
+            }
+            // lane group g now gets component g % 2 of visibility 16 (g / 2) + q
+            const double v = swap_add<false>(half[0], half[1]);
+            if (ok) {
+                if constexpr (MODE == TV_OUT) {
+                    out[2 * (size_t)(pk >> 1) + comp] = comp && (pk & 1u) ? -v : v;
+                } else if constexpr (MODE == TV_RES) {
+                    const double r = v - rv;
+                    out[2 * kv + comp] = r;
+                    acc0 += (double)wv * (r * r);
+                } else {
+                    out[2 * kv + comp] = v;
+                    acc0 += (double)wv * (v * v);
+                    acc1 += (double)wv * (rv * v);
                 }
             }
-            double vr = 0.0, vi = 0.0;
-#pragma unroll
-            for (int t = 0; t < NT; ++t)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const double w = ky[16 * t + 4 * r + g];
-                    vr = fma(w, ar[t][r], vr);
-                    vi = fma(w, ai[t][r], vi);
-                }
-            vr += __shfl_xor(vr, 16, 64);
-            vi += __shfl_xor(vi, 16, 64);
-            vr += __shfl_xor(vr, 32, 64);
-            vi += __shfl_xor(vi, 32, 64);
-            const long long k = k0 + 16 * h + q;
-            if (g == 0 && k < it.kend) V[k] = make_double2(vr, vi);
+            wave_sync();
         }
-        wave_sync();
+    }
+    if constexpr (MODE != TV_OUT) {
+        __shared__ double red[2][TR_WAVES];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            acc0 += __shfl_xor(acc0, o, 64);
+            acc1 += __shfl_xor(acc1, o, 64);
+        }
+        if (lane == 0) {
+            red[0][wave] = acc0;
+            red[1][wave] = acc1;
+        }
+        __syncthreads();
+        if (threadIdx.x < 2)
+            part[(size_t)blockIdx.x * NPART + threadIdx.x] = (red[threadIdx.x][0] + red[threadIdx.x][1]) +
+                                                             (red[threadIdx.x][2] + red[threadIdx.x][3]);
     }
 }
 
-// Spread: one wave per item, the visibilities as the contraction dimension;
-// the item's tile goes to its own slot tiles[item][column][row].  perm (may
-// be null): coef is in the caller's order (index << 1 | negated).
+// Spread, the visibilities as the contraction dimension: as the gather, a
+// workgroup's four waves take one span of items of equal cost each and store
+// an item's tile in its slot, tiles[slot][column][row].  A bin of several
+// items has workgroups of its own (waves[].z = live waves > 0), whose waves
+// take an item each and add their sums in LDS in wave order into one tile.
+// perm (may be null): coef is in the caller's order (index << 1 | negated).
 template <int W>
-__global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const TrItem *__restrict__ items, int n_items,
+__global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restrict__ waves,
+                                                            const TrItem *__restrict__ items,
                                                             const double *__restrict__ a,
                                                             const double *__restrict__ b,
                                                             const double2 *__restrict__ coef,
                                                             const float *__restrict__ w,
                                                             const unsigned *__restrict__ perm,
                                                             double2 *__restrict__ tiles,
-                                                            const double *__restrict__ poly, int L) {
+                                                            const double *__restrict__ poly, int L,
+                                                            long long ztot) {
     constexpr int TB = Win<W>::TB, TS = Win<W>::TS, NT = TS / 16;
-    __shared__ double s[TR_WAVES][2][32][TS + 1];
+    __shared__ __attribute__((aligned(16))) double s[TR_WAVES][2][32][TS + 2];
     __shared__ double2 sc[TR_WAVES][32];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int q = lane & 15, g = lane >> 4;
-    const int item = blockIdx.x * TR_WAVES + wave;
-    if (item >= n_items) return;
-    const TrItem it = items[item];
+    const int4 span = waves[blockIdx.x * TR_WAVES + wave];   // first item, end, live waves of a shared bin
     const double *ab = lane < 32 ? a : b;
-    const int n0 = TB * (lane < 32 ? it.bx : it.by);
     doublex4 ar[NT][NT], ai[NT][NT];
+    // the next batch's data are loaded while the current one computes; the
+    // visibilities of a span are consecutive, so that includes the next item's
+    double xn = 0.0;
+    double2 cn = make_double2(0.0, 0.0);
+    auto fetch = [&](long long k0) {
+        const long long k = k0 + (lane & 31), kc = k < ztot ? k : ztot - 1;
+        xn = ab[kc];
+        const double wv = w ? (double)w[kc] : 1.0;
+        const unsigned pk = perm ? perm[kc] : 0u;
+        const double2 cv = coef[perm ? (long long)(pk >> 1) : kc];
+        cn = make_double2(cv.x * wv, (pk & 1u ? -cv.y : cv.y) * wv);
+    };
+    auto at = [&](int x, int y, int r) { return (16 * x + 4 * r + g) * TS + 16 * y + q; };
+    if (span.x < span.y) fetch(items[span.x].kbeg);
+    for (int item = span.x; item < span.y; ++item) {
+        const TrItem it = items[item];
+        const int n0 = TB * (lane < 32 ? it.bx : it.by);
 #pragma unroll
-    for (int x = 0; x < NT; ++x)
+        for (int x = 0; x < NT; ++x)
 #pragma unroll
-        for (int y = 0; y < NT; ++y) ar[x][y] = ai[x][y] = doublex4{0.0, 0.0, 0.0, 0.0};
-    for (long long k0 = it.kbeg; k0 < it.kend; k0 += 32) {
-        if (lane < 32) {
-            const long long k = k0 + lane;
-            double2 cv = make_double2(0.0, 0.0);
-            if (k < it.kend) {
-                const double wv = w ? (double)w[k] : 1.0;
-                if (perm) {
-                    const unsigned pk = perm[k];
-                    cv = coef[pk >> 1];
-                    if (pk & 1u) cv.y = -cv.y;
-                } else {
-                    cv = coef[k];
+            for (int y = 0; y < NT; ++y) ar[x][y] = ai[x][y] = doublex4{0.0, 0.0, 0.0, 0.0};
+        for (long long k0 = it.kbeg; k0 < it.kend; k0 += 32) {
+            const bool ok = k0 + (lane & 31) < it.kend;
+            if (lane < 32) sc[wave][lane] = ok ? cn : make_double2(0.0, 0.0);
+            windows32<W>(s[wave], xn * (double)L, ok, L, n0, poly);
+            fetch(k0 + 32 < it.kend ? k0 + 32 : it.kend);
+            wave_sync();
+            // halves of 16 visibilities (zero coefficients past the end), all
+            // of a half's operands read ahead of its products
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (k0 + 16 * h >= it.kend) break;
+                double2 cv[4];
+                double kx[4][NT], ky[4][NT];
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    const int v = 16 * h + 4 * m + g;
+                    cv[m] = sc[wave][v];
+#pragma unroll
+                    for (int y = 0; y < NT; ++y) {
+                        kx[m][y] = s[wave][0][v][16 * y + q];
+                        ky[m][y] = s[wave][1][v][16 * y + q];
+                    }
                 }
-                cv.x *= wv;
-                cv.y *= wv;
+#pragma unroll
+                for (int m = 0; m < 4; ++m)
+#pragma unroll
+                    for (int x = 0; x < NT; ++x) {
+                        const double cr = kx[m][x] * cv[m].x, ci = kx[m][x] * cv[m].y;
+#pragma unroll
+                        for (int y = 0; y < NT; ++y) {
+                            ar[x][y] = mma(cr, ky[m][y], ar[x][y]);
+                            ai[x][y] = mma(ci, ky[m][y], ai[x][y]);
+                        }
+                    }
             }
-            sc[wave][lane] = cv;
+            wave_sync();
         }
-        windows32<W>(s[wave], ab, k0, it.kend, L, n0, poly);
-        wave_sync();
+        if (span.z == 0) {
+            double2 *o = tiles + (size_t)it.slot * (TS * TS);
 #pragma unroll
-        for (int m = 0; m < 8; ++m) {
-            if (k0 + 4 * m >= it.kend) break;
-            const int v = 4 * m + g;
-            const double2 cv = sc[wave][v];
-            double ky[NT];
+            for (int x = 0; x < NT; ++x)
 #pragma unroll
-            for (int y = 0; y < NT; ++y) ky[y] = s[wave][1][v][16 * y + q];
+                for (int y = 0; y < NT; ++y)
 #pragma unroll
-            for (int x = 0; x < NT; ++x) {
-                const double kx = s[wave][0][v][16 * x + q];
-                const double cr = kx * cv.x, ci = kx * cv.y;
-#pragma unroll
-                for (int y = 0; y < NT; ++y) {
-                    ar[x][y] = mma(cr, ky[y], ar[x][y]);
-                    ai[x][y] = mma(ci, ky[y], ai[x][y]);
-                }
-            }
+                    for (int r = 0; r < 4; ++r) o[at(x, y, r)] = make_double2(ar[x][y][r], ai[x][y][r]);
         }
-        wave_sync();
     }
-    double2 *o = tiles + (size_t)item * (TS * TS);
+    if (span.z == 0) return;   // uniform over the workgroup
+    // waves 1.. leave their sums in LDS, wave 0 adds them in order
+    double2 *buf = reinterpret_cast<double2 *>(&s[0][0][0][0]);
+    static_assert((TR_WAVES - 1) * TS * TS * 16 <= (int)sizeof(s), "wave sums fit the window buffers");
+    __syncthreads();
+    if (wave > 0 && wave < span.z) {
+#pragma unroll
+        for (int x = 0; x < NT; ++x)
+#pragma unroll
+            for (int y = 0; y < NT; ++y)
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    buf[(wave - 1) * TS * TS + at(x, y, r)] = make_double2(ar[x][y][r], ai[x][y][r]);
+    }
+    __syncthreads();
+    if (wave > 0) return;
+    double2 *o = tiles + (size_t)items[span.x].slot * (TS * TS);
 #pragma unroll
     for (int x = 0; x < NT; ++x)
 #pragma unroll
         for (int y = 0; y < NT; ++y)
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                o[(16 * x + 4 * r + g) * TS + 16 * y + q] = make_double2(ar[x][y][r], ai[x][y][r]);
+            for (int r = 0; r < 4; ++r) {
+                double2 t = make_double2(ar[x][y][r], ai[x][y][r]);
+                for (int v = 1; v < span.z; ++v) t = cadd(t, buf[(v - 1) * TS * TS + at(x, y, r)]);
+                o[at(x, y, r)] = t;
+            }
 }
 
 // Inverse columns: node (q, p) sums the tiles that cover it (at most two bin
-// columns by two bin rows, each bin's items in order), then the transform
+// columns by two bin rows, each bin's slots in order), then the transform
 // over p; the image rows are kept: Y[q][i].
 template <int LG, int W>
 __global__ __launch_bounds__(col_seqs(LG) * fft_threads(LG)) void k_tr_cols_inv(
-    const double2 *__restrict__ tiles, const int *__restrict__ bin_item, double2 *__restrict__ Y,
+    const double2 *__restrict__ tiles, const int *__restrict__ bin_slot, double2 *__restrict__ Y,
     const double2 *__restrict__ tw, int n, int Lx, int nbx) {
     constexpr int L = 1 << LG, T = fft_threads(LG), NF = col_seqs(LG);
     constexpr int H = (W - 1) / 2, TB = Win<W>::TB, TS = Win<W>::TS, NBY = L / TB;
@@ -475,7 +598,7 @@ __global__ __launch_bounds__(col_seqs(LG) * fft_threads(LG)) void k_tr_cols_inv(
     const int f = threadIdx.x / T, t = threadIdx.x % T;
     const int c = blockIdx.y, qc = blockIdx.x * NF + f;
     const bool live = qc < Lx;
-    const int *bins = bin_item + (size_t)c * nbx * NBY;
+    const int *bins = bin_slot + (size_t)c * nbx * NBY;
     double2 v[8];
 #pragma unroll
     for (int r = 0; r < 8; ++r) v[r] = make_double2(0.0, 0.0);
@@ -502,7 +625,15 @@ __global__ __launch_bounds__(col_seqs(LG) * fft_threads(LG)) void k_tr_cols_inv(
 #pragma unroll
                 for (int d = 0; d < 2; ++d) {
                     const double2 *p = tiles + co + pr + (d == 0 ? TB : 0);
-                    for (int x = s0[r][d]; x < s1[r][d]; ++x) v[r] = cadd(v[r], p[(size_t)x * (TS * TS)]);
+                    int x = s0[r][d];
+                    for (; x + 4 <= s1[r][d]; x += 4) {
+                        double2 y[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) y[u] = p[(size_t)(x + u) * (TS * TS)];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) v[r] = cadd(v[r], y[u]);
+                    }
+                    for (; x < s1[r][d]; ++x) v[r] = cadd(v[r], p[(size_t)x * (TS * TS)]);
                 }
             }
         }
@@ -806,10 +937,23 @@ hipError_t inv_lg(const uvmem_ctx *c, hipStream_t st) {
     return hipGetLastError();
 }
 
+template <int W, int MODE>
+void interp_mode(const uvmem_ctx *c, double2 *out, const double2 *ref, hipStream_t st) {
+    hipLaunchKernelGGL((k_tr_interp<W, MODE>), dim3(c->n_trgroup), dim3(64 * TR_WAVES), 0, st, c->d_trspan,
+                       c->d_tritem, c->d_a, c->d_b, c->d_trg, c->d_trpoly, 1 << c->tr_lg, c->tr_lgc,
+                       (long long)c->ztot, (double *)out, (const double *)ref, c->d_w, c->d_trperm, c->d_trpart);
+}
+template <int W>
+hipError_t interp_w(const uvmem_ctx *c, int what, double2 *out, hipStream_t st) {
+    if (what == 0) interp_mode<W, TV_OUT>(c, out, nullptr, st);
+    else if (what == 1) interp_mode<W, TV_RES>(c, c->d_R, c->d_vo, st);
+    else interp_mode<W, TV_DIR>(c, c->d_Vd, c->d_R, st);
+    return hipGetLastError();
+}
+
 }  // namespace
 
-hipError_t launch_tr_forward(const uvmem_ctx *c, const void *bop, hipStream_t st) {
-    if (c->n_tritem == 0) return hipSuccess;
+hipError_t launch_tr_forward(const uvmem_ctx *c, const void *bop, int what, double2 *out, hipStream_t st) {
     hipError_t e = hipErrorInvalidValue;
     switch (c->tr_lg) {
     case 6: e = fwd_lg<6>(c, bop, st); break;
@@ -821,27 +965,18 @@ hipError_t launch_tr_forward(const uvmem_ctx *c, const void *bop, hipStream_t st
     case 12: e = fwd_lg<12>(c, bop, st); break;
     }
     if (e != hipSuccess) return e;
-    const dim3 grid((c->n_tritem + TR_WAVES - 1) / TR_WAVES), blk(64 * TR_WAVES);
-    if (c->tr_w == 17)
-        hipLaunchKernelGGL(k_tr_interp<17>, grid, blk, 0, st, c->d_tritem, c->n_tritem, c->d_a, c->d_b, c->d_trg,
-                           c->d_vpart, c->d_trpoly, 1 << c->tr_lg, c->tr_lgc);
-    else
-        hipLaunchKernelGGL(k_tr_interp<9>, grid, blk, 0, st, c->d_tritem, c->n_tritem, c->d_a, c->d_b, c->d_trg,
-                           c->d_vpart, c->d_trpoly, 1 << c->tr_lg, c->tr_lgc);
-    return hipGetLastError();
+    return c->tr_w == 17 ? interp_w<17>(c, what, out, st) : interp_w<9>(c, what, out, st);
 }
 
 hipError_t launch_tr_adjoint(const uvmem_ctx *c, const double2 *coef, const float *w, const unsigned *perm,
                              hipStream_t st) {
-    if (c->n_tritem) {
-        const dim3 grid((c->n_tritem + TR_WAVES - 1) / TR_WAVES), blk(64 * TR_WAVES);
-        if (c->tr_w == 17)
-            hipLaunchKernelGGL(k_tr_spread<17>, grid, blk, 0, st, c->d_tritem, c->n_tritem, c->d_a, c->d_b, coef, w,
-                               perm, c->d_trtile, c->d_trpoly, 1 << c->tr_lg);
-        else
-            hipLaunchKernelGGL(k_tr_spread<9>, grid, blk, 0, st, c->d_tritem, c->n_tritem, c->d_a, c->d_b, coef, w,
-                               perm, c->d_trtile, c->d_trpoly, 1 << c->tr_lg);
-    }
+    const dim3 grid(c->n_trspread), blk(64 * TR_WAVES);
+    if (c->tr_w == 17)
+        hipLaunchKernelGGL(k_tr_spread<17>, grid, blk, 0, st, c->d_trspread, c->d_tritem, c->d_a, c->d_b, coef, w,
+                           perm, c->d_trtile, c->d_trpoly, 1 << c->tr_lg, (long long)c->ztot);
+    else
+        hipLaunchKernelGGL(k_tr_spread<9>, grid, blk, 0, st, c->d_trspread, c->d_tritem, c->d_a, c->d_b, coef, w,
+                           perm, c->d_trtile, c->d_trpoly, 1 << c->tr_lg, (long long)c->ztot);
     switch (c->tr_lg) {
     case 6: return inv_lg<6>(c, st);
     case 7: return inv_lg<7>(c, st);
