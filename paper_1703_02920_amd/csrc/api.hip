@@ -59,7 +59,7 @@ hipError_t fetch(void *dst, const void *src, size_t n) {
 }
 
 template <typename T>
-hipError_t dalloc(uvmem_ctx *c, T **p, size_t count) {
+hipError_t dalloc(uvmem_ctx *c, T **p, size_t count, bool zero = true) {
     size_t bytes = std::max<size_t>(count, 1) * sizeof(T);
     // test hook: UVMEM_TEST_FAIL_ALLOC=k makes the k-th allocation of a
     // finalize fail as if the device were out of memory
@@ -67,7 +67,7 @@ hipError_t dalloc(uvmem_ctx *c, T **p, size_t count) {
     hipError_t e = hipMalloc((void **)p, bytes);
     if (e == hipSuccess) {
         c->bytes_device += bytes;
-        e = hipMemset(*p, 0, bytes);
+        if (zero) e = hipMemset(*p, 0, bytes);
     }
     return e;
 }
@@ -93,9 +93,8 @@ void free_all(uvmem_ctx *c) {
     dfree(c->d_gtw); dfree(c->d_gx1); dfree(c->d_ggrid); dfree(c->d_gcell); dfree(c->d_gperm);
     dfree(c->d_gfxy); dfree(c->d_gsc); dfree(c->d_gdidx); dfree(c->d_gdlist); dfree(c->d_gdsum);
     dfree(c->d_wscale); dfree(c->d_mask);
-    dfree(c->d_tritem); dfree(c->d_trbin); dfree(c->d_trperm); dfree(c->d_trdec); dfree(c->d_trpoly);
-    dfree(c->d_trspan); dfree(c->d_trspread); dfree(c->d_trgbase); dfree(c->d_trpart);
-    dfree(c->d_trtw); dfree(c->d_trx); dfree(c->d_trg); dfree(c->d_trtile);
+    dfree(c->d_trtab); dfree(c->d_trconst); dfree(c->d_trperm); dfree(c->d_trpart);
+    dfree(c->d_trx); dfree(c->d_trg); dfree(c->d_trtile);
     dfree(c->d_fwdp_m); dfree(c->d_adj_m); dfree(c->d_slot_base_m);
     if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
     if (c->graph) (void)hipGraphDestroy(c->graph);
@@ -133,10 +132,10 @@ void harvest(uvmem_ctx *c) {
 // events when timing is on.
 // Coefficients without weights are a caller's vector, in the caller's order.
 // mode, out: the visibility pass that the fast evaluation's forward includes
-// (launch_forward).
+// (launch_forward); for the adjoint, mode 1 is that of a CG step.
 // flag: the forward operand is a CG direction / the adjoint is a gradient
 // (region-restricted work lists under a focus-of-attention mask).
-hipError_t timed_dft(uvmem_ctx *c, int which, const void *bop, const double2 *coef, const float *w, int flag,
+hipError_t timed_dft(uvmem_ctx *c, int which, const void *I, const double2 *coef, const float *w, int flag,
                      int mode = 0, double2 *out = nullptr) {
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (c->timing) {
@@ -150,8 +149,8 @@ hipError_t timed_dft(uvmem_ctx *c, int which, const void *bop, const double2 *co
             (void)hipEventRecord(e0, c->stream);
         }
     }
-    hipError_t e = which == 0 ? launch_forward(c, bop, c->stream, flag, mode, out)
-                              : launch_adjoint(c, coef, w, c->stream, flag, w == nullptr);
+    hipError_t e = which == 0 ? launch_forward(c, I, c->stream, flag, mode, out)
+                              : launch_adjoint(c, coef, w, c->stream, flag, w == nullptr, mode);
     if (e0) {
         (void)hipEventRecord(e1, c->stream);
         c->pend[which].push_back({e0, e1});
@@ -204,12 +203,15 @@ int pick_schedule(int slots, const std::function<std::vector<double>(int)> &cost
 }
 
 // Direct contraction or the fast evaluation of k_trans.hip (same sums to
-// rounding, O(L^2 log L + W^2 Z) instead of Z N^2)?  Estimated times of one
-// direction in microseconds, per channel on average so that the choice does
-// not depend on how channels are grouped in contexts.  Measured, both
-// directions and everything else of an evaluation: 256^2 x 99,840 FP64 918 us
-// direct, 179 us fast; 1024^2 x 5,000,250 bf16x3 91.6 ms and 0.63 ms; 64^2 x
-// 5,130 FP64 42 us direct (two launches against six, so small problems stay).
+// rounding, O(L^2 log L + W^2 Z) instead of Z N^2)?  Both evaluations of Phi
+// and its gradient in microseconds, as fitted to measurements at sides 32 to
+// 512, 500 to 100,000 visibilities a channel, 1 and 8 channels: a launch-bound
+// part, a part per visibility (the contraction's rate; window and tile work)
+// and, for the transforms, a part per grid point.  Measured around the line
+// (one channel; direct, fast): 64^2 x 5,000 FP64 43.7, 49.4, x 100,000 138.7,
+// 138.1; FP32 x 20,000 50.0, 49.0; 128^2 bf16x3 x 2,000 33.8, 37.4, x 20,000
+// 52.1, 42.7; 100^2 x 500 FP64 61.0, 43.0 and FP32 54.5, 36.8; far from it
+// 256^2 x 100,000 FP64 918, 79; 1024^2 x 5,000,250 bf16x3 92,486, 420.
 void choose_transform(uvmem_ctx *c) {
     c->tr_lg = 0;
     if (c->fwd_model != UVMEM_FWD_DFT || c->ztot == 0 || c->ztot >= (int64_t)1 << 30) return;
@@ -218,10 +220,14 @@ void choose_transform(uvmem_ctx *c) {
     if (lg > 12) return;
     // grids and bin tables within 32 GiB and 2^28 entries
     if ((double)c->nchan * std::ldexp(1.0, 2 * lg) > (double)(1 << 30) * 2) return;
-    const double L = (double)(1 << lg), z = (double)c->ztot / c->nchan;
-    const double rate = c->prec == UVMEM_FP64 ? 55.0 : c->prec == UVMEM_FP32 ? 115.0 : 330.0;   // TFLOP/s
-    const double direct = 4.0 * z * c->np * c->np / rate * 1e-6;
-    const double transform = 8.0 + 5e-6 * L * L + 1e-4 * z;
+    // by padded side 64, 128 and larger; FP64, FP32, split
+    static const double base[3][3] = {{38, 60, 80}, {32, 54, 95}, {31, 32, 46}};        // microseconds
+    static const double rate[3][3] = {{34, 59, 62}, {50, 109, 138}, {88, 226, 450}};    // TFLOP/s
+    const int p = c->prec == UVMEM_FP64 ? 0 : c->prec == UVMEM_FP32 ? 1 : 2, q = c->np == 64 ? 0 : c->np == 128 ? 1 : 2;
+    const double z = (double)c->ztot;
+    const double direct = base[p][q] + 8.0 * z * c->np * c->np / rate[p][q] * 1e-6;
+    const double transform = (p == 0 ? 43.0 : 36.0) + c->nchan * std::ldexp(1.3e-5, 2 * lg) +
+                             z * (p == 0 ? 0.4e-3 : 0.17e-3) * (lg <= 7 ? 2.0 : 1.0);
     bool use = transform < direct;
     if (const char *env = std::getenv("UVMEM_DFT"))
         use = std::strcmp(env, "transform") == 0 ? true : std::strcmp(env, "direct") == 0 ? false : use;
@@ -233,6 +239,7 @@ void choose_transform(uvmem_ctx *c) {
     c->tr_nbx = (1 << lg) / 2 / tb + 1;
     c->tr_nby = (1 << lg) / tb;
     c->tr_lgc = (c->tr_nbx - 1) * tb + 2 * tb;
+    c->n_trrec = (c->n / 2 + tr_row_seqs(lg) - 1) / tr_row_seqs(lg);
 }
 
 // Window of the fast evaluation: phi(x) = I0(beta sqrt(1 - (2 x / W)^2)) /
@@ -632,36 +639,24 @@ hipError_t sort_bins(uvmem_ctx *c) {
         ok(hipMemcpy(vis + 2 * o, c->hvis[ch].data(), nv * 8, hipMemcpyHostToDevice));
         ok(hipMemcpy(w + o, c->hw[ch].data(), nv * 4, hipMemcpyHostToDevice));
     }
-    if (e == hipSuccess) e = launch_tr_sort(c, u, v, vis, w);
-    std::vector<int> start(C * nbin + 1), first(C * nbin + 1);
-    ok(hipMemcpy(start.data(), c->d_trbin, start.size() * sizeof(int), hipMemcpyDeviceToHost));
+    std::vector<int> start, first(C * nbin + 1);
+    if (e == hipSuccess) e = launch_tr_sort(c, u, v, vis, w, start);
     if (e != hipSuccess) return e;
-    // an item's visibilities: about eight waves' shares per SIMD, and at least
-    // two batches
-    const int64_t chunk = std::max<int64_t>(64, std::min<int64_t>(1024, (c->ztot / 8192 + 31) / 32 * 32));
+    // an item's visibilities: two waves' shares per wave slot of the chip, and
+    // one or two batches at least (fewer tiles to sum where they are many)
+    auto up32 = [](int64_t x) { return std::max<int64_t>(32, (x + 31) / 32 * 32); };
+    const int64_t chunk = std::max(std::min<int64_t>(64, up32(c->ztot / 2048)),
+                                   std::min<int64_t>(1024, up32(c->ztot / 8192)));
     std::vector<TrItem> items;
-    std::vector<int4> spread;
-    std::vector<std::pair<int, int>> single;   // runs of consecutive one-item bins
     int slot = 0;
     for (size_t t = 0; t < C * nbin; ++t) {
         first[t] = slot;
-        const int bin = (int)(t % nbin), i0 = (int)items.size();
-        for (int64_t k = start[t]; k < start[t + 1]; k += chunk)
-            items.push_back(TrItem{(int)(t / nbin), bin / c->tr_nby, bin % c->tr_nby,
-                                   slot + ((int)items.size() - i0) / TR_WAVES, (long long)k,
-                                   (long long)std::min<int64_t>(k + chunk, start[t + 1])});
-        const int ni = (int)items.size() - i0;
-        if (ni == 1) {
-            ++slot;
-            if (!single.empty() && single.back().second == i0) ++single.back().second;
-            else single.push_back({i0, i0 + 1});
-        } else {
-            for (int x = 0; x < ni; x += TR_WAVES, ++slot)
-                for (int v = 0; v < TR_WAVES; ++v) {
-                    const int i = std::min(i0 + x + v, i0 + ni);
-                    spread.push_back(make_int4(i, std::min(i + 1, i0 + ni), std::min(TR_WAVES, ni - x), 0));
-                }
-        }
+        const int bin = (int)(t % nbin);
+        int v = 0;
+        for (int64_t k = start[t]; k < start[t + 1]; k += chunk, ++v)
+            items.push_back(TrItem{(int)(t / nbin), bin / c->tr_nby, bin % c->tr_nby, slot + v / TR_WAVES,
+                                   (long long)k, (long long)std::min<int64_t>(k + chunk, start[t + 1])});
+        slot += (v + TR_WAVES - 1) / TR_WAVES;
     }
     first[C * nbin] = slot;
     c->n_tritem = (int)items.size();
@@ -677,13 +672,39 @@ hipError_t sort_bins(uvmem_ctx *c) {
         while (j < end && items[j].chan == items[i].chan && got + cost(items[j]) / 2 < per) got += cost(items[j++]);
         return j;
     };
-    for (auto &run : single)
-        for (int i = run.first; i < run.second;) {
-            const int j = span_end(i, run.second);
-            spread.push_back(make_int4(i, j, 0, 0));
-            i = j;
+    auto same_bin = [&](int i, int j) {
+        return items[i].chan == items[j].chan && items[i].bx == items[j].bx && items[i].by == items[j].by;
+    };
+    std::vector<int4> spread, shared;
+    std::vector<int> sbase(c->nimg + 1, 0);
+    for (int i = 0; i < c->n_tritem;) {
+        // one channel: the bins of several items, then the single ones' spans
+        const int ch = items[i].chan, img = c->nimg == C ? ch : 0;
+        shared.clear();
+        while (i < c->n_tritem && items[i].chan == ch) {
+            int j = i + 1;
+            while (j < c->n_tritem && same_bin(i, j)) ++j;
+            if (j - i > 1) {
+                for (int x = i; x < j; x += TR_WAVES)
+                    for (int v = 0; v < TR_WAVES; ++v) {
+                        const int y = std::min(x + v, j);
+                        shared.push_back(make_int4(y, std::min(y + 1, j), std::min(TR_WAVES, j - x), img));
+                    }
+                i = j;
+                continue;
+            }
+            // a run of one-item bins
+            while (j < c->n_tritem && items[j].chan == ch && !(j + 1 < c->n_tritem && same_bin(j, j + 1))) ++j;
+            while (i < j) {
+                const int k = span_end(i, j);
+                spread.push_back(make_int4(i, k, 0, img));
+                i = k;
+            }
         }
-    while (spread.size() % TR_WAVES) spread.push_back(make_int4(0, 0, 0, 0));
+        while (spread.size() % TR_WAVES) spread.push_back(make_int4(0, 0, 0, img));
+        spread.insert(spread.end(), shared.begin(), shared.end());
+        for (int m = c->nimg == C ? ch + 1 : 1; m <= c->nimg; ++m) sbase[m] = (int)(spread.size() / TR_WAVES);
+    }
     c->n_trspread = (int)(spread.size() / TR_WAVES);
     // gather: the same over all items, workgroups within one channel
     std::vector<int2> spans;
@@ -700,20 +721,32 @@ hipError_t sort_bins(uvmem_ctx *c) {
     }
     c->n_trgroup = (int)(spans.size() / TR_WAVES);
     const size_t ts = 2 * (size_t)(c->tr_w - 1);
-    ok(dalloc(c, &c->d_tritem, items.size()));
-    ok(dalloc(c, &c->d_trspan, spans.size()));
-    ok(dalloc(c, &c->d_trspread, spread.size()));
-    ok(dalloc(c, &c->d_trgbase, gbase.size()));
-    ok(dalloc(c, &c->d_trpart, (size_t)c->n_trgroup * NPART));
-    ok(dalloc(c, &c->d_trtile, slot * ts * ts));
-    auto up = [&](void *dst, const void *src, size_t bytes) {
-        if (e == hipSuccess) e = hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice);
+    // all tables in one allocation and one copy
+    std::vector<char> tab;
+    auto put = [&](const void *src, size_t bytes) {
+        const size_t at = (tab.size() + 15) / 16 * 16;
+        tab.resize(at + bytes);
+        if (bytes) std::memcpy(tab.data() + at, src, bytes);
+        return at;
     };
-    up(c->d_tritem, items.data(), items.size() * sizeof(TrItem));
-    up(c->d_trspan, spans.data(), spans.size() * sizeof(int2));
-    up(c->d_trspread, spread.data(), spread.size() * sizeof(int4));
-    up(c->d_trgbase, gbase.data(), gbase.size() * sizeof(int));
-    up(c->d_trbin, first.data(), first.size() * sizeof(int));
+    const size_t o_item = put(items.data(), items.size() * sizeof(TrItem));
+    const size_t o_span = put(spans.data(), spans.size() * sizeof(int2));
+    const size_t o_spread = put(spread.data(), spread.size() * sizeof(int4));
+    const size_t o_gbase = put(gbase.data(), gbase.size() * sizeof(int));
+    const size_t o_sbase = put(sbase.data(), sbase.size() * sizeof(int));
+    const size_t o_bin = put(first.data(), first.size() * sizeof(int));
+    ok(dalloc(c, &c->d_trtab, tab.size(), false));
+    ok(dalloc(c, &c->d_trpart, (size_t)std::max(c->n_trgroup, c->n_trspread) * NPART, false));
+    ok(dalloc(c, &c->d_trtile, slot * ts * ts, false));
+    if (e == hipSuccess) {
+        c->d_tritem = (TrItem *)(c->d_trtab + o_item);
+        c->d_trspan = (int2 *)(c->d_trtab + o_span);
+        c->d_trspread = (int4 *)(c->d_trtab + o_spread);
+        c->d_trgbase = (int *)(c->d_trtab + o_gbase);
+        c->d_trsbase = (int *)(c->d_trtab + o_sbase);
+        c->d_trbin = (int *)(c->d_trtab + o_bin);
+        ok(hipMemcpy(c->d_trtab, tab.data(), tab.size(), hipMemcpyHostToDevice));
+    }
     // the staging buffers start out as zeros again
     if (e == hipSuccess) ok(hipMemset(c->d_R, 0, c->ztot * sizeof(double2)));
     if (e == hipSuccess) ok(hipMemset(c->d_Vd, 0, c->ztot * sizeof(double2)));
@@ -1001,16 +1034,19 @@ int finalize_impl(uvmem_ctx *c) {
         }
     }
     // ---- fast evaluation: window and twiddles
-    std::vector<double> trpoly, trdec, trtw;
+    std::vector<double> trconst;   // twiddles, then the window's inverse transform, then its polynomials
     if (tr) {
         const int L = 1 << c->tr_lg;
-        transform_window(c->tr_w, c->tr_w == 17 ? TR_NE17 : TR_NE9, n, L, trpoly, trdec);
-        trtw.resize(2 * (size_t)L);
+        std::vector<double> poly, dec;
+        transform_window(c->tr_w, c->tr_w == 17 ? TR_NE17 : TR_NE9, n, L, poly, dec);
+        trconst.resize(2 * (size_t)L);
         for (int k = 0; k < L; ++k) {
             const long double ang = -2.0L * 3.141592653589793238462643383279502884L * k / L;
-            trtw[2 * k] = (double)std::cos(ang);
-            trtw[2 * k + 1] = (double)std::sin(ang);
+            trconst[2 * k] = (double)std::cos(ang);
+            trconst[2 * k + 1] = (double)std::sin(ang);
         }
+        trconst.insert(trconst.end(), dec.begin(), dec.end());
+        trconst.insert(trconst.end(), poly.begin(), poly.end());
     }
     // ---- gridded model: twiddles (FP64, rounded to the transform type) and
     // the visibilities sorted by grid cell (counting sort per channel, stable,
@@ -1112,17 +1148,14 @@ int finalize_impl(uvmem_ctx *c) {
     ok(dalloc(c, &c->d_R, c->ztot));
     ok(dalloc(c, &c->d_Vd, c->ztot));
     ok(dalloc(c, &c->d_vpart, (size_t)c->n_vparts * c->ztot));
-    const size_t planes = tr ? (size_t)C : (size_t)std::max(c->n_slots, c->n_slots_m);
+    const size_t planes = tr ? (size_t)(IMG == C ? 0 : C) : (size_t)std::max(c->n_slots, c->n_slots_m);
     ok(dalloc(c, (char **)&c->d_gpart, planes * np * np * (c->gpart_f32 ? sizeof(float) : sizeof(double))));
     if (tr) {
         const size_t L = (size_t)1 << c->tr_lg;
         const size_t lx = L / 2 + 2 * c->tr_h + 1;
-        ok(dalloc(c, &c->d_trbin, (size_t)C * c->tr_nbx * c->tr_nby + 1));
-        ok(dalloc(c, &c->d_trperm, c->ztot));
-        ok(dalloc(c, &c->d_trdec, trdec.size()));
-        ok(dalloc(c, &c->d_trpoly, trpoly.size()));
-        ok(dalloc(c, &c->d_trtw, L));
-        ok(dalloc(c, &c->d_trx, C * lx * n));
+        ok(dalloc(c, &c->d_trperm, c->ztot, false));
+        ok(dalloc(c, &c->d_trconst, trconst.size() * 8, false));
+        ok(dalloc(c, &c->d_trx, C * lx * n, false));
         ok(dalloc(c, &c->d_trg, C * c->tr_lgc * L));
     }
     if (region) {
@@ -1130,7 +1163,7 @@ int finalize_impl(uvmem_ctx *c) {
         ok(dalloc(c, &c->d_adj_m, adj_m.size()));
         ok(dalloc(c, &c->d_slot_base_m, C + 1));
     }
-    ok(dalloc(c, (char **)&c->d_bop, (size_t)C * np * np * rs));
+    ok(dalloc(c, (char **)&c->d_bop, tr ? 0 : (size_t)C * np * np * rs));
     ok(dalloc(c, (char **)&c->d_g, IMG * npix * rs));
     ok(dalloc(c, (char **)&c->d_gt, IMG * npix * rs));
     ok(dalloc(c, (char **)&c->d_dir, IMG * npix * rs));
@@ -1138,7 +1171,7 @@ int finalize_impl(uvmem_ctx *c) {
     ok(dalloc(c, &c->d_chan, (size_t)IMG * CH_N));
     ok(dalloc(c, &c->d_ls, (size_t)IMG * LSS_N));
     ok(dalloc(c, &c->d_ctr, (size_t)CTR_N * IMG));
-    ok(dalloc(c, &c->d_ppart, (size_t)2 * IMG * c->n_pb * NPART));
+    ok(dalloc(c, &c->d_ppart, (size_t)2 * IMG * std::max(c->n_pb, c->n_trrec) * NPART));
     ok(dalloc(c, &c->d_vispart, (size_t)std::max(c->n_visit, 1) * NPART));
     ok(dalloc(c, &c->d_flag, 4));
     ok(dalloc(c, &c->d_hist_ptr, 1));
@@ -1190,9 +1223,10 @@ int finalize_impl(uvmem_ctx *c) {
     }
     if (any_mask) up(c->d_mask, mask.data(), mask.size());
     if (tr) {
-        up(c->d_trdec, trdec.data(), trdec.size() * 8);
-        up(c->d_trpoly, trpoly.data(), trpoly.size() * 8);
-        up(c->d_trtw, trtw.data(), trtw.size() * 8);
+        up(c->d_trconst, trconst.data(), trconst.size() * 8);
+        c->d_trtw = (double2 *)c->d_trconst;
+        c->d_trdec = (double *)c->d_trconst + 2 * ((size_t)1 << c->tr_lg);
+        c->d_trpoly = c->d_trdec + n;
         if (e == hipSuccess) e = sort_bins(c);
     }
     if (gridded) {
@@ -1234,7 +1268,7 @@ int uvmem_phi_and_grad(uvmem_ctx *c, const void *I, void *grad, double *scal) {
     if (s) return s;
     if (!I || !grad) return fail(c, UVMEM_EINVAL, "null image or gradient");
     HIPCHK(c, launch_prologue(c, I, 1, c->stream));
-    HIPCHK(c, timed_dft(c, 0, c->d_bop, nullptr, nullptr, 0, 1));
+    HIPCHK(c, timed_dft(c, 0, I, nullptr, nullptr, 0, 1));
     HIPCHK(c, launch_vis_sum(c, 1, nullptr, c->stream));
     HIPCHK(c, timed_dft(c, 1, nullptr, c->d_R, c->d_w, 1));
     HIPCHK(c, launch_grad(c, I, grad, 1, scal, c->stream));
@@ -1246,7 +1280,7 @@ int uvmem_forward(uvmem_ctx *c, const void *I, void *vis) {
     if (s) return s;
     if (!I || (!vis && c->ztot)) return fail(c, UVMEM_EINVAL, "null image or output");
     HIPCHK(c, launch_prologue(c, I, 0, c->stream));
-    HIPCHK(c, timed_dft(c, 0, c->d_bop, nullptr, nullptr, 0, 0, (double2 *)vis));
+    HIPCHK(c, timed_dft(c, 0, I, nullptr, nullptr, 0, 0, (double2 *)vis));
     HIPCHK(c, launch_vis_sum(c, 0, (double2 *)vis, c->stream));
     return UVMEM_OK;
 }
@@ -1406,9 +1440,9 @@ int uvmem_cg_step(uvmem_ctx *c, void *I, double *scal) {
     if (!c->cg_ready) return fail(c, UVMEM_ESTATE, "cg_step before cg_init");
     if (I != c->cg_I) return fail(c, UVMEM_EINVAL, "cg_step image differs from cg_init's");
     HIPCHK(c, launch_cg_phase(c, I, scal, 0, c->stream));
-    HIPCHK(c, timed_dft(c, 0, c->d_bop, nullptr, nullptr, 1, 2));
+    HIPCHK(c, timed_dft(c, 0, I, nullptr, nullptr, 1, 2));
     HIPCHK(c, launch_cg_phase(c, I, scal, 1, c->stream));
-    HIPCHK(c, timed_dft(c, 1, nullptr, c->d_R, c->d_w, 1));
+    HIPCHK(c, timed_dft(c, 1, nullptr, c->d_R, c->d_w, 1, 1));
     HIPCHK(c, launch_cg_phase(c, I, scal, 2, c->stream));
     return UVMEM_OK;
 }

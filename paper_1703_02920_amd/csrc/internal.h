@@ -83,6 +83,10 @@ struct TrItem {
     long long kend;
 };
 
+// Sequences (pairs of image rows) per workgroup of its row passes: at least
+// a wave of threads, at most 512 threads and 74 KiB of LDS.
+constexpr int tr_row_seqs(int lg) { return lg <= 6 ? 8 : lg <= 8 ? 4 : lg <= 11 ? 2 : 1; }
+
 // One visibility-reduction workgroup: [kbeg, kend) inside one channel.
 struct VisItem {
     int chan;
@@ -240,17 +244,21 @@ struct uvmem_ctx {
     // in bin order: d_trperm[k] = caller's index << 1 | negated.
     int tr_lg = 0, tr_w = 0, tr_h = 0, tr_lgc = 0, tr_nbx = 0, tr_nby = 0;
     int n_tritem = 0;
+    char *d_trtab = nullptr;                    // the tables below, one allocation
+    char *d_trconst = nullptr;                  // d_trdec, d_trpoly, d_trtw likewise
     uvm::TrItem *d_tritem = nullptr;
     int *d_trbin = nullptr;                     // first tile slot of each bin, [C][nbx][nby] + 1
     // gather: spans of items, TR_WAVES per workgroup, each workgroup within
-    // one channel; its partial records d_trpart [n_trgroup][NPART], those of
+    // one channel; its partial records d_trpart [workgroup][NPART], those of
     // an image in [d_trgbase[img], d_trgbase[img + 1]).  Spread:
     // TR_WAVES per workgroup (first item, end, live waves of a workgroup
-    // whose items share a bin or 0)
+    // whose items share a bin or 0; image), records per image likewise
+    // (d_trsbase; a CG step's chi^2)
     int n_trgroup = 0, n_trspread = 0;
+    int n_trrec = 0;                   // records per image of the row passes
     int2 *d_trspan = nullptr;
     int4 *d_trspread = nullptr;
-    int *d_trgbase = nullptr;
+    int *d_trgbase = nullptr, *d_trsbase = nullptr;
     double *d_trpart = nullptr;
     unsigned *d_trperm = nullptr;
     double *d_trdec = nullptr, *d_trpoly = nullptr;
@@ -285,18 +293,21 @@ namespace uvm {
 // ---------------------------------------------------------------- launchers
 // All return hipSuccess or the launch error; every launch goes to `st`.
 
-// Forward DFT: vpart[part][k] = the image block's share of V_k (see
+// Forward DFT of A o I (the operand that launch_prologue made; the direction
+// for dir != 0): vpart[part][k] = the image block's share of V_k (see
 // k_dft.hip).  dir != 0: the operand is a CG direction, zero outside a focus
 // region, and only the region's blocks are visited (compact partials).  The
 // fast evaluation includes the visibility pass: mode as in launch_vis_sum (2
 // for a direction), out its output for mode 0.
-hipError_t launch_forward(const uvmem_ctx *c, const void *bop, hipStream_t st, int dir, int mode, double2 *out);
+hipError_t launch_forward(const uvmem_ctx *c, const void *I, hipStream_t st, int dir, int mode, double2 *out);
 // Adjoint: gpart[slot] tiles of Re F^H (w coef) without the beam factor.
 // grad != 0: a gradient, needed inside a focus region only (its own tiles
 // and split-K slot table).
 // caller != 0: coef is in the caller's visibility order.
+// step != 0: the adjoint of a CG step, at R + alpha Vd; the fast evaluation
+// then updates the residuals itself (k_cg_update has done it otherwise).
 hipError_t launch_adjoint(const uvmem_ctx *c, const double2 *coef, const float *w, hipStream_t st, int grad = 0,
-                          int caller = 0);
+                          int caller = 0, int step = 0);
 // Workgroups of that adjoint kernel resident on one CU at once (occupancy of
 // the compiled kernel; at least 1).
 int adjoint_wgs_per_cu(const uvmem_ctx *c);
@@ -309,18 +320,23 @@ hipError_t launch_grid_adjoint(const uvmem_ctx *c, const double2 *coef, const fl
 // Fast evaluation of the DFT and its adjoint (k_trans.hip).  The forward's
 // visibility pass is part of it: what = 0 writes V to out in the caller's
 // order, 1 the residuals and their chi^2 partials, 2 the direction
-// visibilities and the partials of a and b.  The adjoint writes the channels'
-// planes; perm (may be null) marks coefficients in the caller's order.  launch_tr_permute copies a visibility
+// visibilities, and the line search started from them (its image is then the
+// direction, I the current point).  The adjoint stops before the row pass,
+// which launch_tr_rows_inv does together with what launch_grad does (modes as
+// there; planes only where an image sums several channels); perm (may be null) marks coefficients in the caller's order.  launch_tr_permute copies a visibility
 // vector from bin order to the caller's (to_bins = 0) or back (1).
-hipError_t launch_tr_forward(const uvmem_ctx *c, const void *bop, int what, double2 *out, hipStream_t st);
+hipError_t launch_tr_forward(const uvmem_ctx *c, const void *I, int what, double2 *out, hipStream_t st);
 hipError_t launch_tr_adjoint(const uvmem_ctx *c, const double2 *coef, const float *w, const unsigned *perm,
-                             hipStream_t st);
+                             int step, hipStream_t st);
 // Finalize: sort the visibilities of raw arrays (device, caller's order) by
-// bin into the context's a, b, V^o, w and permutation; d_trbin gets the first
-// visibility of each bin.  Uses d_Vd as scratch.
-hipError_t launch_tr_sort(const uvmem_ctx *c, const double *u, const double *v, const float *vis, const float *w);
+// bin into the context's a, b, V^o, w and permutation; start (host) gets the
+// first visibility of each bin and the total.  Uses d_Vd as scratch.
+hipError_t launch_tr_sort(const uvmem_ctx *c, const double *u, const double *v, const float *vis, const float *w,
+                          std::vector<int> &start);
 // Gaussian primary beam of a channel.
 hipError_t launch_beam(const uvmem_ctx *c, int chan);
+hipError_t launch_tr_rows_inv(const uvmem_ctx *c, const void *I, void *out, int mode, double *user_scal,
+                              hipStream_t st);
 hipError_t launch_tr_permute(const uvmem_ctx *c, const double2 *src, double2 *dst, int to_bins, hipStream_t st);
 
 // The FP32 forward on explicit buffers (the allocation-free entry point):

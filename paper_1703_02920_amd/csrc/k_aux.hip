@@ -12,150 +12,10 @@
 #include <type_traits>
 
 #include "internal.h"
+#include "reduce.h"
 
 namespace uvm {
 namespace {
-
-// ---------------------------------------------------------------- reductions
-// Sum K doubles over the workgroup; every thread receives the totals.
-template <int K>
-__device__ __forceinline__ void block_sum(double (&v)[K]) {
-    __shared__ double red[K][NTHR / 64];
-#pragma unroll
-    for (int x = 0; x < K; ++x) {
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) v[x] += __shfl_xor(v[x], o, 64);
-    }
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    __syncthreads();
-    if (lane == 0) {
-#pragma unroll
-        for (int x = 0; x < K; ++x) red[x][wave] = v[x];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int x = 0; x < K; ++x) v[x] = (red[x][0] + red[x][1]) + (red[x][2] + red[x][3]);
-}
-
-__device__ __forceinline__ double block_min(double v) {
-    __shared__ double red[NTHR / 64];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    __syncthreads();
-    if (lane == 0) red[wave] = v;
-    __syncthreads();
-    return fmin(fmin(red[0], red[1]), fmin(red[2], red[3]));
-}
-
-// Partial records are written and read at device coherence (relaxed
-// agent-scope atomic stores and loads: they bypass the caches that are not
-// coherent between the chiplets), so that the workgroup that finishes a
-// reduction in the same launch reads every other workgroup's record.
-__device__ __forceinline__ void coh_store(double *p, double v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void coh_store(float *p, float v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ double coh_load(const double *p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Sum slot `s` (K slots starting at s0) of n_items partial records of NPART
-// doubles starting at `base`, in index order (strided per thread, then the
-// fixed workgroup reduction).
-template <int K>
-__device__ __forceinline__ void sum_partials(const double *base, int n_items, int s0, double (&out)[K]) {
-#pragma unroll
-    for (int x = 0; x < K; ++x) out[x] = 0.0;
-    for (int it = threadIdx.x; it < n_items; it += NTHR) {
-#pragma unroll
-        for (int x = 0; x < K; ++x) out[x] += coh_load(base + (size_t)it * NPART + s0 + x);
-    }
-    block_sum<K>(out);
-}
-
-// Two record sets in one pass, their loads issued together (one memory round
-// trip instead of two): slots [s0, s0 + K) of na records at `a` and slots
-// [s1, s1 + L) of nb records at `b`, each summed in index order exactly as
-// sum_partials does.  Past a set's end a thread reads a stand-in record of
-// the other set (never of an empty one) and adds -0.0, an exact identity.
-template <int K, int L>
-__device__ __forceinline__ void sum_partials2(const double *a, int na, int s0, double (&oa)[K], const double *b,
-                                              int nb, int s1, double (&ob)[L]) {
-    double v[K + L];
-#pragma unroll
-    for (int x = 0; x < K + L; ++x) v[x] = 0.0;
-    const int nmax = na > nb ? na : nb;
-    for (int it = threadIdx.x; it < nmax; it += NTHR) {
-        const bool oka = it < na, okb = it < nb;
-        const double *ra = oka ? a + (size_t)it * NPART + s0 : b + (size_t)it * NPART + s1;
-        const double *rb = okb ? b + (size_t)it * NPART + s1 : ra;
-        double la[K], lb[L];
-#pragma unroll
-        for (int x = 0; x < K; ++x) la[x] = coh_load(ra + (oka ? x : 0));
-#pragma unroll
-        for (int x = 0; x < L; ++x) lb[x] = coh_load(rb + (okb ? x : 0));
-#pragma unroll
-        for (int x = 0; x < K; ++x) v[x] += oka ? la[x] : -0.0;
-#pragma unroll
-        for (int x = 0; x < L; ++x) v[K + x] += okb ? lb[x] : -0.0;
-    }
-    block_sum<K + L>(v);
-#pragma unroll
-    for (int x = 0; x < K; ++x) oa[x] = v[x];
-#pragma unroll
-    for (int x = 0; x < L; ++x) ob[x] = v[K + x];
-}
-
-// Sums of slots [0, K) and minima of slots [K, K + MN) of n_items records,
-// one pass over the records (the sums in the order of sum_partials).
-template <int K, int MN>
-__device__ __forceinline__ void sum_min_partials(const double *base, int n_items, double (&sums)[K],
-                                                 double (&mins)[MN]) {
-#pragma unroll
-    for (int x = 0; x < K; ++x) sums[x] = 0.0;
-#pragma unroll
-    for (int x = 0; x < MN; ++x) mins[x] = INFINITY;
-    for (int it = threadIdx.x; it < n_items; it += NTHR) {
-        double l[K + MN];
-#pragma unroll
-        for (int x = 0; x < K + MN; ++x) l[x] = coh_load(base + (size_t)it * NPART + x);
-#pragma unroll
-        for (int x = 0; x < K; ++x) sums[x] += l[x];
-#pragma unroll
-        for (int x = 0; x < MN; ++x) mins[x] = fmin(mins[x], l[K + x]);
-    }
-    block_sum<K>(sums);
-#pragma unroll
-    for (int x = 0; x < MN; ++x) mins[x] = block_min(mins[x]);
-}
-
-// Arrival at the end of a partial-sum pass, once thread 0 has stored this
-// workgroup's partial record (coh_store): returns true (in every thread) in
-// exactly one workgroup per image and launch, the last to arrive at `ctr`,
-// which may then read every record of the image (coh_load) and finish the
-// image's reduction in a fixed order.  Thread 0 waits for its record's store
-// to complete before it counts itself in, so the last arrival finds every
-// record in place.  The counter only elects that workgroup (the sums never
-// depend on arrival order) and is left at zero for the next launch; no
-// workgroup waits for another.
-__device__ __forceinline__ bool arrive_last(unsigned *ctr, unsigned expected) {
-    __shared__ unsigned s_last;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        __builtin_amdgcn_s_waitcnt(0);   // this workgroup's record stored
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        const unsigned t = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const bool last = t + 1 == expected;
-        if (last) __hip_atomic_store(ctr, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s_last = last ? 1u : 0u;
-    }
-    __syncthreads();
-    return s_last != 0;
-}
 
 // ---------------------------------------------------------------- fill
 template <typename R>
@@ -311,9 +171,6 @@ __device__ __forceinline__ void vis_item(const VisItem it, int item, const doubl
     }
 }
 
-__device__ void ls_init(double *st, double a, double b, double e1, double e2, double amax, bool stop,
-                        bool am_eval, double f_am, double h_am);
-
 // Visibility pass over the context's items (modes 0, 1, 3 and 4 above).
 __global__ __launch_bounds__(NTHR) void k_vis(const VisItem *__restrict__ items,
                                               const double2 *__restrict__ vpart, int n_parts, long long ztot,
@@ -337,39 +194,30 @@ __global__ __launch_bounds__(NTHR) void k_vis(const VisItem *__restrict__ items,
 // mode 3: out = scale_img x G without the attenuation (dirty image / PSF).
 // With a focus-of-attention mask, pixels outside it are not free: modes 1
 // and 2 write 0 there (gradient and projected gradient).
-// Image totals finished by the last workgroup of an image (modes 1 and 2):
-//   mode 1: Phi, chi^2 (from the visibility pass's partials) and S (from the
-//           prologue's partials) into the scalars and, if given, `user`;
-//   mode 2: the Polak-Ribiere beta (clipped at 0), |gt|^2 and the iteration
-//           count; all scalars copied to `user`.
-struct GradTail {
-    unsigned *ctr;
-    const double *vispart;
-    const int *ivis_base;
-    const double *pp_S;
-    double *scal;
-    double *chan;
-    double *user;
-    // graph replays of a one-image CG step: the history buffer's address and
-    // the replay counter (the scalars go to row *hist_ctr); null otherwise
-    const long long *hist_ptr;
-    long long *hist_ctr;
+// The last workgroup of an image finishes modes 1 and 2 (grad_tail).
+// TR (fast evaluation, several channels per image): mode 1 also sums S and
+// checks the domain, mode 2 first takes the CG step I <- max(I + alpha d, M).
+struct GradStep {
+    const void *dir;
+    int *flag;
 };
-
-template <typename R, int RP, typename PT>
+template <typename R, int RP, typename PT, bool TR>
 __global__ __launch_bounds__(NTHR) void k_grad(const PT *__restrict__ gpart, const int *__restrict__ slot_base,
                                                const int *__restrict__ ichan_base,
-                                               const R *__restrict__ beam, const R *__restrict__ I,
+                                               const R *__restrict__ beam, R *__restrict__ I,
                                                R *__restrict__ out, R *__restrict__ gt,
                                                double *__restrict__ ppart, const double *__restrict__ img_scale,
                                                const unsigned char *__restrict__ mask, int n, int np, int n_pb,
                                                int pb_len, double M, double Mb, double lam, int mode,
-                                               GradTail tail) {
+                                               GradTail tail, GradStep step) {
     const int c = blockIdx.x / n_pb, pb = blockIdx.x % n_pb;
+    const double al = TR && mode == 2 ? tail.ls[(size_t)c * LSS_N + LSS_ALPHA] : 0.0;
+    int bad = 0;
     const long long npix = (long long)n * n;
     const int ch0 = ichan_base[c], ch1 = ichan_base[c + 1];   // the channels that see this image
     const size_t np2 = (size_t)np * np;
-    double acc[2] = {0.0, 0.0};
+    constexpr int NA = TR ? 3 : 2;
+    double acc[NA] = {};
     // groups of RP pixels per thread; fixed-order sum over the slots with
     // 8 slots x RP pixels of independent loads in flight
     for (int g0 = 0; g0 < pb_len; g0 += RP * NTHR) {
@@ -450,15 +298,24 @@ __global__ __launch_bounds__(NTHR) void k_grad(const PT *__restrict__ gpart, con
             const size_t q = (size_t)c * npix + p;
             double gv = AG[r];
             if (mode == 3) gv *= img_scale[c];
+            double x = (double)xI[r];
             if (mode == 1 || mode == 2) {
-                const double x = (double)xI[r];
-                gv += lam * (log(x / M) + 1.0);
+                if (TR && mode == 2 && al != 0.0) {
+                    const R xr = (R)fmax(x + al * (double)reinterpret_cast<const R *>(step.dir)[q], Mb);
+                    I[q] = xr;
+                    x = (double)xr;
+                }
+                const double lg = log(x / M);
+                if (TR) {
+                    if (!(x > 0.0)) bad = 1;
+                    else acc[mode == 1 ? 0 : NA - 1] += x * lg;
+                }
+                gv += lam * (lg + 1.0);
                 if (mask && !mk[r]) gv = 0.0;
             }
             const R gr = (R)gv;
             out[q] = gr;
             if (mode == 2) {
-                const double x = (double)xI[r];
                 const bool act = (x <= Mb * (1.0 + BOUND_TOL)) && ((double)gr > 0.0);
                 const double gnew = act ? 0.0 : (double)gr;
                 const double gold = (double)xgt[r];
@@ -468,57 +325,15 @@ __global__ __launch_bounds__(NTHR) void k_grad(const PT *__restrict__ gpart, con
             }
         }
     }
-    if (mode == 2) {
-        block_sum<2>(acc);
+    if (mode == 2 || (TR && mode == 1)) {
+        if (TR && bad) atomicOr(step.flag, 1);
+        block_sum<NA>(acc);
         if (threadIdx.x == 0) {
-            coh_store(ppart + ((size_t)c * n_pb + pb) * NPART + 0, acc[0]);
-            coh_store(ppart + ((size_t)c * n_pb + pb) * NPART + 1, acc[1]);
+#pragma unroll
+            for (int x = 0; x < NA; ++x) coh_store(ppart + ((size_t)c * n_pb + pb) * NPART + x, acc[x]);
         }
     }
-    if ((mode != 1 && mode != 2) || !arrive_last(tail.ctr + c, (unsigned)n_pb)) return;
-    double *sc = tail.scal + (size_t)c * UVMEM_NSCAL;
-    if (mode == 1) {
-        double x2[1], S[1];
-        const int v0 = tail.ivis_base[c], v1 = tail.ivis_base[c + 1];
-        sum_partials2<1, 1>(tail.vispart + (size_t)v0 * NPART, v1 - v0, 0, x2,
-                            tail.pp_S + (size_t)c * n_pb * NPART, n_pb, 0, S);
-        if (threadIdx.x == 0) {
-            const double chi2 = 0.5 * x2[0];
-            sc[UVMEM_S_PHI] = chi2 + lam * S[0];
-            sc[UVMEM_S_CHI2] = chi2;
-            sc[UVMEM_S_S] = S[0];
-            if (tail.user) {
-                double *u = tail.user + (size_t)c * UVMEM_NSCAL;
-                u[UVMEM_S_PHI] = sc[UVMEM_S_PHI];
-                u[UVMEM_S_CHI2] = chi2;
-                u[UVMEM_S_S] = S[0];
-            }
-        }
-        return;
-    }
-    double gg[2];
-    sum_partials<2>(ppart + (size_t)c * n_pb * NPART, n_pb, 0, gg);
-    if (threadIdx.x == 0) {
-        double *ch = tail.chan + (size_t)c * CH_N;
-        const double gold = ch[CH_GG_OLD];
-        const bool stop = ch[CH_STOP] != 0.0;
-        double beta = 0.0;
-        if (!stop && gold > 0.0) beta = fmax(0.0, (gg[0] - gg[1]) / gold);
-        sc[UVMEM_S_BETA] = beta;
-        sc[UVMEM_S_GNORM2] = gg[0];
-        if (sc[UVMEM_S_ALPHA] != 0.0) sc[UVMEM_S_ITER] += 1.0;
-        if (tail.user) {
-            for (int x = 0; x < UVMEM_NSCAL; ++x) tail.user[(size_t)c * UVMEM_NSCAL + x] = sc[x];
-        }
-        if (tail.hist_ptr) {
-            double *hb = reinterpret_cast<double *>(tail.hist_ptr[0]);
-            const long long t = tail.hist_ctr[0];
-            if (hb) {
-                for (int x = 0; x < UVMEM_NSCAL; ++x) hb[t * UVMEM_NSCAL + x] = sc[x];
-            }
-            tail.hist_ctr[0] = t + 1;
-        }
-    }
+    grad_tail<NTHR, TR>(mode, c, n_pb, ppart, lam, tail);
 }
 
 // ---------------------------------------------------------------- CG
@@ -569,7 +384,7 @@ __global__ __launch_bounds__(NTHR) void k_cg_init(const R *__restrict__ I, const
 // direction and for the restart direction -gt, of the entropy parts of
 // phi'(0) - b and phi''(0) - a and of alpha_max.  The last workgroup of an
 // image takes step 2: restart with d = -gt when gt . d >= 0 (it then rewrites
-// the image's d and B itself, which a restart alone needs), stop when the
+// the image's d and B itself, which a restart alone needs; bop null: no B), stop when the
 // projected gradient is zero; it keeps the chosen direction's totals and
 // starts the line search of an image that has no visibilities.
 template <typename R>
@@ -608,7 +423,7 @@ __global__ __launch_bounds__(NTHR) void k_cg_dir(const R *__restrict__ I, const 
         // keep an older copy to write back after it
         coh_store(dir + q, dr);
         const int i = (int)(p / n), j = (int)(p % n);
-        for (int ch = ch0; ch < ch1; ++ch)
+        for (int ch = ch0; ch < ch1 && bop; ++ch)
             coh_store(bop + (size_t)ch * np * np + (size_t)i * np + j,
                       (ch == ch0 ? bm0 : beam[(size_t)ch * npix + p]) * dr);
         d = (double)dr;
@@ -660,135 +475,12 @@ __global__ __launch_bounds__(NTHR) void k_cg_dir(const R *__restrict__ I, const 
         const R dr = (R)(-(double)gt[q]);
         coh_store(dir + q, dr);
         const int i = (int)(p / n), j = (int)(p % n);
-        for (int ch = ch0; ch < ch1; ++ch)
+        for (int ch = ch0; ch < ch1 && bop; ++ch)
             coh_store(bop + (size_t)ch * np * np + (size_t)i * np + j, beam[(size_t)ch * npix + p] * dr);
     }
 }
 
-// ---- line search: exact minimisation of the convex phi on [0, alpha_max]
-//   phi'(al)  = b + a al + lambda sum d (ln((I + al d)/M) + 1)
-//   phi''(al) = a + lambda sum d^2 / (I + al d)
-// The entropy part of phi' increases with al, so phi'(al) >= phi'(0) + a al
-// and the minimiser lies below -phi'(0)/a: that bounds a search without
-// alpha_max.  The start knows phi', phi'' at 0 and, from the direction's
-// visibility pass, at alpha_max, which settles a step that reaches alpha_max
-// without any pass.  Each pass evaluates phi', phi'' at LS_K trial steps
-// inside the bracket [LO, HI] and keeps the smallest bracket.  With HI
-// evaluated the trials are the root of the cubic Hermite interpolant of phi'
-// on the bracket, the Newton steps from both ends, the secant step and points
-// 1e-3 and 1e-6 of the bracket either side of the cubic's root; with HI an
-// unevaluated bound, a geometric ladder from the Newton step to HI; with no
-// bound, factors of 4 from the Newton step.  A bracket narrowed to 1e-13 (or
-// the last pass) accepts the cubic's root.  The state is advanced identically
-// by every workgroup of the channel.
-enum { PH_SEARCH = 0, PH_DONE = 3 };
-static_assert(LS_K == 8, "the bracket proposal fills eight trial steps");
-
-__device__ __forceinline__ void ls_finish(double *st, double al) {
-    st[LSS_PHASE] = PH_DONE;
-    st[LSS_ALPHA] = al;
-#pragma unroll
-    for (int m = 0; m < LS_K; ++m) st[LSS_T0 + m] = al;
-}
-
-// Root in [lo, hi] of the cubic Hermite interpolant p of phi' from its values
-// f0 < 0 < f1 and slopes h0, h1 at the ends, by Newton's method on the unit
-// parameter s of the bracket, safeguarded by bisection of the sub-bracket on
-// which p changes sign.
-__device__ double hermite_root(double lo, double hi, double f0, double f1, double h0, double h1) {
-    const double w = hi - lo, d0 = h0 * w, d1 = h1 * w;
-    double sl = 0.0, sh = 1.0;
-    double s = f0 / (f0 - f1);
-    if (!(s > 0.0 && s < 1.0)) s = 0.5;
-    for (int it = 0; it < 64; ++it) {
-        const double s2 = s * s, s3 = s2 * s;
-        const double p = (2.0 * s3 - 3.0 * s2 + 1.0) * f0 + (s3 - 2.0 * s2 + s) * d0 + (3.0 * s2 - 2.0 * s3) * f1 +
-                         (s3 - s2) * d1;
-        if (p == 0.0) break;
-        if (p < 0.0) sl = s;
-        else sh = s;
-        const double dp = 6.0 * (s2 - s) * (f0 - f1) + (3.0 * s2 - 4.0 * s + 1.0) * d0 + (3.0 * s2 - 2.0 * s) * d1;
-        double sn = dp != 0.0 ? s - p / dp : 0.5 * (sl + sh);
-        if (!(sn > sl && sn < sh)) sn = 0.5 * (sl + sh);
-        if (sn == s) break;
-        s = sn;
-    }
-    return fmin(fmax(lo + s * w, lo), hi);
-}
-
-__device__ __forceinline__ double ls_cubic(const double *st) {
-    return hermite_root(st[LSS_LO], st[LSS_HI], st[LSS_FLO], st[LSS_FHI], st[LSS_HLO], st[LSS_HHI]);
-}
-
-__device__ void ls_propose(double *st) {
-    const double lo = st[LSS_LO], hi = st[LSS_HI];
-    const double tn = lo - st[LSS_FLO] / st[LSS_HLO];   // > lo (FLO < 0, HLO > 0)
-    double t[LS_K];
-    if (hi < 0.0) {
-        double x = (tn > lo && isfinite(tn)) ? tn : (lo > 0.0 ? 2.0 * lo : 1.0);
-        for (int m = 0; m < LS_K; ++m, x *= 4.0) t[m] = x;
-    } else if (st[LSS_HI_EVAL] == 0.0) {
-        const double t0 = (tn > lo && tn < hi) ? tn : lo + 0.5 * (hi - lo);
-        const double r = log(hi / t0) / (LS_K - 1);
-        for (int m = 0; m < LS_K - 1; ++m) t[m] = t0 * exp(r * m);
-        t[LS_K - 1] = hi;
-    } else {
-        const double w = hi - lo;
-        const double rc = ls_cubic(st);
-        t[0] = rc;
-        t[1] = tn;
-        t[2] = hi - st[LSS_FHI] / st[LSS_HHI];
-        t[3] = lo - st[LSS_FLO] * w / (st[LSS_FHI] - st[LSS_FLO]);
-        t[4] = rc - 1e-3 * w;
-        t[5] = rc + 1e-3 * w;
-        t[6] = rc - 1e-6 * w;
-        t[7] = rc + 1e-6 * w;
-        for (int m = 0; m < LS_K; ++m)
-            if (!(t[m] > lo && t[m] < hi)) t[m] = lo + (m + 1) * w / (LS_K + 1);
-    }
-    for (int i = 1; i < LS_K; ++i)   // ascending (insertion sort)
-        for (int j = i; j > 0 && t[j] < t[j - 1]; --j) {
-            const double x = t[j]; t[j] = t[j - 1]; t[j - 1] = x;
-        }
-#pragma unroll
-    for (int m = 0; m < LS_K; ++m) st[LSS_T0 + m] = t[m];
-}
-
-// Start from a, b, e1 = lambda sum d (ln(I/M) + 1), e2 = lambda sum d^2/I
-// (so phi'(0) = b + e1, phi''(0) = a + e2), alpha_max and, when am_eval, the
-// entropy parts f_am, h_am of phi', phi'' at alpha_max.
-__device__ void ls_init(double *st, double a, double b, double e1, double e2, double amax, bool stop,
-                        bool am_eval, double f_am, double h_am) {
-    st[LSS_A] = a;
-    st[LSS_B] = b;
-    st[LSS_AMAX] = isfinite(amax) ? amax : -1.0;
-    st[LSS_STOP] = stop ? 1.0 : 0.0;
-    st[LSS_LO] = 0.0;
-    st[LSS_HI] = isfinite(amax) ? amax : -1.0;
-    st[LSS_FLO] = b + e1;
-    st[LSS_HLO] = a + e2;
-    st[LSS_FHI] = 0.0;
-    st[LSS_HHI] = 0.0;
-    st[LSS_HI_EVAL] = 0.0;
-    st[LSS_PHASE] = PH_SEARCH;
-    if (stop || !(st[LSS_FLO] < 0.0) || !(st[LSS_HLO] > 0.0) || (isfinite(amax) && amax <= 0.0)) {
-        ls_finish(st, 0.0);
-        return;
-    }
-    if (isfinite(amax) && am_eval) {
-        const double fa = b + a * amax + f_am;
-        if (fa <= 0.0) {   // phi' <= 0 on all of [0, alpha_max]
-            ls_finish(st, amax);
-            return;
-        }
-        st[LSS_FHI] = fa;
-        st[LSS_HHI] = a + h_am;
-        st[LSS_HI_EVAL] = 1.0;
-    } else if (!isfinite(amax) && a > 0.0) {
-        st[LSS_HI] = -st[LSS_FLO] / a;
-    }
-    ls_propose(st);
-}
+// The line search itself is described with its start (reduce.h).
 
 // Advance the state with phi'(T_m) = f[m], phi''(T_m) = h[m].
 __device__ void ls_update(double *st, const double *f, const double *h) {
@@ -846,15 +538,12 @@ __device__ __forceinline__ void ls_eval(const double *st, const double *pp, int 
 // parts of phi', phi'' at alpha_max (pixel workgroups of the images that have
 // visibilities; zero without a finite alpha_max).  The last workgroup of an
 // image starts its line search from these totals and the direction pass's.
-// n_visit = 0: the forward model has left Vd and the partials already
-// (vispart records rec_base[img] .. of the image).
 template <typename R>
 __global__ __launch_bounds__(NTHR) void k_cg_vis(const VisItem *__restrict__ items, int n_visit,
                                                  const double2 *__restrict__ vpart, int n_parts, long long ztot,
                                                  const float *__restrict__ w, double2 *__restrict__ Rv,
                                                  double2 *__restrict__ Vd, double *__restrict__ vispart,
                                                  const int *__restrict__ chan_img, const int *__restrict__ ivis_base,
-                                                 const int *__restrict__ rec_base,
                                                  const R *__restrict__ I, const R *__restrict__ dir,
                                                  double *__restrict__ ppart, int n, int n_pb, int pb_len, double M,
                                                  double lam, const double *__restrict__ chan,
@@ -896,8 +585,8 @@ __global__ __launch_bounds__(NTHR) void k_cg_vis(const VisItem *__restrict__ ite
             coh_store(ppart + ((size_t)img * n_pb + pb) * NPART + 1, acc[1]);
         }
     }
-    const int v0 = rec_base[img], v1 = rec_base[img + 1];
-    if (!arrive_last(ctr + img, (unsigned)((n_visit ? v1 - v0 : 0) + n_pb))) return;
+    const int v0 = ivis_base[img], v1 = ivis_base[img + 1];
+    if (!arrive_last(ctr + img, (unsigned)(v1 - v0 + n_pb))) return;
     double ab[2], fh[2];
     sum_partials2<2, 2>(vispart + (size_t)v0 * NPART, v1 - v0, 0, ab, ppart + (size_t)img * n_pb * NPART, n_pb, 0,
                         fh);
@@ -1055,7 +744,7 @@ inline int pix_grid(const uvmem_ctx *c) { return c->nimg * c->n_pb; }
 // partials until the evaluation's gradient pass has read them; every CG pass
 // writes buffer 1 and its last workgroups read it in the same launch.
 inline double *pp(const uvmem_ctx *c, int buf) {
-    return c->d_ppart + (size_t)buf * c->nimg * c->n_pb * NPART;
+    return c->d_ppart + (size_t)buf * c->nimg * std::max(c->n_pb, c->n_trrec) * NPART;
 }
 inline unsigned *ctr(const uvmem_ctx *c, int site) { return c->d_ctr + (size_t)site * c->nimg; }
 // The fp16 split adjoint scales its coefficients by the channel's max |w R|,
@@ -1073,34 +762,34 @@ hipError_t t_prologue(const uvmem_ctx *c, const void *I, int with_entropy, hipSt
 // k_grad with 4 pixels per thread and round when the pixel blocks are long
 // enough, else 1 (more workgroups, fewer loads in flight per thread); the
 // split-K partials are FP32 for the split precisions, else FP64
-template <typename R, typename PT>
+template <typename R, typename PT, bool TR>
 void grad_launch_t(const uvmem_ctx *c, const void *I, void *out, double *ppart, int mode, double *user,
                    hipStream_t st) {
     const PT *gp = static_cast<const PT *>(c->d_gpart);
     // gradients (modes 1, 2) follow the region-restricted adjoint and its slots
     const int *slots = (mode == 1 || mode == 2) && c->has_region ? c->d_slot_base_m : c->d_slot_base;
-    const bool hist = mode == 2 && c->hist_in_grad;
-    // an evaluation's chi^2 partials come from the forward's visibility pass
-    const bool tr1 = c->tr_lg && mode == 1;
-    const GradTail tail{ctr(c, CTR_GRAD), tr1 ? c->d_trpart : c->d_vispart, tr1 ? c->d_trgbase : c->d_ivis_base, pp(c, 0), c->d_scal, c->d_chan, user,
-                        hist ? c->d_hist_ptr : nullptr, hist ? c->d_iter_ctr : nullptr};
+    const GradTail tail = make_grad_tail(c, mode, user);
+    const GradStep step{c->d_dir, c->d_flag};
+    R *img = P<R>(const_cast<void *>(I));   // written by a TR step only
     if (c->pix_blk >= 4 * NTHR)
-        hipLaunchKernelGGL((k_grad<R, 4, PT>), dim3(pix_grid(c)), dim3(NTHR), 0, st, gp, slots,
-                           c->d_ichan_base, CP<R>(c->d_beam), CP<R>(I), P<R>(out), P<R>(c->d_gt), ppart,
-                           c->d_wscale, c->d_mask, c->n, c->np, c->n_pb, c->pix_blk, c->M, c->Mb, c->lam, mode, tail);
+        hipLaunchKernelGGL((k_grad<R, 4, PT, TR>), dim3(pix_grid(c)), dim3(NTHR), 0, st, gp, slots, c->d_ichan_base,
+                           CP<R>(c->d_beam), img, P<R>(out), P<R>(c->d_gt), ppart, c->d_wscale, c->d_mask, c->n,
+                           c->np, c->n_pb, c->pix_blk, c->M, c->Mb, c->lam, mode, tail, step);
     else
-        hipLaunchKernelGGL((k_grad<R, 1, PT>), dim3(pix_grid(c)), dim3(NTHR), 0, st, gp, slots,
-                           c->d_ichan_base, CP<R>(c->d_beam), CP<R>(I), P<R>(out), P<R>(c->d_gt), ppart,
-                           c->d_wscale, c->d_mask, c->n, c->np, c->n_pb, c->pix_blk, c->M, c->Mb, c->lam, mode, tail);
+        hipLaunchKernelGGL((k_grad<R, 1, PT, TR>), dim3(pix_grid(c)), dim3(NTHR), 0, st, gp, slots, c->d_ichan_base,
+                           CP<R>(c->d_beam), img, P<R>(out), P<R>(c->d_gt), ppart, c->d_wscale, c->d_mask, c->n,
+                           c->np, c->n_pb, c->pix_blk, c->M, c->Mb, c->lam, mode, tail, step);
 }
 
 template <typename R>
 void grad_launch(const uvmem_ctx *c, const void *I, void *out, double *ppart, int mode, double *user,
                  hipStream_t st) {
-    if (c->gpart_f32)
-        grad_launch_t<R, float>(c, I, out, ppart, mode, user, st);
+    if (c->tr_lg)
+        grad_launch_t<R, double, true>(c, I, out, ppart, mode, user, st);
+    else if (c->gpart_f32)
+        grad_launch_t<R, float, false>(c, I, out, ppart, mode, user, st);
     else
-        grad_launch_t<R, double>(c, I, out, ppart, mode, user, st);
+        grad_launch_t<R, double, false>(c, I, out, ppart, mode, user, st);
 }
 
 template <typename R>
@@ -1120,7 +809,8 @@ hipError_t t_cg_phase(const uvmem_ctx *c, void *I, double *user, int phase, hipS
         // 1-3. direction update and projection, restart test and stop, B = A o d,
         // alpha_max and the entropy parts of phi'(0), phi''(0)
         hipLaunchKernelGGL(k_cg_dir<R>, gp, blk, 0, st, CP<R>(I), CP<R>(c->d_g), CP<R>(c->d_gt), P<R>(c->d_dir),
-                           CP<R>(c->d_beam), P<R>(c->d_bop), c->d_ichan_base, c->d_scal, c->d_chan, pp(c, 1), c->n,
+                           CP<R>(c->d_beam), c->tr_lg ? (R *)nullptr : P<R>(c->d_bop), c->d_ichan_base, c->d_scal,
+                           c->d_chan, pp(c, 1), c->n,
                            c->np, c->n_pb, c->pix_blk, c->M, c->Mb, c->lam, ctr(c, CTR_DIR), c->d_ivis_base,
                            c->d_ls);
         return hipGetLastError();
@@ -1128,13 +818,11 @@ hipError_t t_cg_phase(const uvmem_ctx *c, void *I, double *user, int phase, hipS
     if (phase == 1) {
         // 5. Vd, the quadratic coefficients a, b of chi^2 along d and phi'
         // at alpha_max; the line search starts from them
-        const bool tr = c->tr_lg > 0;
-        const int nv = tr ? 0 : c->n_visit;
-        if (c->n_visit)
-            hipLaunchKernelGGL(k_cg_vis<R>, dim3(nv + pix_grid(c)), blk, 0, st, c->d_vis, nv,
+        // (the fast evaluation's forward has done all of that)
+        if (c->n_visit && !c->tr_lg)
+            hipLaunchKernelGGL(k_cg_vis<R>, dim3(c->n_visit + pix_grid(c)), blk, 0, st, c->d_vis, c->n_visit,
                                c->d_vpart, c->has_region ? c->n_vparts_m : c->n_vparts, (long long)c->ztot,
-                               c->d_w, c->d_R, c->d_Vd, tr ? c->d_trpart : c->d_vispart, c->d_chan_img, c->d_ivis_base,
-                               tr ? c->d_trgbase : c->d_ivis_base, CP<R>(I),
+                               c->d_w, c->d_R, c->d_Vd, c->d_vispart, c->d_chan_img, c->d_ivis_base, CP<R>(I),
                                CP<R>(c->d_dir), pp(c, 1), c->n, c->n_pb, c->pix_blk, c->M, c->lam, c->d_chan,
                                c->d_ls, ctr(c, CTR_VIS));
         // 6-7. line-search passes (the last one accepts a step)
@@ -1145,6 +833,8 @@ hipError_t t_cg_phase(const uvmem_ctx *c, void *I, double *user, int phase, hipS
         // 8-9. I <- max(I + alpha d, M) and its entropy partial (pixel
         // workgroups); R <- R + alpha Vd and the chi^2 partials (visibility
         // workgroups); Phi of the new image
+        // (the fast evaluation does this in its spread and gradient passes)
+        if (c->tr_lg) return hipGetLastError();
         hipLaunchKernelGGL(k_cg_update<R>, dim3(pix_grid(c) + c->n_visit), blk, 0, st, P<R>(I), CP<R>(c->d_dir),
                            c->d_ls, pp(c, 1), c->d_scal, c->d_chan, c->d_flag, c->n, c->n_pb, c->pix_blk, c->M,
                            c->Mb, c->lam, c->d_vis, c->d_w, c->d_R, c->d_Vd, c->d_vispart, c->d_chan_img,
@@ -1152,8 +842,7 @@ hipError_t t_cg_phase(const uvmem_ctx *c, void *I, double *user, int phase, hipS
         return hipGetLastError();
     }
     // 10-12. gradient at the new point, projected gradient, beta and the scalars
-    grad_launch<R>(c, I, c->d_g, pp(c, 1), 2, user, st);
-    return hipGetLastError();
+    return launch_grad(c, I, c->d_g, 2, user, st);
 }
 
 }  // namespace
@@ -1183,6 +872,7 @@ hipError_t launch_fill(const uvmem_ctx *c, void *img, double value, hipStream_t 
 }
 
 hipError_t launch_prologue(const uvmem_ctx *c, const void *I, int with_entropy, hipStream_t st) {
+    if (c->tr_lg) return hipSuccess;   // part of the fast evaluation's first pass
     return c->prec == UVMEM_FP64 ? t_prologue<double>(c, I, with_entropy, st)
                                  : t_prologue<float>(c, I, with_entropy, st);
 }
@@ -1213,6 +903,12 @@ hipError_t launch_coef_max(const uvmem_ctx *c, const double2 *coef, hipStream_t 
 }
 
 hipError_t launch_grad(const uvmem_ctx *c, const void *I, void *out, int mode, double *user_scal, hipStream_t st) {
+    if (c->tr_lg) {
+        // the inverse's last pass; it does the rest itself unless an image
+        // sums several channels
+        const hipError_t e = launch_tr_rows_inv(c, I, out, mode, user_scal, st);
+        if (e != hipSuccess || c->nimg == c->nchan) return e;
+    }
     if (c->prec == UVMEM_FP64) grad_launch<double>(c, I, out, pp(c, 1), mode, user_scal, st);
     else grad_launch<float>(c, I, out, pp(c, 1), mode, user_scal, st);
     return hipGetLastError();
@@ -1242,9 +938,9 @@ hipError_t launch_cg_phase(const uvmem_ctx *c, void *I, double *user, int phase,
 hipError_t launch_cg_step(const uvmem_ctx *c, void *I, double *user, hipStream_t st) {
     hipError_t e;
     if ((e = launch_cg_phase(c, I, user, 0, st)) != hipSuccess) return e;
-    if ((e = launch_forward(c, c->d_bop, st, 1, 2, nullptr)) != hipSuccess) return e;
+    if ((e = launch_forward(c, I, st, 1, 2, nullptr)) != hipSuccess) return e;
     if ((e = launch_cg_phase(c, I, user, 1, st)) != hipSuccess) return e;
-    if ((e = launch_adjoint(c, c->d_R, c->d_w, st, 1)) != hipSuccess) return e;
+    if ((e = launch_adjoint(c, c->d_R, c->d_w, st, 1, 0, 1)) != hipSuccess) return e;
     return launch_cg_phase(c, I, user, 2, st);
 }
 

@@ -1626,9 +1626,10 @@ hipError_t launch_forward_f32_raw(int ib_rows, int jb_cols, const FwdPItem *item
     return hipGetLastError();
 }
 
-hipError_t launch_forward(const uvmem_ctx *c, const void *bop, hipStream_t st, int dir, int mode, double2 *out) {
+hipError_t launch_forward(const uvmem_ctx *c, const void *I, hipStream_t st, int dir, int mode, double2 *out) {
+    const void *bop = c->d_bop;
     if (c->fwd_model == UVMEM_FWD_GRIDDED) return launch_grid_forward(c, bop, st);
-    if (c->tr_lg) return launch_tr_forward(c, bop, mode, out, st);
+    if (c->tr_lg) return launch_tr_forward(c, I, mode, out, st);
     // the direction of a region-restricted CG is zero outside the region
     const bool rg = dir && c->has_region;
     const FwdPItem *it = rg ? c->d_fwdp_m : c->d_fwdp;
@@ -1669,8 +1670,8 @@ int adjoint_wgs_per_cu(const uvmem_ctx *c) {
 }
 
 hipError_t launch_adjoint(const uvmem_ctx *c, const double2 *coef, const float *w, hipStream_t st, int grad,
-                          int caller) {
-    if (c->tr_lg) return launch_tr_adjoint(c, coef, w, caller ? c->d_trperm : nullptr, st);
+                          int caller, int step) {
+    if (c->tr_lg) return launch_tr_adjoint(c, coef, w, caller ? c->d_trperm : nullptr, step, st);
     if (c->fwd_model == UVMEM_FWD_GRIDDED && c->grad_model == UVMEM_GRAD_ADJOINT)
         return launch_grid_adjoint(c, coef, w, st);
     // a gradient of a region-restricted problem is needed inside the region only

@@ -30,8 +30,11 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
+#include <type_traits>
+#include <vector>
 
 #include "internal.h"
+#include "reduce.h"
 
 namespace uvm {
 namespace {
@@ -181,6 +184,14 @@ __device__ __forceinline__ int fft_out(int t, int x) {
     return t + (x / R) * ((1 << LG) / 8) + (x % R) * ((1 << LG) / R);
 }
 
+// Whether output register x, or input leg r, can lie in the image at all: the
+// image takes at most a quarter of the positions at either end (L >= 2 N).
+template <int LG>
+__device__ __forceinline__ constexpr bool fft_live(int x) {
+    return fft_last(LG) == 8 ? (x < 2 || x >= 6) : (x % 4 == 0 || x % 4 == 3);
+}
+__device__ __forceinline__ constexpr bool leg_live(int r) { return r < 2 || r >= 6; }
+
 // Image index of transform position p (pixel offset p or p - L), -1 in the
 // zero padding.
 __device__ __forceinline__ int pix_of(int p, int L, int n) {
@@ -188,33 +199,84 @@ __device__ __forceinline__ int pix_of(int p, int L, int n) {
     return p < half ? p + half : p >= L - half ? p - (L - half) : -1;
 }
 
-// Sequences per workgroup: at least a wave of threads, at most 512 threads
-// and 74 KiB of LDS.
-constexpr int row_seqs(int lg) { return lg <= 8 ? 4 : lg <= 11 ? 2 : 1; }
-constexpr int col_seqs(int lg) { return lg <= 7 ? 4 : lg <= 8 ? 2 : 1; }
+// Sequences per workgroup.
+constexpr int row_seqs(int lg) { return tr_row_seqs(lg); }
+constexpr int col_seqs(int lg) { return lg <= 6 ? 8 : lg <= 7 ? 4 : lg <= 8 ? 2 : 1; }
 
-// Rows: two image rows (i, i + 1) form one complex sequence; their spectra
-// are separated by symmetry and stored as X[q + H][i], i contiguous, for the
-// columns q = -H .. L/2 + H.
-template <int LG, typename R>
+// DIR: the image is a CG direction, and the row pass also sums the entropy
+// parts of phi', phi'' at alpha_max (partials [0], [1]; zero without a finite
+// alpha_max).  Done by the first channel of each image; one record per
+// workgroup, gridDim.x per image.
+template <typename R> struct RowArgs {
+    const R *img;               // the image, or the direction
+    const R *I;                 // DIR: the current point
+    const R *beam;
+    const int *chan_img, *ichan_base;
+    const double *chan;         // DIR: CG bookkeeping
+    double *pp;
+    double M;
+};
+
+// Rows: two rows (i, i + 1) of B = A o img form one complex sequence; their
+// spectra are separated by symmetry and stored as X[q + H][i], i contiguous,
+// for the columns q = -H .. L/2 + H.
+template <int LG, typename R, bool DIR>
 __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_fwd(
-    const R *__restrict__ bop, double2 *__restrict__ X, const double2 *__restrict__ tw,
-    const double *__restrict__ dec, int n, int np, int H) {
+    const RowArgs<R> ra, double2 *__restrict__ X, const double2 *__restrict__ tw, const double *__restrict__ dec,
+    int n, int H) {
     constexpr int L = 1 << LG, T = fft_threads(LG), NF = row_seqs(LG);
     __shared__ double2 s[NF][fpad(L)];
     const int f = threadIdx.x / T, t = threadIdx.x % T;
     const int c = blockIdx.y, i0 = (blockIdx.x * NF + f) * 2;
     const int Lx = L / 2 + 2 * H + 1;
+    const int im = ra.chan_img[c];
     double2 v[8];
     const bool live = i0 < n;   // n is even
-    const R *r0 = bop + ((size_t)c * np + (live ? i0 : 0)) * np;
+    const size_t r0 = (size_t)(live ? i0 : 0) * n, npix = (size_t)n * n;
+    const R *x0 = ra.img + im * npix + r0, *A0 = ra.beam + c * npix + r0;
     const double d0 = live ? dec[i0] : 0.0, d1 = live ? dec[i0 + 1] : 0.0;
+    R px[8], py[8];
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
+        v[r] = make_double2(0.0, 0.0);
+        px[r] = py[r] = R(0);
+        if (!leg_live(r)) continue;
         const int j = pix_of(t + r * T, L, n);
         const int jc = j < 0 ? 0 : j;
-        const double x = (double)r0[jc], y = (double)r0[np + jc], dj = dec[jc];
-        v[r] = j < 0 ? make_double2(0.0, 0.0) : make_double2(x * (d0 * dj), y * (d1 * dj));
+        px[r] = x0[jc];
+        py[r] = x0[n + jc];
+        const R bx = A0[jc] * px[r], by = A0[n + jc] * py[r];
+        const double dj = dec[jc];
+        v[r] = j < 0 ? make_double2(0.0, 0.0) : make_double2((double)bx * (d0 * dj), (double)by * (d1 * dj));
+    }
+    if constexpr (DIR) {
+        if (ra.ichan_base[im] == c) {   // uniform over the workgroup
+            double acc[2] = {0.0, 0.0};
+            const double *ch = ra.chan + (size_t)im * CH_N;
+            const double am = ch[CH_AMAX];
+            if (isfinite(am) && ch[CH_STOP] == 0.0) {
+                const R *I0 = ra.I + im * npix + r0;
+#pragma unroll
+                for (int r = 0; r < 8; ++r) {
+                    const int j = leg_live(r) ? pix_of(t + r * T, L, n) : -1;
+                    if (!live || j < 0) continue;
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        const double d = (double)(u ? py[r] : px[r]);
+                        if (d == 0.0) continue;
+                        const double x = (double)I0[u * n + j] + am * d;
+                        acc[0] += d * (log(x / ra.M) + 1.0);
+                        acc[1] += d * d / x;
+                    }
+                }
+            }
+            block_sum<2, NF * T>(acc);
+            if (threadIdx.x == 0) {
+                double *rec = ra.pp + ((size_t)im * gridDim.x + blockIdx.x) * NPART;
+                rec[0] = acc[0];
+                rec[1] = acc[1];
+            }
+        }
     }
     fft_passes<LG, 0, 1, false>(v, t, s[f], tw);
     __syncthreads();
@@ -247,6 +309,8 @@ __global__ __launch_bounds__(col_seqs(LG) * fft_threads(LG)) void k_tr_cols_fwd(
     double2 v[8];
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
+        v[r] = make_double2(0.0, 0.0);
+        if (!leg_live(r)) continue;
         const int i = pix_of(t + r * T, L, n);
         const double2 y = x[i < 0 ? 0 : i];
         v[r] = i < 0 ? make_double2(0.0, 0.0) : y;
@@ -341,6 +405,18 @@ __device__ __forceinline__ double swap_add(double x, double y) {
 // (each workgroup's partials in record blockIdx.x of `part`).
 enum { TV_OUT, TV_RES, TV_DIR };
 
+// TV_DIR: the last workgroup of an image starts its line search from the
+// totals of a and b, the row pass's entropy parts and the direction pass's.
+struct DirTail {
+    const int *chan_img, *gbase;
+    unsigned *ctr;
+    const double *pp;
+    int n_rec;
+    const double *chan;
+    double *ls;
+    double lam;
+};
+
 // Gather: a workgroup's four waves take one span of consecutive items each
 // (spans are cut to equal cost at finalize); an item's grid tile is held in
 // registers.  The visibilities of a span are consecutive, so the next batch's
@@ -350,7 +426,7 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_interp(
     const int2 *__restrict__ spans, const TrItem *__restrict__ items, const double *__restrict__ a,
     const double *__restrict__ b, const double2 *__restrict__ G, const double *__restrict__ poly, int L, int Lg,
     long long ztot, double *__restrict__ out, const double *__restrict__ ref, const float *__restrict__ w,
-    const unsigned *__restrict__ perm, double *__restrict__ part) {
+    const unsigned *__restrict__ perm, double *__restrict__ part, const DirTail dt) {
     constexpr int H = (W - 1) / 2, TB = Win<W>::TB, TS = Win<W>::TS, NT = TS / 16, NS = TS / 4;
     __shared__ __attribute__((aligned(16))) double s[TR_WAVES][2][32][TS + 2];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -457,9 +533,24 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_interp(
             red[1][wave] = acc1;
         }
         __syncthreads();
-        if (threadIdx.x < 2)
-            part[(size_t)blockIdx.x * NPART + threadIdx.x] = (red[threadIdx.x][0] + red[threadIdx.x][1]) +
-                                                             (red[threadIdx.x][2] + red[threadIdx.x][3]);
+        if (threadIdx.x == 0) {
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+                coh_store(part + (size_t)blockIdx.x * NPART + x, (red[x][0] + red[x][1]) + (red[x][2] + red[x][3]));
+        }
+    }
+    if constexpr (MODE == TV_DIR) {
+        const int im = dt.chan_img[items[spans[blockIdx.x * TR_WAVES].x].chan];
+        const int v0 = dt.gbase[im], v1 = dt.gbase[im + 1];
+        if (!arrive_last(dt.ctr + im, (unsigned)(v1 - v0))) return;
+        double ab2[2], fh[2];
+        sum_partials2<2, 2>(part + (size_t)v0 * NPART, v1 - v0, 0, ab2, dt.pp + (size_t)im * dt.n_rec * NPART,
+                            dt.n_rec, 0, fh);
+        if (threadIdx.x == 0) {
+            const double *ch = dt.chan + (size_t)im * CH_N;
+            ls_init(dt.ls + (size_t)im * LSS_N, ab2[0], ab2[1], dt.lam * ch[CH_E1], dt.lam * ch[CH_E2], ch[CH_AMAX],
+                    ch[CH_STOP] != 0.0, true, dt.lam * fh[0], dt.lam * fh[1]);
+        }
     }
 }
 
@@ -469,7 +560,15 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_interp(
 // items has workgroups of its own (waves[].z = live waves > 0), whose waves
 // take an item each and add their sums in LDS in wave order into one tile.
 // perm (may be null): coef is in the caller's order (index << 1 | negated).
-template <int W>
+// STEP (a CG step): the coefficients are R + alpha Vd, which also replace R;
+// the chi^2 partial of the workgroup goes to its record in part.
+struct StepArgs {
+    double2 *R;
+    const double2 *Vd;
+    const double *ls;
+    double *part;
+};
+template <int W, bool STEP>
 __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restrict__ waves,
                                                             const TrItem *__restrict__ items,
                                                             const double *__restrict__ a,
@@ -479,7 +578,7 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
                                                             const unsigned *__restrict__ perm,
                                                             double2 *__restrict__ tiles,
                                                             const double *__restrict__ poly, int L,
-                                                            long long ztot) {
+                                                            long long ztot, const StepArgs sa) {
     constexpr int TB = Win<W>::TB, TS = Win<W>::TS, NT = TS / 16;
     __shared__ __attribute__((aligned(16))) double s[TR_WAVES][2][32][TS + 2];
     __shared__ double2 sc[TR_WAVES][32];
@@ -490,15 +589,22 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
     doublex4 ar[NT][NT], ai[NT][NT];
     // the next batch's data are loaded while the current one computes; the
     // visibilities of a span are consecutive, so that includes the next item's
-    double xn = 0.0;
-    double2 cn = make_double2(0.0, 0.0);
+    double xn = 0.0, chi = 0.0;
+    float wn = 1.f;
+    double2 cn = make_double2(0.0, 0.0), dn = cn;
+    const double al = STEP ? sa.ls[(size_t)span.w * LSS_N + LSS_ALPHA] : 0.0;
     auto fetch = [&](long long k0) {
         const long long k = k0 + (lane & 31), kc = k < ztot ? k : ztot - 1;
         xn = ab[kc];
-        const double wv = w ? (double)w[kc] : 1.0;
-        const unsigned pk = perm ? perm[kc] : 0u;
-        const double2 cv = coef[perm ? (long long)(pk >> 1) : kc];
-        cn = make_double2(cv.x * wv, (pk & 1u ? -cv.y : cv.y) * wv);
+        if (w) wn = w[kc];
+        if constexpr (STEP) {
+            cn = sa.R[kc];
+            dn = sa.Vd[kc];
+        } else {
+            const unsigned pk = perm ? perm[kc] : 0u;
+            cn = coef[perm ? (long long)(pk >> 1) : kc];
+            if (pk & 1u) cn.y = -cn.y;
+        }
     };
     auto at = [&](int x, int y, int r) { return (16 * x + 4 * r + g) * TS + 16 * y + q; };
     if (span.x < span.y) fetch(items[span.x].kbeg);
@@ -511,7 +617,18 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
             for (int y = 0; y < NT; ++y) ar[x][y] = ai[x][y] = doublex4{0.0, 0.0, 0.0, 0.0};
         for (long long k0 = it.kbeg; k0 < it.kend; k0 += 32) {
             const bool ok = k0 + (lane & 31) < it.kend;
-            if (lane < 32) sc[wave][lane] = ok ? cn : make_double2(0.0, 0.0);
+            if (lane < 32) {
+                double2 cv = cn;
+                if constexpr (STEP) {
+                    cv.x += al * dn.x;
+                    cv.y += al * dn.y;
+                    if (ok) {
+                        sa.R[k0 + lane] = cv;
+                        chi += (double)wn * (cv.x * cv.x + cv.y * cv.y);
+                    }
+                }
+                sc[wave][lane] = ok ? make_double2(cv.x * (double)wn, cv.y * (double)wn) : make_double2(0.0, 0.0);
+            }
             windows32<W>(s[wave], xn * (double)L, ok, L, n0, poly);
             fetch(k0 + 32 < it.kend ? k0 + 32 : it.kend);
             wave_sync();
@@ -555,6 +672,14 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
 #pragma unroll
                     for (int r = 0; r < 4; ++r) o[at(x, y, r)] = make_double2(ar[x][y][r], ai[x][y][r]);
         }
+    }
+    if constexpr (STEP) {
+        __shared__ double red[TR_WAVES];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) chi += __shfl_xor(chi, o, 64);
+        if (lane == 0) red[wave] = chi;
+        __syncthreads();
+        if (threadIdx.x == 0) sa.part[(size_t)blockIdx.x * NPART] = (red[0] + red[1]) + (red[2] + red[3]);
     }
     if (span.z == 0) return;   // uniform over the workgroup
     // waves 1.. leave their sums in LDS, wave 0 adds them in order
@@ -619,22 +744,42 @@ __global__ __launch_bounds__(col_seqs(LG) * fft_threads(LG)) void k_tr_cols_inv(
                 s0[r][1] = bins[bx * NBY + bh];
                 s1[r][1] = bins[bx * NBY + bh + 1];
             }
+            // the first tile of every covering bin in one round of loads
+            // (slot 0 stands in for an empty bin), further ones after them
+            double2 y[8][2];
 #pragma unroll
-            for (int r = 0; r < 8; ++r) {
-                const int pr = (t + r * T + H) & (TB - 1);
+            for (int r = 0; r < 8; ++r)
 #pragma unroll
                 for (int d = 0; d < 2; ++d) {
-                    const double2 *p = tiles + co + pr + (d == 0 ? TB : 0);
-                    int x = s0[r][d];
-                    for (; x + 4 <= s1[r][d]; x += 4) {
-                        double2 y[4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) y[u] = p[(size_t)(x + u) * (TS * TS)];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) v[r] = cadd(v[r], y[u]);
-                    }
-                    for (; x < s1[r][d]; ++x) v[r] = cadd(v[r], p[(size_t)x * (TS * TS)]);
+                    const int off = co + ((t + r * T + H) & (TB - 1)) + (d == 0 ? TB : 0);
+                    const int x = s0[r][d] < s1[r][d] ? s0[r][d] : 0;
+                    y[r][d] = tiles[(size_t)x * (TS * TS) + off];
                 }
+#pragma unroll
+            for (int r = 0; r < 8; ++r)
+#pragma unroll
+                for (int d = 0; d < 2; ++d)
+                    if (s0[r][d] < s1[r][d]) v[r] = cadd(v[r], y[r][d]);
+            int most = 0;
+#pragma unroll
+            for (int r = 0; r < 8; ++r)
+#pragma unroll
+                for (int d = 0; d < 2; ++d) most = max(most, s1[r][d] - s0[r][d]);
+            // (a round of all sixteen at a time: one load latency a round)
+            for (int k = 1; k < most; ++k) {
+#pragma unroll
+                for (int r = 0; r < 8; ++r)
+#pragma unroll
+                    for (int d = 0; d < 2; ++d) {
+                        const int off = co + ((t + r * T + H) & (TB - 1)) + (d == 0 ? TB : 0);
+                        const int x = s0[r][d] + k < s1[r][d] ? s0[r][d] + k : 0;
+                        y[r][d] = tiles[(size_t)x * (TS * TS) + off];
+                    }
+#pragma unroll
+                for (int r = 0; r < 8; ++r)
+#pragma unroll
+                    for (int d = 0; d < 2; ++d)
+                        if (s0[r][d] + k < s1[r][d]) v[r] = cadd(v[r], y[r][d]);
             }
         }
     }
@@ -643,18 +788,35 @@ __global__ __launch_bounds__(col_seqs(LG) * fft_threads(LG)) void k_tr_cols_inv(
     double2 *o = Y + ((size_t)c * Lx + qc) * n;
 #pragma unroll
     for (int x = 0; x < 8; ++x) {
+        if (!fft_live<LG>(x)) continue;
         const int i = pix_of(fft_out<LG>(t, x), L, n);
         if (i >= 0) o[i] = v[x];
     }
 }
 
+// The gradient pass of an image with one channel, pixel by pixel (modes as
+// k_grad with TR): the adjoint, grad Phi with the sum S, the CG's image
+// update, gradient and projected gradient, or the dirty image.
+template <typename R> struct RowGrad {
+    const R *beam, *dir;
+    R *I, *out, *gt;            // I is written by a CG step only
+    int *flag;
+    double *pp;
+    const double *img_scale;
+    const unsigned char *mask;
+    double M, Mb, lam;
+    int mode;
+    GradTail tail;
+};
+
 // Inverse rows: the real part over the half grid of two image rows at once
 // (their Hermitian halves packed as one complex sequence), times the window's
-// inverse transform, into the channel's plane.
-template <int LG>
+// inverse transform: into the channel's plane, or (FUSED) straight through
+// the gradient pass.
+template <int LG, typename R, bool FUSED>
 __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_inv(
-    const double2 *__restrict__ Y, double *__restrict__ plane, const double2 *__restrict__ tw,
-    const double *__restrict__ dec, const int *__restrict__ slot_base, int n, int np, int H) {
+    const double2 *__restrict__ Y, double *__restrict__ plane, const RowGrad<R> rg, const double2 *__restrict__ tw,
+    const double *__restrict__ dec, int n, int np, int H) {
     constexpr int L = 1 << LG, T = fft_threads(LG), NF = row_seqs(LG);
     constexpr int LXM = L / 2 + 2 * TR_HMAX + 1;
     // [NF] half spectra of two rows, then (reused) the transform's exchange
@@ -663,12 +825,47 @@ __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_inv(
     const int f = threadIdx.x / T, t = threadIdx.x % T;
     const int c = blockIdx.y, rows0 = blockIdx.x * NF * 2;
     const int Lx = L / 2 + 2 * H + 1;
-    for (int e = threadIdx.x; e < Lx * NF; e += NF * T) {
-        const int qc = e / NF, g = e % NF;
-        const int i = rows0 + 2 * g;
-        const double2 *y = Y + ((size_t)c * Lx + qc) * n + (i < n ? i : 0);
-        s[g][2 * qc] = y[0];
-        s[g][2 * qc + 1] = y[1];
+    const int i = rows0 + 2 * f;
+    const bool live = i < n;
+    // the half spectra, all loads in flight together (rows past the image:
+    // its first ones, never used)
+    constexpr int NE = (LXM + T - 1) / T;
+    double2 h0[NE], h1[NE];
+#pragma unroll
+    for (int m = 0; m < NE; ++m) {
+        const int e = threadIdx.x + m * NF * T;
+        const int qc = e / NF < Lx ? e / NF : Lx - 1, ir = rows0 + 2 * (e % NF);
+        const double2 *y = Y + ((size_t)c * Lx + qc) * n + (ir < n ? ir : 0);
+        h0[m] = y[0];
+        h1[m] = y[1];
+    }
+    // the pixels' data, loaded ahead of the transform
+    R pI[8][2], pA[8][2], pd[8][2], pg[8][2];
+    double al = 0.0;
+    if constexpr (FUSED) {
+        if (rg.mode == 2) al = rg.tail.ls[(size_t)c * LSS_N + LSS_ALPHA];
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+            if (!fft_live<LG>(x)) continue;
+            const int j = pix_of(fft_out<LG>(t, x), L, n);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const size_t q = live && j >= 0 ? ((size_t)c * n + i + u) * n + j : 0;
+                pA[x][u] = rg.beam[q];
+                if (rg.mode == 1 || rg.mode == 2) pI[x][u] = rg.I[q];
+                if (rg.mode == 2) {
+                    pd[x][u] = rg.dir[q];
+                    pg[x][u] = rg.gt[q];
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < NE; ++m) {
+        const int e = threadIdx.x + m * NF * T;
+        if (e >= Lx * NF) continue;
+        s[e % NF][2 * (e / NF)] = h0[m];
+        s[e % NF][2 * (e / NF) + 1] = h1[m];
     }
     __syncthreads();
     double2 v[8];
@@ -691,17 +888,82 @@ __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_inv(
         v[r] = make_double2(0.5 * z.x, 0.5 * z.y);
     }
     fft_passes<LG, 0, 1, true>(v, t, s[f], tw);
-    const int i = rows0 + 2 * f;
-    if (i >= n) return;
-    double *o = plane + ((size_t)slot_base[c] * np + i) * np;
-    const double d0 = dec[i], d1 = dec[i + 1];
+    const double d0 = live ? dec[i] : 0.0, d1 = live ? dec[i + 1] : 0.0;
+    if constexpr (!FUSED) {
+        if (!live) return;
+        double *o = plane + ((size_t)c * np + i) * np;
 #pragma unroll
-    for (int x = 0; x < 8; ++x) {
-        const int j = pix_of(fft_out<LG>(t, x), L, n);
-        if (j < 0) continue;
-        const double dj = dec[j];
-        o[j] = v[x].x * (d0 * dj);
-        o[np + j] = v[x].y * (d1 * dj);
+        for (int x = 0; x < 8; ++x) {
+            const int j = fft_live<LG>(x) ? pix_of(fft_out<LG>(t, x), L, n) : -1;
+            if (j < 0) continue;
+            const double dj = dec[j];
+            o[j] = v[x].x * (d0 * dj);
+            o[np + j] = v[x].y * (d1 * dj);
+        }
+    } else {
+        const int mode = rg.mode;
+        double acc[3] = {0.0, 0.0, 0.0};
+        int bad = 0;
+        const double scale = mode == 3 ? rg.img_scale[c] : 1.0;
+        // the pixels' logarithms first, without a branch between them: their
+        // long dependent chains then overlap (a pixel off the image: ln 1)
+        double lg[8][2];
+        if (mode == 1 || mode == 2) {
+#pragma unroll
+            for (int x = 0; x < 8; ++x) {
+                if (!fft_live<LG>(x)) continue;
+                const int j = pix_of(fft_out<LG>(t, x), L, n);
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const R x0 = pI[x][u];
+                    if (mode == 2) pI[x][u] = al != 0.0 ? (R)fmax((double)x0 + al * (double)pd[x][u], rg.Mb) : x0;
+                    const double xi = live && j >= 0 ? (double)pI[x][u] : rg.M;
+                    lg[x][u] = log(xi / rg.M);
+                }
+            }
+        }
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+            const int j = fft_live<LG>(x) ? pix_of(fft_out<LG>(t, x), L, n) : -1;
+            if (!live || j < 0) continue;
+            const double dj = dec[j];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const size_t q = ((size_t)c * n + i + u) * n + j;
+                const double G = u ? v[x].y * (d1 * dj) : v[x].x * (d0 * dj);
+                double gv = mode == 3 ? G * scale : (double)pA[x][u] * G;
+                double xi = 0.0;
+                if (mode == 1 || mode == 2) {
+                    xi = (double)pI[x][u];
+                    if (mode == 2 && al != 0.0) rg.I[q] = pI[x][u];
+                    if (!(xi > 0.0)) bad = 1;
+                    else acc[mode == 1 ? 0 : 2] += xi * lg[x][u];
+                    gv += rg.lam * (lg[x][u] + 1.0);
+                    if (rg.mask && !rg.mask[q]) gv = 0.0;
+                }
+                const R gr = (R)gv;
+                rg.out[q] = gr;
+                if (mode == 2) {
+                    const bool act = (xi <= rg.Mb * (1.0 + BOUND_TOL)) && ((double)gr > 0.0);
+                    const double gnew = act ? 0.0 : (double)gr;
+                    const double gold = (double)pg[x][u];
+                    rg.gt[q] = (R)gnew;
+                    acc[0] += gnew * gnew;
+                    acc[1] += gnew * gold;
+                }
+            }
+        }
+        constexpr int NTH = NF * T;
+        const int rows = gridDim.x;
+        if (mode == 1 || mode == 2) {
+            if (bad) atomicOr(rg.flag, 1);
+            block_sum<3, NTH>(acc);
+            if (threadIdx.x == 0) {
+#pragma unroll
+                for (int x = 0; x < 3; ++x) coh_store(rg.pp + ((size_t)c * rows + blockIdx.x) * NPART + x, acc[x]);
+            }
+        }
+        grad_tail<NTH, true>(mode, c, rows, rg.pp, rg.lam, rg.tail);
     }
 }
 
@@ -905,17 +1167,21 @@ __global__ void k_beam(R *__restrict__ beam, int n, double cell, double cx, doub
     }
 }
 
-template <int LG>
-hipError_t fwd_lg(const uvmem_ctx *c, const void *bop, hipStream_t st) {
+inline double *tr_pp(const uvmem_ctx *c, int buf) {
+    return c->d_ppart + (size_t)buf * c->nimg * std::max(c->n_pb, c->n_trrec) * NPART;
+}
+
+template <int LG, typename R>
+hipError_t fwd_lg(const uvmem_ctx *c, const void *I, int what, hipStream_t st) {
     const int H = c->tr_h, L = 1 << LG, Lx = L / 2 + 2 * H + 1;
     constexpr int T = fft_threads(LG), RS = row_seqs(LG), CS = col_seqs(LG);
-    const dim3 gr((c->n / 2 + RS - 1) / RS, c->nchan), gc((Lx + CS - 1) / CS, c->nchan);
-    if (c->prec == UVMEM_FP64)
-        hipLaunchKernelGGL((k_tr_rows_fwd<LG, double>), gr, dim3(RS * T), 0, st, (const double *)bop, c->d_trx,
-                           c->d_trtw, c->d_trdec, c->n, c->np, H);
+    const dim3 gr(c->n_trrec, c->nchan), gc((Lx + CS - 1) / CS, c->nchan), br(RS * T);
+    const RowArgs<R> ra{(const R *)(what == 2 ? c->d_dir : I), (const R *)I, (const R *)c->d_beam, c->d_chan_img,
+                        c->d_ichan_base, c->d_chan, tr_pp(c, 1), c->M};
+    if (what == 2)
+        hipLaunchKernelGGL((k_tr_rows_fwd<LG, R, true>), gr, br, 0, st, ra, c->d_trx, c->d_trtw, c->d_trdec, c->n, H);
     else
-        hipLaunchKernelGGL((k_tr_rows_fwd<LG, float>), gr, dim3(RS * T), 0, st, (const float *)bop, c->d_trx,
-                           c->d_trtw, c->d_trdec, c->n, c->np, H);
+        hipLaunchKernelGGL((k_tr_rows_fwd<LG, R, false>), gr, br, 0, st, ra, c->d_trx, c->d_trtw, c->d_trdec, c->n, H);
     hipLaunchKernelGGL((k_tr_cols_fwd<LG>), gc, dim3(CS * T), 0, st, c->d_trx, c->d_trg, c->d_trtw, c->n, Lx,
                        c->tr_lgc);
     return hipGetLastError();
@@ -924,24 +1190,56 @@ hipError_t fwd_lg(const uvmem_ctx *c, const void *bop, hipStream_t st) {
 template <int LG>
 hipError_t inv_lg(const uvmem_ctx *c, hipStream_t st) {
     const int H = c->tr_h, L = 1 << LG, Lx = L / 2 + 2 * H + 1;
-    constexpr int T = fft_threads(LG), RS = row_seqs(LG), CS = col_seqs(LG);
-    const dim3 gr((c->n / 2 + RS - 1) / RS, c->nchan), gc((Lx + CS - 1) / CS, c->nchan);
+    constexpr int T = fft_threads(LG), CS = col_seqs(LG);
+    const dim3 gc((Lx + CS - 1) / CS, c->nchan);
     if (c->tr_w == 17)
         hipLaunchKernelGGL((k_tr_cols_inv<LG, 17>), gc, dim3(CS * T), 0, st, c->d_trtile, c->d_trbin, c->d_trx,
                            c->d_trtw, c->n, Lx, c->tr_nbx);
     else
         hipLaunchKernelGGL((k_tr_cols_inv<LG, 9>), gc, dim3(CS * T), 0, st, c->d_trtile, c->d_trbin, c->d_trx,
                            c->d_trtw, c->n, Lx, c->tr_nbx);
-    hipLaunchKernelGGL((k_tr_rows_inv<LG>), gr, dim3(RS * T), 0, st, c->d_trx, (double *)c->d_gpart, c->d_trtw,
-                       c->d_trdec, c->d_slot_base, c->n, c->np, H);
     return hipGetLastError();
+}
+
+template <int LG, typename R>
+hipError_t rows_inv_lg(const uvmem_ctx *c, const void *I, void *out, int mode, double *user, hipStream_t st) {
+    constexpr int T = fft_threads(LG), RS = row_seqs(LG);
+    const dim3 gr(c->n_trrec, c->nchan), br(RS * T);
+    if (c->nimg == c->nchan) {
+        const RowGrad<R> rg{(const R *)c->d_beam, (const R *)c->d_dir, (R *)const_cast<void *>(I), (R *)out,
+                            (R *)c->d_gt, c->d_flag, tr_pp(c, 1), c->d_wscale, c->d_mask, c->M, c->Mb, c->lam, mode,
+                            make_grad_tail(c, mode, user)};
+        hipLaunchKernelGGL((k_tr_rows_inv<LG, R, true>), gr, br, 0, st, c->d_trx, (double *)nullptr, rg, c->d_trtw,
+                           c->d_trdec, c->n, c->np, c->tr_h);
+    } else {
+        hipLaunchKernelGGL((k_tr_rows_inv<LG, R, false>), gr, br, 0, st, c->d_trx, (double *)c->d_gpart,
+                           RowGrad<R>{}, c->d_trtw, c->d_trdec, c->n, c->np, c->tr_h);
+    }
+    return hipGetLastError();
+}
+
+// f(std::integral_constant<int, lg>()) for the context's transform length.
+template <typename F>
+hipError_t with_lg(const uvmem_ctx *c, F f) {
+    switch (c->tr_lg) {
+    case 6: return f(std::integral_constant<int, 6>());
+    case 7: return f(std::integral_constant<int, 7>());
+    case 8: return f(std::integral_constant<int, 8>());
+    case 9: return f(std::integral_constant<int, 9>());
+    case 10: return f(std::integral_constant<int, 10>());
+    case 11: return f(std::integral_constant<int, 11>());
+    case 12: return f(std::integral_constant<int, 12>());
+    }
+    return hipErrorInvalidValue;
 }
 
 template <int W, int MODE>
 void interp_mode(const uvmem_ctx *c, double2 *out, const double2 *ref, hipStream_t st) {
     hipLaunchKernelGGL((k_tr_interp<W, MODE>), dim3(c->n_trgroup), dim3(64 * TR_WAVES), 0, st, c->d_trspan,
                        c->d_tritem, c->d_a, c->d_b, c->d_trg, c->d_trpoly, 1 << c->tr_lg, c->tr_lgc,
-                       (long long)c->ztot, (double *)out, (const double *)ref, c->d_w, c->d_trperm, c->d_trpart);
+                       (long long)c->ztot, (double *)out, (const double *)ref, c->d_w, c->d_trperm, c->d_trpart,
+                       DirTail{c->d_chan_img, c->d_trgbase, c->d_ctr + (size_t)CTR_VIS * c->nimg, tr_pp(c, 1),
+                               c->n_trrec, c->d_chan, c->d_ls, c->lam});
 }
 template <int W>
 hipError_t interp_w(const uvmem_ctx *c, int what, double2 *out, hipStream_t st) {
@@ -951,42 +1249,40 @@ hipError_t interp_w(const uvmem_ctx *c, int what, double2 *out, hipStream_t st) 
     return hipGetLastError();
 }
 
+template <int W, bool STEP>
+void spread_w(const uvmem_ctx *c, const double2 *coef, const float *w, const unsigned *perm, hipStream_t st) {
+    hipLaunchKernelGGL((k_tr_spread<W, STEP>), dim3(c->n_trspread), dim3(64 * TR_WAVES), 0, st, c->d_trspread,
+                       c->d_tritem, c->d_a, c->d_b, coef, w, perm, c->d_trtile, c->d_trpoly, 1 << c->tr_lg,
+                       (long long)c->ztot, StepArgs{c->d_R, c->d_Vd, c->d_ls, c->d_trpart});
+}
+
 }  // namespace
 
-hipError_t launch_tr_forward(const uvmem_ctx *c, const void *bop, int what, double2 *out, hipStream_t st) {
-    hipError_t e = hipErrorInvalidValue;
-    switch (c->tr_lg) {
-    case 6: e = fwd_lg<6>(c, bop, st); break;
-    case 7: e = fwd_lg<7>(c, bop, st); break;
-    case 8: e = fwd_lg<8>(c, bop, st); break;
-    case 9: e = fwd_lg<9>(c, bop, st); break;
-    case 10: e = fwd_lg<10>(c, bop, st); break;
-    case 11: e = fwd_lg<11>(c, bop, st); break;
-    case 12: e = fwd_lg<12>(c, bop, st); break;
-    }
+hipError_t launch_tr_forward(const uvmem_ctx *c, const void *I, int what, double2 *out, hipStream_t st) {
+    const hipError_t e = with_lg(c, [&](auto lg) {
+        constexpr int LG = decltype(lg)::value;
+        return c->prec == UVMEM_FP64 ? fwd_lg<LG, double>(c, I, what, st) : fwd_lg<LG, float>(c, I, what, st);
+    });
     if (e != hipSuccess) return e;
     return c->tr_w == 17 ? interp_w<17>(c, what, out, st) : interp_w<9>(c, what, out, st);
 }
 
 hipError_t launch_tr_adjoint(const uvmem_ctx *c, const double2 *coef, const float *w, const unsigned *perm,
-                             hipStream_t st) {
-    const dim3 grid(c->n_trspread), blk(64 * TR_WAVES);
-    if (c->tr_w == 17)
-        hipLaunchKernelGGL(k_tr_spread<17>, grid, blk, 0, st, c->d_trspread, c->d_tritem, c->d_a, c->d_b, coef, w,
-                           perm, c->d_trtile, c->d_trpoly, 1 << c->tr_lg, (long long)c->ztot);
+                             int step, hipStream_t st) {
+    if (step)
+        c->tr_w == 17 ? spread_w<17, true>(c, coef, w, perm, st) : spread_w<9, true>(c, coef, w, perm, st);
     else
-        hipLaunchKernelGGL(k_tr_spread<9>, grid, blk, 0, st, c->d_trspread, c->d_tritem, c->d_a, c->d_b, coef, w,
-                           perm, c->d_trtile, c->d_trpoly, 1 << c->tr_lg, (long long)c->ztot);
-    switch (c->tr_lg) {
-    case 6: return inv_lg<6>(c, st);
-    case 7: return inv_lg<7>(c, st);
-    case 8: return inv_lg<8>(c, st);
-    case 9: return inv_lg<9>(c, st);
-    case 10: return inv_lg<10>(c, st);
-    case 11: return inv_lg<11>(c, st);
-    case 12: return inv_lg<12>(c, st);
-    }
-    return hipErrorInvalidValue;
+        c->tr_w == 17 ? spread_w<17, false>(c, coef, w, perm, st) : spread_w<9, false>(c, coef, w, perm, st);
+    return with_lg(c, [&](auto lg) { return inv_lg<decltype(lg)::value>(c, st); });
+}
+
+hipError_t launch_tr_rows_inv(const uvmem_ctx *c, const void *I, void *out, int mode, double *user_scal,
+                              hipStream_t st) {
+    return with_lg(c, [&](auto lg) {
+        constexpr int LG = decltype(lg)::value;
+        return c->prec == UVMEM_FP64 ? rows_inv_lg<LG, double>(c, I, out, mode, user_scal, st)
+                                     : rows_inv_lg<LG, float>(c, I, out, mode, user_scal, st);
+    });
 }
 
 hipError_t launch_beam(const uvmem_ctx *c, int chan) {
@@ -1001,18 +1297,23 @@ hipError_t launch_beam(const uvmem_ctx *c, int chan) {
     return hipGetLastError();
 }
 
-hipError_t launch_tr_sort(const uvmem_ctx *c, const double *u, const double *v, const float *vis, const float *w) {
+hipError_t launch_tr_sort(const uvmem_ctx *c, const double *u, const double *v, const float *vis, const float *w,
+                          std::vector<int> &start) {
     const long long count = c->ztot;
     const int L = 1 << c->tr_lg, nblk = (int)((count + SORT_BLK - 1) / SORT_BLK);
     const unsigned nkeys = (unsigned)c->nchan * c->tr_nbx * c->tr_nby;
     unsigned *key = (unsigned *)c->d_Vd, *val = key + count, *key2 = val + count, *val2 = key2 + count;
-    unsigned *hist = nullptr;
-    double2 *centre = nullptr;
+    // one scratch allocation: pointing centres, digit counts, bin starts
+    char *scratch = nullptr;
     std::vector<double2> hc(c->nchan);
     for (int ch = 0; ch < c->nchan; ++ch) hc[ch] = make_double2(c->cx[ch], c->cy[ch]);
-    hipError_t e = hipMalloc((void **)&hist, ((size_t)nblk + 1) * 256 * sizeof(unsigned));
-    if (e == hipSuccess) e = hipMalloc((void **)&centre, hc.size() * sizeof(double2));
-    if (e == hipSuccess) e = hipMemcpy(centre, hc.data(), hc.size() * sizeof(double2), hipMemcpyHostToDevice);
+    const size_t cbytes = hc.size() * sizeof(double2), hcount = ((size_t)nblk + 1) * 256;
+    start.resize((size_t)nkeys + 1);
+    hipError_t e = hipMalloc((void **)&scratch, cbytes + (hcount + start.size()) * sizeof(int));
+    double2 *centre = (double2 *)scratch;
+    unsigned *hist = (unsigned *)(scratch + cbytes);
+    int *dstart = (int *)(hist + hcount);
+    if (e == hipSuccess) e = hipMemcpy(centre, hc.data(), cbytes, hipMemcpyHostToDevice);
     if (e == hipSuccess) {
         unsigned *tot = hist + (size_t)nblk * 256;
         hipLaunchKernelGGL(k_tr_keys, dim3(c->n_visit), dim3(NTHR), 0, nullptr, c->d_vis, u, v, c->cell, key, val, L,
@@ -1026,16 +1327,16 @@ hipError_t launch_tr_sort(const uvmem_ctx *c, const double *u, const double *v, 
             std::swap(val, val2);
         }
         hipLaunchKernelGGL(k_tr_bounds, dim3((unsigned)(count / NTHR + 1)), dim3(NTHR), 0, nullptr, key, count,
-                           c->d_trbin, nkeys);
+                           dstart, nkeys);
         hipLaunchKernelGGL(k_tr_gather, dim3(c->n_visit), dim3(NTHR), 0, nullptr, c->d_vis, u, v,
                            (const float2 *)vis, w, val, c->cell, centre, c->d_a, c->d_b, c->d_vo, c->d_w,
                            c->d_trperm);
         e = hipGetLastError();
-        const hipError_t e2 = hipDeviceSynchronize();
+        // (waits for the kernels)
+        const hipError_t e2 = hipMemcpy(start.data(), dstart, start.size() * sizeof(int), hipMemcpyDeviceToHost);
         if (e == hipSuccess) e = e2;
     }
-    if (hist) (void)hipFree(hist);
-    if (centre) (void)hipFree(centre);
+    if (scratch) (void)hipFree(scratch);
     return e;
 }
 
