@@ -261,8 +261,10 @@ struct uvmem_ctx {
     int *d_trgbase = nullptr, *d_trsbase = nullptr;
     double *d_trpart = nullptr;
     unsigned *d_trperm = nullptr;
-    double *d_trdec = nullptr, *d_trpoly = nullptr;
-    double2 *d_trtw = nullptr, *d_trx = nullptr, *d_trg = nullptr, *d_trtile = nullptr;
+    bool tr_f32 = false;               // grids, windows and tiles in FP32 (split precisions), else FP64
+    double *d_trdec = nullptr;
+    double2 *d_trtw = nullptr;
+    void *d_trpoly = nullptr, *d_trx = nullptr, *d_trg = nullptr, *d_trtile = nullptr;
     size_t bytes_device = 0;
 
     // CG

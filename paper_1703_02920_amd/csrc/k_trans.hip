@@ -40,11 +40,36 @@ namespace uvm {
 namespace {
 
 typedef double doublex4 __attribute__((ext_vector_type(4)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ doublex4 mma(double a, double b, doublex4 c) {
-    // lane l: A[l%16][l/16], B[l/16][l%16]; D[4 r + l/16][l%16] in register r
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-}
+// Type S of the stored grids and tiles, of the windows and of the tile
+// products (the transforms compute in FP64 whatever it is): double, or float
+// for the split-precision contexts, whose contraction accumulates in FP32.
+// Matrix instructions 16 x 16 x 4: lane l supplies A[l%16][l/16] and
+// B[l/16][l%16] and holds D[drow(l/16, r)][l%16] in register r.
+template <typename S> struct Tile;
+template <> struct Tile<double> {
+    typedef doublex4 acc;
+    typedef double2 c2;
+    static __device__ __forceinline__ acc mma(double a, double b, acc c) {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ int drow(int g, int r) { return 4 * r + g; }
+    static constexpr int PAD = 2;   // row padding of the LDS windows: 16 bytes
+};
+template <> struct Tile<float> {
+    typedef floatx4 acc;
+    typedef float2 c2;
+    static __device__ __forceinline__ acc mma(float a, float b, acc c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ int drow(int g, int r) { return 4 * g + r; }
+    static constexpr int PAD = 4;
+};
+template <typename S> using C2 = typename Tile<S>::c2;
+__device__ __forceinline__ double2 wide(double2 a) { return a; }
+__device__ __forceinline__ double2 wide(float2 a) { return make_double2((double)a.x, (double)a.y); }
+template <typename S> __device__ __forceinline__ C2<S> narrow(double x, double y) { return C2<S>{(S)x, (S)y}; }
 
 __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
     return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
@@ -220,9 +245,9 @@ template <typename R> struct RowArgs {
 // Rows: two rows (i, i + 1) of B = A o img form one complex sequence; their
 // spectra are separated by symmetry and stored as X[q + H][i], i contiguous,
 // for the columns q = -H .. L/2 + H.
-template <int LG, typename R, bool DIR>
+template <int LG, typename R, typename S, bool DIR>
 __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_fwd(
-    const RowArgs<R> ra, double2 *__restrict__ X, const double2 *__restrict__ tw, const double *__restrict__ dec,
+    const RowArgs<R> ra, C2<S> *__restrict__ X, const double2 *__restrict__ tw, const double *__restrict__ dec,
     int n, int H) {
     constexpr int L = 1 << LG, T = fft_threads(LG), NF = row_seqs(LG);
     __shared__ double2 s[NF][fpad(L)];
@@ -290,36 +315,36 @@ __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_fwd(
         if (i >= n) continue;
         const int q = (qc - H) & (L - 1), qm = (H - qc) & (L - 1);
         const double2 z = s[g][fpad(q)], zm = s[g][fpad(qm)];
-        double2 *o = X + ((size_t)c * Lx + qc) * n + i;
-        o[0] = make_double2(0.5 * (z.x + zm.x), 0.5 * (z.y - zm.y));
-        o[1] = make_double2(0.5 * (z.y + zm.y), 0.5 * (zm.x - z.x));
+        C2<S> *o = X + ((size_t)c * Lx + qc) * n + i;
+        o[0] = narrow<S>(0.5 * (z.x + zm.x), 0.5 * (z.y - zm.y));
+        o[1] = narrow<S>(0.5 * (z.y + zm.y), 0.5 * (zm.x - z.x));
     }
 }
 
 // Columns: X[q][i] -> G[q][p], p = 0 .. L - 1 contiguous.
-template <int LG>
+template <int LG, typename S>
 __global__ __launch_bounds__(col_seqs(LG) * fft_threads(LG)) void k_tr_cols_fwd(
-    const double2 *__restrict__ X, double2 *__restrict__ G, const double2 *__restrict__ tw, int n, int Lx, int Lg) {
+    const C2<S> *__restrict__ X, C2<S> *__restrict__ G, const double2 *__restrict__ tw, int n, int Lx, int Lg) {
     constexpr int L = 1 << LG, T = fft_threads(LG), NF = col_seqs(LG);
     __shared__ double2 s[NF][fpad(L)];
     const int f = threadIdx.x / T, t = threadIdx.x % T;
     const int c = blockIdx.y, qc = blockIdx.x * NF + f;
     const bool live = qc < Lx;
-    const double2 *x = X + ((size_t)c * Lx + (live ? qc : 0)) * n;
+    const C2<S> *x = X + ((size_t)c * Lx + (live ? qc : 0)) * n;
     double2 v[8];
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
         v[r] = make_double2(0.0, 0.0);
         if (!leg_live(r)) continue;
         const int i = pix_of(t + r * T, L, n);
-        const double2 y = x[i < 0 ? 0 : i];
+        const double2 y = wide(x[i < 0 ? 0 : i]);
         v[r] = i < 0 ? make_double2(0.0, 0.0) : y;
     }
     fft_passes<LG, 0, 1, false>(v, t, s[f], tw);
     if (!live) return;
-    double2 *o = G + ((size_t)c * Lg + qc) * L;
+    C2<S> *o = G + ((size_t)c * Lg + qc) * L;
 #pragma unroll
-    for (int y = 0; y < 8; ++y) o[fft_out<LG>(t, y)] = v[y];
+    for (int y = 0; y < 8; ++y) o[fft_out<LG>(t, y)] = narrow<S>(v[y].x, v[y].y);
 }
 
 // ---------------------------------------------------------------- windows
@@ -332,46 +357,6 @@ template <> struct Win<17> {
     static constexpr int TB = 16, TS = 32, NE = TR_NE17;
 };
 
-// Window values of 32 visibilities into s[axis][visibility][TS + 2] (zero off
-// the window): lane l takes visibility l % 32 of the batch, axis l / 32 (0:
-// columns, 1: rows), whose grid coordinate is X = a L or b L.  Tap u of a
-// visibility whose nearest node is at tile offset `off` sits at off + u; taps
-// u and W - 1 - u are E +- z O, E and O the even and odd parts in z = 2 (X -
-// nearest node) of the tap's polynomial (coefficients in poly: NE even and NE
-// odd ones per tap pair, uniform over the wave).  A lane past the item's end
-// (ok false) writes some finite window at offset 0; whoever uses it drops the
-// result or multiplies by a zero coefficient.
-template <int W>
-__device__ __forceinline__ void windows32(double (*s)[32][Win<W>::TS + 2], double X, bool ok, int L, int n0,
-                                          const double *__restrict__ poly) {
-    constexpr int H = (W - 1) / 2, TS = Win<W>::TS, NE = Win<W>::NE;
-    const int lane = threadIdx.x & 63, vv = lane & 31, axis = lane >> 5;
-    const double nd = rint(X);
-    const double z = 2.0 * (X - nd), z2 = z * z;
-    const int off = ok ? (((int)nd & (L - 1)) - n0) : 0;
-    double *row = &s[axis][vv][0];
-    double2 *r2 = reinterpret_cast<double2 *>(row);
-#pragma unroll
-    for (int u = 0; u < TS / 2; ++u) r2[u] = make_double2(0.0, 0.0);
-    row += off;
-#pragma unroll
-    for (int u = 0; u <= H; ++u) {
-        const double *pe = poly + u * 2 * NE, *po = pe + NE;
-        double e = pe[NE - 1], o = po[NE - 1];
-#pragma unroll
-        for (int m = NE - 2; m >= 0; --m) {
-            e = fma(e, z2, pe[m]);
-            if (u < H) o = fma(o, z2, po[m]);
-        }
-        if (u < H) {
-            row[u] = fma(z, o, e);
-            row[W - 1 - u] = fma(-z, o, e);
-        } else {
-            row[u] = e;
-        }
-    }
-}
-
 // The per-wave LDS exchange: other lanes' stores are visible after it.
 __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -379,23 +364,85 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Window buffers of one wave, per axis, laid out for the reader: the gather
+// takes four consecutive nodes of a visibility at a time (VIS: rows of
+// visibilities), the spread four consecutive visibilities of a node; rows
+// padded by 16 bytes so that the 16 rows a 128-bit read takes start in
+// different banks.
+template <int W, typename S, bool VIS> struct WinBuf {
+    static constexpr int ROWS = VIS ? 32 : Win<W>::TS, LEN = (VIS ? Win<W>::TS : 32) + Tile<S>::PAD;
+    S v[2][ROWS][LEN];
+    __device__ __forceinline__ S &at(int axis, int vis, int node) {
+        return VIS ? v[axis][vis][node] : v[axis][node][vis];
+    }
+};
+
+// Window values of 32 visibilities into s (zero off the window): lane l takes
+// visibility l % 32 of the batch, axis l / 32 (0: columns, 1: rows), whose
+// grid coordinate is X = a L or b L.  Tap u of a visibility whose nearest node
+// is at tile offset `off` sits at off + u; taps u and W - 1 - u are E +- z O,
+// E and O the even and odd parts in z = 2 (X - nearest node) of the tap's
+// polynomial (coefficients in poly: NE even and NE odd ones per tap pair,
+// uniform over the wave).  A lane past the item's end (ok false) writes some
+// finite window at offset 0; whoever uses it drops the result or multiplies
+// by a zero coefficient.
+template <int W, typename S, bool VIS>
+__device__ __forceinline__ void windows32(WinBuf<W, S, VIS> &s, double X, bool ok, int L, int n0,
+                                          const S *__restrict__ poly) {
+    constexpr int H = (W - 1) / 2, NE = Win<W>::NE;
+    typedef float floatv4 __attribute__((ext_vector_type(4)));
+    const int lane = threadIdx.x & 63, vv = lane & 31, axis = lane >> 5;
+    floatv4 *z4 = reinterpret_cast<floatv4 *>(&s);
+    static_assert(sizeof(s) % (64 * 16) == 0 || sizeof(s) % 16 == 0, "whole 16-byte elements");
+    constexpr int N4 = (int)(sizeof(s) / 16);
+#pragma unroll
+    for (int m = 0; m < (N4 + 63) / 64; ++m)
+        if (N4 % 64 == 0 || lane + 64 * m < N4) z4[lane + 64 * m] = floatv4{0.f, 0.f, 0.f, 0.f};
+    const double nd = rint(X);
+    const S z = (S)(2.0 * (X - nd)), z2 = z * z;
+    const int off = ok ? (((int)nd & (L - 1)) - n0) : 0;
+    wave_sync();
+    S *row = &s.at(axis, vv, off);
+    constexpr int ST = VIS ? 1 : WinBuf<W, S, VIS>::LEN;   // from node to node
+#pragma unroll
+    for (int u = 0; u <= H; ++u) {
+        const S *pe = poly + u * 2 * NE, *po = pe + NE;
+        S e = pe[NE - 1], o = po[NE - 1];
+#pragma unroll
+        for (int m = NE - 2; m >= 0; --m) {
+            e = fma(e, z2, pe[m]);
+            if (u < H) o = fma(o, z2, po[m]);
+        }
+        if (u < H) {
+            row[u * ST] = fma(z, o, e);
+            row[(W - 1 - u) * ST] = fma(-z, o, e);
+        } else {
+            row[u * ST] = e;
+        }
+    }
+}
+
 // x + y after exchanging 16-lane rows (SW16: odd rows of x with even rows of
 // y) or half waves (upper half of x with lower half of y): row or half r of
 // the result holds the sum over a pair of rows (halves) of x (r even / lower)
 // or of y.
+typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+template <bool SW16>
+__device__ __forceinline__ uintx2 swap32(unsigned x, unsigned y) {
+    if constexpr (SW16) return __builtin_amdgcn_permlane16_swap(x, y, false, false);
+    else return __builtin_amdgcn_permlane32_swap(x, y, false, false);
+}
 template <bool SW16>
 __device__ __forceinline__ double swap_add(double x, double y) {
     const long long bx = __double_as_longlong(x), by = __double_as_longlong(y);
-    typedef unsigned u2 __attribute__((ext_vector_type(2)));
-    u2 lo, hi;
-    if constexpr (SW16) {
-        lo = __builtin_amdgcn_permlane16_swap((unsigned)bx, (unsigned)by, false, false);
-        hi = __builtin_amdgcn_permlane16_swap((unsigned)(bx >> 32), (unsigned)(by >> 32), false, false);
-    } else {
-        lo = __builtin_amdgcn_permlane32_swap((unsigned)bx, (unsigned)by, false, false);
-        hi = __builtin_amdgcn_permlane32_swap((unsigned)(bx >> 32), (unsigned)(by >> 32), false, false);
-    }
+    const uintx2 lo = swap32<SW16>((unsigned)bx, (unsigned)by);
+    const uintx2 hi = swap32<SW16>((unsigned)(bx >> 32), (unsigned)(by >> 32));
     return __longlong_as_double(((long long)hi.x << 32) | lo.x) + __longlong_as_double(((long long)hi.y << 32) | lo.y);
+}
+template <bool SW16>
+__device__ __forceinline__ float swap_add(float x, float y) {
+    const uintx2 v = swap32<SW16>(__float_as_uint(x), __float_as_uint(y));
+    return __uint_as_float(v.x) + __uint_as_float(v.y);
 }
 
 // What the gather does with V_k (component by component):
@@ -421,14 +468,19 @@ struct DirTail {
 // (spans are cut to equal cost at finalize); an item's grid tile is held in
 // registers.  The visibilities of a span are consecutive, so the next batch's
 // coordinates are loaded while the current one computes.
-template <int W, int MODE>
+template <int W, typename S, int MODE>
 __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_interp(
     const int2 *__restrict__ spans, const TrItem *__restrict__ items, const double *__restrict__ a,
-    const double *__restrict__ b, const double2 *__restrict__ G, const double *__restrict__ poly, int L, int Lg,
+    const double *__restrict__ b, const C2<S> *__restrict__ G, const S *__restrict__ poly, int L, int Lg,
     long long ztot, double *__restrict__ out, const double *__restrict__ ref, const float *__restrict__ w,
     const unsigned *__restrict__ perm, double *__restrict__ part, const DirTail dt) {
     constexpr int H = (W - 1) / 2, TB = Win<W>::TB, TS = Win<W>::TS, NT = TS / 16, NS = TS / 4;
-    __shared__ __attribute__((aligned(16))) double s[TR_WAVES][2][32][TS + 2];
+    typedef typename Tile<S>::acc acc_t;
+    __shared__ __attribute__((aligned(16))) WinBuf<W, S, true> s[TR_WAVES];
+    // step x of a contraction takes the columns 16 (x / 4) + 4 g + x % 4, and
+    // the tile's rows are permuted so that register r of lane group g holds
+    // row 4 g + r: a lane then reads its windows four at a time
+    auto ccol = [&](int x, int g) { return 16 * (x / 4) + 4 * g + x % 4; };
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int q = lane & 15, g = lane >> 4;
     const int2 span = spans[blockIdx.x * TR_WAVES + wave];
@@ -441,13 +493,14 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_interp(
     }
     for (int item = span.x; item < span.y; ++item) {
         const TrItem it = items[item];
-        double gr[NT][NS], gi[NT][NS];
+        S gr[NT][NS], gi[NT][NS];
+        const int qr = sizeof(S) == 8 ? 4 * (q & 3) + (q >> 2) : q;
 #pragma unroll
         for (int x = 0; x < NS; ++x) {
-            const double2 *col = G + ((size_t)it.chan * Lg + it.bx * TB + 4 * x + g) * L;
+            const C2<S> *col = G + ((size_t)it.chan * Lg + it.bx * TB + ccol(x, g)) * L;
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
-                const double2 v = col[(it.by * TB - H + 16 * t + q) & (L - 1)];
+                const C2<S> v = col[(it.by * TB - H + 16 * t + qr) & (L - 1)];
                 gr[t][x] = v.x;
                 gi[t][x] = v.y;
             }
@@ -473,38 +526,42 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_interp(
                 rv = ref[2 * kc + comp];
                 wv = w[kc];
             }
-            windows32<W>(s[wave], X, k0 + (lane & 31) < it.kend, L, n0, poly);
+            windows32<W, S, true>(s[wave], X, k0 + (lane & 31) < it.kend, L, n0, poly);
             wave_sync();
-            double half[2] = {0.0, 0.0};
+            S half[2] = {S(0), S(0)};
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 if (k0 + 16 * h >= it.kend) break;
-                const double *kx = &s[wave][0][16 * h + q][0], *ky = &s[wave][1][16 * h + q][0];
-                doublex4 ar[NT], ai[NT];
+                typedef S S4 __attribute__((ext_vector_type(4)));
+                const S *kx = &s[wave].v[0][16 * h + q][4 * g], *ky = &s[wave].v[1][16 * h + q][4 * g];
+                acc_t ar[NT], ai[NT];
 #pragma unroll
-                for (int t = 0; t < NT; ++t) ar[t] = ai[t] = doublex4{0.0, 0.0, 0.0, 0.0};
+                for (int t = 0; t < NT; ++t) ar[t] = ai[t] = acc_t{S(0), S(0), S(0), S(0)};
 #pragma unroll
-                for (int x = 0; x < NS; ++x) {
-                    const double wx = kx[4 * x + g];
+                for (int cb = 0; cb < NS / 4; ++cb) {
+                    const S4 wx = *reinterpret_cast<const S4 *>(kx + 16 * cb);
 #pragma unroll
-                    for (int t = 0; t < NT; ++t) {
-                        ar[t] = mma(gr[t][x], wx, ar[t]);
-                        ai[t] = mma(gi[t][x], wx, ai[t]);
-                    }
+                    for (int x = 0; x < 4; ++x)
+#pragma unroll
+                        for (int t = 0; t < NT; ++t) {
+                            ar[t] = Tile<S>::mma(gr[t][4 * cb + x], wx[x], ar[t]);
+                            ai[t] = Tile<S>::mma(gi[t][4 * cb + x], wx[x], ai[t]);
+                        }
                 }
-                double vr = 0.0, vi = 0.0;
+                S vr = S(0), vi = S(0);
 #pragma unroll
-                for (int t = 0; t < NT; ++t)
+                for (int t = 0; t < NT; ++t) {
+                    const S4 wy = *reinterpret_cast<const S4 *>(ky + 16 * t);
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        const double wy = ky[16 * t + 4 * r + g];
-                        vr = fma(wy, ar[t][r], vr);
-                        vi = fma(wy, ai[t][r], vi);
+                        vr = fma(wy[r], ar[t][r], vr);
+                        vi = fma(wy[r], ai[t][r], vi);
                     }
+                }
                 half[h] = swap_add<true>(vr, vi);
             }
             // lane group g now gets component g % 2 of visibility 16 (g / 2) + q
-            const double v = swap_add<false>(half[0], half[1]);
+            const double v = (double)swap_add<false>(half[0], half[1]);
             if (ok) {
                 if constexpr (MODE == TV_OUT) {
                     out[2 * (size_t)(pk >> 1) + comp] = comp && (pk & 1u) ? -v : v;
@@ -568,7 +625,7 @@ struct StepArgs {
     const double *ls;
     double *part;
 };
-template <int W, bool STEP>
+template <int W, typename S, bool STEP>
 __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restrict__ waves,
                                                             const TrItem *__restrict__ items,
                                                             const double *__restrict__ a,
@@ -576,17 +633,18 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
                                                             const double2 *__restrict__ coef,
                                                             const float *__restrict__ w,
                                                             const unsigned *__restrict__ perm,
-                                                            double2 *__restrict__ tiles,
-                                                            const double *__restrict__ poly, int L,
+                                                            C2<S> *__restrict__ tiles,
+                                                            const S *__restrict__ poly, int L,
                                                             long long ztot, const StepArgs sa) {
     constexpr int TB = Win<W>::TB, TS = Win<W>::TS, NT = TS / 16;
-    __shared__ __attribute__((aligned(16))) double s[TR_WAVES][2][32][TS + 2];
-    __shared__ double2 sc[TR_WAVES][32];
+    typedef typename Tile<S>::acc acc_t;
+    __shared__ __attribute__((aligned(16))) WinBuf<W, S, false> s[TR_WAVES];
+    __shared__ __attribute__((aligned(16))) S sc[TR_WAVES][2][32];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int q = lane & 15, g = lane >> 4;
     const int4 span = waves[blockIdx.x * TR_WAVES + wave];   // first item, end, live waves of a shared bin
     const double *ab = lane < 32 ? a : b;
-    doublex4 ar[NT][NT], ai[NT][NT];
+    acc_t ar[NT][NT], ai[NT][NT];
     // the next batch's data are loaded while the current one computes; the
     // visibilities of a span are consecutive, so that includes the next item's
     double xn = 0.0, chi = 0.0;
@@ -606,7 +664,7 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
             if (pk & 1u) cn.y = -cn.y;
         }
     };
-    auto at = [&](int x, int y, int r) { return (16 * x + 4 * r + g) * TS + 16 * y + q; };
+    auto at = [&](int x, int y, int r) { return (16 * x + Tile<S>::drow(g, r)) * TS + 16 * y + q; };
     if (span.x < span.y) fetch(items[span.x].kbeg);
     for (int item = span.x; item < span.y; ++item) {
         const TrItem it = items[item];
@@ -614,7 +672,7 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
 #pragma unroll
         for (int x = 0; x < NT; ++x)
 #pragma unroll
-            for (int y = 0; y < NT; ++y) ar[x][y] = ai[x][y] = doublex4{0.0, 0.0, 0.0, 0.0};
+            for (int y = 0; y < NT; ++y) ar[x][y] = ai[x][y] = acc_t{S(0), S(0), S(0), S(0)};
         for (long long k0 = it.kbeg; k0 < it.kend; k0 += 32) {
             const bool ok = k0 + (lane & 31) < it.kend;
             if (lane < 32) {
@@ -627,50 +685,49 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
                         chi += (double)wn * (cv.x * cv.x + cv.y * cv.y);
                     }
                 }
-                sc[wave][lane] = ok ? make_double2(cv.x * (double)wn, cv.y * (double)wn) : make_double2(0.0, 0.0);
+                sc[wave][0][lane] = ok ? (S)(cv.x * (double)wn) : S(0);
+                sc[wave][1][lane] = ok ? (S)(cv.y * (double)wn) : S(0);
             }
-            windows32<W>(s[wave], xn * (double)L, ok, L, n0, poly);
+            windows32<W, S, false>(s[wave], xn * (double)L, ok, L, n0, poly);
             fetch(k0 + 32 < it.kend ? k0 + 32 : it.kend);
             wave_sync();
-            // halves of 16 visibilities (zero coefficients past the end), all
-            // of a half's operands read ahead of its products
+            // halves of 16 visibilities (zero coefficients past the end), the
+            // contraction's step m of lane group g taking visibility 4 g + m
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 if (k0 + 16 * h >= it.kend) break;
-                double2 cv[4];
-                double kx[4][NT], ky[4][NT];
+                typedef S S4 __attribute__((ext_vector_type(4)));
+                const int v0 = 16 * h + 4 * g;
+                const S4 cr = *reinterpret_cast<const S4 *>(&sc[wave][0][v0]);
+                const S4 ci = *reinterpret_cast<const S4 *>(&sc[wave][1][v0]);
+                S4 kx[NT], ky[NT];
 #pragma unroll
-                for (int m = 0; m < 4; ++m) {
-                    const int v = 16 * h + 4 * m + g;
-                    cv[m] = sc[wave][v];
-#pragma unroll
-                    for (int y = 0; y < NT; ++y) {
-                        kx[m][y] = s[wave][0][v][16 * y + q];
-                        ky[m][y] = s[wave][1][v][16 * y + q];
-                    }
+                for (int y = 0; y < NT; ++y) {
+                    kx[y] = *reinterpret_cast<const S4 *>(&s[wave].v[0][16 * y + q][v0]);
+                    ky[y] = *reinterpret_cast<const S4 *>(&s[wave].v[1][16 * y + q][v0]);
                 }
 #pragma unroll
                 for (int m = 0; m < 4; ++m)
 #pragma unroll
                     for (int x = 0; x < NT; ++x) {
-                        const double cr = kx[m][x] * cv[m].x, ci = kx[m][x] * cv[m].y;
+                        const S pr = kx[x][m] * cr[m], pi = kx[x][m] * ci[m];
 #pragma unroll
                         for (int y = 0; y < NT; ++y) {
-                            ar[x][y] = mma(cr, ky[m][y], ar[x][y]);
-                            ai[x][y] = mma(ci, ky[m][y], ai[x][y]);
+                            ar[x][y] = Tile<S>::mma(pr, ky[y][m], ar[x][y]);
+                            ai[x][y] = Tile<S>::mma(pi, ky[y][m], ai[x][y]);
                         }
                     }
             }
             wave_sync();
         }
         if (span.z == 0) {
-            double2 *o = tiles + (size_t)it.slot * (TS * TS);
+            C2<S> *o = tiles + (size_t)it.slot * (TS * TS);
 #pragma unroll
             for (int x = 0; x < NT; ++x)
 #pragma unroll
                 for (int y = 0; y < NT; ++y)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) o[at(x, y, r)] = make_double2(ar[x][y][r], ai[x][y][r]);
+                    for (int r = 0; r < 4; ++r) o[at(x, y, r)] = C2<S>{ar[x][y][r], ai[x][y][r]};
         }
     }
     if constexpr (STEP) {
@@ -683,8 +740,8 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
     }
     if (span.z == 0) return;   // uniform over the workgroup
     // waves 1.. leave their sums in LDS, wave 0 adds them in order
-    double2 *buf = reinterpret_cast<double2 *>(&s[0][0][0][0]);
-    static_assert((TR_WAVES - 1) * TS * TS * 16 <= (int)sizeof(s), "wave sums fit the window buffers");
+    C2<S> *buf = reinterpret_cast<C2<S> *>(&s[0]);
+    static_assert((TR_WAVES - 1) * TS * TS * sizeof(C2<S>) <= sizeof(s), "wave sums fit the window buffers");
     __syncthreads();
     if (wave > 0 && wave < span.z) {
 #pragma unroll
@@ -693,19 +750,23 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
             for (int y = 0; y < NT; ++y)
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    buf[(wave - 1) * TS * TS + at(x, y, r)] = make_double2(ar[x][y][r], ai[x][y][r]);
+                    buf[(wave - 1) * TS * TS + at(x, y, r)] = C2<S>{ar[x][y][r], ai[x][y][r]};
     }
     __syncthreads();
     if (wave > 0) return;
-    double2 *o = tiles + (size_t)items[span.x].slot * (TS * TS);
+    C2<S> *o = tiles + (size_t)items[span.x].slot * (TS * TS);
 #pragma unroll
     for (int x = 0; x < NT; ++x)
 #pragma unroll
         for (int y = 0; y < NT; ++y)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                double2 t = make_double2(ar[x][y][r], ai[x][y][r]);
-                for (int v = 1; v < span.z; ++v) t = cadd(t, buf[(v - 1) * TS * TS + at(x, y, r)]);
+                C2<S> t{ar[x][y][r], ai[x][y][r]};
+                for (int v = 1; v < span.z; ++v) {
+                    const C2<S> w = buf[(v - 1) * TS * TS + at(x, y, r)];
+                    t.x += w.x;
+                    t.y += w.y;
+                }
                 o[at(x, y, r)] = t;
             }
 }
@@ -713,9 +774,9 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
 // Inverse columns: node (q, p) sums the tiles that cover it (at most two bin
 // columns by two bin rows, each bin's slots in order), then the transform
 // over p; the image rows are kept: Y[q][i].
-template <int LG, int W>
+template <int LG, int W, typename S>
 __global__ __launch_bounds__(col_seqs(LG) * fft_threads(LG)) void k_tr_cols_inv(
-    const double2 *__restrict__ tiles, const int *__restrict__ bin_slot, double2 *__restrict__ Y,
+    const C2<S> *__restrict__ tiles, const int *__restrict__ bin_slot, C2<S> *__restrict__ Y,
     const double2 *__restrict__ tw, int n, int Lx, int nbx) {
     constexpr int L = 1 << LG, T = fft_threads(LG), NF = col_seqs(LG);
     constexpr int H = (W - 1) / 2, TB = Win<W>::TB, TS = Win<W>::TS, NBY = L / TB;
@@ -746,7 +807,7 @@ __global__ __launch_bounds__(col_seqs(LG) * fft_threads(LG)) void k_tr_cols_inv(
             }
             // the first tile of every covering bin in one round of loads
             // (slot 0 stands in for an empty bin), further ones after them
-            double2 y[8][2];
+            C2<S> y[8][2];
 #pragma unroll
             for (int r = 0; r < 8; ++r)
 #pragma unroll
@@ -759,7 +820,7 @@ __global__ __launch_bounds__(col_seqs(LG) * fft_threads(LG)) void k_tr_cols_inv(
             for (int r = 0; r < 8; ++r)
 #pragma unroll
                 for (int d = 0; d < 2; ++d)
-                    if (s0[r][d] < s1[r][d]) v[r] = cadd(v[r], y[r][d]);
+                    if (s0[r][d] < s1[r][d]) v[r] = cadd(v[r], wide(y[r][d]));
             int most = 0;
 #pragma unroll
             for (int r = 0; r < 8; ++r)
@@ -779,18 +840,18 @@ __global__ __launch_bounds__(col_seqs(LG) * fft_threads(LG)) void k_tr_cols_inv(
                 for (int r = 0; r < 8; ++r)
 #pragma unroll
                     for (int d = 0; d < 2; ++d)
-                        if (s0[r][d] + k < s1[r][d]) v[r] = cadd(v[r], y[r][d]);
+                        if (s0[r][d] + k < s1[r][d]) v[r] = cadd(v[r], wide(y[r][d]));
             }
         }
     }
     fft_passes<LG, 0, 1, true>(v, t, s[f], tw);
     if (!live) return;
-    double2 *o = Y + ((size_t)c * Lx + qc) * n;
+    C2<S> *o = Y + ((size_t)c * Lx + qc) * n;
 #pragma unroll
     for (int x = 0; x < 8; ++x) {
         if (!fft_live<LG>(x)) continue;
         const int i = pix_of(fft_out<LG>(t, x), L, n);
-        if (i >= 0) o[i] = v[x];
+        if (i >= 0) o[i] = narrow<S>(v[x].x, v[x].y);
     }
 }
 
@@ -813,9 +874,9 @@ template <typename R> struct RowGrad {
 // (their Hermitian halves packed as one complex sequence), times the window's
 // inverse transform: into the channel's plane, or (FUSED) straight through
 // the gradient pass.
-template <int LG, typename R, bool FUSED>
+template <int LG, typename R, typename S, bool FUSED>
 __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_inv(
-    const double2 *__restrict__ Y, double *__restrict__ plane, const RowGrad<R> rg, const double2 *__restrict__ tw,
+    const C2<S> *__restrict__ Y, double *__restrict__ plane, const RowGrad<R> rg, const double2 *__restrict__ tw,
     const double *__restrict__ dec, int n, int np, int H) {
     constexpr int L = 1 << LG, T = fft_threads(LG), NF = row_seqs(LG);
     constexpr int LXM = L / 2 + 2 * TR_HMAX + 1;
@@ -830,12 +891,12 @@ __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_inv(
     // the half spectra, all loads in flight together (rows past the image:
     // its first ones, never used)
     constexpr int NE = (LXM + T - 1) / T;
-    double2 h0[NE], h1[NE];
+    C2<S> h0[NE], h1[NE];
 #pragma unroll
     for (int m = 0; m < NE; ++m) {
         const int e = threadIdx.x + m * NF * T;
         const int qc = e / NF < Lx ? e / NF : Lx - 1, ir = rows0 + 2 * (e % NF);
-        const double2 *y = Y + ((size_t)c * Lx + qc) * n + (ir < n ? ir : 0);
+        const C2<S> *y = Y + ((size_t)c * Lx + qc) * n + (ir < n ? ir : 0);
         h0[m] = y[0];
         h1[m] = y[1];
     }
@@ -864,8 +925,8 @@ __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_inv(
     for (int m = 0; m < NE; ++m) {
         const int e = threadIdx.x + m * NF * T;
         if (e >= Lx * NF) continue;
-        s[e % NF][2 * (e / NF)] = h0[m];
-        s[e % NF][2 * (e / NF) + 1] = h1[m];
+        s[e % NF][2 * (e / NF)] = wide(h0[m]);
+        s[e % NF][2 * (e / NF) + 1] = wide(h1[m]);
     }
     __syncthreads();
     double2 v[8];
@@ -1171,49 +1232,46 @@ inline double *tr_pp(const uvmem_ctx *c, int buf) {
     return c->d_ppart + (size_t)buf * c->nimg * std::max(c->n_pb, c->n_trrec) * NPART;
 }
 
-template <int LG, typename R>
+template <int LG, typename R, typename S>
 hipError_t fwd_lg(const uvmem_ctx *c, const void *I, int what, hipStream_t st) {
     const int H = c->tr_h, L = 1 << LG, Lx = L / 2 + 2 * H + 1;
     constexpr int T = fft_threads(LG), RS = row_seqs(LG), CS = col_seqs(LG);
     const dim3 gr(c->n_trrec, c->nchan), gc((Lx + CS - 1) / CS, c->nchan), br(RS * T);
     const RowArgs<R> ra{(const R *)(what == 2 ? c->d_dir : I), (const R *)I, (const R *)c->d_beam, c->d_chan_img,
                         c->d_ichan_base, c->d_chan, tr_pp(c, 1), c->M};
+    C2<S> *X = (C2<S> *)c->d_trx;
     if (what == 2)
-        hipLaunchKernelGGL((k_tr_rows_fwd<LG, R, true>), gr, br, 0, st, ra, c->d_trx, c->d_trtw, c->d_trdec, c->n, H);
+        hipLaunchKernelGGL((k_tr_rows_fwd<LG, R, S, true>), gr, br, 0, st, ra, X, c->d_trtw, c->d_trdec, c->n, H);
     else
-        hipLaunchKernelGGL((k_tr_rows_fwd<LG, R, false>), gr, br, 0, st, ra, c->d_trx, c->d_trtw, c->d_trdec, c->n, H);
-    hipLaunchKernelGGL((k_tr_cols_fwd<LG>), gc, dim3(CS * T), 0, st, c->d_trx, c->d_trg, c->d_trtw, c->n, Lx,
+        hipLaunchKernelGGL((k_tr_rows_fwd<LG, R, S, false>), gr, br, 0, st, ra, X, c->d_trtw, c->d_trdec, c->n, H);
+    hipLaunchKernelGGL((k_tr_cols_fwd<LG, S>), gc, dim3(CS * T), 0, st, X, (C2<S> *)c->d_trg, c->d_trtw, c->n, Lx,
                        c->tr_lgc);
     return hipGetLastError();
 }
 
-template <int LG>
+template <int LG, int W, typename S>
 hipError_t inv_lg(const uvmem_ctx *c, hipStream_t st) {
     const int H = c->tr_h, L = 1 << LG, Lx = L / 2 + 2 * H + 1;
     constexpr int T = fft_threads(LG), CS = col_seqs(LG);
-    const dim3 gc((Lx + CS - 1) / CS, c->nchan);
-    if (c->tr_w == 17)
-        hipLaunchKernelGGL((k_tr_cols_inv<LG, 17>), gc, dim3(CS * T), 0, st, c->d_trtile, c->d_trbin, c->d_trx,
-                           c->d_trtw, c->n, Lx, c->tr_nbx);
-    else
-        hipLaunchKernelGGL((k_tr_cols_inv<LG, 9>), gc, dim3(CS * T), 0, st, c->d_trtile, c->d_trbin, c->d_trx,
-                           c->d_trtw, c->n, Lx, c->tr_nbx);
+    hipLaunchKernelGGL((k_tr_cols_inv<LG, W, S>), dim3((Lx + CS - 1) / CS, c->nchan), dim3(CS * T), 0, st,
+                       (const C2<S> *)c->d_trtile, c->d_trbin, (C2<S> *)c->d_trx, c->d_trtw, c->n, Lx, c->tr_nbx);
     return hipGetLastError();
 }
 
-template <int LG, typename R>
+template <int LG, typename R, typename S>
 hipError_t rows_inv_lg(const uvmem_ctx *c, const void *I, void *out, int mode, double *user, hipStream_t st) {
     constexpr int T = fft_threads(LG), RS = row_seqs(LG);
     const dim3 gr(c->n_trrec, c->nchan), br(RS * T);
+    const C2<S> *Y = (const C2<S> *)c->d_trx;
     if (c->nimg == c->nchan) {
         const RowGrad<R> rg{(const R *)c->d_beam, (const R *)c->d_dir, (R *)const_cast<void *>(I), (R *)out,
                             (R *)c->d_gt, c->d_flag, tr_pp(c, 1), c->d_wscale, c->d_mask, c->M, c->Mb, c->lam, mode,
                             make_grad_tail(c, mode, user)};
-        hipLaunchKernelGGL((k_tr_rows_inv<LG, R, true>), gr, br, 0, st, c->d_trx, (double *)nullptr, rg, c->d_trtw,
+        hipLaunchKernelGGL((k_tr_rows_inv<LG, R, S, true>), gr, br, 0, st, Y, (double *)nullptr, rg, c->d_trtw,
                            c->d_trdec, c->n, c->np, c->tr_h);
     } else {
-        hipLaunchKernelGGL((k_tr_rows_inv<LG, R, false>), gr, br, 0, st, c->d_trx, (double *)c->d_gpart,
-                           RowGrad<R>{}, c->d_trtw, c->d_trdec, c->n, c->np, c->tr_h);
+        hipLaunchKernelGGL((k_tr_rows_inv<LG, R, S, false>), gr, br, 0, st, Y, (double *)c->d_gpart, RowGrad<R>{},
+                           c->d_trtw, c->d_trdec, c->n, c->np, c->tr_h);
     }
     return hipGetLastError();
 }
@@ -1233,55 +1291,68 @@ hipError_t with_lg(const uvmem_ctx *c, F f) {
     return hipErrorInvalidValue;
 }
 
-template <int W, int MODE>
+template <int W, typename S, int MODE>
 void interp_mode(const uvmem_ctx *c, double2 *out, const double2 *ref, hipStream_t st) {
-    hipLaunchKernelGGL((k_tr_interp<W, MODE>), dim3(c->n_trgroup), dim3(64 * TR_WAVES), 0, st, c->d_trspan,
-                       c->d_tritem, c->d_a, c->d_b, c->d_trg, c->d_trpoly, 1 << c->tr_lg, c->tr_lgc,
-                       (long long)c->ztot, (double *)out, (const double *)ref, c->d_w, c->d_trperm, c->d_trpart,
+    hipLaunchKernelGGL((k_tr_interp<W, S, MODE>), dim3(c->n_trgroup), dim3(64 * TR_WAVES), 0, st, c->d_trspan,
+                       c->d_tritem, c->d_a, c->d_b, (const C2<S> *)c->d_trg, (const S *)c->d_trpoly, 1 << c->tr_lg,
+                       c->tr_lgc, (long long)c->ztot, (double *)out, (const double *)ref, c->d_w, c->d_trperm,
+                       c->d_trpart,
                        DirTail{c->d_chan_img, c->d_trgbase, c->d_ctr + (size_t)CTR_VIS * c->nimg, tr_pp(c, 1),
                                c->n_trrec, c->d_chan, c->d_ls, c->lam});
 }
-template <int W>
+template <int W, typename S>
 hipError_t interp_w(const uvmem_ctx *c, int what, double2 *out, hipStream_t st) {
-    if (what == 0) interp_mode<W, TV_OUT>(c, out, nullptr, st);
-    else if (what == 1) interp_mode<W, TV_RES>(c, c->d_R, c->d_vo, st);
-    else interp_mode<W, TV_DIR>(c, c->d_Vd, c->d_R, st);
+    if (what == 0) interp_mode<W, S, TV_OUT>(c, out, nullptr, st);
+    else if (what == 1) interp_mode<W, S, TV_RES>(c, c->d_R, c->d_vo, st);
+    else interp_mode<W, S, TV_DIR>(c, c->d_Vd, c->d_R, st);
     return hipGetLastError();
 }
 
-template <int W, bool STEP>
+template <int W, typename S, bool STEP>
 void spread_w(const uvmem_ctx *c, const double2 *coef, const float *w, const unsigned *perm, hipStream_t st) {
-    hipLaunchKernelGGL((k_tr_spread<W, STEP>), dim3(c->n_trspread), dim3(64 * TR_WAVES), 0, st, c->d_trspread,
-                       c->d_tritem, c->d_a, c->d_b, coef, w, perm, c->d_trtile, c->d_trpoly, 1 << c->tr_lg,
-                       (long long)c->ztot, StepArgs{c->d_R, c->d_Vd, c->d_ls, c->d_trpart});
+    hipLaunchKernelGGL((k_tr_spread<W, S, STEP>), dim3(c->n_trspread), dim3(64 * TR_WAVES), 0, st, c->d_trspread,
+                       c->d_tritem, c->d_a, c->d_b, coef, w, perm, (C2<S> *)c->d_trtile, (const S *)c->d_trpoly,
+                       1 << c->tr_lg, (long long)c->ztot, StepArgs{c->d_R, c->d_Vd, c->d_ls, c->d_trpart});
+}
+
+// f(image type, S, width) of the context's precision.
+template <int W> using width = std::integral_constant<int, W>;
+template <typename F>
+hipError_t with_prec(const uvmem_ctx *c, F f) {
+    if (c->prec == UVMEM_FP64) return f(double(), double(), width<17>());
+    if (c->prec == UVMEM_FP32) return f(float(), double(), width<9>());
+    return f(float(), float(), width<9>());
 }
 
 }  // namespace
 
 hipError_t launch_tr_forward(const uvmem_ctx *c, const void *I, int what, double2 *out, hipStream_t st) {
-    const hipError_t e = with_lg(c, [&](auto lg) {
-        constexpr int LG = decltype(lg)::value;
-        return c->prec == UVMEM_FP64 ? fwd_lg<LG, double>(c, I, what, st) : fwd_lg<LG, float>(c, I, what, st);
+    return with_prec(c, [&](auto r, auto s, auto w) {
+        typedef decltype(r) R;
+        typedef decltype(s) S;
+        const hipError_t e =
+            with_lg(c, [&](auto lg) { return fwd_lg<decltype(lg)::value, R, S>(c, I, what, st); });
+        return e != hipSuccess ? e : interp_w<decltype(w)::value, S>(c, what, out, st);
     });
-    if (e != hipSuccess) return e;
-    return c->tr_w == 17 ? interp_w<17>(c, what, out, st) : interp_w<9>(c, what, out, st);
 }
 
 hipError_t launch_tr_adjoint(const uvmem_ctx *c, const double2 *coef, const float *w, const unsigned *perm,
                              int step, hipStream_t st) {
-    if (step)
-        c->tr_w == 17 ? spread_w<17, true>(c, coef, w, perm, st) : spread_w<9, true>(c, coef, w, perm, st);
-    else
-        c->tr_w == 17 ? spread_w<17, false>(c, coef, w, perm, st) : spread_w<9, false>(c, coef, w, perm, st);
-    return with_lg(c, [&](auto lg) { return inv_lg<decltype(lg)::value>(c, st); });
+    return with_prec(c, [&](auto, auto s, auto ww) {
+        typedef decltype(s) S;
+        constexpr int W = decltype(ww)::value;
+        if (step) spread_w<W, S, true>(c, coef, w, perm, st);
+        else spread_w<W, S, false>(c, coef, w, perm, st);
+        return with_lg(c, [&](auto lg) { return inv_lg<decltype(lg)::value, W, S>(c, st); });
+    });
 }
 
 hipError_t launch_tr_rows_inv(const uvmem_ctx *c, const void *I, void *out, int mode, double *user_scal,
                               hipStream_t st) {
-    return with_lg(c, [&](auto lg) {
-        constexpr int LG = decltype(lg)::value;
-        return c->prec == UVMEM_FP64 ? rows_inv_lg<LG, double>(c, I, out, mode, user_scal, st)
-                                     : rows_inv_lg<LG, float>(c, I, out, mode, user_scal, st);
+    return with_prec(c, [&](auto r, auto s, auto) {
+        return with_lg(c, [&](auto lg) {
+            return rows_inv_lg<decltype(lg)::value, decltype(r), decltype(s)>(c, I, out, mode, user_scal, st);
+        });
     });
 }
 
