@@ -902,6 +902,7 @@ __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_inv(
     }
     // the pixels' data, loaded ahead of the transform
     R pI[8][2], pA[8][2], pd[8][2], pg[8][2];
+    double lg[8][2];
     double al = 0.0;
     if constexpr (FUSED) {
         if (rg.mode == 2) al = rg.tail.ls[(size_t)c * LSS_N + LSS_ALPHA];
@@ -917,6 +918,23 @@ __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_inv(
                 if (rg.mode == 2) {
                     pd[x][u] = rg.dir[q];
                     pg[x][u] = rg.gt[q];
+                }
+            }
+        }
+        // the pixels' logarithms, while the spectra are on their way and without
+        // a branch between them: their long dependent chains overlap (a pixel
+        // off the image: ln 1)
+        if (rg.mode == 1 || rg.mode == 2) {
+#pragma unroll
+            for (int x = 0; x < 8; ++x) {
+                if (!fft_live<LG>(x)) continue;
+                const int j = pix_of(fft_out<LG>(t, x), L, n);
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const R x0 = pI[x][u];
+                    if (rg.mode == 2) pI[x][u] = al != 0.0 ? (R)fmax((double)x0 + al * (double)pd[x][u], rg.Mb) : x0;
+                    const double xi = live && j >= 0 ? (double)pI[x][u] : rg.M;
+                    lg[x][u] = log(xi / rg.M);
                 }
             }
         }
@@ -966,23 +984,6 @@ __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_inv(
         double acc[3] = {0.0, 0.0, 0.0};
         int bad = 0;
         const double scale = mode == 3 ? rg.img_scale[c] : 1.0;
-        // the pixels' logarithms first, without a branch between them: their
-        // long dependent chains then overlap (a pixel off the image: ln 1)
-        double lg[8][2];
-        if (mode == 1 || mode == 2) {
-#pragma unroll
-            for (int x = 0; x < 8; ++x) {
-                if (!fft_live<LG>(x)) continue;
-                const int j = pix_of(fft_out<LG>(t, x), L, n);
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const R x0 = pI[x][u];
-                    if (mode == 2) pI[x][u] = al != 0.0 ? (R)fmax((double)x0 + al * (double)pd[x][u], rg.Mb) : x0;
-                    const double xi = live && j >= 0 ? (double)pI[x][u] : rg.M;
-                    lg[x][u] = log(xi / rg.M);
-                }
-            }
-        }
 #pragma unroll
         for (int x = 0; x < 8; ++x) {
             const int j = fft_live<LG>(x) ? pix_of(fft_out<LG>(t, x), L, n) : -1;
@@ -1047,8 +1048,10 @@ __global__ void k_tr_permute(const double2 *__restrict__ src, double2 *__restric
 // have period one in both; the reduction is exact), and whether the pair was
 // negated.
 __device__ __forceinline__ bool reduce_ab(double u, double v, double cell, double &a, double &b) {
-    a = u * cell;
-    b = v * cell;
+    // (products rounded before the reduction, as the coordinates of the direct
+    // contraction are: no fused multiply-subtract)
+    a = __dmul_rn(u, cell);
+    b = __dmul_rn(v, cell);
     a -= rint(a);
     b -= rint(b);
     const bool neg = a < 0.0;
