@@ -218,8 +218,12 @@ void choose_transform(uvmem_ctx *c) {
     int lg = 6;
     while ((1 << lg) < 2 * c->n) ++lg;
     if (lg > 12) return;
-    // grids and bin tables within 32 GiB and 2^28 entries
-    if ((double)c->nchan * std::ldexp(1.0, 2 * lg) > (double)(1 << 30) * 2) return;
+    // bin tables within 2^28 entries; grids and tiles (at most one per bin and
+    // visibility, and one per 128 visibilities) within 48 GiB
+    const double nodes = (double)c->nchan * std::ldexp(1.0, 2 * lg);
+    const double tb = c->prec == UVMEM_FP64 ? 16 : 8;
+    const double slots = std::min(nodes / (2 * tb * tb) + nodes / std::ldexp(tb, lg), (double)c->ztot) + c->ztot / 128.0;
+    if (nodes > std::ldexp(1.0, 31) || 16 * nodes + 64 * tb * tb * slots > std::ldexp(48.0, 30)) return;
     // by padded side 64, 128 and larger; FP64, FP32, split
     static const double base[3][3] = {{38, 60, 80}, {32, 54, 95}, {31, 32, 46}};        // microseconds
     static const double rate[3][3] = {{34, 59, 62}, {50, 109, 138}, {88, 226, 450}};    // TFLOP/s
