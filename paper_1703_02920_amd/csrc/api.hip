@@ -221,9 +221,10 @@ void choose_transform(uvmem_ctx *c) {
     // bin tables within 2^28 entries; grids and tiles (at most one per bin and
     // visibility, and one per 128 visibilities) within 48 GiB
     const double nodes = (double)c->nchan * std::ldexp(1.0, 2 * lg);
-    const double tb = c->prec == UVMEM_FP64 ? 16 : 8;
-    const double slots = std::min(nodes / (2 * tb * tb) + nodes / std::ldexp(tb, lg), (double)c->ztot) + c->ztot / 128.0;
-    if (nodes > std::ldexp(1.0, 31) || 16 * nodes + 64 * tb * tb * slots > std::ldexp(48.0, 30)) return;
+    const double side = c->prec == UVMEM_FP64 ? 16 : 8;   // nodes per bin side
+    const double slots =
+        std::min(nodes / (2 * side * side) + nodes / std::ldexp(side, lg), (double)c->ztot) + (double)c->ztot / 128.0;
+    if (nodes > std::ldexp(1.0, 31) || 16 * nodes + 64 * side * side * slots > std::ldexp(48.0, 30)) return;
     // by padded side 64, 128 and larger; FP64, FP32, split
     static const double base[3][3] = {{38, 60, 80}, {32, 54, 95}, {31, 32, 46}};        // microseconds
     static const double rate[3][3] = {{34, 59, 62}, {50, 109, 138}, {88, 226, 450}};    // TFLOP/s
