@@ -207,11 +207,11 @@ int pick_schedule(int slots, const std::function<std::vector<double>(int)> &cost
 // and its gradient in microseconds, as fitted to measurements at sides 32 to
 // 512, 500 to 100,000 visibilities a channel, 1 and 8 channels: a launch-bound
 // part, a part per visibility (the contraction's rate; window and tile work)
-// and, for the transforms, a part per grid point.  Measured around the line
-// (one channel; direct, fast): 64^2 x 5,000 FP64 43.7, 49.4, x 100,000 138.7,
-// 138.1; FP32 x 20,000 50.0, 49.0; 128^2 bf16x3 x 2,000 33.8, 37.4, x 20,000
-// 52.1, 42.7; 100^2 x 500 FP64 61.0, 43.0 and FP32 54.5, 36.8; far from it
-// 256^2 x 100,000 FP64 918, 79; 1024^2 x 5,000,250 bf16x3 92,486, 420.
+// part and, for the transforms, a part per grid point.  Measured around the
+// line (one channel; direct, fast): 64^2 x 5,000 FP64 36.3, 47.5, x 100,000
+// 138.7, 138.1; FP32 x 20,000 49.5, 48.0; 128^2 bf16x3 x 3,000 34.8, 37.5, x
+// 20,000 52.1, 42.7; 128^2 x 3,000 FP64 51.2, 43.5 and FP32 47.0, 37.5; far
+// from it 256^2 x 100,000 FP64 918, 77; 1024^2 x 5,000,250 bf16x3 92,486, 279.
 void choose_transform(uvmem_ctx *c) {
     c->tr_lg = 0;
     if (c->fwd_model != UVMEM_FWD_DFT || c->ztot == 0 || c->ztot >= (int64_t)1 << 30) return;
@@ -226,7 +226,7 @@ void choose_transform(uvmem_ctx *c) {
         std::min(nodes / (2 * side * side) + nodes / std::ldexp(side, lg), (double)c->ztot) + (double)c->ztot / 128.0;
     if (nodes > std::ldexp(1.0, 31) || 16 * nodes + 64 * side * side * slots > std::ldexp(48.0, 30)) return;
     // by padded side 64, 128 and larger; FP64, FP32, split
-    static const double base[3][3] = {{38, 60, 80}, {32, 54, 95}, {31, 32, 46}};        // microseconds
+    static const double base[3][3] = {{32, 48, 75}, {30, 44, 85}, {30, 31, 46}};        // microseconds
     static const double rate[3][3] = {{34, 59, 62}, {50, 109, 138}, {88, 226, 450}};    // TFLOP/s
     const int p = c->prec == UVMEM_FP64 ? 0 : c->prec == UVMEM_FP32 ? 1 : 2, q = c->np == 64 ? 0 : c->np == 128 ? 1 : 2;
     const double z = (double)c->ztot;
@@ -812,7 +812,11 @@ void direct_lists(const uvmem_ctx *c, DirectLists &d) {
         for (char t : tile_used) tiles += t ? 1 : 0;
         auto adj_klen = [&](int64_t target) {
             int64_t klen = (c->ztot * std::max(tiles, 1) + target - 1) / target;
-            klen = std::max<int64_t>(klen, ADJ_KMIN);
+            // short chunks only while they leave CUs without a workgroup (64^2
+            // FP64 evaluation: x 1,000 33.8 -> 30.3 us, x 5,130 36.9 -> 36.3;
+            // 4 channels x 5,000, already 320 workgroups, 53.2 -> 58.1)
+            const bool few = c->ztot * std::max(tiles, 1) <= 256 * (ADJ_KMIN / 2);
+            klen = std::max<int64_t>(klen, few ? ADJ_KMIN / 2 : ADJ_KMIN);
             if (split) klen = std::min<int64_t>(klen, ADJ_KMAX_SPLIT);
             return ((klen + 15) / 16) * 16;
         };
@@ -884,9 +888,15 @@ void direct_lists(const uvmem_ctx *c, DirectLists &d) {
         constexpr double FWD_OVERHEAD = 128.0;
         auto shares = [&](int64_t wgs, int ch) {
             const int64_t nv = c->nvis[ch];
-            const int64_t L = std::max<int64_t>(16, (c->ztot * nblk + wgs - 1) / wgs);
-            const int64_t tl = (nv + 15) / 16;   // 16-visibility wave tiles
-            return std::max<int64_t>(1, std::min<int64_t>((nv + L - 1) / L, (tl + 7) / 8));
+            // at least one wave tile per workgroup (32 visibilities in the
+            // split kernel of 128-row blocks, else 16).  Few tiles go to as
+            // many workgroups, even if seven of their eight waves then only
+            // help to stage the block: the tiles run on CUs of their own
+            // (64^2 x 5,130 FP64 evaluation: 41 workgroups of eight tiles
+            // 41.9 us, 257 of one or two 36.9 us)
+            const int64_t tile = split && c->ib_rows == 128 ? 32 : 16;
+            const int64_t L = std::max<int64_t>(tile, (c->ztot * nblk + wgs - 1) / wgs);
+            return std::max<int64_t>(1, (nv + L - 1) / L);
         };
         int fwd_m = pick_schedule(256, [&](int m) {
             std::vector<double> w;

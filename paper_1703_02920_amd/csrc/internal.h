@@ -19,7 +19,8 @@ constexpr int NTHR = 256;
 // visibilities, a pixel block a multiple of NTHR pixels.
 constexpr int VIS_WGS = 1024;
 constexpr int PIX_WGS = 1024;
-// Minimum visibilities per adjoint split-K chunk (multiple of 16).
+// Minimum visibilities per adjoint split-K chunk (multiple of 32; half of it
+// while the whole list has at most a workgroup per CU).
 constexpr int ADJ_KMIN = 64;
 // Maximum visibilities per split-K chunk of the split-precision adjoint,
 // whose chunk sums are FP32 only (bounds their rounding growth).
