@@ -246,6 +246,9 @@ void choose_transform(uvmem_ctx *c) {
     c->tr_nby = (1 << lg) / tb;
     c->tr_lgc = (c->tr_nbx - 1) * tb + 2 * tb;
     c->n_trrec = (c->n / 2 + tr_row_seqs(lg) - 1) / tr_row_seqs(lg);
+    // planes of an image of several channels: enough workgroups to fill the
+    // chip (about four per CU at 512 threads a CU)
+    c->n_trplane = std::min(c->nchan, (1024 + c->n_trrec - 1) / c->n_trrec);
 }
 
 // Window of the fast evaluation: phi(x) = I0(beta sqrt(1 - (2 x / W)^2)) /
@@ -645,7 +648,8 @@ hipError_t sort_bins(uvmem_ctx *c) {
         ok(hipMemcpy(vis + 2 * o, c->hvis[ch].data(), nv * 8, hipMemcpyHostToDevice));
         ok(hipMemcpy(w + o, c->hw[ch].data(), nv * 4, hipMemcpyHostToDevice));
     }
-    std::vector<int> start, first(C * nbin + 1);
+    std::vector<int> start;
+    std::vector<int2> first(C * nbin);
     if (e == hipSuccess) e = launch_tr_sort(c, u, v, vis, w, start);
     if (e != hipSuccess) return e;
     // an item's visibilities: two waves' shares per wave slot of the chip, and
@@ -656,15 +660,15 @@ hipError_t sort_bins(uvmem_ctx *c) {
     std::vector<TrItem> items;
     int slot = 0;
     for (size_t t = 0; t < C * nbin; ++t) {
-        first[t] = slot;
+        first[t].x = slot;
         const int bin = (int)(t % nbin);
         int v = 0;
         for (int64_t k = start[t]; k < start[t + 1]; k += chunk, ++v)
             items.push_back(TrItem{(int)(t / nbin), bin / c->tr_nby, bin % c->tr_nby, slot + v / TR_WAVES,
                                    (long long)k, (long long)std::min<int64_t>(k + chunk, start[t + 1])});
         slot += (v + TR_WAVES - 1) / TR_WAVES;
+        first[t].y = slot;
     }
-    first[C * nbin] = slot;
     c->n_tritem = (int)items.size();
     // spans of consecutive items of equal cost: whole batches of 32
     // visibilities plus one for the tile, two spans per wave slot of the chip
@@ -740,7 +744,7 @@ hipError_t sort_bins(uvmem_ctx *c) {
     const size_t o_spread = put(spread.data(), spread.size() * sizeof(int4));
     const size_t o_gbase = put(gbase.data(), gbase.size() * sizeof(int));
     const size_t o_sbase = put(sbase.data(), sbase.size() * sizeof(int));
-    const size_t o_bin = put(first.data(), first.size() * sizeof(int));
+    const size_t o_bin = put(first.data(), first.size() * sizeof(int2));
     ok(dalloc(c, &c->d_trtab, tab.size(), false));
     ok(dalloc(c, &c->d_trpart, (size_t)std::max(c->n_trgroup, c->n_trspread) * NPART, false));
     ok(dalloc(c, (char **)&c->d_trtile, slot * ts * ts * (c->tr_f32 ? sizeof(float2) : sizeof(double2)), false));
@@ -750,7 +754,7 @@ hipError_t sort_bins(uvmem_ctx *c) {
         c->d_trspread = (int4 *)(c->d_trtab + o_spread);
         c->d_trgbase = (int *)(c->d_trtab + o_gbase);
         c->d_trsbase = (int *)(c->d_trtab + o_sbase);
-        c->d_trbin = (int *)(c->d_trtab + o_bin);
+        c->d_trbin = (int2 *)(c->d_trtab + o_bin);
         ok(hipMemcpy(c->d_trtab, tab.data(), tab.size(), hipMemcpyHostToDevice));
     }
     // the staging buffers start out as zeros again
@@ -1005,10 +1009,10 @@ int finalize_impl(uvmem_ctx *c) {
     c->has_region = region;
     c->h_slot_base = d.slot_base;
     if (tr) {
-        // one forward partial and one FP64 adjoint plane per channel; a
+        // adjoint planes (with A) of an image that sums several channels; a
         // region saves nothing there, so every pass covers the whole image
-        c->h_slot_base.resize(C + 1);
-        for (int ch = 0; ch <= C; ++ch) c->h_slot_base[ch] = ch;
+        c->h_slot_base.assign(C + 1, c->n_trplane);
+        c->h_slot_base[0] = 0;
         c->n_vparts = c->n_vparts_m = 1;
         c->gpart_f32 = false;
     }
@@ -1171,7 +1175,7 @@ int finalize_impl(uvmem_ctx *c) {
     ok(dalloc(c, &c->d_R, c->ztot));
     ok(dalloc(c, &c->d_Vd, c->ztot));
     ok(dalloc(c, &c->d_vpart, (size_t)c->n_vparts * c->ztot));
-    const size_t planes = tr ? (size_t)(IMG == C ? 0 : C) : (size_t)std::max(c->n_slots, c->n_slots_m);
+    const size_t planes = tr ? (size_t)(IMG == C ? 0 : c->n_trplane) : (size_t)std::max(c->n_slots, c->n_slots_m);
     ok(dalloc(c, (char **)&c->d_gpart, planes * np * np * (c->gpart_f32 ? sizeof(float) : sizeof(double))));
     if (tr) {
         const size_t L = (size_t)1 << c->tr_lg;

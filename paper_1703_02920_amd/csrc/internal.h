@@ -248,7 +248,7 @@ struct uvmem_ctx {
     char *d_trtab = nullptr;                    // the tables below, one allocation
     char *d_trconst = nullptr;                  // d_trdec, d_trpoly, d_trtw likewise
     uvm::TrItem *d_tritem = nullptr;
-    int *d_trbin = nullptr;                     // first tile slot of each bin, [C][nbx][nby] + 1
+    int2 *d_trbin = nullptr;                    // tile slots [x, y) of each bin, [C][nbx][nby]
     // gather: spans of items, TR_WAVES per workgroup, each workgroup within
     // one channel; its partial records d_trpart [workgroup][NPART], those of
     // an image in [d_trgbase[img], d_trgbase[img + 1]).  Spread:
@@ -257,6 +257,7 @@ struct uvmem_ctx {
     // (d_trsbase; a CG step's chi^2)
     int n_trgroup = 0, n_trspread = 0;
     int n_trrec = 0;                   // records per image of the row passes
+    int n_trplane = 0;                 // adjoint planes of an image that sums several channels
     int2 *d_trspan = nullptr;
     int4 *d_trspread = nullptr;
     int *d_trgbase = nullptr, *d_trsbase = nullptr;

@@ -195,8 +195,9 @@ __global__ __launch_bounds__(NTHR) void k_vis(const VisItem *__restrict__ items,
 // With a focus-of-attention mask, pixels outside it are not free: modes 1
 // and 2 write 0 there (gradient and projected gradient).
 // The last workgroup of an image finishes modes 1 and 2 (grad_tail).
-// TR (fast evaluation, several channels per image): mode 1 also sums S and
-// checks the domain, mode 2 first takes the CG step I <- max(I + alpha d, M).
+// TR (fast evaluation, several channels per image): the planes hold sums over
+// channels with A applied already; mode 1 also sums S and checks the domain,
+// mode 2 first takes the CG step I <- max(I + alpha d, M).
 struct GradStep {
     const void *dir;
     int *flag;
@@ -254,7 +255,7 @@ __global__ __launch_bounds__(NTHR) void k_grad(const PT *__restrict__ gpart, con
         double AG[RP];
 #pragma unroll
         for (int r = 0; r < RP; ++r) AG[r] = 0.0;
-        for (int ch = ch0; ch < ch1; ++ch) {
+        for (int ch = ch0; ch < (TR ? ch0 + 1 : ch1); ++ch) {
             const int s0 = slot_base[ch], s1 = slot_base[ch + 1];
             double Gs[RP];
 #pragma unroll
@@ -287,7 +288,7 @@ __global__ __launch_bounds__(NTHR) void k_grad(const PT *__restrict__ gpart, con
 #pragma unroll
             for (int r = 0; r < RP; ++r) {
                 const long long p = (long long)pb * pb_len + g0 + r * NTHR + threadIdx.x;
-                const double A = mode == 3 ? 1.0 : ch == ch0 ? (double)bm0[r] : (double)beam[(size_t)ch * npix + p];
+                const double A = TR || mode == 3 ? 1.0 : ch == ch0 ? (double)bm0[r] : (double)beam[(size_t)ch * npix + p];
                 if (okp[r]) AG[r] += A * Gs[r];
             }
         }

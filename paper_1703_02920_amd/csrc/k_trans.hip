@@ -776,7 +776,7 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
 // over p; the image rows are kept: Y[q][i].
 template <int LG, int W, typename S>
 __global__ __launch_bounds__(col_seqs(LG) * fft_threads(LG)) void k_tr_cols_inv(
-    const C2<S> *__restrict__ tiles, const int *__restrict__ bin_slot, C2<S> *__restrict__ Y,
+    const C2<S> *__restrict__ tiles, const int2 *__restrict__ bin_slot, C2<S> *__restrict__ Y,
     const double2 *__restrict__ tw, int n, int Lx, int nbx) {
     constexpr int L = 1 << LG, T = fft_threads(LG), NF = col_seqs(LG);
     constexpr int H = (W - 1) / 2, TB = Win<W>::TB, TS = Win<W>::TS, NBY = L / TB;
@@ -784,7 +784,7 @@ __global__ __launch_bounds__(col_seqs(LG) * fft_threads(LG)) void k_tr_cols_inv(
     const int f = threadIdx.x / T, t = threadIdx.x % T;
     const int c = blockIdx.y, qc = blockIdx.x * NF + f;
     const bool live = qc < Lx;
-    const int *bins = bin_slot + (size_t)c * nbx * NBY;
+    const int2 *bins = bin_slot + (size_t)c * nbx * NBY;
     double2 v[8];
 #pragma unroll
     for (int r = 0; r < 8; ++r) v[r] = make_double2(0.0, 0.0);
@@ -800,10 +800,11 @@ __global__ __launch_bounds__(col_seqs(LG) * fft_threads(LG)) void k_tr_cols_inv(
             for (int r = 0; r < 8; ++r) {
                 const int pr = (t + r * T + H) & (L - 1);
                 const int bh = pr / TB, bl = (bh - 1) & (NBY - 1);
-                s0[r][0] = bins[bx * NBY + bl];
-                s1[r][0] = bins[bx * NBY + bl + 1];
-                s0[r][1] = bins[bx * NBY + bh];
-                s1[r][1] = bins[bx * NBY + bh + 1];
+                const int2 l = bins[bx * NBY + bl], h = bins[bx * NBY + bh];
+                s0[r][0] = l.x;
+                s1[r][0] = l.y;
+                s0[r][1] = h.x;
+                s1[r][1] = h.y;
             }
             // the first tile of every covering bin in one round of loads
             // (slot 0 stands in for an empty bin), further ones after them
@@ -872,161 +873,218 @@ template <typename R> struct RowGrad {
 
 // Inverse rows: the real part over the half grid of two image rows at once
 // (their Hermitian halves packed as one complex sequence), times the window's
-// inverse transform: into the channel's plane, or (FUSED) straight through
-// the gradient pass.
-template <int LG, typename R, typename S, bool FUSED>
+// inverse transform.  The workgroup's NF row pairs start at rows0.
+template <int LG, typename S> struct RowsInv {
+    static constexpr int L = 1 << LG, T = fft_threads(LG), NF = row_seqs(LG);
+    static constexpr int LXM = L / 2 + 2 * TR_HMAX + 1;
+    // per pair: the half spectra of two rows, then (reused) the exchange of
+    // the transform
+    static constexpr int NSH = 2 * LXM > fpad(L) ? 2 * LXM : fpad(L);
+    static constexpr int NE = (LXM + T - 1) / T;
+    C2<S> h0[NE], h1[NE];
+
+    // The half spectra, all loads in flight together (rows past the image:
+    // its first ones, never used).
+    __device__ __forceinline__ void load(const C2<S> *Y, int c, int rows0, int n, int H) {
+        const int Lx = L / 2 + 2 * H + 1;
+#pragma unroll
+        for (int m = 0; m < NE; ++m) {
+            const int e = threadIdx.x + m * NF * T;
+            const int qc = e / NF < Lx ? e / NF : Lx - 1, ir = rows0 + 2 * (e % NF);
+            const C2<S> *y = Y + ((size_t)c * Lx + qc) * n + (ir < n ? ir : 0);
+            h0[m] = y[0];
+            h1[m] = y[1];
+        }
+    }
+    // Transforms them; register x then holds the two rows' sums at position
+    // fft_out(t, x).
+    __device__ __forceinline__ void run(double2 (*s)[NSH], double2 (&v)[8], const double2 *tw, int H) {
+        const int f = threadIdx.x / T, t = threadIdx.x % T;
+        const int Lx = L / 2 + 2 * H + 1;
+#pragma unroll
+        for (int m = 0; m < NE; ++m) {
+            const int e = threadIdx.x + m * NF * T;
+            if (e >= Lx * NF) continue;
+            s[e % NF][2 * (e / NF)] = wide(h0[m]);
+            s[e % NF][2 * (e / NF) + 1] = wide(h1[m]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const int q = t + r * T, qm = (L - q) & (L - 1);
+            auto col = [&](int x) { return x <= L / 2 + H ? x + H : x >= L - H ? x - (L - H) : -1; };
+            const int cp = col(q), cm = col(qm);
+            double2 z = make_double2(0.0, 0.0);
+            if (cp >= 0) {
+                const double2 a = s[f][2 * cp], b = s[f][2 * cp + 1];
+                z.x += a.x - b.y;
+                z.y += a.y + b.x;
+            }
+            if (cm >= 0) {
+                const double2 a = s[f][2 * cm], b = s[f][2 * cm + 1];
+                z.x += a.x + b.y;
+                z.y += b.x - a.y;
+            }
+            v[r] = make_double2(0.5 * z.x, 0.5 * z.y);
+        }
+        fft_passes<LG, 0, 1, true>(v, t, s[f], tw);
+    }
+};
+
+// Several channels of one image: workgroup (x, y) sums A_c x (its rows) over
+// the y-th share of the channels (no A for the dirty image, mode 3) into plane
+// y, which the gradient kernel then sums (a plane per channel cost 56 us here
+// and 51 us there on 23 channels of 512^2; shares of three channels 58 and 28).
+template <int LG, typename R, typename S>
+__global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_sum(
+    const C2<S> *__restrict__ Y, double *__restrict__ plane, const R *__restrict__ beam, int nchan, int mode,
+    const double2 *__restrict__ tw, const double *__restrict__ dec, int n, int np, int H) {
+    typedef RowsInv<LG, S> RI;
+    constexpr int L = RI::L, T = RI::T, NF = RI::NF;
+    __shared__ double2 s[NF][RI::NSH];
+    const int f = threadIdx.x / T, t = threadIdx.x % T;
+    const int rows0 = blockIdx.x * NF * 2, i = rows0 + 2 * f;
+    const bool live = i < n;
+    const int c0 = (int)((long long)nchan * blockIdx.y / gridDim.y);
+    const int c1 = (int)((long long)nchan * (blockIdx.y + 1) / gridDim.y);
+    double acc[8][2];
+#pragma unroll
+    for (int x = 0; x < 8; ++x) acc[x][0] = acc[x][1] = 0.0;
+    RI ri;
+    ri.load(Y, c0, rows0, n, H);
+    for (int c = c0; c < c1; ++c) {
+        R A[8][2];
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+            if (!fft_live<LG>(x)) continue;
+            const int j = pix_of(fft_out<LG>(t, x), L, n);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) A[x][u] = beam[live && j >= 0 ? ((size_t)c * n + i + u) * n + j : 0];
+        }
+        double2 v[8];
+        __syncthreads();   // the last channel's exchange has been read
+        ri.run(s, v, tw, H);
+        if (c + 1 < c1) ri.load(Y, c + 1, rows0, n, H);
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+            if (!fft_live<LG>(x)) continue;
+            acc[x][0] += mode == 3 ? v[x].x : (double)A[x][0] * v[x].x;
+            acc[x][1] += mode == 3 ? v[x].y : (double)A[x][1] * v[x].y;
+        }
+    }
+    if (!live) return;
+    const double d0 = dec[i], d1 = dec[i + 1];
+    double *o = plane + ((size_t)blockIdx.y * np + i) * np;
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+        const int j = fft_live<LG>(x) ? pix_of(fft_out<LG>(t, x), L, n) : -1;
+        if (j < 0) continue;
+        const double dj = dec[j];
+        o[j] = acc[x][0] * (d0 * dj);
+        o[np + j] = acc[x][1] * (d1 * dj);
+    }
+}
+
+// One channel per image: the rows go straight through the gradient pass.
+template <int LG, typename R, typename S>
 __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_inv(
-    const C2<S> *__restrict__ Y, double *__restrict__ plane, const RowGrad<R> rg, const double2 *__restrict__ tw,
-    const double *__restrict__ dec, int n, int np, int H) {
-    constexpr int L = 1 << LG, T = fft_threads(LG), NF = row_seqs(LG);
-    constexpr int LXM = L / 2 + 2 * TR_HMAX + 1;
-    // [NF] half spectra of two rows, then (reused) the transform's exchange
-    constexpr int NSH = 2 * LXM > fpad(L) ? 2 * LXM : fpad(L);
-    __shared__ double2 s[NF][NSH];
+    const C2<S> *__restrict__ Y, const RowGrad<R> rg, const double2 *__restrict__ tw,
+    const double *__restrict__ dec, int n, int H) {
+    typedef RowsInv<LG, S> RI;
+    constexpr int L = RI::L, T = RI::T, NF = RI::NF;
+    __shared__ double2 s[NF][RI::NSH];
     const int f = threadIdx.x / T, t = threadIdx.x % T;
     const int c = blockIdx.y, rows0 = blockIdx.x * NF * 2;
-    const int Lx = L / 2 + 2 * H + 1;
     const int i = rows0 + 2 * f;
     const bool live = i < n;
-    // the half spectra, all loads in flight together (rows past the image:
-    // its first ones, never used)
-    constexpr int NE = (LXM + T - 1) / T;
-    C2<S> h0[NE], h1[NE];
-#pragma unroll
-    for (int m = 0; m < NE; ++m) {
-        const int e = threadIdx.x + m * NF * T;
-        const int qc = e / NF < Lx ? e / NF : Lx - 1, ir = rows0 + 2 * (e % NF);
-        const C2<S> *y = Y + ((size_t)c * Lx + qc) * n + (ir < n ? ir : 0);
-        h0[m] = y[0];
-        h1[m] = y[1];
-    }
+    RI ri;
+    ri.load(Y, c, rows0, n, H);
     // the pixels' data, loaded ahead of the transform
     R pI[8][2], pA[8][2], pd[8][2], pg[8][2];
     double lg[8][2];
     double al = 0.0;
-    if constexpr (FUSED) {
-        if (rg.mode == 2) al = rg.tail.ls[(size_t)c * LSS_N + LSS_ALPHA];
+    if (rg.mode == 2) al = rg.tail.ls[(size_t)c * LSS_N + LSS_ALPHA];
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+        if (!fft_live<LG>(x)) continue;
+        const int j = pix_of(fft_out<LG>(t, x), L, n);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const size_t q = live && j >= 0 ? ((size_t)c * n + i + u) * n + j : 0;
+            pA[x][u] = rg.beam[q];
+            if (rg.mode == 1 || rg.mode == 2) pI[x][u] = rg.I[q];
+            if (rg.mode == 2) {
+                pd[x][u] = rg.dir[q];
+                pg[x][u] = rg.gt[q];
+            }
+        }
+    }
+    // the pixels' logarithms, while the spectra are on their way and without
+    // a branch between them: their long dependent chains overlap (a pixel
+    // off the image: ln 1)
+    if (rg.mode == 1 || rg.mode == 2) {
 #pragma unroll
         for (int x = 0; x < 8; ++x) {
             if (!fft_live<LG>(x)) continue;
             const int j = pix_of(fft_out<LG>(t, x), L, n);
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-                const size_t q = live && j >= 0 ? ((size_t)c * n + i + u) * n + j : 0;
-                pA[x][u] = rg.beam[q];
-                if (rg.mode == 1 || rg.mode == 2) pI[x][u] = rg.I[q];
-                if (rg.mode == 2) {
-                    pd[x][u] = rg.dir[q];
-                    pg[x][u] = rg.gt[q];
-                }
-            }
-        }
-        // the pixels' logarithms, while the spectra are on their way and without
-        // a branch between them: their long dependent chains overlap (a pixel
-        // off the image: ln 1)
-        if (rg.mode == 1 || rg.mode == 2) {
-#pragma unroll
-            for (int x = 0; x < 8; ++x) {
-                if (!fft_live<LG>(x)) continue;
-                const int j = pix_of(fft_out<LG>(t, x), L, n);
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const R x0 = pI[x][u];
-                    if (rg.mode == 2) pI[x][u] = al != 0.0 ? (R)fmax((double)x0 + al * (double)pd[x][u], rg.Mb) : x0;
-                    const double xi = live && j >= 0 ? (double)pI[x][u] : rg.M;
-                    lg[x][u] = log(xi / rg.M);
-                }
+                const R x0 = pI[x][u];
+                if (rg.mode == 2) pI[x][u] = al != 0.0 ? (R)fmax((double)x0 + al * (double)pd[x][u], rg.Mb) : x0;
+                const double xi = live && j >= 0 ? (double)pI[x][u] : rg.M;
+                lg[x][u] = log(xi / rg.M);
             }
         }
     }
-#pragma unroll
-    for (int m = 0; m < NE; ++m) {
-        const int e = threadIdx.x + m * NF * T;
-        if (e >= Lx * NF) continue;
-        s[e % NF][2 * (e / NF)] = wide(h0[m]);
-        s[e % NF][2 * (e / NF) + 1] = wide(h1[m]);
-    }
-    __syncthreads();
     double2 v[8];
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        const int q = t + r * T, qm = (L - q) & (L - 1);
-        auto col = [&](int x) { return x <= L / 2 + H ? x + H : x >= L - H ? x - (L - H) : -1; };
-        const int cp = col(q), cm = col(qm);
-        double2 z = make_double2(0.0, 0.0);
-        if (cp >= 0) {
-            const double2 a = s[f][2 * cp], b = s[f][2 * cp + 1];
-            z.x += a.x - b.y;
-            z.y += a.y + b.x;
-        }
-        if (cm >= 0) {
-            const double2 a = s[f][2 * cm], b = s[f][2 * cm + 1];
-            z.x += a.x + b.y;
-            z.y += b.x - a.y;
-        }
-        v[r] = make_double2(0.5 * z.x, 0.5 * z.y);
-    }
-    fft_passes<LG, 0, 1, true>(v, t, s[f], tw);
+    ri.run(s, v, tw, H);
     const double d0 = live ? dec[i] : 0.0, d1 = live ? dec[i + 1] : 0.0;
-    if constexpr (!FUSED) {
-        if (!live) return;
-        double *o = plane + ((size_t)c * np + i) * np;
+    const int mode = rg.mode;
+    double acc[3] = {0.0, 0.0, 0.0};
+    int bad = 0;
+    const double scale = mode == 3 ? rg.img_scale[c] : 1.0;
 #pragma unroll
-        for (int x = 0; x < 8; ++x) {
-            const int j = fft_live<LG>(x) ? pix_of(fft_out<LG>(t, x), L, n) : -1;
-            if (j < 0) continue;
-            const double dj = dec[j];
-            o[j] = v[x].x * (d0 * dj);
-            o[np + j] = v[x].y * (d1 * dj);
-        }
-    } else {
-        const int mode = rg.mode;
-        double acc[3] = {0.0, 0.0, 0.0};
-        int bad = 0;
-        const double scale = mode == 3 ? rg.img_scale[c] : 1.0;
+    for (int x = 0; x < 8; ++x) {
+        const int j = fft_live<LG>(x) ? pix_of(fft_out<LG>(t, x), L, n) : -1;
+        if (!live || j < 0) continue;
+        const double dj = dec[j];
 #pragma unroll
-        for (int x = 0; x < 8; ++x) {
-            const int j = fft_live<LG>(x) ? pix_of(fft_out<LG>(t, x), L, n) : -1;
-            if (!live || j < 0) continue;
-            const double dj = dec[j];
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const size_t q = ((size_t)c * n + i + u) * n + j;
-                const double G = u ? v[x].y * (d1 * dj) : v[x].x * (d0 * dj);
-                double gv = mode == 3 ? G * scale : (double)pA[x][u] * G;
-                double xi = 0.0;
-                if (mode == 1 || mode == 2) {
-                    xi = (double)pI[x][u];
-                    if (mode == 2 && al != 0.0) rg.I[q] = pI[x][u];
-                    if (!(xi > 0.0)) bad = 1;
-                    else acc[mode == 1 ? 0 : 2] += xi * lg[x][u];
-                    gv += rg.lam * (lg[x][u] + 1.0);
-                    if (rg.mask && !rg.mask[q]) gv = 0.0;
-                }
-                const R gr = (R)gv;
-                rg.out[q] = gr;
-                if (mode == 2) {
-                    const bool act = (xi <= rg.Mb * (1.0 + BOUND_TOL)) && ((double)gr > 0.0);
-                    const double gnew = act ? 0.0 : (double)gr;
-                    const double gold = (double)pg[x][u];
-                    rg.gt[q] = (R)gnew;
-                    acc[0] += gnew * gnew;
-                    acc[1] += gnew * gold;
-                }
+        for (int u = 0; u < 2; ++u) {
+            const size_t q = ((size_t)c * n + i + u) * n + j;
+            const double G = u ? v[x].y * (d1 * dj) : v[x].x * (d0 * dj);
+            double gv = mode == 3 ? G * scale : (double)pA[x][u] * G;
+            double xi = 0.0;
+            if (mode == 1 || mode == 2) {
+                xi = (double)pI[x][u];
+                if (mode == 2 && al != 0.0) rg.I[q] = pI[x][u];
+                if (!(xi > 0.0)) bad = 1;
+                else acc[mode == 1 ? 0 : 2] += xi * lg[x][u];
+                gv += rg.lam * (lg[x][u] + 1.0);
+                if (rg.mask && !rg.mask[q]) gv = 0.0;
+            }
+            const R gr = (R)gv;
+            rg.out[q] = gr;
+            if (mode == 2) {
+                const bool act = (xi <= rg.Mb * (1.0 + BOUND_TOL)) && ((double)gr > 0.0);
+                const double gnew = act ? 0.0 : (double)gr;
+                const double gold = (double)pg[x][u];
+                rg.gt[q] = (R)gnew;
+                acc[0] += gnew * gnew;
+                acc[1] += gnew * gold;
             }
         }
-        constexpr int NTH = NF * T;
-        const int rows = gridDim.x;
-        if (mode == 1 || mode == 2) {
-            if (bad) atomicOr(rg.flag, 1);
-            block_sum<3, NTH>(acc);
-            if (threadIdx.x == 0) {
-#pragma unroll
-                for (int x = 0; x < 3; ++x) coh_store(rg.pp + ((size_t)c * rows + blockIdx.x) * NPART + x, acc[x]);
-            }
-        }
-        grad_tail<NTH, true>(mode, c, rows, rg.pp, rg.lam, rg.tail);
     }
+    constexpr int NTH = NF * T;
+    const int rows = gridDim.x;
+    if (mode == 1 || mode == 2) {
+        if (bad) atomicOr(rg.flag, 1);
+        block_sum<3, NTH>(acc);
+        if (threadIdx.x == 0) {
+#pragma unroll
+            for (int x = 0; x < 3; ++x) coh_store(rg.pp + ((size_t)c * rows + blockIdx.x) * NPART + x, acc[x]);
+        }
+    }
+    grad_tail<NTH, true>(mode, c, rows, rg.pp, rg.lam, rg.tail);
 }
 
 // dst[caller's order] = src[bin order], conjugated where negated (dir = 0);
@@ -1264,17 +1322,18 @@ hipError_t inv_lg(const uvmem_ctx *c, hipStream_t st) {
 template <int LG, typename R, typename S>
 hipError_t rows_inv_lg(const uvmem_ctx *c, const void *I, void *out, int mode, double *user, hipStream_t st) {
     constexpr int T = fft_threads(LG), RS = row_seqs(LG);
-    const dim3 gr(c->n_trrec, c->nchan), br(RS * T);
+    const dim3 br(RS * T);
     const C2<S> *Y = (const C2<S> *)c->d_trx;
     if (c->nimg == c->nchan) {
         const RowGrad<R> rg{(const R *)c->d_beam, (const R *)c->d_dir, (R *)const_cast<void *>(I), (R *)out,
                             (R *)c->d_gt, c->d_flag, tr_pp(c, 1), c->d_wscale, c->d_mask, c->M, c->Mb, c->lam, mode,
                             make_grad_tail(c, mode, user)};
-        hipLaunchKernelGGL((k_tr_rows_inv<LG, R, S, true>), gr, br, 0, st, Y, (double *)nullptr, rg, c->d_trtw,
-                           c->d_trdec, c->n, c->np, c->tr_h);
+        hipLaunchKernelGGL((k_tr_rows_inv<LG, R, S>), dim3(c->n_trrec, c->nchan), br, 0, st, Y, rg, c->d_trtw,
+                           c->d_trdec, c->n, c->tr_h);
     } else {
-        hipLaunchKernelGGL((k_tr_rows_inv<LG, R, S, false>), gr, br, 0, st, Y, (double *)c->d_gpart, RowGrad<R>{},
-                           c->d_trtw, c->d_trdec, c->n, c->np, c->tr_h);
+        hipLaunchKernelGGL((k_tr_rows_sum<LG, R, S>), dim3(c->n_trrec, c->n_trplane), br, 0, st, Y,
+                           (double *)c->d_gpart, (const R *)c->d_beam, c->nchan, mode, c->d_trtw, c->d_trdec, c->n,
+                           c->np, c->tr_h);
     }
     return hipGetLastError();
 }
