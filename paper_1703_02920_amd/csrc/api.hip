@@ -240,6 +240,7 @@ void choose_transform(uvmem_ctx *c) {
     c->tr_lg = lg;
     c->tr_w = c->prec == UVMEM_FP64 ? 17 : 9;
     c->tr_h = (c->tr_w - 1) / 2;
+    c->tr_s32 = p != 0;
     c->tr_f32 = p == 2;
     const int tb = c->tr_w - 1;   // nodes per bin side: 8 or 16
     c->tr_nbx = (1 << lg) / 2 / tb + 1;
@@ -747,7 +748,7 @@ hipError_t sort_bins(uvmem_ctx *c) {
     const size_t o_bin = put(first.data(), first.size() * sizeof(int2));
     ok(dalloc(c, &c->d_trtab, tab.size(), false));
     ok(dalloc(c, &c->d_trpart, (size_t)std::max(c->n_trgroup, c->n_trspread) * NPART, false));
-    ok(dalloc(c, (char **)&c->d_trtile, slot * ts * ts * (c->tr_f32 ? sizeof(float2) : sizeof(double2)), false));
+    ok(dalloc(c, (char **)&c->d_trtile, slot * ts * ts * (c->tr_s32 ? sizeof(float2) : sizeof(double2)), false));
     if (e == hipSuccess) {
         c->d_tritem = (TrItem *)(c->d_trtab + o_item);
         c->d_trspan = (int2 *)(c->d_trtab + o_span);
@@ -1182,7 +1183,7 @@ int finalize_impl(uvmem_ctx *c) {
         const size_t lx = L / 2 + 2 * c->tr_h + 1;
         ok(dalloc(c, &c->d_trperm, c->ztot, false));
         ok(dalloc(c, &c->d_trconst, trconst.size() * 8, false));
-        const size_t cs = c->tr_f32 ? sizeof(float2) : sizeof(double2);
+        const size_t cs = c->tr_s32 ? sizeof(float2) : sizeof(double2);
         ok(dalloc(c, (char **)&c->d_trx, C * lx * n * cs, false));
         ok(dalloc(c, (char **)&c->d_trg, C * c->tr_lgc * L * cs));
     }

@@ -263,7 +263,8 @@ struct uvmem_ctx {
     int *d_trgbase = nullptr, *d_trsbase = nullptr;
     double *d_trpart = nullptr;
     unsigned *d_trperm = nullptr;
-    bool tr_f32 = false;               // grids, windows and tiles in FP32 (split precisions), else FP64
+    bool tr_s32 = false;               // grids and tiles stored in FP32 (below FP64)
+    bool tr_f32 = false;               // windows and tile products in FP32 too (split precisions)
     double *d_trdec = nullptr;
     double2 *d_trtw = nullptr;
     void *d_trpoly = nullptr, *d_trx = nullptr, *d_trg = nullptr, *d_trtile = nullptr;

@@ -42,10 +42,11 @@ namespace {
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
-// Type S of the stored grids and tiles, of the windows and of the tile
-// products (the transforms compute in FP64 whatever it is): double, or float
-// for the split-precision contexts, whose contraction accumulates in FP32.
-// Matrix instructions 16 x 16 x 4: lane l supplies A[l%16][l/16] and
+// Two types follow the precision: S, in which grids, half spectra and tiles
+// are stored (float below FP64; the transforms compute in FP64 whatever it
+// is), and A, that of the windows and the tile products (float for the split
+// precisions only, whose contraction accumulates in FP32 too).  Matrix
+// instructions 16 x 16 x 4: lane l supplies A[l%16][l/16] and
 // B[l/16][l%16] and holds D[drow(l/16, r)][l%16] in register r.
 template <typename S> struct Tile;
 template <> struct Tile<double> {
@@ -468,15 +469,15 @@ struct DirTail {
 // (spans are cut to equal cost at finalize); an item's grid tile is held in
 // registers.  The visibilities of a span are consecutive, so the next batch's
 // coordinates are loaded while the current one computes.
-template <int W, typename S, int MODE>
+template <int W, typename S, typename A, int MODE>
 __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_interp(
     const int2 *__restrict__ spans, const TrItem *__restrict__ items, const double *__restrict__ a,
-    const double *__restrict__ b, const C2<S> *__restrict__ G, const S *__restrict__ poly, int L, int Lg,
+    const double *__restrict__ b, const C2<S> *__restrict__ G, const A *__restrict__ poly, int L, int Lg,
     long long ztot, double *__restrict__ out, const double *__restrict__ ref, const float *__restrict__ w,
     const unsigned *__restrict__ perm, double *__restrict__ part, const DirTail dt) {
     constexpr int H = (W - 1) / 2, TB = Win<W>::TB, TS = Win<W>::TS, NT = TS / 16, NS = TS / 4;
-    typedef typename Tile<S>::acc acc_t;
-    __shared__ __attribute__((aligned(16))) WinBuf<W, S, true> s[TR_WAVES];
+    typedef typename Tile<A>::acc acc_t;
+    __shared__ __attribute__((aligned(16))) WinBuf<W, A, true> s[TR_WAVES];
     // step x of a contraction takes the columns 16 (x / 4) + 4 g + x % 4, and
     // the tile's rows are permuted so that register r of lane group g holds
     // row 4 g + r: a lane then reads its windows four at a time
@@ -493,16 +494,16 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_interp(
     }
     for (int item = span.x; item < span.y; ++item) {
         const TrItem it = items[item];
-        S gr[NT][NS], gi[NT][NS];
-        const int qr = sizeof(S) == 8 ? 4 * (q & 3) + (q >> 2) : q;
+        A gr[NT][NS], gi[NT][NS];
+        const int qr = sizeof(A) == 8 ? 4 * (q & 3) + (q >> 2) : q;
 #pragma unroll
         for (int x = 0; x < NS; ++x) {
             const C2<S> *col = G + ((size_t)it.chan * Lg + it.bx * TB + ccol(x, g)) * L;
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
                 const C2<S> v = col[(it.by * TB - H + 16 * t + qr) & (L - 1)];
-                gr[t][x] = v.x;
-                gi[t][x] = v.y;
+                gr[t][x] = (A)v.x;
+                gi[t][x] = (A)v.y;
             }
         }
         const int n0 = TB * (lane < 32 ? it.bx : it.by);
@@ -526,17 +527,17 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_interp(
                 rv = ref[2 * kc + comp];
                 wv = w[kc];
             }
-            windows32<W, S, true>(s[wave], X, k0 + (lane & 31) < it.kend, L, n0, poly);
+            windows32<W, A, true>(s[wave], X, k0 + (lane & 31) < it.kend, L, n0, poly);
             wave_sync();
-            S half[2] = {S(0), S(0)};
+            A half[2] = {A(0), A(0)};
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 if (k0 + 16 * h >= it.kend) break;
-                typedef S S4 __attribute__((ext_vector_type(4)));
-                const S *kx = &s[wave].v[0][16 * h + q][4 * g], *ky = &s[wave].v[1][16 * h + q][4 * g];
+                typedef A S4 __attribute__((ext_vector_type(4)));
+                const A *kx = &s[wave].v[0][16 * h + q][4 * g], *ky = &s[wave].v[1][16 * h + q][4 * g];
                 acc_t ar[NT], ai[NT];
 #pragma unroll
-                for (int t = 0; t < NT; ++t) ar[t] = ai[t] = acc_t{S(0), S(0), S(0), S(0)};
+                for (int t = 0; t < NT; ++t) ar[t] = ai[t] = acc_t{A(0), A(0), A(0), A(0)};
 #pragma unroll
                 for (int cb = 0; cb < NS / 4; ++cb) {
                     const S4 wx = *reinterpret_cast<const S4 *>(kx + 16 * cb);
@@ -544,11 +545,11 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_interp(
                     for (int x = 0; x < 4; ++x)
 #pragma unroll
                         for (int t = 0; t < NT; ++t) {
-                            ar[t] = Tile<S>::mma(gr[t][4 * cb + x], wx[x], ar[t]);
-                            ai[t] = Tile<S>::mma(gi[t][4 * cb + x], wx[x], ai[t]);
+                            ar[t] = Tile<A>::mma(gr[t][4 * cb + x], wx[x], ar[t]);
+                            ai[t] = Tile<A>::mma(gi[t][4 * cb + x], wx[x], ai[t]);
                         }
                 }
-                S vr = S(0), vi = S(0);
+                A vr = A(0), vi = A(0);
 #pragma unroll
                 for (int t = 0; t < NT; ++t) {
                     const S4 wy = *reinterpret_cast<const S4 *>(ky + 16 * t);
@@ -625,7 +626,7 @@ struct StepArgs {
     const double *ls;
     double *part;
 };
-template <int W, typename S, bool STEP>
+template <int W, typename S, typename A, bool STEP>
 __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restrict__ waves,
                                                             const TrItem *__restrict__ items,
                                                             const double *__restrict__ a,
@@ -634,12 +635,12 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
                                                             const float *__restrict__ w,
                                                             const unsigned *__restrict__ perm,
                                                             C2<S> *__restrict__ tiles,
-                                                            const S *__restrict__ poly, int L,
+                                                            const A *__restrict__ poly, int L,
                                                             long long ztot, const StepArgs sa) {
     constexpr int TB = Win<W>::TB, TS = Win<W>::TS, NT = TS / 16;
-    typedef typename Tile<S>::acc acc_t;
-    __shared__ __attribute__((aligned(16))) WinBuf<W, S, false> s[TR_WAVES];
-    __shared__ __attribute__((aligned(16))) S sc[TR_WAVES][2][32];
+    typedef typename Tile<A>::acc acc_t;
+    __shared__ __attribute__((aligned(16))) WinBuf<W, A, false> s[TR_WAVES];
+    __shared__ __attribute__((aligned(16))) A sc[TR_WAVES][2][32];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int q = lane & 15, g = lane >> 4;
     const int4 span = waves[blockIdx.x * TR_WAVES + wave];   // first item, end, live waves of a shared bin
@@ -664,7 +665,7 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
             if (pk & 1u) cn.y = -cn.y;
         }
     };
-    auto at = [&](int x, int y, int r) { return (16 * x + Tile<S>::drow(g, r)) * TS + 16 * y + q; };
+    auto at = [&](int x, int y, int r) { return (16 * x + Tile<A>::drow(g, r)) * TS + 16 * y + q; };
     if (span.x < span.y) fetch(items[span.x].kbeg);
     for (int item = span.x; item < span.y; ++item) {
         const TrItem it = items[item];
@@ -672,7 +673,7 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
 #pragma unroll
         for (int x = 0; x < NT; ++x)
 #pragma unroll
-            for (int y = 0; y < NT; ++y) ar[x][y] = ai[x][y] = acc_t{S(0), S(0), S(0), S(0)};
+            for (int y = 0; y < NT; ++y) ar[x][y] = ai[x][y] = acc_t{A(0), A(0), A(0), A(0)};
         for (long long k0 = it.kbeg; k0 < it.kend; k0 += 32) {
             const bool ok = k0 + (lane & 31) < it.kend;
             if (lane < 32) {
@@ -685,10 +686,10 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
                         chi += (double)wn * (cv.x * cv.x + cv.y * cv.y);
                     }
                 }
-                sc[wave][0][lane] = ok ? (S)(cv.x * (double)wn) : S(0);
-                sc[wave][1][lane] = ok ? (S)(cv.y * (double)wn) : S(0);
+                sc[wave][0][lane] = ok ? (A)(cv.x * (double)wn) : A(0);
+                sc[wave][1][lane] = ok ? (A)(cv.y * (double)wn) : A(0);
             }
-            windows32<W, S, false>(s[wave], xn * (double)L, ok, L, n0, poly);
+            windows32<W, A, false>(s[wave], xn * (double)L, ok, L, n0, poly);
             fetch(k0 + 32 < it.kend ? k0 + 32 : it.kend);
             wave_sync();
             // halves of 16 visibilities (zero coefficients past the end), the
@@ -696,7 +697,7 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 if (k0 + 16 * h >= it.kend) break;
-                typedef S S4 __attribute__((ext_vector_type(4)));
+                typedef A S4 __attribute__((ext_vector_type(4)));
                 const int v0 = 16 * h + 4 * g;
                 const S4 cr = *reinterpret_cast<const S4 *>(&sc[wave][0][v0]);
                 const S4 ci = *reinterpret_cast<const S4 *>(&sc[wave][1][v0]);
@@ -710,11 +711,11 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
                 for (int m = 0; m < 4; ++m)
 #pragma unroll
                     for (int x = 0; x < NT; ++x) {
-                        const S pr = kx[x][m] * cr[m], pi = kx[x][m] * ci[m];
+                        const A pr = kx[x][m] * cr[m], pi = kx[x][m] * ci[m];
 #pragma unroll
                         for (int y = 0; y < NT; ++y) {
-                            ar[x][y] = Tile<S>::mma(pr, ky[y][m], ar[x][y]);
-                            ai[x][y] = Tile<S>::mma(pi, ky[y][m], ai[x][y]);
+                            ar[x][y] = Tile<A>::mma(pr, ky[y][m], ar[x][y]);
+                            ai[x][y] = Tile<A>::mma(pi, ky[y][m], ai[x][y]);
                         }
                     }
             }
@@ -727,7 +728,7 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
 #pragma unroll
                 for (int y = 0; y < NT; ++y)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) o[at(x, y, r)] = C2<S>{ar[x][y][r], ai[x][y][r]};
+                    for (int r = 0; r < 4; ++r) o[at(x, y, r)] = C2<S>{(S)ar[x][y][r], (S)ai[x][y][r]};
         }
     }
     if constexpr (STEP) {
@@ -740,8 +741,8 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
     }
     if (span.z == 0) return;   // uniform over the workgroup
     // waves 1.. leave their sums in LDS, wave 0 adds them in order
-    C2<S> *buf = reinterpret_cast<C2<S> *>(&s[0]);
-    static_assert((TR_WAVES - 1) * TS * TS * sizeof(C2<S>) <= sizeof(s), "wave sums fit the window buffers");
+    C2<A> *buf = reinterpret_cast<C2<A> *>(&s[0]);
+    static_assert((TR_WAVES - 1) * TS * TS * sizeof(C2<A>) <= sizeof(s), "wave sums fit the window buffers");
     __syncthreads();
     if (wave > 0 && wave < span.z) {
 #pragma unroll
@@ -750,7 +751,7 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
             for (int y = 0; y < NT; ++y)
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    buf[(wave - 1) * TS * TS + at(x, y, r)] = C2<S>{ar[x][y][r], ai[x][y][r]};
+                    buf[(wave - 1) * TS * TS + at(x, y, r)] = C2<A>{ar[x][y][r], ai[x][y][r]};
     }
     __syncthreads();
     if (wave > 0) return;
@@ -761,13 +762,13 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
         for (int y = 0; y < NT; ++y)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                C2<S> t{ar[x][y][r], ai[x][y][r]};
+                C2<A> t{ar[x][y][r], ai[x][y][r]};
                 for (int v = 1; v < span.z; ++v) {
-                    const C2<S> w = buf[(v - 1) * TS * TS + at(x, y, r)];
+                    const C2<A> w = buf[(v - 1) * TS * TS + at(x, y, r)];
                     t.x += w.x;
                     t.y += w.y;
                 }
-                o[at(x, y, r)] = t;
+                o[at(x, y, r)] = C2<S>{(S)t.x, (S)t.y};
             }
 }
 
@@ -898,8 +899,8 @@ template <int LG, typename S> struct RowsInv {
     }
     // Transforms them; register x then holds the two rows' sums at position
     // fft_out(t, x).
-    __device__ __forceinline__ void run(double2 (*s)[NSH], double2 (&v)[8], const double2 *tw, int H) {
-        const int f = threadIdx.x / T, t = threadIdx.x % T;
+    __device__ __forceinline__ void run(double2 (*s)[NSH], double2 (&v)[8], const double2 *tw, int H, int t) {
+        const int f = threadIdx.x / T;
         const int Lx = L / 2 + 2 * H + 1;
 #pragma unroll
         for (int m = 0; m < NE; ++m) {
@@ -934,7 +935,8 @@ template <int LG, typename S> struct RowsInv {
 // Several channels of one image: workgroup (x, y) sums A_c x (its rows) over
 // the y-th share of the channels (no A for the dirty image, mode 3) into plane
 // y, which the gradient kernel then sums (a plane per channel cost 56 us here
-// and 51 us there on 23 channels of 512^2; shares of three channels 58 and 28).
+// and 51 us there on 23 channels of 512^2; shares of three channels 49 and 28
+// with FP32 half spectra).
 template <int LG, typename R, typename S>
 __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_sum(
     const C2<S> *__restrict__ Y, double *__restrict__ plane, const R *__restrict__ beam, int nchan, int mode,
@@ -950,9 +952,10 @@ __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_sum(
     double acc[8][2];
 #pragma unroll
     for (int x = 0; x < 8; ++x) acc[x][0] = acc[x][1] = 0.0;
-    RI ri;
-    ri.load(Y, c0, rows0, n, H);
+#pragma unroll 1
     for (int c = c0; c < c1; ++c) {
+        RI ri;
+        ri.load(Y, c, rows0, n, H);
         R A[8][2];
 #pragma unroll
         for (int x = 0; x < 8; ++x) {
@@ -963,8 +966,7 @@ __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_sum(
         }
         double2 v[8];
         __syncthreads();   // the last channel's exchange has been read
-        ri.run(s, v, tw, H);
-        if (c + 1 < c1) ri.load(Y, c + 1, rows0, n, H);
+        ri.run(s, v, tw, H, t);
 #pragma unroll
         for (int x = 0; x < 8; ++x) {
             if (!fft_live<LG>(x)) continue;
@@ -1037,7 +1039,7 @@ __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_inv(
         }
     }
     double2 v[8];
-    ri.run(s, v, tw, H);
+    ri.run(s, v, tw, H, t);
     const double d0 = live ? dec[i] : 0.0, d1 = live ? dec[i + 1] : 0.0;
     const int mode = rg.mode;
     double acc[3] = {0.0, 0.0, 0.0};
@@ -1353,65 +1355,66 @@ hipError_t with_lg(const uvmem_ctx *c, F f) {
     return hipErrorInvalidValue;
 }
 
-template <int W, typename S, int MODE>
+template <int W, typename S, typename A, int MODE>
 void interp_mode(const uvmem_ctx *c, double2 *out, const double2 *ref, hipStream_t st) {
-    hipLaunchKernelGGL((k_tr_interp<W, S, MODE>), dim3(c->n_trgroup), dim3(64 * TR_WAVES), 0, st, c->d_trspan,
-                       c->d_tritem, c->d_a, c->d_b, (const C2<S> *)c->d_trg, (const S *)c->d_trpoly, 1 << c->tr_lg,
+    hipLaunchKernelGGL((k_tr_interp<W, S, A, MODE>), dim3(c->n_trgroup), dim3(64 * TR_WAVES), 0, st, c->d_trspan,
+                       c->d_tritem, c->d_a, c->d_b, (const C2<S> *)c->d_trg, (const A *)c->d_trpoly, 1 << c->tr_lg,
                        c->tr_lgc, (long long)c->ztot, (double *)out, (const double *)ref, c->d_w, c->d_trperm,
                        c->d_trpart,
                        DirTail{c->d_chan_img, c->d_trgbase, c->d_ctr + (size_t)CTR_VIS * c->nimg, tr_pp(c, 1),
                                c->n_trrec, c->d_chan, c->d_ls, c->lam});
 }
-template <int W, typename S>
+template <int W, typename S, typename A>
 hipError_t interp_w(const uvmem_ctx *c, int what, double2 *out, hipStream_t st) {
-    if (what == 0) interp_mode<W, S, TV_OUT>(c, out, nullptr, st);
-    else if (what == 1) interp_mode<W, S, TV_RES>(c, c->d_R, c->d_vo, st);
-    else interp_mode<W, S, TV_DIR>(c, c->d_Vd, c->d_R, st);
+    if (what == 0) interp_mode<W, S, A, TV_OUT>(c, out, nullptr, st);
+    else if (what == 1) interp_mode<W, S, A, TV_RES>(c, c->d_R, c->d_vo, st);
+    else interp_mode<W, S, A, TV_DIR>(c, c->d_Vd, c->d_R, st);
     return hipGetLastError();
 }
 
-template <int W, typename S, bool STEP>
+template <int W, typename S, typename A, bool STEP>
 void spread_w(const uvmem_ctx *c, const double2 *coef, const float *w, const unsigned *perm, hipStream_t st) {
-    hipLaunchKernelGGL((k_tr_spread<W, S, STEP>), dim3(c->n_trspread), dim3(64 * TR_WAVES), 0, st, c->d_trspread,
-                       c->d_tritem, c->d_a, c->d_b, coef, w, perm, (C2<S> *)c->d_trtile, (const S *)c->d_trpoly,
+    hipLaunchKernelGGL((k_tr_spread<W, S, A, STEP>), dim3(c->n_trspread), dim3(64 * TR_WAVES), 0, st, c->d_trspread,
+                       c->d_tritem, c->d_a, c->d_b, coef, w, perm, (C2<S> *)c->d_trtile, (const A *)c->d_trpoly,
                        1 << c->tr_lg, (long long)c->ztot, StepArgs{c->d_R, c->d_Vd, c->d_ls, c->d_trpart});
 }
 
-// f(image type, S, width) of the context's precision.
+// f(image type, S, A, width) of the context's precision.
 template <int W> using width = std::integral_constant<int, W>;
 template <typename F>
 hipError_t with_prec(const uvmem_ctx *c, F f) {
-    if (c->prec == UVMEM_FP64) return f(double(), double(), width<17>());
-    if (c->prec == UVMEM_FP32) return f(float(), double(), width<9>());
-    return f(float(), float(), width<9>());
+    if (c->prec == UVMEM_FP64) return f(double(), double(), double(), width<17>());
+    if (c->prec == UVMEM_FP32) return f(float(), float(), double(), width<9>());
+    return f(float(), float(), float(), width<9>());
 }
 
 }  // namespace
 
 hipError_t launch_tr_forward(const uvmem_ctx *c, const void *I, int what, double2 *out, hipStream_t st) {
-    return with_prec(c, [&](auto r, auto s, auto w) {
+    return with_prec(c, [&](auto r, auto s, auto a, auto w) {
         typedef decltype(r) R;
         typedef decltype(s) S;
         const hipError_t e =
             with_lg(c, [&](auto lg) { return fwd_lg<decltype(lg)::value, R, S>(c, I, what, st); });
-        return e != hipSuccess ? e : interp_w<decltype(w)::value, S>(c, what, out, st);
+        return e != hipSuccess ? e : interp_w<decltype(w)::value, S, decltype(a)>(c, what, out, st);
     });
 }
 
 hipError_t launch_tr_adjoint(const uvmem_ctx *c, const double2 *coef, const float *w, const unsigned *perm,
                              int step, hipStream_t st) {
-    return with_prec(c, [&](auto, auto s, auto ww) {
+    return with_prec(c, [&](auto, auto s, auto a, auto ww) {
         typedef decltype(s) S;
+        typedef decltype(a) A;
         constexpr int W = decltype(ww)::value;
-        if (step) spread_w<W, S, true>(c, coef, w, perm, st);
-        else spread_w<W, S, false>(c, coef, w, perm, st);
+        if (step) spread_w<W, S, A, true>(c, coef, w, perm, st);
+        else spread_w<W, S, A, false>(c, coef, w, perm, st);
         return with_lg(c, [&](auto lg) { return inv_lg<decltype(lg)::value, W, S>(c, st); });
     });
 }
 
 hipError_t launch_tr_rows_inv(const uvmem_ctx *c, const void *I, void *out, int mode, double *user_scal,
                               hipStream_t st) {
-    return with_prec(c, [&](auto r, auto s, auto) {
+    return with_prec(c, [&](auto r, auto s, auto, auto) {
         return with_lg(c, [&](auto lg) {
             return rows_inv_lg<decltype(lg)::value, decltype(r), decltype(s)>(c, I, out, mode, user_scal, st);
         });
