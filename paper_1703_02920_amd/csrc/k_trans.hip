@@ -229,6 +229,19 @@ __device__ __forceinline__ int pix_of(int p, int L, int n) {
 constexpr int row_seqs(int lg) { return tr_row_seqs(lg); }
 constexpr int col_seqs(int lg) { return lg <= 6 ? 8 : lg <= 7 ? 4 : lg <= 8 ? 2 : 1; }
 
+// Row block of a workgroup.  The row passes touch 2 NF rows of every column,
+// less than a 128-byte line of X or Y: the blocks of a line go to one XCD
+// (workgroups are dealt to the eight in turn), next to each other in time, so
+// that its L2 holds the line for all of them.  1024^2,
+// FP32: forward rows 11.8 -> 9.9 us, inverse rows 42.3 -> 39.8; 23 channels of
+// 512^2: 32.6 -> 29.5 and 49.3 -> 43.0.
+template <typename S, int NF> __device__ __forceinline__ int row_block() {
+    constexpr int G = NF >= 8 ? 1 : 64 / ((int)sizeof(C2<S>) * NF) > 1 ? 64 / ((int)sizeof(C2<S>) * NF) : 1;
+    const int b = blockIdx.x, k = b / 8;
+    if (G == 1 || b >= (int)gridDim.x / (8 * G) * (8 * G)) return b;
+    return (k / G * 8 + b % 8) * G + k % G;
+}
+
 // DIR: the image is a CG direction, and the row pass also sums the entropy
 // parts of phi', phi'' at alpha_max (partials [0], [1]; zero without a finite
 // alpha_max).  Done by the first channel of each image; one record per
@@ -253,7 +266,8 @@ __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_fwd(
     constexpr int L = 1 << LG, T = fft_threads(LG), NF = row_seqs(LG);
     __shared__ double2 s[NF][fpad(L)];
     const int f = threadIdx.x / T, t = threadIdx.x % T;
-    const int c = blockIdx.y, i0 = (blockIdx.x * NF + f) * 2;
+    const int rows0 = row_block<S, NF>() * NF * 2;
+    const int c = blockIdx.y, i0 = rows0 + 2 * f;
     const int Lx = L / 2 + 2 * H + 1;
     const int im = ra.chan_img[c];
     double2 v[8];
@@ -309,7 +323,6 @@ __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_fwd(
 #pragma unroll
     for (int x = 0; x < 8; ++x) s[f][fpad(fft_out<LG>(t, x))] = v[x];
     __syncthreads();
-    const int rows0 = blockIdx.x * NF * 2;
     for (int e = threadIdx.x; e < Lx * NF; e += NF * T) {
         const int qc = e / NF, g = e % NF;
         const int i = rows0 + 2 * g;
@@ -935,8 +948,7 @@ template <int LG, typename S> struct RowsInv {
 // Several channels of one image: workgroup (x, y) sums A_c x (its rows) over
 // the y-th share of the channels (no A for the dirty image, mode 3) into plane
 // y, which the gradient kernel then sums (a plane per channel cost 56 us here
-// and 51 us there on 23 channels of 512^2; shares of three channels 49 and 28
-// with FP32 half spectra).
+// and 51 us there on 23 channels of 512^2; shares of three channels 43 and 28).
 template <int LG, typename R, typename S>
 __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_sum(
     const C2<S> *__restrict__ Y, double *__restrict__ plane, const R *__restrict__ beam, int nchan, int mode,
@@ -945,7 +957,7 @@ __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_sum(
     constexpr int L = RI::L, T = RI::T, NF = RI::NF;
     __shared__ double2 s[NF][RI::NSH];
     const int f = threadIdx.x / T, t = threadIdx.x % T;
-    const int rows0 = blockIdx.x * NF * 2, i = rows0 + 2 * f;
+    const int rows0 = row_block<S, NF>() * NF * 2, i = rows0 + 2 * f;
     const bool live = i < n;
     const int c0 = (int)((long long)nchan * blockIdx.y / gridDim.y);
     const int c1 = (int)((long long)nchan * (blockIdx.y + 1) / gridDim.y);
@@ -996,7 +1008,7 @@ __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_inv(
     constexpr int L = RI::L, T = RI::T, NF = RI::NF;
     __shared__ double2 s[NF][RI::NSH];
     const int f = threadIdx.x / T, t = threadIdx.x % T;
-    const int c = blockIdx.y, rows0 = blockIdx.x * NF * 2;
+    const int c = blockIdx.y, rows0 = row_block<S, NF>() * NF * 2;
     const int i = rows0 + 2 * f;
     const bool live = i < n;
     RI ri;
