@@ -1199,7 +1199,7 @@ int finalize_impl(uvmem_ctx *c) {
     ok(dalloc(c, &c->d_scal, (size_t)IMG * UVMEM_NSCAL));
     ok(dalloc(c, &c->d_chan, (size_t)IMG * CH_N));
     ok(dalloc(c, &c->d_ls, (size_t)IMG * LSS_N));
-    ok(dalloc(c, &c->d_ctr, (size_t)CTR_N * IMG));
+    ok(dalloc(c, &c->d_ctr, (size_t)CTR_N * IMG * CTR_STRIDE));
     ok(dalloc(c, &c->d_ppart, (size_t)2 * IMG * std::max(c->n_pb, c->n_trrec) * NPART));
     ok(dalloc(c, &c->d_vispart, (size_t)std::max(c->n_visit, 1) * NPART));
     ok(dalloc(c, &c->d_flag, 4));

@@ -129,7 +129,10 @@ enum {
 };
 
 // Arrival counters of the per-image reductions finished by the last
-// workgroup to arrive ([CTR_N][nimg] unsigned, zero between launches).
+// workgroup to arrive ([CTR_N][nimg][CTR_STRIDE] unsigned, zero between
+// launches): a main counter and CTR_SUB sub-counters, each in a 128-byte line
+// of its own (see arrive_last).
+constexpr int CTR_SUB = 16, CTR_LINE = 32, CTR_STRIDE = (1 + CTR_SUB) * CTR_LINE;
 enum {
     CTR_DIR = 0,     // k_cg_dir: gt . d, alpha_max and the entropy parts of phi', phi''
     CTR_VIS,         // k_cg_vis: a, b, phi'(alpha_max); line-search start

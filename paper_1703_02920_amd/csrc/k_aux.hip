@@ -334,7 +334,7 @@ __global__ __launch_bounds__(NTHR) void k_grad(const PT *__restrict__ gpart, con
             for (int x = 0; x < NA; ++x) coh_store(ppart + ((size_t)c * n_pb + pb) * NPART + x, acc[x]);
         }
     }
-    grad_tail<NTHR, TR>(mode, c, n_pb, ppart, lam, tail);
+    grad_tail<NTHR, TR>(mode, c, pb, n_pb, ppart, lam, tail);
 }
 
 // ---------------------------------------------------------------- CG
@@ -362,7 +362,7 @@ __global__ __launch_bounds__(NTHR) void k_cg_init(const R *__restrict__ I, const
     }
     block_sum<1>(acc);
     if (threadIdx.x == 0) coh_store(ppart + ((size_t)c * n_pb + pb) * NPART + 0, acc[0]);
-    if (!arrive_last(ctr + c, (unsigned)n_pb)) return;
+    if (!arrive_last(ctr, c, pb, n_pb)) return;
     double gg[1];
     sum_partials<1>(ppart + (size_t)c * n_pb * NPART, n_pb, 0, gg);
     if (threadIdx.x == 0) {
@@ -447,7 +447,7 @@ __global__ __launch_bounds__(NTHR) void k_cg_dir(const R *__restrict__ I, const 
         coh_store(pp + 5, am_d);
         coh_store(pp + 6, am_s);
     }
-    if (!arrive_last(ctr + c, (unsigned)n_pb)) return;
+    if (!arrive_last(ctr, c, pb, n_pb)) return;
     double t[5];
     double amm[2];
     sum_min_partials<5, 2>(ppart + (size_t)c * n_pb * NPART, n_pb, t, amm);
@@ -549,7 +549,7 @@ __global__ __launch_bounds__(NTHR) void k_cg_vis(const VisItem *__restrict__ ite
                                                  double *__restrict__ ppart, int n, int n_pb, int pb_len, double M,
                                                  double lam, const double *__restrict__ chan,
                                                  double *__restrict__ ls, unsigned *__restrict__ ctr) {
-    int img;
+    int img, rank = -1;   // the workgroup's pixel block, if it has one
     if ((int)blockIdx.x < n_visit) {
         const VisItem it = items[blockIdx.x];
         img = chan_img[it.chan];
@@ -557,7 +557,7 @@ __global__ __launch_bounds__(NTHR) void k_cg_vis(const VisItem *__restrict__ ite
     } else {
         const int blk = (int)blockIdx.x - n_visit;
         img = blk / n_pb;
-        const int pb = blk % n_pb;
+        const int pb = rank = blk % n_pb;
         const long long npix = (long long)n * n;
         // the thread's first pixel, loaded ahead of the image's scalars
         // (pixel 0 stands in past the end)
@@ -587,7 +587,7 @@ __global__ __launch_bounds__(NTHR) void k_cg_vis(const VisItem *__restrict__ ite
         }
     }
     const int v0 = ivis_base[img], v1 = ivis_base[img + 1];
-    if (!arrive_last(ctr + img, (unsigned)(v1 - v0 + n_pb))) return;
+    if (!arrive_last(ctr, img, rank < 0 ? (int)blockIdx.x - v0 : v1 - v0 + rank, v1 - v0 + n_pb)) return;
     double ab[2], fh[2];
     sum_partials2<2, 2>(vispart + (size_t)v0 * NPART, v1 - v0, 0, ab, ppart + (size_t)img * n_pb * NPART, n_pb, 0,
                         fh);
@@ -645,7 +645,7 @@ __global__ __launch_bounds__(NTHR) void k_ls_step(const R *__restrict__ I, const
 #pragma unroll
         for (int m = 0; m < 2 * LS_K; ++m) coh_store(ppart + ((size_t)c * n_pb + pb) * NPART + m, acc[m]);
     }
-    if (!arrive_last(ctr + c, (unsigned)n_pb)) return;
+    if (!arrive_last(ctr, c, pb, n_pb)) return;
     double f[LS_K], h[LS_K];
     ls_eval(st, ppart + (size_t)c * n_pb * NPART, n_pb, lam, f, h);
     if (threadIdx.x == 0) {
@@ -702,7 +702,7 @@ __global__ __launch_bounds__(NTHR) void k_cg_update(R *__restrict__ I, const R *
         if (threadIdx.x == 0) coh_store(pp_out + ((size_t)c * n_pb + pb) * NPART + 0, acc[0]);
     }
     const int v0 = ivis_base[c], v1 = ivis_base[c + 1];
-    if (!arrive_last(ctr + c, (unsigned)(n_pb + v1 - v0))) return;
+    if (!arrive_last(ctr, c, visw ? n_pb + vi - v0 : pb, n_pb + v1 - v0)) return;
     double x2[1], S[1];
     sum_partials2<1, 1>(vispart + (size_t)v0 * NPART, v1 - v0, 0, x2, pp_out + (size_t)c * n_pb * NPART, n_pb, 0,
                         S);
@@ -747,7 +747,7 @@ inline int pix_grid(const uvmem_ctx *c) { return c->nimg * c->n_pb; }
 inline double *pp(const uvmem_ctx *c, int buf) {
     return c->d_ppart + (size_t)buf * c->nimg * std::max(c->n_pb, c->n_trrec) * NPART;
 }
-inline unsigned *ctr(const uvmem_ctx *c, int site) { return c->d_ctr + (size_t)site * c->nimg; }
+inline unsigned *ctr(const uvmem_ctx *c, int site) { return c->d_ctr + (size_t)site * c->nimg * CTR_STRIDE; }
 // The fp16 split adjoint scales its coefficients by the channel's max |w R|,
 // which the visibility pass leaves in slot 2 of its partial records.
 inline int adj_scaled(const uvmem_ctx *c) { return c->prec == UVMEM_FP16X3 && !c->tr_lg ? 1 : 0; }

@@ -613,7 +613,7 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_interp(
     if constexpr (MODE == TV_DIR) {
         const int im = dt.chan_img[items[spans[blockIdx.x * TR_WAVES].x].chan];
         const int v0 = dt.gbase[im], v1 = dt.gbase[im + 1];
-        if (!arrive_last(dt.ctr + im, (unsigned)(v1 - v0))) return;
+        if (!arrive_last(dt.ctr, im, (int)blockIdx.x - v0, v1 - v0)) return;
         double ab2[2], fh[2];
         sum_partials2<2, 2>(part + (size_t)v0 * NPART, v1 - v0, 0, ab2, dt.pp + (size_t)im * dt.n_rec * NPART,
                             dt.n_rec, 0, fh);
@@ -1098,7 +1098,7 @@ __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_inv(
             for (int x = 0; x < 3; ++x) coh_store(rg.pp + ((size_t)c * rows + blockIdx.x) * NPART + x, acc[x]);
         }
     }
-    grad_tail<NTH, true>(mode, c, rows, rg.pp, rg.lam, rg.tail);
+    grad_tail<NTH, true>(mode, c, blockIdx.x, rows, rg.pp, rg.lam, rg.tail);
 }
 
 // dst[caller's order] = src[bin order], conjugated where negated (dir = 0);
@@ -1373,7 +1373,7 @@ void interp_mode(const uvmem_ctx *c, double2 *out, const double2 *ref, hipStream
                        c->d_tritem, c->d_a, c->d_b, (const C2<S> *)c->d_trg, (const A *)c->d_trpoly, 1 << c->tr_lg,
                        c->tr_lgc, (long long)c->ztot, (double *)out, (const double *)ref, c->d_w, c->d_trperm,
                        c->d_trpart,
-                       DirTail{c->d_chan_img, c->d_trgbase, c->d_ctr + (size_t)CTR_VIS * c->nimg, tr_pp(c, 1),
+                       DirTail{c->d_chan_img, c->d_trgbase, c->d_ctr + (size_t)CTR_VIS * c->nimg * CTR_STRIDE, tr_pp(c, 1),
                                c->n_trrec, c->d_chan, c->d_ls, c->lam});
 }
 template <int W, typename S, typename A>

@@ -182,3 +182,20 @@ def test_direct_short_last_round(prec):
     ref = prob.oracle_forward(0, I.cpu().numpy()[0].astype(np.float64))
     tail = slice(nfull * tv, nvis)
     assert rel(V, ref) < TOL[prec] and rel(V[tail], ref[tail]) < TOL[prec]
+
+
+@pytest.mark.parametrize("path,n", [("direct", 180), ("direct", 182), ("transform", 182), ("transform", 530)])
+def test_every_partial_is_counted(path, n):
+    """Per-image reductions on either side of the number of workgroups from
+    which they arrive on several counters (127 and 130 pixel blocks; 133 row
+    blocks): the scalars of a CG step are those of its image.  Bar: the
+    residuals were carried over the steps, FP64 rounding of two of them."""
+    prob = Problem.random(n, [300, 200], seed=21)
+    ctx = _context(prob, "fp64", path)
+    J = ctx.image()
+    ctx.cg_init(J, init_to_floor=True)
+    hist = ctx.cg_run(J, 2, graph=False).clone()
+    scal, _ = ctx.phi_and_grad(J)
+    got, want = hist[-1].cpu().numpy()[:, :3], scal.cpu().numpy()[:, :3]
+    flush(f"arrivals {path} n={n}: {rel(got, want):.2e}")
+    assert rel(got, want) < 1e-10
