@@ -371,6 +371,13 @@ template <> struct Win<17> {
     static constexpr int TB = 16, TS = 32, NE = TR_NE17;
 };
 
+// Index of the wave in its workgroup; SC: uniform to the compiler, so that
+// spans, items and loop bounds are scalar.
+template <bool SC> __device__ __forceinline__ int wave_index() {
+    const int wave = threadIdx.x >> 6;
+    return SC ? __builtin_amdgcn_readfirstlane(wave) : wave;
+}
+
 // The per-wave LDS exchange: other lanes' stores are visible after it.
 __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -416,6 +423,13 @@ __device__ __forceinline__ void windows32(WinBuf<W, S, VIS> &s, double X, bool o
     const S z = (S)(2.0 * (X - nd)), z2 = z * z;
     const int off = ok ? (((int)nd & (L - 1)) - n0) : 0;
     wave_sync();
+    // 140 FP64 coefficients are more than the scalar registers hold: they are
+    // read again for every batch (the compiler is kept from moving them out of
+    // the batch loop, where it spilled them to vector lanes, 240 instructions
+    // a batch to read back; 256^2 FP64 x 99,840: spread 24.8 -> 22.9 us)
+    int at0 = 0;
+    if constexpr (W == 17) asm volatile("" : "+s"(at0));
+    poly += at0;
     S *row = &s.at(axis, vv, off);
     constexpr int ST = VIS ? 1 : WinBuf<W, S, VIS>::LEN;   // from node to node
 #pragma unroll
@@ -489,22 +503,31 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_interp(
     long long ztot, double *__restrict__ out, const double *__restrict__ ref, const float *__restrict__ w,
     const unsigned *__restrict__ perm, double *__restrict__ part, const DirTail dt) {
     constexpr int H = (W - 1) / 2, TB = Win<W>::TB, TS = Win<W>::TS, NT = TS / 16, NS = TS / 4;
+    // PAIR: both halves of a batch side by side, and scalar spans and loop
+    // bounds (256^2 x 64 channels, split: 219 -> 205 us; 512^2 27.3 -> 25.6).
+    // Nine FP64 taps fill the scalar registers with coefficients: spilled
+    // there, 1024^2 FP32 158 -> 167 us.
+    constexpr bool PAIR = W == 17 || sizeof(A) == 4;
     typedef typename Tile<A>::acc acc_t;
     __shared__ __attribute__((aligned(16))) WinBuf<W, A, true> s[TR_WAVES];
     // step x of a contraction takes the columns 16 (x / 4) + 4 g + x % 4, and
     // the tile's rows are permuted so that register r of lane group g holds
     // row 4 g + r: a lane then reads its windows four at a time
     auto ccol = [&](int x, int g) { return 16 * (x / 4) + 4 * g + x % 4; };
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = wave_index<PAIR>(), lane = threadIdx.x & 63;
     const int q = lane & 15, g = lane >> 4;
     const int2 span = spans[blockIdx.x * TR_WAVES + wave];
     const double *ab = lane < 32 ? a : b;
     double acc0 = 0.0, acc1 = 0.0;
     double xn = 0.0;
-    if (span.x < span.y) {
-        const long long k = items[span.x].kbeg + (lane & 31);
+    // coordinates of the batch at k (past the end: some visibility's)
+    auto fetch = [&](long long k) {
+        k += lane & 31;
         xn = ab[k < ztot ? k : ztot - 1];
-    }
+    };
+    if (span.x < span.y) fetch(items[span.x].kbeg);
+    // this lane's visibility in a batch and component of the result
+    const int vl = 16 * (g >> 1) + q, comp = g & 1;
     for (int item = span.x; item < span.y; ++item) {
         const TrItem it = items[item];
         A gr[NT][NS], gi[NT][NS];
@@ -522,15 +545,10 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_interp(
         const int n0 = TB * (lane < 32 ? it.bx : it.by);
         for (long long k0 = it.kbeg; k0 < it.kend; k0 += 32) {
             const double X = xn * (double)L;
-            {
-                const long long k = (k0 + 32 < it.kend ? k0 + 32 : it.kend) + (lane & 31);
-                xn = ab[k < ztot ? k : ztot - 1];
-            }
-            // this lane's visibility and component of the result
-            const long long kv = k0 + 16 * (g >> 1) + q;
+            fetch(k0 + 32 < it.kend ? k0 + 32 : it.kend);
+            const long long kv = k0 + vl;
             const bool ok = kv < it.kend;
             const long long kc = ok ? kv : it.kend - 1;
-            const int comp = g & 1;
             double rv = 0.0;
             float wv = 0.f;
             unsigned pk = 0;
@@ -542,37 +560,55 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_interp(
             }
             windows32<W, A, true>(s[wave], X, k0 + (lane & 31) < it.kend, L, n0, poly);
             wave_sync();
+            // the sums of N halves of 16 visibilities, side by side, from h0
             A half[2] = {A(0), A(0)};
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                if (k0 + 16 * h >= it.kend) break;
+            auto sums = [&](auto N, int h0) {
+                constexpr int NHALF = decltype(N)::value;
                 typedef A S4 __attribute__((ext_vector_type(4)));
-                const A *kx = &s[wave].v[0][16 * h + q][4 * g], *ky = &s[wave].v[1][16 * h + q][4 * g];
-                acc_t ar[NT], ai[NT];
+                acc_t ar[NHALF][NT], ai[NHALF][NT];
 #pragma unroll
-                for (int t = 0; t < NT; ++t) ar[t] = ai[t] = acc_t{A(0), A(0), A(0), A(0)};
+                for (int h = 0; h < NHALF; ++h)
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) ar[h][t] = ai[h][t] = acc_t{A(0), A(0), A(0), A(0)};
 #pragma unroll
                 for (int cb = 0; cb < NS / 4; ++cb) {
-                    const S4 wx = *reinterpret_cast<const S4 *>(kx + 16 * cb);
+                    S4 wx[NHALF];
+#pragma unroll
+                    for (int h = 0; h < NHALF; ++h)
+                        wx[h] = *reinterpret_cast<const S4 *>(&s[wave].v[0][16 * (h0 + h) + q][4 * g + 16 * cb]);
 #pragma unroll
                     for (int x = 0; x < 4; ++x)
 #pragma unroll
-                        for (int t = 0; t < NT; ++t) {
-                            ar[t] = Tile<A>::mma(gr[t][4 * cb + x], wx[x], ar[t]);
-                            ai[t] = Tile<A>::mma(gi[t][4 * cb + x], wx[x], ai[t]);
+                        for (int h = 0; h < NHALF; ++h)
+#pragma unroll
+                            for (int t = 0; t < NT; ++t) {
+                                ar[h][t] = Tile<A>::mma(gr[t][4 * cb + x], wx[h][x], ar[h][t]);
+                                ai[h][t] = Tile<A>::mma(gi[t][4 * cb + x], wx[h][x], ai[h][t]);
+                            }
+                }
+#pragma unroll
+                for (int h = 0; h < NHALF; ++h) {
+                    A vr = A(0), vi = A(0);
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        const S4 wy = *reinterpret_cast<const S4 *>(&s[wave].v[1][16 * (h0 + h) + q][4 * g + 16 * t]);
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            vr = fma(wy[r], ar[h][t][r], vr);
+                            vi = fma(wy[r], ai[h][t][r], vi);
                         }
-                }
-                A vr = A(0), vi = A(0);
-#pragma unroll
-                for (int t = 0; t < NT; ++t) {
-                    const S4 wy = *reinterpret_cast<const S4 *>(ky + 16 * t);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        vr = fma(wy[r], ar[t][r], vr);
-                        vi = fma(wy[r], ai[t][r], vi);
                     }
+                    half[h0 + h] = swap_add<true>(vr, vi);
                 }
-                half[h] = swap_add<true>(vr, vi);
+            };
+            constexpr std::integral_constant<int, 1> one;
+            constexpr std::integral_constant<int, 2> two;
+            if constexpr (PAIR) {
+                if (k0 + 16 < it.kend) sums(two, 0);
+                else sums(one, 0);
+            } else {
+                sums(one, 0);
+                if (k0 + 16 < it.kend) sums(one, 1);
             }
             // lane group g now gets component g % 2 of visibility 16 (g / 2) + q
             const double v = (double)swap_add<false>(half[0], half[1]);
