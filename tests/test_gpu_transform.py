@@ -199,3 +199,19 @@ def test_every_partial_is_counted(path, n):
     got, want = hist[-1].cpu().numpy()[:, :3], scal.cpu().numpy()[:, :3]
     flush(f"arrivals {path} n={n}: {rel(got, want):.2e}")
     assert rel(got, want) < 1e-10
+
+
+@pytest.mark.parametrize("nvis", [[300], [300, 200]])
+def test_phi_function_result_is_a_tensor_of_its_own(nvis):
+    """One image and several: the value is the sum of Phi, may be changed in
+    place by the caller, and its gradient is the evaluation's (exactly: the
+    same kernels, scaled by a power of two)."""
+    from paper_1703_02920_amd.uvmem import PhiFunction
+    ctx = _context(Problem.random(64, nvis, seed=31), "fp32", "transform")
+    I = torch.full((len(nvis), 64, 64), 0.3, dtype=ctx.dtype, device="cuda", requires_grad=True)
+    scal, grad = ctx.phi_and_grad(I.detach())
+    loss = PhiFunction.apply(I, ctx)
+    assert not loss._is_view() and loss.shape == () and loss.item() == scal[:, 0].sum().item()
+    loss *= 0.5
+    loss.backward()
+    assert I.grad.dtype == ctx.dtype and torch.equal(I.grad, 0.5 * grad)
