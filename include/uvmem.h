@@ -276,7 +276,10 @@ int uvmem_check(uvmem_ctx *ctx);
 /* Kernel timing (benchmarking): when enabled, the forward and adjoint
  * launches of every hot call are bracketed by HIP events on the context's
  * stream.  which = 0 forward, 1 adjoint; total_ms and count accumulate over
- * completed launches (reading synchronises the stream); reset clears them. */
+ * completed launches (reading synchronises the stream); reset clears them.
+ * With the fast evaluation the forward bracket holds the visibility pass too,
+ * and the last row pass lies outside the adjoint bracket (it is the gradient
+ * pass). */
 int uvmem_timing_enable(uvmem_ctx *ctx, int enable);
 int uvmem_timing_read(uvmem_ctx *ctx, int which, double *total_ms, int64_t *count, int reset);
 

@@ -211,7 +211,7 @@ int pick_schedule(int slots, const std::function<std::vector<double>(int)> &cost
 // line (one channel; direct, fast): 64^2 x 5,000 FP64 36.3, 47.5, x 100,000
 // 138.7, 138.1; FP32 x 20,000 49.5, 48.0; 128^2 bf16x3 x 3,000 34.8, 37.5, x
 // 20,000 52.1, 42.7; 128^2 x 3,000 FP64 51.2, 43.5 and FP32 47.0, 37.5; far
-// from it 256^2 x 100,000 FP64 918, 77; 1024^2 x 5,000,250 bf16x3 92,486, 279.
+// from it 256^2 x 100,000 FP64 918, 72; 1024^2 x 5,000,250 bf16x3 92,486, 267.
 void choose_transform(uvmem_ctx *c) {
     c->tr_lg = 0;
     if (c->fwd_model != UVMEM_FWD_DFT || c->ztot == 0 || c->ztot >= (int64_t)1 << 30) return;

@@ -225,7 +225,9 @@ __device__ __forceinline__ int pix_of(int p, int L, int n) {
     return p < half ? p + half : p >= L - half ? p - (L - half) : -1;
 }
 
-// Sequences per workgroup.
+// Sequences per workgroup: enough for a whole wave at the short lengths, two
+// rows above so that a column access has 32 bytes (one row at L = 1024: one
+// 512^2 image 6.3 -> 5.9 us, but 23 channels 29.5 -> 34.7), one column.
 constexpr int row_seqs(int lg) { return tr_row_seqs(lg); }
 constexpr int col_seqs(int lg) { return lg <= 6 ? 8 : lg <= 7 ? 4 : lg <= 8 ? 2 : 1; }
 
@@ -258,7 +260,10 @@ template <typename R> struct RowArgs {
 
 // Rows: two rows (i, i + 1) of B = A o img form one complex sequence; their
 // spectra are separated by symmetry and stored as X[q + H][i], i contiguous,
-// for the columns q = -H .. L/2 + H.
+// for the columns q = -H .. L/2 + H.  Bound by latency (loads, three or four
+// exchanges through LDS, stores) for one image: 5 us at 256^2, 9.5 at 1024^2,
+// 51 MB stored in 29.5 us for 23 channels of 512^2.  With the attenuation
+// in a launch of its own and FP64 half spectra 1024^2 took 9.5 + 12.
 template <int LG, typename R, typename S, bool DIR>
 __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_fwd(
     const RowArgs<R> ra, C2<S> *__restrict__ X, const double2 *__restrict__ tw, const double *__restrict__ dec,
@@ -335,7 +340,9 @@ __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_fwd(
     }
 }
 
-// Columns: X[q][i] -> G[q][p], p = 0 .. L - 1 contiguous.
+// Columns: X[q][i] -> G[q][p], p = 0 .. L - 1 contiguous.  One sequence a
+// workgroup: 8 bytes a node written, 12 us at 1024^2 (17 MB; 14 with FP64
+// grids), 3.6 at 256^2, where it is latency.
 template <int LG, typename S>
 __global__ __launch_bounds__(col_seqs(LG) * fft_threads(LG)) void k_tr_cols_fwd(
     const C2<S> *__restrict__ X, C2<S> *__restrict__ G, const double2 *__restrict__ tw, int n, int Lx, int Lg) {
@@ -495,7 +502,11 @@ struct DirTail {
 // Gather: a workgroup's four waves take one span of consecutive items each
 // (spans are cut to equal cost at finalize); an item's grid tile is held in
 // registers.  The visibilities of a span are consecutive, so the next batch's
-// coordinates are loaded while the current one computes.
+// coordinates are loaded while the current one computes.  Bound by the issue
+// of matrix (46 % of the cycles in FP64) and vector instructions (29 %) and by
+// LDS (40 %), not by its 52 bytes a visibility.  1024^2 x 5,000,250 with the
+// residual: FP32 159 us (gather 216 and a residual pass of 47 apart), split
+// 97 (FP64 tiles 160); 256^2 x 99,840 FP64 18.4.
 template <int W, typename S, typename A, int MODE>
 __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_interp(
     const int2 *__restrict__ spans, const TrItem *__restrict__ items, const double *__restrict__ a,
@@ -666,6 +677,9 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_interp(
 // an item's tile in its slot, tiles[slot][column][row].  A bin of several
 // items has workgroups of its own (waves[].z = live waves > 0), whose waves
 // take an item each and add their sums in LDS in wave order into one tile.
+// Bound as the gather, its matrix share smaller (37 % in FP64).  1024^2 x
+// 5,000,250: FP32 195 us (items of unequal cost in groups of four 273), split
+// 112 (FP64 tiles 196); 256^2 x 99,840 FP64 22.9.
 // perm (may be null): coef is in the caller's order (index << 1 | negated).
 // STEP (a CG step): the coefficients are R + alpha Vd, which also replace R;
 // the chi^2 partial of the workgroup goes to its record in part.
@@ -823,7 +837,10 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
 
 // Inverse columns: node (q, p) sums the tiles that cover it (at most two bin
 // columns by two bin rows, each bin's slots in order), then the transform
-// over p; the image rows are kept: Y[q][i].
+// over p; the image rows are kept: Y[q][i].  Bound by the latency of the tile
+// loads (slots, tiles, further tiles in rounds): 19 us at 1024^2 (31 with a
+// tile at a time), 7 at 256^2, 72 for 23 channels of 512^2 (101 with FP64
+// tiles).
 template <int LG, int W, typename S>
 __global__ __launch_bounds__(col_seqs(LG) * fft_threads(LG)) void k_tr_cols_inv(
     const C2<S> *__restrict__ tiles, const int2 *__restrict__ bin_slot, C2<S> *__restrict__ Y,
@@ -1035,7 +1052,10 @@ __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_sum(
     }
 }
 
-// One channel per image: the rows go straight through the gradient pass.
+// One channel per image: the rows go straight through the gradient pass (14 +
+// 25 us apart at 1024^2, 28.5 together in an evaluation, 47 at the end of a CG
+// step).  A third of it is the end of the reductions: stores drained, two
+// atomics and two rounds of loads across chiplets.
 template <int LG, typename R, typename S>
 __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_inv(
     const C2<S> *__restrict__ Y, const RowGrad<R> rg, const double2 *__restrict__ tw,
