@@ -205,9 +205,12 @@ int pick_schedule(int slots, const std::function<std::vector<double>(int)> &cost
 // Direct contraction or the fast evaluation of k_trans.hip (same sums to
 // rounding, O(L^2 log L + W^2 Z) instead of Z N^2)?  Both evaluations of Phi
 // and its gradient in microseconds, as fitted to measurements at sides 32 to
-// 512, 500 to 100,000 visibilities a channel, 1 and 8 channels: a launch-bound
-// part, a part per visibility (the contraction's rate; window and tile work)
-// part and, for the transforms, a part per grid point.  Measured around the
+// 512, 300 to 100,000 visibilities a channel, 1 to 64 channels, as a cube and
+// with one image: a launch-bound part, a part per visibility (the contraction's
+// rate; window and tile work), per channel (direct) and per grid point (fast).
+// Of 816 such evaluations none that the rule gives to the fast path was slower
+// there beyond the noise (one image of 64 channels of 128^2 x 480 bf16x3: 154
+// direct, 75 fast).  Measured around the
 // line (one channel; direct, fast): 64^2 x 5,000 FP64 36.3, 47.5, x 100,000
 // 138.7, 138.1; FP32 x 20,000 49.5, 48.0; 128^2 bf16x3 x 3,000 34.8, 37.5, x
 // 20,000 52.1, 42.7; 128^2 x 3,000 FP64 51.2, 43.5 and FP32 47.0, 37.5; far
@@ -229,11 +232,18 @@ void choose_transform(uvmem_ctx *c) {
     static const double base[3][3] = {{32, 48, 75}, {30, 44, 85}, {30, 31, 46}};        // microseconds
     static const double rate[3][3] = {{34, 59, 62}, {50, 109, 138}, {88, 226, 450}};    // TFLOP/s
     const int p = c->prec == UVMEM_FP64 ? 0 : c->prec == UVMEM_FP32 ? 1 : 2, q = c->np == 64 ? 0 : c->np == 128 ? 1 : 2;
-    const double z = (double)c->ztot;
-    const double direct = base[p][q] + 8.0 * z * c->np * c->np / rate[p][q] * 1e-6;
-    const double transform = (p == 0 ? 43.0 : 36.0) + c->nchan * std::ldexp(1.3e-5, 2 * lg) +
-                             z * (p == 0 ? 0.4e-3 : 0.17e-3) * (lg <= 7 ? 2.0 : 1.0);
-    bool use = transform < direct;
+    // (up to 64^2 a channel's visibilities lie in few bins)
+    const double z = (double)c->ztot, zmax = (double)*std::max_element(c->nvis.begin(), c->nvis.end());
+    // channels: their uneven tails, and an image of several reads their planes
+    // one after the other in the gradient pass
+    const double direct = base[p][q] + 8.0 * z * c->np * c->np / rate[p][q] * 1e-6 +
+                          (c->nimg < c->nchan ? 1.3 : q > 0 ? 0.5 : 0.0) * (c->nchan - 1);
+    const double transform = (p == 0 ? 43.0 : 36.0) + c->nchan * std::ldexp(p == 0 ? 1.1e-5 : 0.9e-5, 2 * lg) +
+                             (p == 0 ? 0.4e-3 : 0.17e-3) * (z + (lg > 7 ? 0.0 : p == 0 ? z : zmax));
+    // a margin: an evaluation decides, and a dirty image has two adjoints and no
+    // forward pass (128^2 bf16x3, 64 channels x 480: evaluations 71.4 and 71.4,
+    // dirty images 68.4 and 76.3)
+    bool use = transform < 0.92 * direct;
     if (const char *env = std::getenv("UVMEM_DFT"))
         use = std::strcmp(env, "transform") == 0 ? true : std::strcmp(env, "direct") == 0 ? false : use;
     if (!use) return;
