@@ -1193,7 +1193,7 @@ int finalize_impl(uvmem_ctx *c) {
         const size_t lx = L / 2 + 2 * c->tr_h + 1;
         ok(dalloc(c, &c->d_trperm, c->ztot, false));
         ok(dalloc(c, &c->d_trconst, trconst.size() * 8, false));
-        const size_t cs = c->tr_s32 ? sizeof(float2) : sizeof(double2);
+        const size_t cs = c->tr_f32 ? sizeof(float2) : sizeof(double2);
         ok(dalloc(c, (char **)&c->d_trx, C * lx * n * cs, false));
         ok(dalloc(c, (char **)&c->d_trg, C * c->tr_lgc * L * cs));
     }

@@ -266,8 +266,8 @@ struct uvmem_ctx {
     int *d_trgbase = nullptr, *d_trsbase = nullptr;
     double *d_trpart = nullptr;
     unsigned *d_trperm = nullptr;
-    bool tr_s32 = false;               // grids and tiles stored in FP32 (below FP64)
-    bool tr_f32 = false;               // windows and tile products in FP32 too (split precisions)
+    bool tr_s32 = false;               // tiles and inverse half spectra stored in FP32 (below FP64)
+    bool tr_f32 = false;               // forward grids, windows and tile products too (split precisions)
     double *d_trdec = nullptr;
     double2 *d_trtw = nullptr;
     void *d_trpoly = nullptr, *d_trx = nullptr, *d_trg = nullptr, *d_trtile = nullptr;

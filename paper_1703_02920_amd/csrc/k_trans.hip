@@ -43,9 +43,16 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 // Two types follow the precision: S, in which grids, half spectra and tiles
-// are stored (float below FP64; the transforms compute in FP64 whatever it
-// is), and A, that of the windows and the tile products (float for the split
-// precisions only, whose contraction accumulates in FP32 too).  Matrix
+// are stored (the transforms compute in FP64 whatever it is), and A, that of
+// the windows and the tile products (float for the split precisions only,
+// whose contraction accumulates in FP32 too).  S is float for the split
+// precisions, double for FP64; FP32 contexts store the forward's half spectra
+// and grid as double and the adjoint's tiles and half spectra as float.  The
+// window's correction makes the forward grid of a source in the image's corner
+// eleven times its visibilities, cancelled again by the window sums: rounded
+// to FP32 there, a corner source was 1.1e-7 off (the FP32 contraction 6e-8),
+// in FP64 4e-8, and images whose flux passes FP32 overflowed.  (23 channels
+// of 512^2, shared: 291 -> 334 us; one image 0 to 2 %.)  Matrix
 // instructions 16 x 16 x 4: lane l supplies A[l%16][l/16] and
 // B[l/16][l%16] and holds D[drow(l/16, r)][l%16] in register r.
 template <typename S> struct Tile;
@@ -1447,19 +1454,19 @@ void spread_w(const uvmem_ctx *c, const double2 *coef, const float *w, const uns
                        1 << c->tr_lg, (long long)c->ztot, StepArgs{c->d_R, c->d_Vd, c->d_ls, c->d_trpart});
 }
 
-// f(image type, S, A, width) of the context's precision.
+// f(image type, S forward, S adjoint, A, width) of the context's precision.
 template <int W> using width = std::integral_constant<int, W>;
 template <typename F>
 hipError_t with_prec(const uvmem_ctx *c, F f) {
-    if (c->prec == UVMEM_FP64) return f(double(), double(), double(), width<17>());
-    if (c->prec == UVMEM_FP32) return f(float(), float(), double(), width<9>());
-    return f(float(), float(), float(), width<9>());
+    if (c->prec == UVMEM_FP64) return f(double(), double(), double(), double(), width<17>());
+    if (c->prec == UVMEM_FP32) return f(float(), double(), float(), double(), width<9>());
+    return f(float(), float(), float(), float(), width<9>());
 }
 
 }  // namespace
 
 hipError_t launch_tr_forward(const uvmem_ctx *c, const void *I, int what, double2 *out, hipStream_t st) {
-    return with_prec(c, [&](auto r, auto s, auto a, auto w) {
+    return with_prec(c, [&](auto r, auto s, auto, auto a, auto w) {
         typedef decltype(r) R;
         typedef decltype(s) S;
         const hipError_t e =
@@ -1470,7 +1477,7 @@ hipError_t launch_tr_forward(const uvmem_ctx *c, const void *I, int what, double
 
 hipError_t launch_tr_adjoint(const uvmem_ctx *c, const double2 *coef, const float *w, const unsigned *perm,
                              int step, hipStream_t st) {
-    return with_prec(c, [&](auto, auto s, auto a, auto ww) {
+    return with_prec(c, [&](auto, auto, auto s, auto a, auto ww) {
         typedef decltype(s) S;
         typedef decltype(a) A;
         constexpr int W = decltype(ww)::value;
@@ -1482,7 +1489,7 @@ hipError_t launch_tr_adjoint(const uvmem_ctx *c, const double2 *coef, const floa
 
 hipError_t launch_tr_rows_inv(const uvmem_ctx *c, const void *I, void *out, int mode, double *user_scal,
                               hipStream_t st) {
-    return with_prec(c, [&](auto r, auto s, auto, auto) {
+    return with_prec(c, [&](auto r, auto, auto s, auto, auto) {
         return with_lg(c, [&](auto lg) {
             return rows_inv_lg<decltype(lg)::value, decltype(r), decltype(s)>(c, I, out, mode, user_scal, st);
         });

@@ -1,0 +1,64 @@
+"""The fast evaluation of the direct DFT at the limits of its inputs, held to
+what the direct contraction of the same precision gives there."""
+import os
+
+import numpy as np
+import pytest
+import torch
+
+from _common import TOL, Problem, flush, rel
+from test_gpu_transform import _context
+
+pytestmark = pytest.mark.gpu
+
+
+def _phases(prob, i, j):
+    """exp(-2 pi i (u x_j + v y_i)) of every visibility of the first channel."""
+    ch = prob.chans[0]
+    p = ch["u"] * prob.cell * (j - prob.n // 2) + ch["v"] * prob.cell * (i - prob.n // 2)
+    return np.exp(-2j * np.pi * (p - np.rint(p)))
+
+
+@pytest.mark.parametrize("n", [64, 100, 256, 1024])
+def test_fp32_source_anywhere_in_the_image(n):
+    """One source in a corner, on an edge and in the centre, without
+    attenuation.  The FP32 contraction rounds its table of phases to FP32, so
+    one such rounding, 2^-24 of the source, is the bar (rms over the
+    visibilities)."""
+    from paper_1703_02920_amd.uvmem import Context
+    prob = Problem.random(n, [600], seed=61)
+    ch = prob.chans[0]
+    os.environ["UVMEM_DFT"] = "transform"
+    try:
+        ctx = Context(n, 1, "fp32")
+        ctx.set_uv(0, ch["u"], ch["v"], prob.cell)
+        ctx.set_vis(0, ch["vis"])
+        ctx.set_weights(0, ch["w"])
+        ctx.set_beam_image(0, np.ones((n, n), np.float32))
+        ctx.set_prior(prob.M, prob.lam)
+        ctx.finalize()
+    finally:
+        del os.environ["UVMEM_DFT"]
+    assert ctx.info()["transform_side"] > 0
+    for i, j in ((0, 0), (n - 1, n - 1), (0, n - 1), (0, n // 2), (n // 2, n // 2)):
+        I = torch.zeros((1, n, n), dtype=torch.float32, device="cuda")
+        I[0, i, j] = 0.7
+        e = rel(ctx.forward(I).cpu().numpy(), float(I[0, i, j]) * _phases(prob, i, j))
+        flush(f"source at ({i}, {j}) of {n}^2: {e:.2e}")
+        assert e < 2.0 ** -24
+
+
+@pytest.mark.parametrize("scale", [1e-36, 1e36])
+def test_fp32_image_near_the_ends_of_the_range(scale):
+    """FP32 images whose total flux passes the range of FP32 have finite FP64
+    visibilities, as the contraction gives them; faint ones keep their bar."""
+    n = 100
+    prob = Problem.random(n, [500], seed=62)
+    img = (np.random.default_rng(8).uniform(0.1, 1.0, (1, n, n)) * scale).astype(np.float32)
+    ref = prob.oracle_forward(0, img[0].astype(np.float64))
+    for path in ("direct", "transform"):
+        V = _context(prob, "fp32", path).forward(torch.tensor(img, device="cuda")).cpu().numpy()
+        assert np.isfinite(V).all()
+        e = rel(V / scale, ref / scale)
+        flush(f"image of {scale:g}, {path}: {e:.2e}")
+        assert e < TOL["fp32"]
