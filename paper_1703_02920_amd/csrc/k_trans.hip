@@ -54,10 +54,13 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 // in FP64 4e-8, and images whose flux passes FP32 overflowed.  (23 channels
 // of 512^2, shared: 291 -> 334 us; one image 0 to 2 %.)  Matrix
 // instructions 16 x 16 x 4: lane l supplies A[l%16][l/16] and
-// B[l/16][l%16] and holds D[drow(l/16, r)][l%16] in register r.
+// B[l/16][l%16] and holds D[drow(l/16, r)][l%16] in register r.  vec4: four
+// window values read from LDS at once, aligned as their rows are (16 bytes; a
+// plain vector of four doubles claims 32, which every other row is not).
 template <typename S> struct Tile;
 template <> struct Tile<double> {
     typedef doublex4 acc;
+    typedef double vec4 __attribute__((ext_vector_type(4), aligned(16)));
     typedef double2 c2;
     static __device__ __forceinline__ acc mma(double a, double b, acc c) {
         return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
@@ -67,6 +70,7 @@ template <> struct Tile<double> {
 };
 template <> struct Tile<float> {
     typedef floatx4 acc;
+    typedef float vec4 __attribute__((ext_vector_type(4), aligned(16)));
     typedef float2 c2;
     static __device__ __forceinline__ acc mma(float a, float b, acc c) {
         return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
@@ -407,6 +411,8 @@ __device__ __forceinline__ void wave_sync() {
 template <int W, typename S, bool VIS> struct WinBuf {
     static constexpr int ROWS = VIS ? 32 : Win<W>::TS, LEN = (VIS ? Win<W>::TS : 32) + Tile<S>::PAD;
     S v[2][ROWS][LEN];
+    static_assert(sizeof(S) * LEN % alignof(typename Tile<S>::vec4) == 0 && alignof(typename Tile<S>::vec4) <= 16,
+                  "rows of the 16-byte aligned buffer are aligned for reads of four");
     __device__ __forceinline__ S &at(int axis, int vis, int node) {
         return VIS ? v[axis][vis][node] : v[axis][node][vis];
     }
@@ -582,7 +588,7 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_interp(
             A half[2] = {A(0), A(0)};
             auto sums = [&](auto N, int h0) {
                 constexpr int NHALF = decltype(N)::value;
-                typedef A S4 __attribute__((ext_vector_type(4)));
+                typedef typename Tile<A>::vec4 S4;
                 acc_t ar[NHALF][NT], ai[NHALF][NT];
 #pragma unroll
                 for (int h = 0; h < NHALF; ++h)
@@ -767,7 +773,7 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 if (k0 + 16 * h >= it.kend) break;
-                typedef A S4 __attribute__((ext_vector_type(4)));
+                typedef typename Tile<A>::vec4 S4;
                 const int v0 = 16 * h + 4 * g;
                 const S4 cr = *reinterpret_cast<const S4 *>(&sc[wave][0][v0]);
                 const S4 ci = *reinterpret_cast<const S4 *>(&sc[wave][1][v0]);
