@@ -78,10 +78,10 @@ void dfree(T *&p) {
     p = nullptr;
 }
 
-// Release every device buffer, graph, stream and event of the context and
+// Release every device buffer, graph and capture stream of the context and
 // reset the handles, so that a second call (destroy after a failed finalize)
 // frees nothing twice.
-void free_all(uvmem_ctx *c) {
+void free_buffers(uvmem_ctx *c) {
     dfree(c->d_a); dfree(c->d_b); dfree(c->d_vo); dfree(c->d_w); dfree(c->d_beam);
     dfree(c->d_fwdp); dfree(c->d_adj); dfree(c->d_vis);
     dfree(c->d_slot_base); dfree(c->d_vis_base); dfree(c->d_ivis_base); dfree(c->d_ichan_base);
@@ -103,13 +103,18 @@ void free_all(uvmem_ctx *c) {
     c->graph_I = nullptr;
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
     c->cap_stream = nullptr;
+    c->bytes_device = 0;
+}
+
+// The same, and the timing events.
+void free_all(uvmem_ctx *c) {
+    free_buffers(c);
     for (auto &pr : c->pend[0]) { c->ev_pool.push_back(pr.first); c->ev_pool.push_back(pr.second); }
     for (auto &pr : c->pend[1]) { c->ev_pool.push_back(pr.first); c->ev_pool.push_back(pr.second); }
     c->pend[0].clear();
     c->pend[1].clear();
     for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
     c->ev_pool.clear();
-    c->bytes_device = 0;
 }
 
 // ---------------------------------------------------------------- timing
@@ -216,13 +221,13 @@ int pick_schedule(int slots, const std::function<std::vector<double>(int)> &cost
 // 20,000 52.1, 42.7; 128^2 x 3,000 FP64 51.2, 43.5 and FP32 47.0, 37.5; far
 // from it 256^2 x 100,000 FP64 918, 72; 1024^2 x 5,000,250 bf16x3 92,486, 267.
 void choose_transform(uvmem_ctx *c) {
-    c->tr_lg = 0;
     if (c->fwd_model != UVMEM_FWD_DFT || c->ztot == 0 || c->ztot >= (int64_t)1 << 30) return;
     int lg = 6;
     while ((1 << lg) < 2 * c->n) ++lg;
     if (lg > 12) return;
-    // bin tables within 2^28 entries; grids and tiles (at most one per bin and
-    // visibility, and one per 128 visibilities) within 48 GiB
+    // 2^31 nodes (2^25 bins at most); grids and tiles (at most one per bin and
+    // visibility, and one per 128 visibilities) within 48 GiB.  If the card
+    // has less to give, finalize falls back on the contraction
     const double nodes = (double)c->nchan * std::ldexp(1.0, 2 * lg);
     const double side = c->prec == UVMEM_FP64 ? 16 : 8;   // nodes per bin side
     const double slots =
@@ -311,7 +316,8 @@ void transform_window(int W, int ne, int n, int L, std::vector<double> &poly, st
     }
 }
 
-int build_layout(uvmem_ctx *c) {
+// direct: the fast evaluation is not to be used.
+int build_layout(uvmem_ctx *c, bool direct) {
     const int C = c->nchan;
     c->np = ((c->n + 63) / 64) * 64;
     // persistent forward: image blocks resident in LDS, 128 x 256 where the
@@ -359,7 +365,8 @@ int build_layout(uvmem_ctx *c) {
     c->pix_blk = (int)std::max<int64_t>(NTHR, roundup((npix * c->nimg + pix_wgs - 1) / pix_wgs, NTHR));
     c->n_pb = (int)((npix + c->pix_blk - 1) / c->pix_blk);
     c->vis_blk = (int)std::max<int64_t>(2 * NTHR, roundup((c->ztot + vis_wgs - 1) / vis_wgs, 2 * NTHR));
-    choose_transform(c);
+    c->tr_lg = c->n_trrec = c->n_trplane = 0;
+    if (!direct) choose_transform(c);
     return UVMEM_OK;
 }
 
@@ -609,23 +616,32 @@ int uvmem_set_prior(uvmem_ctx *c, double M, double lambda) {
 
 extern "C++" {
 namespace {
-int finalize_impl(uvmem_ctx *c);
+int finalize_impl(uvmem_ctx *c, bool direct);
 }
 }
 
 int uvmem_finalize(uvmem_ctx *c) {
     if (!c) return UVMEM_EINVAL;
     if (c->finalized) return fail(c, UVMEM_ESTATE, "finalize called twice");
+    c->fail_alloc_at = -1;
+    c->n_alloc = 0;
+    if (const char *env = std::getenv("UVMEM_TEST_FAIL_ALLOC")) c->fail_alloc_at = std::atoi(env);
     // host-side tables may not fit in memory: no exception crosses the ABI
-    try {
-        return finalize_impl(c);
-    } catch (const std::bad_alloc &) {
-        free_all(c);
-        return fail(c, UVMEM_ENOMEM, "host memory for the finalize tables");
-    } catch (...) {
-        free_all(c);
-        return fail(c, UVMEM_EINVAL, "finalize failed");
-    }
+    auto attempt = [&](bool direct) {
+        try {
+            return finalize_impl(c, direct);
+        } catch (const std::bad_alloc &) {
+            free_buffers(c);
+            return fail(c, UVMEM_ENOMEM, "host memory for the finalize tables");
+        } catch (...) {
+            free_buffers(c);
+            return fail(c, UVMEM_EINVAL, "finalize failed");
+        }
+    };
+    const int s = attempt(false);
+    // the contraction's buffers may fit where the grids of the fast evaluation
+    // do not (many channels of few visibilities, a card shared with others)
+    return s == UVMEM_ENOMEM && c->tr_lg ? attempt(true) : s;
 }
 
 extern "C++" {
@@ -958,7 +974,7 @@ void direct_lists(const uvmem_ctx *c, DirectLists &d) {
     }
 }
 
-int finalize_impl(uvmem_ctx *c) {
+int finalize_impl(uvmem_ctx *c, bool direct) {
     const int C = c->nchan;
     for (int ch = 0; ch < C; ++ch) {
         if (!c->has_uv[ch]) return fail(c, UVMEM_ESTATE, "channel %d has no uv", ch);
@@ -977,10 +993,7 @@ int finalize_impl(uvmem_ctx *c) {
                         (long long)L);
     }
     HIPCHK(c, hipSetDevice(c->device));
-    c->fail_alloc_at = -1;
-    c->n_alloc = 0;
-    if (const char *env = std::getenv("UVMEM_TEST_FAIL_ALLOC")) c->fail_alloc_at = std::atoi(env);
-    build_layout(c);
+    build_layout(c, direct);
     const int n = c->n, np = c->np;
     const size_t npix = (size_t)n * n;
     const size_t rs = real_size(c);
@@ -1230,7 +1243,7 @@ int finalize_impl(uvmem_ctx *c) {
         ok(dalloc(c, &c->d_gdsum, (size_t)c->n_gdense * 4));
     }
     if (e != hipSuccess) {
-        free_all(c);
+        free_buffers(c);
         (void)hipGetLastError();
         return fail(c, e == hipErrorOutOfMemory ? UVMEM_ENOMEM : UVMEM_EDEVICE, "device allocation: %s",
                     hipGetErrorString(e));
@@ -1278,13 +1291,13 @@ int finalize_impl(uvmem_ctx *c) {
     }
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking);
     if (e != hipSuccess) {
-        free_all(c);
+        free_buffers(c);
         (void)hipGetLastError();
         return fail(c, e == hipErrorOutOfMemory ? UVMEM_ENOMEM : UVMEM_EDEVICE, "upload: %s", hipGetErrorString(e));
     }
     e = hipDeviceSynchronize();
     if (e != hipSuccess) {
-        free_all(c);
+        free_buffers(c);
         (void)hipGetLastError();
         return fail(c, UVMEM_EDEVICE, "finalize: %s", hipGetErrorString(e));
     }

@@ -62,3 +62,37 @@ def test_fp32_image_near_the_ends_of_the_range(scale):
         e = rel(V / scale, ref / scale)
         flush(f"image of {scale:g}, {path}: {e:.2e}")
         assert e < TOL["fp32"]
+
+
+@pytest.mark.parametrize("fail_at", [0, 19, 20, 37, 38])
+def test_contraction_used_where_the_grids_do_not_fit(fail_at):
+    """An allocation of the fast evaluation's finalize fails (the first one,
+    half spectra, grid, the tiles as the last of 38): the context is built with
+    the direct contraction instead, holds what a direct one holds, keeps its
+    timing events and gives its results."""
+    from paper_1703_02920_amd.uvmem import Context
+    prob = Problem.random(128, [9000], seed=63)
+    ch = prob.chans[0]
+    want = _context(prob, "fp32", "direct").info()
+    ctx = Context(128, 1, "fp32")
+    ctx.set_uv(0, ch["u"], ch["v"], prob.cell)
+    ctx.set_vis(0, ch["vis"])
+    ctx.set_weights(0, ch["w"])
+    ctx.set_beam(0, ch["fwhm"])
+    ctx.set_prior(prob.M, prob.lam)
+    ctx.timing(True)
+    os.environ["UVMEM_TEST_FAIL_ALLOC"] = str(fail_at)
+    try:
+        ctx.finalize()
+    finally:
+        del os.environ["UVMEM_TEST_FAIL_ALLOC"]
+    info = ctx.info()
+    flush(f"allocation {fail_at} fails: transform side {info['transform_side']}")
+    assert info["transform_side"] == (256 if fail_at == 38 else 0)
+    assert fail_at == 38 or info == want
+    I = torch.full((1, 128, 128), 0.4, dtype=torch.float32, device="cuda")
+    scal, grad = ctx.phi_and_grad(I)
+    r = prob.oracle_phi_grad(0, I.cpu().numpy()[0].astype(np.float64))
+    assert rel(grad.cpu().numpy()[0], r["grad"]) < TOL["fp32"]
+    assert abs(float(scal[0, 0]) - r["phi"]) < TOL["fp32"] * abs(r["phi"])
+    assert [ctx.timing_read(k)[1] for k in (0, 1)] == [1, 1]
