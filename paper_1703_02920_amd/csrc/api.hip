@@ -684,16 +684,30 @@ hipError_t sort_bins(uvmem_ctx *c) {
     auto up32 = [](int64_t x) { return std::max<int64_t>(32, (x + 31) / 32 * 32); };
     const int64_t chunk = std::max(std::min<int64_t>(64, up32(c->ztot / 2048)),
                                    std::min<int64_t>(1024, up32(c->ztot / 8192)));
+    // items that a wave of the spread sums in a bin of m items, TR_WAVES waves
+    // a tile: the inverse column pass reads a bin's tiles one after the other
+    // (0.8 us each), a wave of the spread takes batches of 32 (0.85 us, FP64
+    // 2.3), and the sum of both is least where they are equal.  One item, but
+    // for deep bins (ordinary coverage: at most 28 items a bin, two a wave
+    // from 32 items on at 64 visibilities an item); at most 1024 visibilities
+    // in an FP32 sum.  100,000 visibilities in one bin (direct contraction;
+    // one item a wave; now): 64^2 FP32 98, 292, 87 us; 128^2 bf16x3 91, 342,
+    // 81; 256^2 FP64 908, 395, 144.
+    auto per_wave = [&](int64_t m) {
+        const int64_t k = (int64_t)std::sqrt((c->tr_w == 17 ? 3.0 : 8.0) * (double)m / (double)chunk);
+        return std::max<int64_t>(1, c->tr_f32 ? std::min<int64_t>(k, 1024 / chunk) : k);
+    };
     std::vector<TrItem> items;
     int slot = 0;
     for (size_t t = 0; t < C * nbin; ++t) {
         first[t].x = slot;
         const int bin = (int)(t % nbin);
+        const int64_t m = (start[t + 1] - start[t] + chunk - 1) / chunk, tile = TR_WAVES * per_wave(m);
         int v = 0;
         for (int64_t k = start[t]; k < start[t + 1]; k += chunk, ++v)
-            items.push_back(TrItem{(int)(t / nbin), bin / c->tr_nby, bin % c->tr_nby, slot + v / TR_WAVES,
+            items.push_back(TrItem{(int)(t / nbin), bin / c->tr_nby, bin % c->tr_nby, slot + (int)(v / tile),
                                    (long long)k, (long long)std::min<int64_t>(k + chunk, start[t + 1])});
-        slot += (v + TR_WAVES - 1) / TR_WAVES;
+        slot += (int)((m + tile - 1) / tile);
         first[t].y = slot;
     }
     c->n_tritem = (int)items.size();
@@ -722,10 +736,12 @@ hipError_t sort_bins(uvmem_ctx *c) {
             int j = i + 1;
             while (j < c->n_tritem && same_bin(i, j)) ++j;
             if (j - i > 1) {
-                for (int x = i; x < j; x += TR_WAVES)
+                const int pw = (int)per_wave(j - i);
+                for (int x = i; x < j; x += TR_WAVES * pw)
                     for (int v = 0; v < TR_WAVES; ++v) {
-                        const int y = std::min(x + v, j);
-                        shared.push_back(make_int4(y, std::min(y + 1, j), std::min(TR_WAVES, j - x), img));
+                        const int y = std::min(x + v * pw, j);
+                        shared.push_back(
+                            make_int4(y, std::min(y + pw, j), std::min(TR_WAVES, (j - x + pw - 1) / pw), img));
                     }
                 i = j;
                 continue;

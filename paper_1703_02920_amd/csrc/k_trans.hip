@@ -689,7 +689,8 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_interp(
 // workgroup's four waves take one span of items of equal cost each and store
 // an item's tile in its slot, tiles[slot][column][row].  A bin of several
 // items has workgroups of its own (waves[].z = live waves > 0), whose waves
-// take an item each and add their sums in LDS in wave order into one tile.
+// sum an item each (several in a deep bin) and add their sums in LDS in wave
+// order into one tile.
 // Bound as the gather, its matrix share smaller (37 % in FP64).  1024^2 x
 // 5,000,250: FP32 195 us (items of unequal cost in groups of four 273), split
 // 112 (FP64 tiles 196); 256^2 x 99,840 FP64 22.9.
@@ -746,10 +747,12 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
     for (int item = span.x; item < span.y; ++item) {
         const TrItem it = items[item];
         const int n0 = TB * (lane < 32 ? it.bx : it.by);
+        if (span.z == 0 || item == span.x) {   // else the same bin's sums go on
 #pragma unroll
-        for (int x = 0; x < NT; ++x)
+            for (int x = 0; x < NT; ++x)
 #pragma unroll
-            for (int y = 0; y < NT; ++y) ar[x][y] = ai[x][y] = acc_t{A(0), A(0), A(0), A(0)};
+                for (int y = 0; y < NT; ++y) ar[x][y] = ai[x][y] = acc_t{A(0), A(0), A(0), A(0)};
+        }
         for (long long k0 = it.kbeg; k0 < it.kend; k0 += 32) {
             const bool ok = k0 + (lane & 31) < it.kend;
             if (lane < 32) {

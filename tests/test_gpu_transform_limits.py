@@ -96,3 +96,68 @@ def test_contraction_used_where_the_grids_do_not_fit(fail_at):
     assert rel(grad.cpu().numpy()[0], r["grad"]) < TOL["fp32"]
     assert abs(float(scal[0, 0]) - r["phi"]) < TOL["fp32"] * abs(r["phi"])
     assert [ctx.timing_read(k)[1] for k in (0, 1)] == [1, 1]
+
+
+def _one_spot(n, nvis, seed):
+    """Every visibility but a few within a thousandth of a cycle."""
+    prob = Problem.random(n, [nvis], seed=seed)
+    ch, rng = prob.chans[0], np.random.default_rng(seed)
+    ch["u"][5:] = (0.1 + 1e-4 * rng.uniform(-1, 1, nvis - 5)) / prob.cell
+    ch["v"][5:] = (-0.2 + 1e-4 * rng.uniform(-1, 1, nvis - 5)) / prob.cell
+    return prob
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16x3"])
+@pytest.mark.parametrize("nvis", [485, 517, 9006])
+def test_deep_bin(prec, nvis):
+    """A bin of 15 items of 32 visibilities (one a wave), of 16 (two a wave
+    below FP64) and of 282 (several a wave, the last workgroup and wave short),
+    against the oracle;
+    the residuals and chi^2 of a CG step, which the spread updates, against a
+    fresh evaluation of its image (FP64 rounding of the carried residuals; the
+    other precisions' bar)."""
+    prob = _one_spot(64, nvis, 64)
+    ctx = _context(prob, prec, "transform")
+    bar = TOL["fp64" if prec == "fp64" else "fp32"]
+    rng = np.random.default_rng(9)
+    I = torch.tensor(rng.uniform(1e-3, 1.0, (1, 64, 64)), dtype=ctx.dtype, device="cuda")
+    coef = rng.normal(size=nvis) + 1j * rng.normal(size=nvis)
+    adj = ctx.adjoint(torch.tensor(coef, device="cuda")).cpu().numpy()[0]
+    scal, grad = ctx.phi_and_grad(I)
+    r = prob.oracle_phi_grad(0, I.cpu().numpy()[0].astype(np.float64))
+    e_a, e_g = rel(adj, prob.oracle_adjoint(0, coef)), rel(grad.cpu().numpy()[0], r["grad"])
+    e_p = abs(float(scal[0, 0]) - r["phi"]) / abs(r["phi"])
+    J = ctx.image()
+    ctx.cg_init(J, init_to_floor=True)
+    step = ctx.cg_step(J).cpu().numpy()[0, :3]
+    R = ctx.residual().cpu().numpy()
+    s2, _ = ctx.phi_and_grad(J)
+    e_s, e_r = rel(step, s2.cpu().numpy()[0, :3]), rel(R, ctx.residual().cpu().numpy())
+    flush(f"deep bin {prec} x {nvis}: adjoint {e_a:.2e} grad {e_g:.2e} phi {e_p:.2e} step {e_s:.2e} R {e_r:.2e}")
+    assert max(e_a, e_g, e_p) < bar
+    assert max(e_s, e_r) < (1e-10 if prec == "fp64" else 10 * bar)
+
+
+@pytest.mark.parametrize("prec,n", [("fp32", 64), ("bf16x3", 128)])
+def test_one_spot_is_not_slow(prec, n):
+    """100,000 visibilities in one bin: with a tile per four items the chosen
+    path took three times the contraction; it may not be slower (a third is
+    left to the noise of the clock)."""
+    prob = _one_spot(n, 100000, 65)
+    best = {}
+    for path in ("direct", "transform"):
+        ctx = _context(prob, prec, path)
+        I = torch.full((1, n, n), 0.3, dtype=ctx.dtype, device="cuda")
+        grad, scal = torch.empty_like(I), ctx.scalars()
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        times = []
+        for _ in range(6):
+            e[0].record()
+            for _ in range(20):
+                ctx.phi_and_grad(I, grad, scal)
+            e[1].record()
+            e[1].synchronize()
+            times.append(50.0 * e[0].elapsed_time(e[1]))
+        best[path] = min(times)
+    flush(f"one spot {prec} {n}^2: {best}")
+    assert best["transform"] < 1.33 * best["direct"]
