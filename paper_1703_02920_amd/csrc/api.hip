@@ -1680,23 +1680,26 @@ int uvmem_timing_read(uvmem_ctx *c, int which, double *total_ms, int64_t *count,
 
 int uvmem_info(const uvmem_ctx *c, int64_t *out, int nout) {
     if (!c || !out) return UVMEM_EINVAL;
-    // with the fast evaluation the direct contraction's lists exist for this
-    // call only (and only if asked for: entry 7 is the first of them)
-    DirectLists d;
+    // with the fast evaluation the direct contraction's lists are made here,
+    // for their lengths, which are kept (0.2 to 1.2 ms of host time, once; and
+    // only if asked for: entry 7 is the first of them)
     const bool tr = c->tr_lg > 0;
-    if (tr && nout > 7) {
+    uvmem_ctx::ListSizes &d = c->would;
+    if (tr && nout > 7 && !d.known) {
         try {
-            direct_lists(c, d);
+            DirectLists l;
+            direct_lists(c, l);
+            d = {true, l.slots, (int)l.fwdp.size(), (int)l.adj.size(), (int)l.fwdp_m.size(), (int)l.adj_m.size()};
         } catch (...) {
             return UVMEM_ENOMEM;
         }
     }
     const int64_t vals[] = {c->n, c->np, c->nchan, c->prec, c->ztot, c->n_fparts, c->adj_tt,
-                            tr ? d.slots : c->n_slots, tr ? (int64_t)d.fwdp.size() : c->n_fwdp,
-                            tr ? (int64_t)d.adj.size() : c->n_adj, c->n_visit, (int64_t)c->bytes_device, c->n_pb, c->pix_blk,
+                            tr ? d.slots : c->n_slots, tr ? d.fwdp : c->n_fwdp, tr ? d.adj : c->n_adj,
+                            c->n_visit, (int64_t)c->bytes_device, c->n_pb, c->pix_blk,
                             c->vis_blk, c->nimg, c->fwd_model,
                             c->fwd_model == UVMEM_FWD_GRIDDED ? (int64_t)1 << c->grid_lg : 0, c->grad_model,
-                            tr ? (int64_t)d.fwdp_m.size() : c->n_fwdp_m, tr ? (int64_t)d.adj_m.size() : c->n_adj_m,
+                            tr ? d.fwdp_m : c->n_fwdp_m, tr ? d.adj_m : c->n_adj_m,
                             c->tr_lg ? (int64_t)1 << c->tr_lg : 0};
     const int nv = (int)(sizeof vals / sizeof vals[0]);
     for (int i = 0; i < nout && i < nv; ++i) out[i] = vals[i];

@@ -271,6 +271,12 @@ struct uvmem_ctx {
     double *d_trdec = nullptr;
     double2 *d_trtw = nullptr;
     void *d_trpoly = nullptr, *d_trx = nullptr, *d_trg = nullptr, *d_trtile = nullptr;
+    // lengths of the lists that the direct contraction would use (uvmem_info)
+    struct ListSizes {
+        bool known = false;
+        int slots = 0, fwdp = 0, adj = 0, fwdp_m = 0, adj_m = 0;
+    };
+    mutable ListSizes would;
     size_t bytes_device = 0;
 
     // CG

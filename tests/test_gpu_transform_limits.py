@@ -1,6 +1,7 @@
 """The fast evaluation of the direct DFT at the limits of its inputs, held to
 what the direct contraction of the same precision gives there."""
 import os
+import time
 
 import numpy as np
 import pytest
@@ -161,3 +162,21 @@ def test_one_spot_is_not_slow(prec, n):
         best[path] = min(times)
     flush(f"one spot {prec} {n}^2: {best}")
     assert best["transform"] < 1.33 * best["direct"]
+
+
+def test_info_is_cheap_to_repeat():
+    """uvmem_info of a context with the fast evaluation reports the direct
+    contraction's lists without making them again on each call (5 us of host
+    time with the contraction itself; 206 us when they were)."""
+    prob = Problem.random(256, [100000], seed=66)
+    want = _context(prob, "fp32", "direct").info()
+    ctx = _context(prob, "fp32", "transform")
+    times = []
+    for _ in range(20):
+        t0 = time.perf_counter()
+        info = ctx.info()
+        times.append(time.perf_counter() - t0)
+        for k in ("n_slots", "n_fwd_wgs", "n_adj_items", "n_fwd_wgs_region", "n_adj_wgs_region"):
+            assert info[k] == want[k]
+    flush(f"info: {1e6 * times[0]:.0f} us, then {1e6 * min(times):.0f}")
+    assert min(times) < 60e-6
