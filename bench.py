@@ -35,19 +35,35 @@ KERNELS = {"fp32": ("k_forward_p", "k_adjoint_w"), "fp64": ("k_forward_p", "k_ad
            "bf16x3": ("k_forward_h16m", "k_adjoint_h16s"), "fp16x3": ("k_forward_h16m", "k_adjoint_h16s")}
 
 
+# ... and those of the fast evaluation, whose directions are several launches
+FAST_KERNELS = ("k_tr_rows_fwd + k_tr_cols_fwd + k_tr_interp", "k_tr_spread + k_tr_cols_inv")
+
+
 def direction_work(ctx, pairs, n_vis, precision):
     """(matrix flops of one direction, their peak in TFLOP/s, instruction form,
-    kernel names (forward, adjoint)): four per pair of the direct sum, or two
-    real products of a visibility's windows with a tile of 16 x 16 nodes (32 x
-    32 in FP64) in the fast evaluation, whose tiles are FP64, FP32 in split
-    precision."""
+    the kernels in its event bracket (forward, adjoint)): four per pair of the
+    direct sum, or two real products of a visibility's windows with a tile of
+    16 x 16 nodes (32 x 32 in FP64) in the fast evaluation, whose tile products
+    are FP64, FP32 in split precision.  The time that goes with them is that of
+    all the kernels named, of which only the last of the forward and the first
+    of the adjoint issue matrix instructions."""
     if not ctx.info()["transform_side"]:
         form = {"fp32": "fp32", "fp64": "fp64", "bf16x3": "bf16", "fp16x3": "fp16"}[precision]
         return 4.0 * pairs, PEAK[precision], form, KERNELS[precision]
     split = precision in ("bf16x3", "fp16x3")
     nodes = 32 * 32 if precision == "fp64" else 16 * 16
     form = "fp32" if split else "fp64"
-    return 4.0 * nodes * n_vis, PEAK[form], form, ("k_tr_interp", "k_tr_spread")
+    return 4.0 * nodes * n_vis, PEAK[form], form, FAST_KERNELS
+
+
+def evaluation(ctx, precision) -> str:
+    """How a context evaluates the sums, in words."""
+    side = ctx.info()["transform_side"]
+    if not side:
+        return f"direct sum, {precision} products"
+    tiles = "FP32" if precision in ("bf16x3", "fp16x3") else "FP64"
+    return (f"oversampled transform, side {side}, {tiles} windows and tile products; "
+            "the value counts the pairs of the sums, which are not evaluated one by one")
 
 
 def kernel_hash(kernel: str) -> str:
@@ -651,6 +667,7 @@ def main():
     value = pairs * args.steps / (ms / 1e3)
     flops_per_launch, peak, form, names = direction_work(ctx, pairs, ds.total_vis, args.precision)
     fast = ctx.info()["transform_side"]
+    how = evaluation(ctx, args.precision)
     roof = None
     if kern:
         dom = max(kern, key=kern.get)
@@ -690,7 +707,7 @@ def main():
                 mixed[mp] = {"value": pairs * args.steps / (mms / 1e3),
                              "ms_per_step": mms / args.steps, "cg_iters_per_s": args.steps / (mms / 1e3),
                              "kernel_ms": mkern,
-                             "transform_side": mfast,
+                             "transform_side": mfast, "evaluation": evaluation(mctx, mp),
                              "mfma_frac": {k: mflops / (v / 1e3) / 1e12 / mpeak for k, v in mkern.items()},
                              "mfma_frac_3_product_issued": None if mfast else
                              {k: 3 * mflops / (v / 1e3) / 1e12 / mpeak for k, v in mkern.items()},
@@ -724,7 +741,7 @@ def main():
         "config": {"workload": ds.description + "; one projected-CG iteration per step",
                    "n": ds.n, "channels": ds.n_chan, "visibilities": ds.total_vis,
                    "pairs_per_pass": pairs, "precision": args.precision,
-                   "graph": bool(args.graph), "parallelism": "single GPU"},
+                   "graph": bool(args.graph), "parallelism": "single GPU", "evaluation": how},
         "cg_iters_per_s": args.steps / (ms / 1e3),
         "wall_s": t_wall,
         "roofline": roof,
