@@ -97,12 +97,6 @@ __device__ __forceinline__ double2 crot(double2 a) {
 // ---------------------------------------------------------------- FFT
 // In-place radix-R butterflies, outputs in natural order.
 template <bool INV>
-__device__ __forceinline__ void dft2(double2 &a, double2 &b) {
-    const double2 t = csub(a, b);
-    a = cadd(a, b);
-    b = t;
-}
-template <bool INV>
 __device__ __forceinline__ void dft4(double2 &a0, double2 &a1, double2 &a2, double2 &a3) {
     const double2 s0 = cadd(a0, a2), d0 = csub(a0, a2), s1 = cadd(a1, a3), d1 = crot<INV>(csub(a1, a3));
     a0 = cadd(s0, s1);
