@@ -20,18 +20,13 @@ def _phases(prob, i, j):
     return np.exp(-2j * np.pi * (p - np.rint(p)))
 
 
-@pytest.mark.parametrize("n", [64, 100, 256, 1024])
-def test_fp32_source_anywhere_in_the_image(n):
-    """One source in a corner, on an edge and in the centre, without
-    attenuation.  The FP32 contraction rounds its table of phases to FP32, so
-    one such rounding, 2^-24 of the source, is the bar (rms over the
-    visibilities)."""
+def _unattenuated(n, nvis, seed, prec):
     from paper_1703_02920_amd.uvmem import Context
-    prob = Problem.random(n, [600], seed=61)
+    prob = Problem.random(n, [nvis], seed=seed)
     ch = prob.chans[0]
     os.environ["UVMEM_DFT"] = "transform"
     try:
-        ctx = Context(n, 1, "fp32")
+        ctx = Context(n, 1, prec)
         ctx.set_uv(0, ch["u"], ch["v"], prob.cell)
         ctx.set_vis(0, ch["vis"])
         ctx.set_weights(0, ch["w"])
@@ -41,12 +36,46 @@ def test_fp32_source_anywhere_in_the_image(n):
     finally:
         del os.environ["UVMEM_DFT"]
     assert ctx.info()["transform_side"] > 0
+    return prob, ctx
+
+
+@pytest.mark.parametrize("n", [64, 100, 256, 1024])
+def test_fp32_source_anywhere_in_the_image(n):
+    """One source in a corner, on an edge and in the centre, without
+    attenuation.  The FP32 contraction rounds its table of phases to FP32, so
+    one such rounding, 2^-24 of the source, is the bar (rms over the
+    visibilities)."""
+    prob, ctx = _unattenuated(n, 600, 61, "fp32")
     for i, j in ((0, 0), (n - 1, n - 1), (0, n - 1), (0, n // 2), (n // 2, n // 2)):
         I = torch.zeros((1, n, n), dtype=torch.float32, device="cuda")
         I[0, i, j] = 0.7
         e = rel(ctx.forward(I).cpu().numpy(), float(I[0, i, j]) * _phases(prob, i, j))
         flush(f"source at ({i}, {j}) of {n}^2: {e:.2e}")
         assert e < 2.0 ** -24
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16x3", "fp16x3"])
+@pytest.mark.parametrize("n", [64, 256])
+def test_corner_flux(prec, n):
+    """Where the window's correction is largest, both directions: a source in
+    either corner, and the adjoint of its visibilities over the corner's 8 x 8
+    pixels (against the peak, the number of visibilities).  Bars as everywhere:
+    1e-12 in FP64; below it 1e-6, here a rounding of FP32 windows and products
+    (2^-24) times the eleven of the correction."""
+    prob, ctx = _unattenuated(n, 600, 68, prec)
+    ch = prob.chans[0]
+    bar = TOL["fp64" if prec == "fp64" else "fp32"]
+    for i, j in ((0, 0), (n - 1, n - 1)):
+        p = _phases(prob, i, j)
+        I = torch.zeros((1, n, n), dtype=ctx.dtype, device="cuda")
+        I[0, i, j] = 0.5
+        e_f = rel(ctx.forward(I).cpu().numpy(), 0.5 * p)
+        adj = ctx.adjoint(torch.tensor(p, device="cuda")).cpu().numpy()[0]
+        ys, xs = np.mgrid[max(0, i - 7):min(n, i + 8), max(0, j - 7):min(n, j + 8)]
+        want = [(p * np.conj(_phases(prob, y, x))).real.sum() for y, x in zip(ys.ravel(), xs.ravel())]
+        e_a = float(np.abs(adj[ys, xs].ravel() - want).max() / len(ch["u"]))
+        flush(f"corner ({i}, {j}) of {n}^2 {prec}: forward {e_f:.2e} adjoint {e_a:.2e}")
+        assert max(e_f, e_a) < bar
 
 
 @pytest.mark.parametrize("scale", [1e-36, 1e36])
