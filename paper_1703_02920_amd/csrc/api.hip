@@ -687,15 +687,14 @@ hipError_t sort_bins(uvmem_ctx *c) {
     // items that a wave of the spread sums in a bin of m items, TR_WAVES waves
     // a tile: the inverse column pass reads a bin's tiles one after the other
     // (0.8 us each), a wave of the spread takes batches of 32 (0.85 us, FP64
-    // 2.3), and the sum of both is least where they are equal.  One item, but
-    // for deep bins (ordinary coverage: at most 28 items a bin, two a wave
-    // from 32 items on at 64 visibilities an item); at most 1024 visibilities
-    // in an FP32 sum.  100,000 visibilities in one bin (direct contraction;
-    // one item a wave; now): 64^2 FP32 98, 292, 87 us; 128^2 bf16x3 91, 342,
-    // 81; 256^2 FP64 908, 395, 144.
+    // 2.3), and the sum of both is least where they are equal.  One item up to
+    // eight tiles (256^2 x 99,840: 28 items at most).  100,000 visibilities in
+    // one bin (direct contraction; one item a wave; now): 64^2 FP32 98, 292,
+    // 87 us; 128^2 bf16x3 91, 342, 81; 256^2 FP64 908, 395, 144.
+    c->tr_deep = false;
     auto per_wave = [&](int64_t m) {
-        const int64_t k = (int64_t)std::sqrt((c->tr_w == 17 ? 3.0 : 8.0) * (double)m / (double)chunk);
-        return std::max<int64_t>(1, c->tr_f32 ? std::min<int64_t>(k, 1024 / chunk) : k);
+        if (m <= 8 * TR_WAVES) return (int64_t)1;
+        return std::max<int64_t>(1, (int64_t)std::sqrt((c->tr_w == 17 ? 3.0 : 8.0) * (double)m / (double)chunk));
     };
     std::vector<TrItem> items;
     int slot = 0;
@@ -737,6 +736,7 @@ hipError_t sort_bins(uvmem_ctx *c) {
             while (j < c->n_tritem && same_bin(i, j)) ++j;
             if (j - i > 1) {
                 const int pw = (int)per_wave(j - i);
+                c->tr_deep = c->tr_deep || pw > 1;
                 for (int x = i; x < j; x += TR_WAVES * pw)
                     for (int v = 0; v < TR_WAVES; ++v) {
                         const int y = std::min(x + v * pw, j);
@@ -790,7 +790,8 @@ hipError_t sort_bins(uvmem_ctx *c) {
     const size_t o_bin = put(first.data(), first.size() * sizeof(int2));
     ok(dalloc(c, &c->d_trtab, tab.size(), false));
     ok(dalloc(c, &c->d_trpart, (size_t)std::max(c->n_trgroup, c->n_trspread) * NPART, false));
-    ok(dalloc(c, (char **)&c->d_trtile, slot * ts * ts * (c->tr_s32 ? sizeof(float2) : sizeof(double2)), false));
+    ok(dalloc(c, (char **)&c->d_trtile, slot * ts * ts * (c->tr_s32 && !c->tr_deep ? sizeof(float2) : sizeof(double2)),
+              false));
     if (e == hipSuccess) {
         c->d_tritem = (TrItem *)(c->d_trtab + o_item);
         c->d_trspan = (int2 *)(c->d_trtab + o_span);

@@ -259,6 +259,7 @@ struct uvmem_ctx {
     // whose items share a bin or 0; image), records per image likewise
     // (d_trsbase; a CG step's chi^2)
     int n_trgroup = 0, n_trspread = 0;
+    bool tr_deep = false;              // a wave of the spread sums several items of a bin, into FP64 tiles
     int n_trrec = 0;                   // records per image of the row passes
     int n_trplane = 0;                 // adjoint planes of an image that sums several channels
     int2 *d_trspan = nullptr;

@@ -683,8 +683,11 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_interp(
 // workgroup's four waves take one span of items of equal cost each and store
 // an item's tile in its slot, tiles[slot][column][row].  A bin of several
 // items has workgroups of its own (waves[].z = live waves > 0), whose waves
-// sum an item each (several in a deep bin) and add their sums in LDS in wave
-// order into one tile.
+// sum an item each and add their sums in LDS in wave order into one tile.
+// DEEP (contexts with a deep bin): its waves sum several items each.  Where
+// an item's sum is FP32 these are added in FP64 (sixteen registers, a wave or
+// two less on a SIMD, hence a variant of its own), and the tiles, fewer but
+// larger, are stored in FP64.
 // Bound as the gather, its matrix share smaller (37 % in FP64).  1024^2 x
 // 5,000,250: FP32 195 us (items of unequal cost in groups of four 273), split
 // 112 (FP64 tiles 196); 256^2 x 99,840 FP64 22.9.
@@ -697,7 +700,7 @@ struct StepArgs {
     const double *ls;
     double *part;
 };
-template <int W, typename S, typename A, bool STEP>
+template <int W, typename S, typename A, bool STEP, bool DEEP>
 __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restrict__ waves,
                                                             const TrItem *__restrict__ items,
                                                             const double *__restrict__ a,
@@ -717,6 +720,9 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
     const int4 span = waves[blockIdx.x * TR_WAVES + wave];   // first item, end, live waves of a shared bin
     const double *ab = lane < 32 ? a : b;
     acc_t ar[NT][NT], ai[NT][NT];
+    constexpr bool WIDE = DEEP && sizeof(A) == 4;
+    static_assert(!WIDE || NT == 1, "one accumulator tile");
+    double wr[4] = {0.0, 0.0, 0.0, 0.0}, wi[4] = {0.0, 0.0, 0.0, 0.0};
     // the next batch's data are loaded while the current one computes; the
     // visibilities of a span are consecutive, so that includes the next item's
     double xn = 0.0, chi = 0.0;
@@ -741,7 +747,8 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
     for (int item = span.x; item < span.y; ++item) {
         const TrItem it = items[item];
         const int n0 = TB * (lane < 32 ? it.bx : it.by);
-        if (span.z == 0 || item == span.x) {   // else the same bin's sums go on
+        // (FP64 sums of the same bin go on; a scalar branch)
+        if (!DEEP || WIDE || __builtin_amdgcn_readfirstlane(span.z == 0 || item == span.x)) {
 #pragma unroll
             for (int x = 0; x < NT; ++x)
 #pragma unroll
@@ -794,6 +801,13 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
             }
             wave_sync();
         }
+        if (WIDE && span.z != 0) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                wr[r] += (double)ar[0][0][r];
+                wi[r] += (double)ai[0][0][r];
+            }
+        }
         if (span.z == 0) {
             C2<S> *o = tiles + (size_t)it.slot * (TS * TS);
 #pragma unroll
@@ -814,8 +828,13 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
     }
     if (span.z == 0) return;   // uniform over the workgroup
     // waves 1.. leave their sums in LDS, wave 0 adds them in order
-    C2<A> *buf = reinterpret_cast<C2<A> *>(&s[0]);
-    static_assert((TR_WAVES - 1) * TS * TS * sizeof(C2<A>) <= sizeof(s), "wave sums fit the window buffers");
+    typedef typename std::conditional<WIDE, double, A>::type B;
+    auto sum = [&](int x, int y, int r) {
+        if constexpr (WIDE) return make_double2(wr[r], wi[r]);
+        else return C2<A>{ar[x][y][r], ai[x][y][r]};
+    };
+    C2<B> *buf = reinterpret_cast<C2<B> *>(&s[0]);
+    static_assert((TR_WAVES - 1) * TS * TS * sizeof(C2<B>) <= sizeof(s), "wave sums fit the window buffers");
     __syncthreads();
     if (wave > 0 && wave < span.z) {
 #pragma unroll
@@ -823,8 +842,7 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
 #pragma unroll
             for (int y = 0; y < NT; ++y)
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    buf[(wave - 1) * TS * TS + at(x, y, r)] = C2<A>{ar[x][y][r], ai[x][y][r]};
+                for (int r = 0; r < 4; ++r) buf[(wave - 1) * TS * TS + at(x, y, r)] = sum(x, y, r);
     }
     __syncthreads();
     if (wave > 0) return;
@@ -835,9 +853,9 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
         for (int y = 0; y < NT; ++y)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                C2<A> t{ar[x][y][r], ai[x][y][r]};
+                C2<B> t = sum(x, y, r);
                 for (int v = 1; v < span.z; ++v) {
-                    const C2<A> w = buf[(v - 1) * TS * TS + at(x, y, r)];
+                    const C2<B> w = buf[(v - 1) * TS * TS + at(x, y, r)];
                     t.x += w.x;
                     t.y += w.y;
                 }
@@ -851,9 +869,9 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
 // loads (slots, tiles, further tiles in rounds): 19 us at 1024^2 (31 with a
 // tile at a time), 7 at 256^2, 72 for 23 channels of 512^2 (101 with FP64
 // tiles).
-template <int LG, int W, typename S>
+template <int LG, int W, typename TT, typename S>
 __global__ __launch_bounds__(col_seqs(LG) * fft_threads(LG)) void k_tr_cols_inv(
-    const C2<S> *__restrict__ tiles, const int2 *__restrict__ bin_slot, C2<S> *__restrict__ Y,
+    const C2<TT> *__restrict__ tiles, const int2 *__restrict__ bin_slot, C2<S> *__restrict__ Y,
     const double2 *__restrict__ tw, int n, int Lx, int nbx) {
     constexpr int L = 1 << LG, T = fft_threads(LG), NF = col_seqs(LG);
     constexpr int H = (W - 1) / 2, TB = Win<W>::TB, TS = Win<W>::TS, NBY = L / TB;
@@ -885,7 +903,7 @@ __global__ __launch_bounds__(col_seqs(LG) * fft_threads(LG)) void k_tr_cols_inv(
             }
             // the first tile of every covering bin in one round of loads
             // (slot 0 stands in for an empty bin), further ones after them
-            C2<S> y[8][2];
+            C2<TT> y[8][2];
 #pragma unroll
             for (int r = 0; r < 8; ++r)
 #pragma unroll
@@ -1390,12 +1408,12 @@ hipError_t fwd_lg(const uvmem_ctx *c, const void *I, int what, hipStream_t st) {
     return hipGetLastError();
 }
 
-template <int LG, int W, typename S>
+template <int LG, int W, typename TT, typename S>
 hipError_t inv_lg(const uvmem_ctx *c, hipStream_t st) {
     const int H = c->tr_h, L = 1 << LG, Lx = L / 2 + 2 * H + 1;
     constexpr int T = fft_threads(LG), CS = col_seqs(LG);
-    hipLaunchKernelGGL((k_tr_cols_inv<LG, W, S>), dim3((Lx + CS - 1) / CS, c->nchan), dim3(CS * T), 0, st,
-                       (const C2<S> *)c->d_trtile, c->d_trbin, (C2<S> *)c->d_trx, c->d_trtw, c->n, Lx, c->tr_nbx);
+    hipLaunchKernelGGL((k_tr_cols_inv<LG, W, TT, S>), dim3((Lx + CS - 1) / CS, c->nchan), dim3(CS * T), 0, st,
+                       (const C2<TT> *)c->d_trtile, c->d_trbin, (C2<S> *)c->d_trx, c->d_trtw, c->n, Lx, c->tr_nbx);
     return hipGetLastError();
 }
 
@@ -1450,9 +1468,9 @@ hipError_t interp_w(const uvmem_ctx *c, int what, double2 *out, hipStream_t st) 
     return hipGetLastError();
 }
 
-template <int W, typename S, typename A, bool STEP>
+template <int W, typename S, typename A, bool STEP, bool DEEP>
 void spread_w(const uvmem_ctx *c, const double2 *coef, const float *w, const unsigned *perm, hipStream_t st) {
-    hipLaunchKernelGGL((k_tr_spread<W, S, A, STEP>), dim3(c->n_trspread), dim3(64 * TR_WAVES), 0, st, c->d_trspread,
+    hipLaunchKernelGGL((k_tr_spread<W, S, A, STEP, DEEP>), dim3(c->n_trspread), dim3(64 * TR_WAVES), 0, st, c->d_trspread,
                        c->d_tritem, c->d_a, c->d_b, coef, w, perm, (C2<S> *)c->d_trtile, (const A *)c->d_trpoly,
                        1 << c->tr_lg, (long long)c->ztot, StepArgs{c->d_R, c->d_Vd, c->d_ls, c->d_trpart});
 }
@@ -1484,9 +1502,14 @@ hipError_t launch_tr_adjoint(const uvmem_ctx *c, const double2 *coef, const floa
         typedef decltype(s) S;
         typedef decltype(a) A;
         constexpr int W = decltype(ww)::value;
-        if (step) spread_w<W, S, A, true>(c, coef, w, perm, st);
-        else spread_w<W, S, A, false>(c, coef, w, perm, st);
-        return with_lg(c, [&](auto lg) { return inv_lg<decltype(lg)::value, W, S>(c, st); });
+        auto run = [&](auto deep) {
+            constexpr bool DEEP = decltype(deep)::value;
+            typedef typename std::conditional<DEEP, double, S>::type TT;   // of the tiles
+            if (step) spread_w<W, TT, A, true, DEEP>(c, coef, w, perm, st);
+            else spread_w<W, TT, A, false, DEEP>(c, coef, w, perm, st);
+            return with_lg(c, [&](auto lg) { return inv_lg<decltype(lg)::value, W, TT, S>(c, st); });
+        };
+        return c->tr_deep ? run(std::true_type()) : run(std::false_type());
     });
 }
 

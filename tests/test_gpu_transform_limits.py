@@ -138,14 +138,15 @@ def _one_spot(n, nvis, seed):
 
 
 @pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16x3"])
-@pytest.mark.parametrize("nvis", [485, 517, 9006])
+@pytest.mark.parametrize("nvis", [1029, 1061, 9006])
 def test_deep_bin(prec, nvis):
-    """A bin of 15 items of 32 visibilities (one a wave), of 16 (two a wave
+    """A bin of 32 items of 32 visibilities (one a wave), of 33 (two a wave
     below FP64) and of 282 (several a wave, the last workgroup and wave short),
-    against the oracle;
-    the residuals and chi^2 of a CG step, which the spread updates, against a
-    fresh evaluation of its image (FP64 rounding of the carried residuals; the
-    other precisions' bar)."""
+    against the oracle; the residuals and chi^2 of a CG step, which the spread
+    updates, against a fresh evaluation of its image (FP64 rounding of the
+    carried residuals; the other precisions' bar).  An FP32 sum ends with its
+    item, so the split adjoint's error does not grow with the bin: half an FP32
+    rounding times the eleven of the window's correction."""
     prob = _one_spot(64, nvis, 64)
     ctx = _context(prob, prec, "transform")
     bar = TOL["fp64" if prec == "fp64" else "fp32"]
@@ -164,7 +165,7 @@ def test_deep_bin(prec, nvis):
     s2, _ = ctx.phi_and_grad(J)
     e_s, e_r = rel(step, s2.cpu().numpy()[0, :3]), rel(R, ctx.residual().cpu().numpy())
     flush(f"deep bin {prec} x {nvis}: adjoint {e_a:.2e} grad {e_g:.2e} phi {e_p:.2e} step {e_s:.2e} R {e_r:.2e}")
-    assert max(e_a, e_g, e_p) < bar
+    assert max(e_a, e_g, e_p) < bar and (prec == "fp64" or e_a < 11 * 2.0 ** -25)
     assert max(e_s, e_r) < (1e-10 if prec == "fp64" else 10 * bar)
 
 
