@@ -829,10 +829,6 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
     if (span.z == 0) return;   // uniform over the workgroup
     // waves 1.. leave their sums in LDS, wave 0 adds them in order
     typedef typename std::conditional<WIDE, double, A>::type B;
-    auto sum = [&](int x, int y, int r) {
-        if constexpr (WIDE) return make_double2(wr[r], wi[r]);
-        else return C2<A>{ar[x][y][r], ai[x][y][r]};
-    };
     C2<B> *buf = reinterpret_cast<C2<B> *>(&s[0]);
     static_assert((TR_WAVES - 1) * TS * TS * sizeof(C2<B>) <= sizeof(s), "wave sums fit the window buffers");
     __syncthreads();
@@ -842,7 +838,9 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
 #pragma unroll
             for (int y = 0; y < NT; ++y)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) buf[(wave - 1) * TS * TS + at(x, y, r)] = sum(x, y, r);
+                for (int r = 0; r < 4; ++r)
+                    buf[(wave - 1) * TS * TS + at(x, y, r)] =
+                        C2<B>{WIDE ? (B)wr[r] : (B)ar[x][y][r], WIDE ? (B)wi[r] : (B)ai[x][y][r]};
     }
     __syncthreads();
     if (wave > 0) return;
@@ -853,7 +851,7 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
         for (int y = 0; y < NT; ++y)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                C2<B> t = sum(x, y, r);
+                C2<B> t{WIDE ? (B)wr[r] : (B)ar[x][y][r], WIDE ? (B)wi[r] : (B)ai[x][y][r]};
                 for (int v = 1; v < span.z; ++v) {
                     const C2<B> w = buf[(v - 1) * TS * TS + at(x, y, r)];
                     t.x += w.x;
