@@ -20,11 +20,21 @@
  *
  * How the sums are evaluated: small problems by the separable direct
  * contraction on matrix cores in the chosen precision; larger ones (where it
- * is faster) through an oversampled grid with FP64 windows and sums, an
- * evaluation of the same sums to working precision: FP64 contexts to FP64
- * rounding (as the direct sum, ~1e-14), the other precisions to ~2e-8, below
- * the rounding of their own contraction.  The choice depends on the sizes
- * and the precision only.
+ * is faster, image sides up to 2048) through an oversampled grid, an
+ * evaluation of the same sums to working precision.  Types and measured
+ * relative l2 errors there (of the contraction in parentheses):
+ *   FP64: everything FP64; ~1e-14 (the same).
+ *   FP32: FP64 windows, tile products, transforms and forward grid, FP32
+ *     adjoint tiles and half spectra; 0.3 to 0.8e-7 (0.3 to 8e-7).
+ *   BF16X3, FP16X3: one path, without bf16 or fp16 products: FP32 windows,
+ *     tile products, grids and tiles, FP64 transforms; 0.3 to 3e-7 (0.2e-6 to
+ *     1.5e-5).  Its range is that of FP32: sums of |A I| or |w c| beyond
+ *     3e38 overflow and coefficients below 1e-38 lose bits (FP16X3's
+ *     contraction scales its operands).
+ * The choice depends on the sizes and the precision, and is the contraction
+ * where the device memory does not hold the grids; the environment variable
+ * UVMEM_DFT (direct or transform), read by uvmem_finalize, overrides it for
+ * tests and measurements.
  *
  * Geometry: image side N (even), pixel (i, j) at x_j = (j - N/2) cell,
  * y_i = (i - N/2) cell (Alg. 3 with the phase centre at pixel (N/2, N/2));
@@ -184,10 +194,11 @@ int uvmem_set_forward_model(uvmem_ctx *ctx, int model, int oversample, int grad)
  * uint8[N][N] (host or device; nonzero = free pixel).  NULL (the default)
  * makes every pixel free.  Pixels outside the mask are not free parameters:
  * the CG keeps them at their current value and uvmem_phi_and_grad reports
- * grad Phi = 0 there; Phi, chi^2 and S still cover every pixel.  With the
- * exact DFT, the CG's direction forward model visits only the image blocks
- * that meet a mask, and gradients only the pixel tiles that meet one
- * (work lists built at finalize for the union of the planes' masks).  Call before
+ * grad Phi = 0 there; Phi, chi^2 and S still cover every pixel.  In the
+ * direct contraction the CG's direction forward model visits only the image
+ * blocks that meet a mask, and gradients only the pixel tiles that meet one
+ * (work lists built at finalize for the union of the planes' masks); the
+ * oversampled grid covers the whole image.  Call before
  * finalize; UVMEM_EINVAL for a bad plane, UVMEM_ESTATE after finalize. */
 int uvmem_set_mask(uvmem_ctx *ctx, int img, const uint8_t *mask);
 /* Image floor M > 0 (the paper's G, Eq. minproblem) and entropy weight
@@ -291,8 +302,8 @@ int uvmem_timing_read(uvmem_ctx *ctx, int which, double *total_ms, int64_t *coun
  * model, gridded-model grid side L (0 for the DFT), gradient model,
  * forward and adjoint workgroups of the focus-of-attention region's work
  * lists (0 without a region), side of the oversampled grid in use (0: direct
- * contraction; the work-list entries then describe the lists that the direct
- * contraction would use).  uvmem_chan_range gives a channel's offset into the concatenated
+ * contraction).  With an oversampled grid no work lists exist: their entries
+ * then give the lengths of those that the direct contraction would use.  uvmem_chan_range gives a channel's offset into the concatenated
  * visibility arrays and its count. */
 int uvmem_info(const uvmem_ctx *ctx, int64_t *out, int nout);
 int uvmem_chan_range(const uvmem_ctx *ctx, int chan, int64_t *offset, int64_t *nvis);
@@ -300,8 +311,8 @@ int uvmem_chan_range(const uvmem_ctx *ctx, int chan, int64_t *offset, int64_t *n
 /* Allocation-free forward model, for callers that cannot allocate device
  * memory (code under HIP graph capture, tight serving loops, harnesses that
  * forbid hipMalloc).  Same result as uvmem_forward of an FP32 context with
- * one channel whose beam image is `beam`, on the same FP32 matrix-core
- * kernels, but without a context:
+ * one channel whose beam image is `beam`, to the rounding of FP32 (always
+ * the direct contraction's FP32 matrix-core kernels), but without a context:
  *   vis_k = sum_ij A_ij I_ij exp(-2 pi i (u_k x_j + v_k y_i)),
  * x_j = (j - n/2) cell_rad, y_i = (i - n/2) cell_rad.
  * Arguments: n even in [2, 8192]; nvis >= 0; u, v: device double[nvis]

@@ -213,13 +213,19 @@ int pick_schedule(int slots, const std::function<std::vector<double>(int)> &cost
 // 512, 300 to 100,000 visibilities a channel, 1 to 64 channels, as a cube and
 // with one image: a launch-bound part, a part per visibility (the contraction's
 // rate; window and tile work), per channel (direct) and per grid point (fast).
-// Of 816 such evaluations none that the rule gives to the fast path was slower
-// there beyond the noise (one image of 64 channels of 128^2 x 480 bf16x3: 154
-// direct, 75 fast).  Measured around the
-// line (one channel; direct, fast): 64^2 x 5,000 FP64 36.3, 47.5, x 100,000
-// 138.7, 138.1; FP32 x 20,000 49.5, 48.0; 128^2 bf16x3 x 3,000 34.8, 37.5, x
-// 20,000 52.1, 42.7; 128^2 x 3,000 FP64 51.2, 43.5 and FP32 47.0, 37.5; far
-// from it 256^2 x 100,000 FP64 918, 72; 1024^2 x 5,000,250 bf16x3 92,486, 267.
+// Of 816 such evaluations it gives 550 to the fast path, none of which was
+// slower there, and 266 to the contraction, of which 91 would have been more
+// than 5 % faster on the fast path and 42 more than 20 %: the contraction's
+// model has no part per channel that grows with the image, and in FP64 up to
+// 64^2 the visibilities count twice over all channels (one image of 5 channels
+// of 64^2 x 20,000 FP64: 152 direct, 85 fast; of 64 channels of 256^2 x 1,000
+// fp16x3: 273, 154).  Measured around the line (one channel; direct, fast):
+// 64^2 x 5,000 FP64 36.3, 47.5, x 100,000 142, 84; FP32 x 20,000 49.5, 48.0;
+// 128^2 bf16x3 x 3,000 34.8, 37.5, x 20,000 48, 33; 128^2 x 5,000 FP64 57, 40
+// and FP32 53, 32; far from it 256^2 x 100,000 FP64 908, 77; 1024^2 x
+// 5,000,250 bf16x3 92,486, 266.  With all visibilities in one bin, where the
+// fast path is slowest, none of its choices was slower either (128^2 x 5,000
+// FP64 57.7, 57.2; 128^2 x 100,000 bf16x3 91, 78).
 void choose_transform(uvmem_ctx *c) {
     if (c->fwd_model != UVMEM_FWD_DFT || c->ztot == 0 || c->ztot >= (int64_t)1 << 30) return;
     int lg = 6;

@@ -12,16 +12,16 @@
 // and the adjoint is the transpose of that map.  eps is set by W alone:
 // W = 17 reaches FP64 rounding (measured against extended precision: 4e-15 of
 // |V| on 64^2 to 300^2 images, where the direct FP64 sum is at 4e-15 to
-// 1.1e-14), W = 9 stays near 1e-8 (the FP32 contraction is at 1e-7, the
-// split ones above).  Everything is computed in FP64 whatever the context's
-// precision, so only W changes with it.
+// 1.1e-14), W = 9 stays near 1e-8 (4e-8 for a source in a corner of the image).
+// The transforms compute in FP64 in every context; windows, tile products and
+// what is stored between kernels follow the precision (see Tile below).
 //
 // The image is real, hence V(-u, -v) = conj V(u, v): visibilities are kept
 // with a_k in [0, 1/2] (the others negated and conjugated once at finalize)
 // and the grid holds only the columns q = -H .. L/2 + H, H = (W - 1) / 2.
 // Visibilities are sorted by bin of TB x TB nearest nodes; a bin's windows
 // fit one TS x TS node tile (TS = TB + W - 1 = 16 or 32), and both directions
-// work on such tiles with FP64 matrix instructions: gathering is
+// work on such tiles with FP64 or FP32 matrix instructions: gathering is
 // T = (tile) (column windows) followed by a short dot with the row windows,
 // spreading is (column windows x coefficient)^T (row windows) with the
 // visibilities as the contraction dimension.  Overlapping tiles are summed
@@ -231,16 +231,17 @@ __device__ __forceinline__ int pix_of(int p, int L, int n) {
 }
 
 // Sequences per workgroup: enough for a whole wave at the short lengths, two
-// rows above so that a column access has 32 bytes (one row at L = 1024: one
-// 512^2 image 6.3 -> 5.9 us, but 23 channels 29.5 -> 34.7), one column.
+// rows above so that a column access has 32 bytes (FP32 half spectra, one row
+// at L = 1024: one 512^2 image 6.3 -> 5.9 us, but 23 channels 29.5 -> 34.7),
+// one column.
 constexpr int row_seqs(int lg) { return tr_row_seqs(lg); }
 constexpr int col_seqs(int lg) { return lg <= 6 ? 8 : lg <= 7 ? 4 : lg <= 8 ? 2 : 1; }
 
 // Row block of a workgroup.  The row passes touch 2 NF rows of every column,
 // less than a 128-byte line of X or Y: the blocks of a line go to one XCD
 // (workgroups are dealt to the eight in turn), next to each other in time, so
-// that its L2 holds the line for all of them.  1024^2,
-// FP32: forward rows 11.8 -> 9.9 us, inverse rows 42.3 -> 39.8; 23 channels of
+// that its L2 holds the line for all of them.  FP32 half spectra, 1024^2:
+// forward rows 11.8 -> 9.9 us, inverse rows 42.3 -> 39.8; 23 channels of
 // 512^2: 32.6 -> 29.5 and 49.3 -> 43.0.
 template <typename S, int NF> __device__ __forceinline__ int row_block() {
     constexpr int G = NF >= 8 ? 1 : 64 / ((int)sizeof(C2<S>) * NF) > 1 ? 64 / ((int)sizeof(C2<S>) * NF) : 1;
@@ -266,9 +267,10 @@ template <typename R> struct RowArgs {
 // Rows: two rows (i, i + 1) of B = A o img form one complex sequence; their
 // spectra are separated by symmetry and stored as X[q + H][i], i contiguous,
 // for the columns q = -H .. L/2 + H.  Bound by latency (loads, three or four
-// exchanges through LDS, stores) for one image: 5 us at 256^2, 9.5 at 1024^2,
-// 51 MB stored in 29.5 us for 23 channels of 512^2.  With the attenuation
-// in a launch of its own and FP64 half spectra 1024^2 took 9.5 + 12.
+// exchanges through LDS, stores) for one image: 5 us at 256^2, at 1024^2 9.6
+// (split precisions) and 12.0 (FP32, whose half spectra are FP64); 23 channels
+// of 512^2 in FP32 102 MB stored in 36.8 us (51 MB as FP32 in 29.5).  With the
+// attenuation in a launch of its own 1024^2 took 9.5 + 12.
 template <int LG, typename R, typename S, bool DIR>
 __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_fwd(
     const RowArgs<R> ra, C2<S> *__restrict__ X, const double2 *__restrict__ tw, const double *__restrict__ dec,
@@ -346,8 +348,8 @@ __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_fwd(
 }
 
 // Columns: X[q][i] -> G[q][p], p = 0 .. L - 1 contiguous.  One sequence a
-// workgroup: 8 bytes a node written, 12 us at 1024^2 (17 MB; 14 with FP64
-// grids), 3.6 at 256^2, where it is latency.
+// workgroup: 12 us at 1024^2 in split precision (17 MB written; 14 in FP32,
+// whose grid is FP64), 3.4 to 3.9 at 256^2, where it is latency.
 template <int LG, typename S>
 __global__ __launch_bounds__(col_seqs(LG) * fft_threads(LG)) void k_tr_cols_fwd(
     const C2<S> *__restrict__ X, C2<S> *__restrict__ G, const double2 *__restrict__ tw, int n, int Lx, int Lg) {
@@ -510,10 +512,11 @@ struct DirTail {
 // (spans are cut to equal cost at finalize); an item's grid tile is held in
 // registers.  The visibilities of a span are consecutive, so the next batch's
 // coordinates are loaded while the current one computes.  Bound by the issue
-// of matrix (46 % of the cycles in FP64) and vector instructions (29 %) and by
-// LDS (40 %), not by its 52 bytes a visibility.  1024^2 x 5,000,250 with the
-// residual: FP32 159 us (gather 216 and a residual pass of 47 apart), split
-// 97 (FP64 tiles 160); 256^2 x 99,840 FP64 18.4.
+// of matrix (FP64 products 42 % of the cycles, FP32 34 %) and vector
+// instructions (22 and 30 %) and by LDS (35 %), at three waves a SIMD, not by
+// its 52 bytes a visibility.  1024^2 x 5,000,250 with the residual: FP32 158
+// us (gather 216 and a residual pass of 47 apart), split 100 (FP64 tiles 160);
+// 256^2 x 99,840 FP64 18.5.
 template <int W, typename S, typename A, int MODE>
 __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_interp(
     const int2 *__restrict__ spans, const TrItem *__restrict__ items, const double *__restrict__ a,
@@ -688,9 +691,9 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_interp(
 // an item's sum is FP32 these are added in FP64 (sixteen registers, a wave or
 // two less on a SIMD, hence a variant of its own), and the tiles, fewer but
 // larger, are stored in FP64.
-// Bound as the gather, its matrix share smaller (37 % in FP64).  1024^2 x
+// Bound as the gather, its matrix share smaller (33 % in FP64).  1024^2 x
 // 5,000,250: FP32 195 us (items of unequal cost in groups of four 273), split
-// 112 (FP64 tiles 196); 256^2 x 99,840 FP64 22.9.
+// 116 (FP64 tiles 196); 256^2 x 99,840 FP64 22.8.
 // perm (may be null): coef is in the caller's order (index << 1 | negated).
 // STEP (a CG step): the coefficients are R + alpha Vd, which also replace R;
 // the chi^2 partial of the workgroup goes to its record in part.
@@ -865,7 +868,7 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_spread(const int4 *__restr
 // columns by two bin rows, each bin's slots in order), then the transform
 // over p; the image rows are kept: Y[q][i].  Bound by the latency of the tile
 // loads (slots, tiles, further tiles in rounds): 19 us at 1024^2 (31 with a
-// tile at a time), 7 at 256^2, 72 for 23 channels of 512^2 (101 with FP64
+// tile at a time), 7.4 at 256^2, 76 for 23 channels of 512^2 (101 with FP64
 // tiles).
 template <int LG, int W, typename TT, typename S>
 __global__ __launch_bounds__(col_seqs(LG) * fft_threads(LG)) void k_tr_cols_inv(
@@ -1027,7 +1030,7 @@ template <int LG, typename S> struct RowsInv {
 // Several channels of one image: workgroup (x, y) sums A_c x (its rows) over
 // the y-th share of the channels (no A for the dirty image, mode 3) into plane
 // y, which the gradient kernel then sums (a plane per channel cost 56 us here
-// and 51 us there on 23 channels of 512^2; shares of three channels 43 and 28).
+// and 51 us there on 23 channels of 512^2; shares of three channels 46 and 20).
 template <int LG, typename R, typename S>
 __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_sum(
     const C2<S> *__restrict__ Y, double *__restrict__ plane, const R *__restrict__ beam, int nchan, int mode,
@@ -1079,7 +1082,7 @@ __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_sum(
 }
 
 // One channel per image: the rows go straight through the gradient pass (14 +
-// 25 us apart at 1024^2, 28.5 together in an evaluation, 47 at the end of a CG
+// 25 us apart at 1024^2, 29 together in an evaluation, 47 at the end of a CG
 // step).  A third of it is the end of the reductions: stores drained, two
 // atomics and two rounds of loads across chiplets.
 template <int LG, typename R, typename S>

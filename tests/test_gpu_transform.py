@@ -1,10 +1,14 @@
-"""The fast evaluation of the direct DFT (oversampled transform with FP64
-windows) against the oracle and against the direct contraction.
+"""The fast evaluation of the direct DFT (oversampled transform) against the
+oracle and against the direct contraction.
 
 UVMEM_DFT=transform / direct, read at finalize, forces either path.  Bars:
 the fast evaluation is held to the same tolerances as the direct kernels
 (FP64: rounding of FP64 sums, 1e-12; below FP64: the FP32 bar 1e-6 in every
-precision, since its window error is about 2e-8 and its sums are FP64).
+precision.  In FP32 it has to cover the window error, about 1e-8, and FP32
+adjoint tiles and half spectra around FP64 sums; in the split precisions FP32
+windows, tile products, the sums of up to 1,024 visibilities of an item, grids
+and tiles, whose rounding the window's correction magnifies up to eleven times
+in the corners of the image).
 """
 import os
 
