@@ -26,11 +26,11 @@
  *   FP64: everything FP64; ~1e-14 (the same).
  *   FP32: FP64 windows, tile products, transforms and forward grid, FP32
  *     adjoint tiles and half spectra; 0.3 to 0.8e-7 (0.3 to 8e-7).
- *   BF16X3, FP16X3: one path, without bf16 or fp16 products: FP32 windows,
- *     tile products, grids and tiles, FP64 transforms; 0.3 to 3e-7 (0.2e-6 to
- *     1.5e-5).  Its range is that of FP32: sums of |A I| or |w c| beyond
- *     3e38 overflow and coefficients below 1e-38 lose bits (FP16X3's
- *     contraction scales its operands).
+ *   BF16X3, FP16X3: no bf16 or fp16 products: FP32 windows, tile products,
+ *     tiles and adjoint half spectra, FP64 transforms, the forward grid FP32
+ *     and FP64 (scaled into the products tile by tile); 0.3 to 3e-7 (0.2e-6
+ *     to 1.5e-5).  Adjoint coefficients have the range of FP32: below 1e-38
+ *     they lose bits.
  * The choice depends on the sizes and the precision, and is the contraction
  * where the device memory does not hold the grids; the environment variable
  * UVMEM_DFT (direct or transform), read by uvmem_finalize, overrides it for

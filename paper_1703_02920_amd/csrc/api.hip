@@ -214,12 +214,12 @@ int pick_schedule(int slots, const std::function<std::vector<double>(int)> &cost
 // with one image: a launch-bound part, a part per visibility (the contraction's
 // rate; window and tile work), per channel (direct) and per grid point (fast).
 // Of 816 such evaluations it gives 550 to the fast path, none of which was
-// slower there, and 266 to the contraction, of which 91 would have been more
-// than 5 % faster on the fast path and 42 more than 20 %: the contraction's
+// slower there, and 266 to the contraction, of which 81 would have been more
+// than 5 % faster on the fast path and 36 more than 20 %: the contraction's
 // model has no part per channel that grows with the image, and in FP64 up to
 // 64^2 the visibilities count twice over all channels (one image of 5 channels
-// of 64^2 x 20,000 FP64: 152 direct, 85 fast; of 64 channels of 256^2 x 1,000
-// fp16x3: 273, 154).  Measured around the line (one channel; direct, fast):
+// of 64^2 x 20,000 FP64: 151 direct, 85 fast; of 64 channels of 256^2 x 1,000
+// bf16x3: 267, 153).  Measured around the line (one channel; direct, fast):
 // 64^2 x 5,000 FP64 36.3, 47.5, x 100,000 142, 84; FP32 x 20,000 49.5, 48.0;
 // 128^2 bf16x3 x 3,000 34.8, 37.5, x 20,000 48, 33; 128^2 x 5,000 FP64 57, 40
 // and FP32 53, 32; far from it 256^2 x 100,000 FP64 908, 77; 1024^2 x
@@ -1229,7 +1229,7 @@ int finalize_impl(uvmem_ctx *c, bool direct) {
         const size_t lx = L / 2 + 2 * c->tr_h + 1;
         ok(dalloc(c, &c->d_trperm, c->ztot, false));
         ok(dalloc(c, &c->d_trconst, trconst.size() * 8, false));
-        const size_t cs = c->tr_f32 ? sizeof(float2) : sizeof(double2);
+        const size_t cs = c->prec == UVMEM_BF16X3 ? sizeof(float2) : sizeof(double2);
         ok(dalloc(c, (char **)&c->d_trx, C * lx * n * cs, false));
         ok(dalloc(c, (char **)&c->d_trg, C * c->tr_lgc * L * cs));
     }

@@ -268,7 +268,7 @@ struct uvmem_ctx {
     double *d_trpart = nullptr;
     unsigned *d_trperm = nullptr;
     bool tr_s32 = false;               // tiles and inverse half spectra stored in FP32 (below FP64)
-    bool tr_f32 = false;               // forward grids, windows and tile products too (split precisions)
+    bool tr_f32 = false;               // windows and tile products in FP32 too (split precisions)
     double *d_trdec = nullptr;
     double2 *d_trtw = nullptr;
     void *d_trpoly = nullptr, *d_trx = nullptr, *d_trg = nullptr, *d_trtile = nullptr;

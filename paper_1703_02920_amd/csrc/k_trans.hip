@@ -46,13 +46,16 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 // are stored (the transforms compute in FP64 whatever it is), and A, that of
 // the windows and the tile products (float for the split precisions only,
 // whose contraction accumulates in FP32 too).  S is float for the split
-// precisions, double for FP64; FP32 contexts store the forward's half spectra
-// and grid as double and the adjoint's tiles and half spectra as float.  The
+// precisions, double for FP64; FP32 and FP16X3 contexts store the forward's
+// half spectra and grid as double and the adjoint's tiles and half spectra as
+// float.  The
 // window's correction makes the forward grid of a source in the image's corner
 // eleven times its visibilities, cancelled again by the window sums: rounded
 // to FP32 there, a corner source was 1.1e-7 off (the FP32 contraction 6e-8),
-// in FP64 4e-8, and images whose flux passes FP32 overflowed.  (23 channels
-// of 512^2, shared: 291 -> 334 us; one image 0 to 2 %.)  Matrix
+// in FP64 4e-8, and images whose flux passes FP32 overflowed, in
+// FP16X3 too, whose contraction scales its operands.  (FP32, 23 channels of
+// 512^2, shared: 291 -> 334 us, one image 0 to 3 %; FP16X3 512^2 x 999,600
+// 93 -> 97 to 100, many channels up to 14 %.)  Matrix
 // instructions 16 x 16 x 4: lane l supplies A[l%16][l/16] and
 // B[l/16][l%16] and holds D[drow(l/16, r)][l%16] in register r.  vec4: four
 // window values read from LDS at once, aligned as their rows are (16 bytes; a
@@ -268,7 +271,7 @@ template <typename R> struct RowArgs {
 // spectra are separated by symmetry and stored as X[q + H][i], i contiguous,
 // for the columns q = -H .. L/2 + H.  Bound by latency (loads, three or four
 // exchanges through LDS, stores) for one image: 5 us at 256^2, at 1024^2 9.6
-// (split precisions) and 12.0 (FP32, whose half spectra are FP64); 23 channels
+// (bf16x3) and 12.0 (FP32, whose half spectra are FP64); 23 channels
 // of 512^2 in FP32 102 MB stored in 36.8 us (51 MB as FP32 in 29.5).  With the
 // attenuation in a launch of its own 1024^2 took 9.5 + 12.
 template <int LG, typename R, typename S, bool DIR>
@@ -348,8 +351,8 @@ __global__ __launch_bounds__(row_seqs(LG) * fft_threads(LG)) void k_tr_rows_fwd(
 }
 
 // Columns: X[q][i] -> G[q][p], p = 0 .. L - 1 contiguous.  One sequence a
-// workgroup: 12 us at 1024^2 in split precision (17 MB written; 14 in FP32,
-// whose grid is FP64), 3.4 to 3.9 at 256^2, where it is latency.
+// workgroup: 12 us at 1024^2 in bf16x3 (17 MB written; 14 in FP32, whose grid
+// is FP64), 3.4 to 3.9 at 256^2, where it is latency.
 template <int LG, typename S>
 __global__ __launch_bounds__(col_seqs(LG) * fft_threads(LG)) void k_tr_cols_fwd(
     const C2<S> *__restrict__ X, C2<S> *__restrict__ G, const double2 *__restrict__ tw, int n, int Lx, int Lg) {
@@ -489,6 +492,13 @@ __device__ __forceinline__ float swap_add(float x, float y) {
     return __uint_as_float(v.x) + __uint_as_float(v.y);
 }
 
+// e with 2^(e-1) <= |x| < 2^e (the least for zero, subnormal and non-finite x).
+constexpr int EXP_LEAST = -1022;
+__device__ __forceinline__ int exponent(double x) {
+    const int e = (int)((unsigned long long)__double_as_longlong(x) >> 52 & 2047u);
+    return e == 0 || e == 2047 ? EXP_LEAST : e - 1022;
+}
+
 // What the gather does with V_k (component by component):
 //   TV_OUT: out[caller's index] = V_k
 //   TV_RES: R_k = V_k - Vo_k; partial [0] = sum w |R|^2
@@ -530,6 +540,9 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_interp(
     // there, 1024^2 FP32 158 -> 167 us.
     constexpr bool PAIR = W == 17 || sizeof(A) == 4;
     typedef typename Tile<A>::acc acc_t;
+    // an FP64 grid into FP32 products: each tile is scaled by its own power of
+    // two, exactly, so that the products have the range of the grid
+    constexpr bool SCALED = sizeof(S) > sizeof(A);
     __shared__ __attribute__((aligned(16))) WinBuf<W, A, true> s[TR_WAVES];
     // step x of a contraction takes the columns 16 (x / 4) + 4 g + x % 4, and
     // the tile's rows are permuted so that register r of lane group g holds
@@ -553,16 +566,34 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_interp(
         const TrItem it = items[item];
         A gr[NT][NS], gi[NT][NS];
         const int qr = sizeof(A) == 8 ? 4 * (q & 3) + (q >> 2) : q;
+        C2<S> raw[NT][NS];
 #pragma unroll
         for (int x = 0; x < NS; ++x) {
             const C2<S> *col = G + ((size_t)it.chan * Lg + it.bx * TB + ccol(x, g)) * L;
 #pragma unroll
             for (int t = 0; t < NT; ++t) {
-                const C2<S> v = col[(it.by * TB - H + 16 * t + qr) & (L - 1)];
-                gr[t][x] = (A)v.x;
-                gi[t][x] = (A)v.y;
+                raw[t][x] = col[(it.by * TB - H + 16 * t + qr) & (L - 1)];
             }
         }
+        // SCALED: the tile's power of two, the largest exponent in it
+        int ex = 0;
+        if constexpr (SCALED) {
+            ex = EXP_LEAST;
+#pragma unroll
+            for (int x = 0; x < NS; ++x)
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+                    ex = max(ex, max(exponent(raw[t][x].x), exponent(raw[t][x].y)));
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) ex = max(ex, __shfl_xor(ex, o, 64));
+        }
+#pragma unroll
+        for (int x = 0; x < NS; ++x)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                gr[t][x] = (A)(SCALED ? (S)ldexp((double)raw[t][x].x, -ex) : raw[t][x].x);
+                gi[t][x] = (A)(SCALED ? (S)ldexp((double)raw[t][x].y, -ex) : raw[t][x].y);
+            }
         const int n0 = TB * (lane < 32 ? it.bx : it.by);
         for (long long k0 = it.kbeg; k0 < it.kend; k0 += 32) {
             const double X = xn * (double)L;
@@ -632,7 +663,8 @@ __global__ __launch_bounds__(64 * TR_WAVES) void k_tr_interp(
                 if (k0 + 16 < it.kend) sums(one, 1);
             }
             // lane group g now gets component g % 2 of visibility 16 (g / 2) + q
-            const double v = (double)swap_add<false>(half[0], half[1]);
+            double v = (double)swap_add<false>(half[0], half[1]);
+            if constexpr (SCALED) v = ldexp(v, ex);
             if (ok) {
                 if constexpr (MODE == TV_OUT) {
                     out[2 * (size_t)(pk >> 1) + comp] = comp && (pk & 1u) ? -v : v;
@@ -1482,6 +1514,7 @@ template <typename F>
 hipError_t with_prec(const uvmem_ctx *c, F f) {
     if (c->prec == UVMEM_FP64) return f(double(), double(), double(), double(), width<17>());
     if (c->prec == UVMEM_FP32) return f(float(), double(), float(), double(), width<9>());
+    if (c->prec == UVMEM_FP16X3) return f(float(), double(), float(), float(), width<9>());
     return f(float(), float(), float(), float(), width<9>());
 }
 

@@ -78,20 +78,22 @@ def test_corner_flux(prec, n):
         assert max(e_f, e_a) < bar
 
 
+@pytest.mark.parametrize("prec", ["fp32", "fp16x3"])
 @pytest.mark.parametrize("scale", [1e-36, 1e36])
-def test_fp32_image_near_the_ends_of_the_range(scale):
+def test_image_near_the_ends_of_the_range(prec, scale):
     """FP32 images whose total flux passes the range of FP32 have finite FP64
-    visibilities, as the contraction gives them; faint ones keep their bar."""
+    visibilities, as the contraction gives them in FP32 and, with scaled
+    operands, in FP16X3; faint ones keep their bar."""
     n = 100
     prob = Problem.random(n, [500], seed=62)
     img = (np.random.default_rng(8).uniform(0.1, 1.0, (1, n, n)) * scale).astype(np.float32)
     ref = prob.oracle_forward(0, img[0].astype(np.float64))
     for path in ("direct", "transform"):
-        V = _context(prob, "fp32", path).forward(torch.tensor(img, device="cuda")).cpu().numpy()
+        V = _context(prob, prec, path).forward(torch.tensor(img, device="cuda")).cpu().numpy()
         assert np.isfinite(V).all()
         e = rel(V / scale, ref / scale)
-        flush(f"image of {scale:g}, {path}: {e:.2e}")
-        assert e < TOL["fp32"]
+        flush(f"image of {scale:g}, {prec} {path}: {e:.2e}")
+        assert e < TOL[prec if path == "direct" else "fp32"]
 
 
 @pytest.mark.parametrize("fail_at", [0, 19, 20, 37, 38])
